@@ -62,6 +62,8 @@ def kernel_class(r, bf16=True):
         # the bf16 first-layer weight gradient with its Adam update: four
         # waves per 64x64 tile, direct-to-LDS slices (one kernel for both)
         return "erase_wgrad_adam_w4"
+    if r["tile_m"] == 256:
+        return {"wgrad_gemm": "erase_wide_wgrad", "bwd_gemm": "erase_wide_bwd"}.get(r["kind"], "erase_wide_nt")
     if r["tile_m"]:
         return f"{KIND_SYMBOL[r['kind']]}<{t},{r['tile_m']},{r['tile_n']}>"
     return f"{KIND_SYMBOL[r['kind']]}<{t}>"
@@ -75,7 +77,8 @@ def kernel_source_hash(extra=()):
     sources are stale.  The transformer's figures also hash its own kernels
     and launch plan (`extra`)."""
     h = hashlib.sha256()
-    for f in ("csrc/kernels.hip", "csrc/embed.hip", "csrc/internal.h", "build.py") + tuple(extra):
+    for f in ("csrc/kernels.hip", "csrc/wide.hip", "csrc/device.h", "csrc/wide_plan.h", "csrc/embed.hip", "csrc/internal.h",
+              "build.py") + tuple(extra):
         with open(os.path.join(ROOT, "paper_2608_18469_amd", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -26,6 +26,7 @@
 
 #include "erase.h"
 #include "internal.h"
+#include "wide_plan.h"
 
 namespace {
 
@@ -225,6 +226,15 @@ GemmPlan choose_gemm(int bf16, int64_t Mg, int64_t Ng, int64_t Kc, bool allow_sp
   return finish(64, 64, 1);
 }
 
+// 256x256 tiles over `split` slices of the contraction.
+GemmPlan wide_plan(int64_t Kc, int split) {
+  GemmPlan p;
+  p.bm = p.bn = 256;
+  p.kps = (int)roundup(cdiv(std::max<int64_t>(Kc, 1), split), 64);
+  p.split = (int)cdiv(std::max<int64_t>(Kc, 1), p.kps);
+  return p;
+}
+
 size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
   P->bf16 = c.dtype == ERASE_BF16;
   P->esz = P->bf16 ? 2 : 4;
@@ -292,15 +302,22 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
       // launch shapes (contraction lengths padded to the k-step)
       const int BK = P->bf16 ? 64 : 32;
       R.fwd = choose_gemm(P->bf16, M, R.N, roundup(R.K, BK), false);
+      if (P->bf16 && wide_nt_pays(M, R.N, R.K)) R.fwd = wide_plan(roundup(R.K, 64), 1);
       R.wgrad = choose_gemm(P->bf16, R.N, R.K, roundup(M, BK), true);
       if (l == 0 && dgrad) {
         R.dgrad = choose_gemm(P->bf16, M, R.K, roundup(R.N, BK), false);
+        if (P->bf16 && wide_nt_pays(M, R.K, R.N)) R.dgrad = wide_plan(roundup(R.N, 64), 1);
         R.dgrad.group = xcd_group((int)cdiv(M, R.dgrad.bm), (int)cdiv(R.K, R.dgrad.bn), 1, R.dgrad.bm, R.dgrad.bn);
       }
       if (l >= 1) {
         R.dgrad = choose_gemm(P->bf16, M, R.K, roundup(R.N, BK), false);
         // one launch for both backward GEMMs when they can share a tile
-        if (R.dgrad.bm != R.wgrad.bm || R.dgrad.bn != R.wgrad.bn) {
+        int wsplit = 1;
+        const bool wide = P->bf16 && wide_pair_pays(M, R.N, R.K, &wsplit);
+        if (wide) {
+          R.dgrad = wide_plan(roundup(R.N, 64), 1);
+          R.wgrad = wide_plan(roundup(M, 64), wsplit);
+        } else if (R.dgrad.bm != R.wgrad.bm || R.dgrad.bn != R.wgrad.bn) {
           GemmPlan d64 = choose_gemm(P->bf16, 1, 1, roundup(R.N, BK), false);  // 64x64, split 1
           d64.kgroups = 1;  // the grouped launch runs 256-thread workgroups at 64x64
           GemmPlan w64 = d64;
@@ -312,8 +329,8 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
           R.dgrad = d64;
           R.wgrad = w64;
         }
-        R.grouped = (R.dgrad.bm == 64 && R.dgrad.bn == 64) || (R.dgrad.bm == 128 && R.dgrad.bn == 128);
-        if (R.grouped && R.wgrad.split > 1) {
+        R.grouped = wide || (R.dgrad.bm == 64 && R.dgrad.bn == 64) || (R.dgrad.bm == 128 && R.dgrad.bn == 128);
+        if (!wide && R.grouped && R.wgrad.split > 1) {
           // the input-gradient tiles of the same launch fill the chip: the
           // weight gradient keeps slices of >= 512 batch rows, so Adam reads
           // fewer fp32 partial slices.  CTR layers 2 and 3, A/B on one MI355X of
@@ -340,7 +357,17 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
       // in that launch's epilogue and no partial slice goes to memory.  Not
       // when the transposed GEMM copy is needed (the undetached schedule's
       // input gradient), which only the Adam kernel writes.
-      if (l == 0 && !dgrad) {
+      // Large batches take 256x256 tiles and slices instead: the 64x64 tiles
+      // cost 0.62 us per 128 batch rows with one on a compute unit, 1.07 us
+      // with two (512 x 1677 over 32768 rows 166 us, 1677 x 1677 over 16384
+      // rows 273 us).
+      const int64_t t64 = cdiv(R.N, 64) * cdiv(R.K, 64);
+      const double t64_us = double(cdiv(M, 128)) * (t64 <= 256 ? 0.62 : 1.07 * double(cdiv(t64, 512)));
+      const WideSplit ws = wide_wgrad_split(R.N, R.K, M);
+      if (P->bf16 && l == 0 && ws.us < (dgrad ? wide_core_wgrad_us(R.N, R.K, M) : t64_us)) {
+        R.wgrad = wide_plan(roundup(M, 64), ws.split);
+        R.wgrad.group = xcd_group((int)cdiv(R.N, 256), (int)cdiv(R.K, 256), R.wgrad.split, 256, 256);
+      } else if (l == 0 && !dgrad) {
         R.fused_adam = true;
         R.wgrad.bm = R.wgrad.bn = 64;
         R.wgrad.split = 1;

@@ -116,6 +116,12 @@ hipError_t launch_gemm(int bf16, int kind, const GemmDesc& g, const EpiParams& e
 hipError_t launch_bwd_gemm(int bf16, const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
                            hipStream_t s, const LaunchEv& ev = {});
 
+// The wide tiles (bf16): GK_FWD_RELU/CROSS/LIN/GELU, GK_DGRAD(_GELU) and
+// GK_WGRAD in 256x256 tiles, and a layer's two backward GEMMs in one launch.
+hipError_t launch_wide(int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev = {});
+hipError_t launch_wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
+                           hipStream_t s, const LaunchEv& ev = {});
+
 // Step prologue: t += 1 and the zero-padded copy xp[m][k] = x[m][k] (its
 // padding stays zero).
 // Workspace header (first 256 bytes): step counter t (int64 at 0), status

@@ -19,6 +19,7 @@
 
 #include "erase_tf.h"
 #include "internal.h"
+#include "wide_plan.h"
 
 namespace {
 
@@ -94,6 +95,13 @@ int64_t param_count(const Dims& D, int b) {
 struct Plan1 {
   int bm = 64, bn = 64, split = 1, kps = 0;
 };
+Plan1 wide_plan(int64_t K, int split) {
+  Plan1 p;
+  p.bm = p.bn = 256;
+  p.kps = (int)rup(cdv(std::max<int64_t>(K, 1), split), 64);
+  p.split = (int)cdv(std::max<int64_t>(K, 1), p.kps);
+  return p;
+}
 Plan1 choose(int64_t M, int64_t N, int64_t K, bool wgrad) {
   Plan1 p;
   const int64_t target = 384;
@@ -121,6 +129,14 @@ Plan1 choose(int64_t M, int64_t N, int64_t K, bool wgrad) {
 // (measured on the 16384-row shapes: logits 1.10 vs 1.20 ms, MLP-up 87 vs
 // 97 us; the 512-wide outputs are faster with 128x128).
 Plan1 choose_fwd(int64_t M, int64_t N, int64_t K) {
+  if (wide_nt_pays(M, N, K)) return wide_plan(K, 1);
+  Plan1 p = choose(M, N, K, false);
+  if (N >= 2048 && p.bm == 128 && p.bn == 128) p.bm = 64;
+  return p;
+}
+
+// The vocabulary logits in the GEMM core's tiles.
+Plan1 choose_logits(int64_t M, int64_t N, int64_t K) {
   Plan1 p = choose(M, N, K, false);
   if (N >= 2048 && p.bm == 128 && p.bn == 128) p.bm = 64;
   return p;
@@ -165,6 +181,7 @@ struct Block {
   int32_t* flag = nullptr;
   int ntiles = 0, nloss = 0;
   Lin fwd[NW], dgr[NW], wgr[NW];
+  bool pair_wide[NW] = {};  // weight gradient (and input gradient, when grouped) in 256x256 tiles
   bool grouped[NW] = {};  // input- and weight-gradient GEMMs of the weight in one launch
   std::vector<AdamSeg> segs;
   AdamSeg* segs_dev = nullptr;
@@ -250,7 +267,7 @@ size_t build_layout(const erase_tf_config& c, uintptr_t base, Layout* P) {
     B.r3 = f32(Np);
     B.lse = f32(BHT);
     B.dsum = f32(BHT);
-    const Plan1 ph = choose_fwd(D.N, D.V, d);
+    const Plan1 ph = choose_logits(D.N, D.V, d);
     B.ntiles = (int)cdv(D.V, logits_wide(D) ? 128 : ph.bn);
     B.lstat = f32(Np * B.ntiles);
     B.xref = f32(Np);
@@ -261,6 +278,21 @@ size_t build_layout(const erase_tf_config& c, uintptr_t base, Layout* P) {
     B.ploss = f32(B.nloss);
     for (int i = 0; i < NW; ++i) {
       B.wp[i] = choose(D.rows[i], D.cols[i], rup(D.N, 64), true);
+      // 256x256 tiles where they pay: with the input gradient in one launch
+      // (the MLP-up and attention projections), or the weight gradient alone
+      int split = 1;
+      if (i == W1 || i == WO || (i == WQKV && b == 0)) {
+        B.pair_wide[i] = wide_pair_pays(D.N, D.rows[i], D.cols[i], &split);
+      } else if (i == WH) {
+        // the input gradient contracts over the vocabulary: in 256x256 tiles
+        // only when they fill the chip (16384 x 512 over 32768: 764 us in 128
+        // of them, 680 us in 512 tiles of the core)
+        B.pair_wide[i] = wide_tiles(D.N, d) >= kWideCus && wide_pair_pays(D.N, D.V, d, &split);
+      } else {
+        const WideSplit ws = wide_wgrad_split(D.rows[i], D.cols[i], D.N);
+        if (ws.us < wide_core_wgrad_us(D.rows[i], D.cols[i], D.N)) split = ws.split, B.pair_wide[i] = true;
+      }
+      if (B.pair_wide[i]) B.wp[i] = wide_plan(rup(D.N, 64), split);
       B.part[i] = f32(int64_t(B.wp[i].split) * D.rows[i] * D.cols[i]);
     }
     B.segs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * (NW + 1)));
@@ -299,7 +331,8 @@ void build_gemms(const erase_tf_config& c, Layout* P) {
     auto fwd = [&](int w, const void* A, int64_t lda, int kind, void* y, int64_t ldy) {
       Lin& L = B.fwd[w];
       L.kind = kind;
-      L.g = gdesc(A, lda, B.sh[w], D.cols[w], N, D.rows[w], D.cols[w], choose_fwd(N, D.rows[w], D.cols[w]));
+      L.g = gdesc(A, lda, B.sh[w], D.cols[w], N, D.rows[w], D.cols[w],
+                  kind == GK_FWD_LOGITS ? choose_logits(N, D.rows[w], D.cols[w]) : choose_fwd(N, D.rows[w], D.cols[w]));
       L.e = EpiParams{};
       L.e.y = y;
       L.e.ldy = ldy;
@@ -334,7 +367,8 @@ void build_gemms(const erase_tf_config& c, Layout* P) {
     auto dgr = [&](int w, const void* A, int64_t lda, int kind, void* out, int64_t ldo) {
       Lin& L = B.dgr[w];
       L.kind = kind;
-      L.g = gdesc(A, lda, B.sht[w], D.rows[w], N, D.cols[w], D.rows[w], choose_fwd(N, D.cols[w], D.rows[w]));
+      L.g = gdesc(A, lda, B.sht[w], D.rows[w], N, D.cols[w], D.rows[w],
+                  w == WH && !B.pair_wide[w] ? choose_logits(N, D.cols[w], D.rows[w]) : choose_fwd(N, D.cols[w], D.rows[w]));
       L.e = EpiParams{};
       L.e.dmn = out;
       L.e.lddmn = ldo;
@@ -370,7 +404,10 @@ void build_gemms(const erase_tf_config& c, Layout* P) {
       if (B.dgr[w].g.M == 0 || B.dgr[w].kind != GK_DGRAD) continue;
       GemmDesc& gd = B.dgr[w].g;
       GemmDesc& gw = B.wgr[w].g;
-      if (gd.bm == gw.bm && gd.bn == gw.bn && (gd.bm == 128 || gd.bm == 64) && gd.bm == gd.bn) {
+      if (B.pair_wide[w]) {
+        gd.bm = gd.bn = 256;
+        B.grouped[w] = true;
+      } else if (gd.bm == gw.bm && gd.bn == gw.bn && (gd.bm == 128 || gd.bm == 64) && gd.bm == gd.bn) {
         B.grouped[w] = true;
       } else if (gw.bm == 64 && gw.bn == 64) {
         gd.bm = gd.bn = 64;

@@ -1,0 +1,593 @@
+// Wide GEMM tiles (bf16, gfx950) for launches that fill the chip with them:
+// 256 x 256 outputs per workgroup of eight waves, one workgroup per compute
+// unit (128 KB of LDS stages).
+//
+// What bounds the GEMM core's 128 x 128 tiles is operand movement: a byte
+// loaded feeds 64 multiply-adds, through registers and an LDS store, and one
+// barrier per k-step drains the loads in flight.  Here
+//  * a byte loaded feeds 128, and goes from global memory straight into LDS
+//    (global_load_lds_dwordx4: no registers, no LDS store instructions);
+//  * a 64-wide k-step is four phases, one per 128 x 128 quadrant of the tile:
+//    the quadrant's fragments are read, one half of an operand of a later
+//    k-step is issued, then the 16 MFMAs of each wave run.  A half is free as
+//    soon as its quadrants are done, so a whole k-step (64 KB per compute
+//    unit) is always in flight and no wait ever drains the loads: the waits
+//    count the newest halves off;
+//  * the two rows of waves run half a phase apart (one barrier more at the
+//    start of the second): while one row's MFMAs run, the other's LDS reads
+//    and loads are issued on the same SIMDs;
+//  * the MFMA computes the transposed block (weight rows as the A operand),
+//    and the two 16-row blocks of a quadrant take interleaved groups of four
+//    weight rows, so a lane ends with eight consecutive output columns:
+//    16-byte loads and stores in the epilogue, no LDS pass.
+// Measured on one MI355X against the core's best tile: 16384 x 1677 x 1677
+// 94 us (979 TFLOP/s) and 138 us, 16384 x 1024 x 1677 50 and 78 us,
+// 8192 x 8192 x 8192 930 us (1182 TFLOP/s) and 1274 us; weight gradients
+// 1677 x 1677 over 16384 rows 112 us (5 slices) and 165 us, 512 x 1677 over
+// 32768 rows 73 us (16 slices) and 88 us.  A 128 x 256 form (8 MFMAs per
+// phase) reached 771 TFLOP/s where this reaches 1116.
+//
+// Rows (columns, k-major) past the operands' logical extent are read clamped
+// to the last one: they only reach outputs that are not stored.
+#include <hip/hip_ext.h>
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <type_traits>
+
+#include "device.h"
+
+namespace erase {
+
+namespace wide {
+constexpr int BK = 64, NW = 8, NT = 64 * NW;
+
+// HA, HB: rows (forward, input gradient: "NT", both operands contiguous along
+// the contraction) or columns (weight gradient: k-major, both operands
+// row-major over the contraction) of one half of the A and B tile.  A stage
+// is A0 | A1 | B0 | B1; two stages.  NT rows are 128 bytes with 16-byte chunk
+// c at c ^ (3 bits of the row); k-major rows hold HA (HB) elements with the
+// chunks permuted by kperm: fragment reads are conflict-free both ways.
+template <int HA, int HB>
+struct Geo {
+  static constexpr int BM = 2 * HA, BN = 2 * HB;
+  static constexpr int AH = HA * BK * 2, BH = HB * BK * 2;  // bytes of a half
+  static constexpr int STAGE = 2 * (AH + BH);
+  static constexpr int BYTES = 2 * STAGE;
+  static constexpr int LA = AH / 1024 / NW, LB = BH / 1024 / NW;  // 1 KB loads per wave and half
+  static constexpr int TA = HA / 32, TB = HB / 64;                // a wave's 16-wide blocks of a half
+  static_assert(LA >= 1 && LB >= 1, "at least one load per wave and half");
+};
+
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void bar() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// permutation of the 16-byte chunks of a k-major row (8 or 16 chunks)
+template <int CP>
+__device__ __forceinline__ int kperm(int r) {
+  return 2 * ((r >> 1) & 1) + 4 * ((r >> 3) & 1) + (CP == 16 ? 8 * (r & 1) : 0);
+}
+
+// One workgroup's part of a GEMM: output tiles t0, t0 + G, ... < ntiles, as
+// one stream of k-steps (the loads run on into the next tile).
+//
+// Order of a wave's loads in the stream, two per half (LA, LB): k-step p + 1's
+// B1 in phase 0 of p and A1 in phase 1, p + 2's A0 in phase 2 and B0 in phase
+// 3.  A half is overwritten two phases or more after its last read (A0, B0
+// are read in phase 0 of the k-step that used the stage, B1 in 1, A1 in 2):
+// both wave rows are then past the MFMAs that waited for those reads.  A half
+// read in phase q has been waited for by every wave in phase q - 1 or before,
+// in front of a barrier: the waits leave the four newest halves in flight.
+template <int HA, int HB, bool KM, class Epi>
+__device__ __forceinline__ void run(const GemmDesc& g, int t0, int G, int ntiles, bool want_rows, char* smem,
+                                    Epi&& epi) {
+  using X = Geo<HA, HB>;
+  constexpr int TA = X::TA, TB = X::TB, LA = X::LA, LB = X::LB;
+  static_assert(KM || TB == 2, "NT tiles: 128 weight rows per half");
+  if (t0 >= ntiles) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wv >> 2, wn = wv & 3;
+  const int fr = lane & 15, fg = lane >> 4;
+  const int gm = (g.M + X::BM - 1) / X::BM, gn = (g.N + X::BN - 1) / X::BN, grp = g.group;
+  const int M = g.M, N = g.N, K = g.K, kps = g.kps;
+  const int64_t lda = g.lda, ldb = g.ldb;
+  const char* gA = static_cast<const char*>(g.A);
+  const char* gB = static_cast<const char*>(g.B);
+  const uint32_t lbase = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)smem);
+
+  // ---- loads: cursor h walks the stream of (tile, k-step) for half h of
+  // both operands
+  struct Cur {
+    const char* a;
+    const char* b;
+    uint32_t oa[LA], ob[LB];
+    int k, t;  // k-steps left in the tile; tile
+    bool live;
+  };
+  Cur cu[2];
+  auto aim = [&](Cur& c, int h) {  // start of tile c.t
+    const TileIdx ti = tile_from(xcd_linear(c.t, ntiles), gm, gn, grp);
+    const int m0 = ti.m * X::BM, n0 = ti.n * X::BN, kb = ti.z * kps;
+    c.k = (min(K, kb + kps) - kb + BK - 1) / BK;
+    if constexpr (KM) {
+      constexpr int CA = HA / 8, CB = HB / 8;  // chunks per k-major row
+      c.a = gA + ((int64_t)kb * lda + m0) * 2;
+      c.b = gB + ((int64_t)kb * ldb + n0) * 2;
+      const int ml = ((M + 63) & ~63) - 8 - m0, nl = ((N + 63) & ~63) - 8 - n0;  // last whole chunk
+#pragma unroll
+      for (int u = 0; u < LA; ++u) {
+        const int r = (wv * LA + u) * (64 / CA) + lane / CA, ch = (lane % CA) ^ kperm<CA>(r);
+        c.oa[u] = (uint32_t)((int64_t)r * lda + min(h * HA + ch * 8, ml)) * 2;
+      }
+#pragma unroll
+      for (int u = 0; u < LB; ++u) {
+        const int r = (wv * LB + u) * (64 / CB) + lane / CB, ch = (lane % CB) ^ kperm<CB>(r);
+        c.ob[u] = (uint32_t)((int64_t)r * ldb + min(h * HB + ch * 8, nl)) * 2;
+      }
+    } else {
+      c.a = gA + ((int64_t)m0 * lda + kb) * 2;
+      c.b = gB + ((int64_t)n0 * ldb + kb) * 2;
+#pragma unroll
+      for (int u = 0; u < LA; ++u) {
+        const int r = (wv * LA + u) * 8 + (lane >> 3), ch = (lane & 7) ^ (r & 7);
+        c.oa[u] = (uint32_t)(min(h * HA + r, M - 1 - m0) * (int)lda + ch * 8) * 2;
+      }
+#pragma unroll
+      for (int u = 0; u < LB; ++u) {
+        const int r = (wv * LB + u) * 8 + (lane >> 3), ch = (lane & 7) ^ ((r & 3) | ((r >> 1) & 4));
+        c.ob[u] = (uint32_t)(min(h * HB + r, N - 1 - n0) * (int)ldb + ch * 8) * 2;
+      }
+    }
+  };
+  auto load_a = [&](const Cur& c, int h, int st) {
+#pragma unroll
+    for (int u = 0; u < LA; ++u)
+      lds_dma16s(c.a, c.oa[u], lbase + st * X::STAGE + h * X::AH + (wv * LA + u) * 1024);
+  };
+  auto load_b = [&](const Cur& c, int h, int st) {
+#pragma unroll
+    for (int u = 0; u < LB; ++u)
+      lds_dma16s(c.b, c.ob[u], lbase + st * X::STAGE + 2 * X::AH + h * X::BH + (wv * LB + u) * 1024);
+  };
+  auto next = [&](Cur& c, int h) {
+    if (--c.k > 0) {
+      c.a += KM ? BK * lda * 2 : BK * 2;
+      c.b += KM ? BK * ldb * 2 : BK * 2;
+    } else {
+      c.t += G;
+      c.live = c.t < ntiles;
+      if (c.live) aim(c, h);
+    }
+  };
+
+  // ---- fragments
+  const int tq = (lane & 15) >> 2, tc = lane & 3, trow = 8 * fg + tq;
+  // NT: row of the 16-row block and permuted chunk; k half 1 flips bit 6
+  const int fa0 = fr * 128 + ((fg ^ (fr & 7)) * 16);
+  const int fb0o = (8 * (fr >> 2) + (fr & 3)) * 128 + ((fg ^ (fr & 7)) * 16);
+  int ka[TA], kb_[TB];
+#pragma unroll
+  for (int i = 0; i < TA; ++i)
+    ka[i] = KM ? (trow * HA + (((((wm * HA / 2) + i * 16) >> 3) + (tc >> 1)) ^ kperm<HA / 8>(trow)) * 8 + (tc & 1) * 4) * 2
+               : 0;
+#pragma unroll
+  for (int j = 0; j < TB; ++j)
+    kb_[j] = KM ? (trow * HB + (((((wn * HB / 4) + j * 16) >> 3) + (tc >> 1)) ^ kperm<HB / 8>(trow)) * 8 + (tc & 1) * 4) * 2
+                : 0;
+
+  u32x4_t fa[TA][2], fb[2][TB][2];
+  auto read_a = [&](int h, int st) {
+    const char* p = smem + st * X::STAGE + h * X::AH;
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+      for (int i = 0; i < TA; ++i) {
+        if constexpr (KM)
+          fa[i][kh] = tr_frag(reinterpret_cast<const uint16_t*>(p + ka[i] + kh * 32 * HA * 2), HA);
+        else
+          fa[i][kh] = *reinterpret_cast<const u32x4_t*>(p + (wm * (HA / 2) + i * 16) * 128 + (fa0 ^ (kh * 64)));
+      }
+  };
+  auto read_b = [&](int h, int st) {
+    const char* p = smem + st * X::STAGE + 2 * X::AH + h * X::BH;
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+      for (int j = 0; j < TB; ++j) {
+        if constexpr (KM)
+          fb[h][j][kh] = tr_frag(reinterpret_cast<const uint16_t*>(p + kb_[j] + kh * 32 * HB * 2), HB);
+        else
+          fb[h][j][kh] = *reinterpret_cast<const u32x4_t*>(p + (wn * 32 + 4 * j) * 128 + (fb0o ^ (kh * 64)));
+      }
+  };
+
+  f32x4_t acc[2][2][TA][TB];
+  f32x4_t accr[2];
+  auto clear = [&] {
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      accr[a] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+          for (int j = 0; j < TB; ++j) acc[a][b][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  bool rows = false;
+  auto mma = [&](auto ac, auto bc) {
+    constexpr int a = decltype(ac)::value, b = decltype(bc)::value;
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+      for (int i = 0; i < TA; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+          acc[a][b][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fb[b][j][kh]),
+                                                                    __builtin_bit_cast(bf16x8_t, fa[i][kh]),
+                                                                    acc[a][b][i][j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  // row sums of A half a: ones times the block of this wave (blocks over wn)
+  auto rowsum = [&](int a) {
+    if constexpr (KM) {
+      if (rows) {
+        const u32x4_t one = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+          if (wn == i) {
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh)
+              accr[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, one),
+                                                                __builtin_bit_cast(bf16x8_t, fa[i][kh]), accr[a], 0, 0, 0);
+          }
+      }
+    }
+  };
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, 1> c1{};
+
+  // ---- stream
+  cu[0].t = cu[1].t = t0;
+  cu[0].live = cu[1].live = true;
+  aim(cu[0], 0);
+  aim(cu[1], 1);
+  load_a(cu[0], 0, 0);
+  load_b(cu[0], 0, 0);
+  next(cu[0], 0);
+  load_b(cu[1], 1, 0);
+  load_a(cu[1], 1, 0);
+  next(cu[1], 1);
+  if (cu[0].live) {
+    load_a(cu[0], 0, 1);
+    load_b(cu[0], 0, 1);
+    next(cu[0], 0);
+    wait_vm<2 * LA + 2 * LB>();
+  } else {
+    wait_vm<LA + LB>();
+  }
+  bar();
+  if (wm == 1) bar();  // the two wave rows run half a phase apart
+
+  int st = 0;
+  for (int t = t0; t < ntiles; t += G) {
+    const TileIdx ti = tile_from(xcd_linear(t, ntiles), gm, gn, grp);
+    const int kb = ti.z * kps;
+    int k = (min(K, kb + kps) - kb + BK - 1) / BK;
+    rows = want_rows && ti.n == 0;
+    clear();
+    for (; k > 0; --k, st ^= 1) {
+      const bool more = cu[1].live;  // a next stream position exists
+      // phase 0: A0 x B0; waits for B1
+      read_b(0, st);
+      read_a(0, st);
+      if (more) {
+        load_b(cu[1], 1, st ^ 1);
+        wait_vm<2 * LA + 2 * LB>();
+      } else {
+        wait_vm<LA>();
+      }
+      bar();
+      wait_lds();
+      mma(c0, c0);
+      rowsum(0);
+      bar();
+      // phase 1: A0 x B1; waits for A1
+      read_b(1, st);
+      if (more) {
+        load_a(cu[1], 1, st ^ 1);
+        next(cu[1], 1);
+        wait_vm<2 * LA + 2 * LB>();
+      } else {
+        wait_vm<0>();
+      }
+      bar();
+      wait_lds();
+      mma(c0, c1);
+      bar();
+      // phase 2: A1 x B1
+      const bool more2 = cu[0].live;
+      read_a(1, st);
+      if (more2) load_a(cu[0], 0, st);
+      bar();
+      wait_lds();
+      mma(c1, c1);
+      rowsum(1);
+      bar();
+      // phase 3: A1 x B0 (in registers); waits for the next k-step's A0, B0
+      if (more2) {
+        load_b(cu[0], 0, st);
+        next(cu[0], 0);
+        wait_vm<2 * LA + 2 * LB>();
+      } else if (more) {
+        wait_vm<LA + LB>();
+      }
+      bar();
+      mma(c1, c0);
+      bar();
+    }
+    epi(acc, accr, ti, rows, wm, wn, fr, fg);
+  }
+  if (wm == 0) bar();
+}
+
+__device__ __forceinline__ void unpack8(const u32x4_t& w, float f[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f[2 * i] = __uint_as_float(w[i] << 16);
+    f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+  }
+}
+__device__ __forceinline__ u32x4_t pack8(const float f[8]) {
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  u32x4_t o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    o[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{f[2 * i], f[2 * i + 1]}), bf16x2_t));
+  return o;
+}
+// eight columns from n of a row; the operands' rows are padded to whole chunks
+__device__ __forceinline__ u32x4_t ld8(const void* p, int64_t ld, int m, int n) {
+  return *reinterpret_cast<const __attribute__((address_space(1))) u32x4_t*>(
+      gmem(static_cast<const uint16_t*>(p)) + (int64_t)m * ld + n);
+}
+__device__ __forceinline__ void stn(void* p, int64_t ld, int m, int n, int N, const u32x4_t& v) {
+  uint16_t* d = static_cast<uint16_t*>(p) + (int64_t)m * ld + n;
+  if (n + 8 <= N) {
+    *reinterpret_cast<u32x4_t*>(d) = v;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (n + k < N) d[k] = (uint16_t)(k & 1 ? v[k / 2] >> 16 : v[k / 2] & 0xffffu);
+  }
+}
+
+// Epilogue of an NT tile: a lane holds eight consecutive columns of TA rows
+// per quadrant.  The operands of one quadrant are loaded together.
+template <int HA, int HB, int KIND, class A>
+__device__ __forceinline__ void epi_nt(const EpiParams& e, const A& acc, int M, int N, const TileIdx& ti, int wm,
+                                       int wn, int fr, int fg) {
+  constexpr int TA = HA / 32;
+  const int m0 = ti.m * 2 * HA, n0 = ti.n * 2 * HB;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int n = n0 + b * HB + wn * 32 + fg * 8;
+    if (n >= N) continue;
+    float bias[8];
+    if constexpr (KIND == GK_FWD_RELU || KIND == GK_FWD_CROSS) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) bias[k] = n + k < N ? e.bias[n + k] : 0.f;
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      u32x4_t r0[TA], r1[TA];
+#pragma unroll
+      for (int i = 0; i < TA; ++i) {
+        const int m = min(m0 + a * HA + wm * (HA / 2) + i * 16 + fr, M - 1);
+        if constexpr (KIND == GK_FWD_CROSS) {
+          r0[i] = ld8(e.x0, e.ldx0, m, n);
+          r1[i] = ld8(e.xl, e.ldxl, m, n);
+        }
+        if constexpr (KIND == GK_FWD_LIN) {
+          if (e.res) r0[i] = ld8(e.res, e.ldres, m, n);
+        }
+        if constexpr (KIND == GK_DGRAD_GELU) r0[i] = ld8(e.mask, e.ldmask, m, n);
+        if constexpr (KIND == GK_DGRAD) {
+          if (e.res) r0[i] = ld8(e.res, e.ldres, m, n);
+          if (e.below_cross)
+            r1[i] = ld8(e.x0, e.ldx0, m, n);
+          else if (e.mask)
+            r1[i] = ld8(e.mask, e.ldmask, m, n);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < TA; ++i) {
+        const int m = m0 + a * HA + wm * (HA / 2) + i * 16 + fr;
+        if (m >= M) continue;
+        float v[8], p[8], q[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = acc[a][b][i][k >> 2][k & 3];
+        if constexpr (KIND == GK_FWD_RELU) {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            v[k] += bias[k];
+            v[k] = v[k] < 0.f ? 0.f : v[k];  // keeps NaN
+          }
+          stn(e.y, e.ldy, m, n, N, pack8(v));
+        } else if constexpr (KIND == GK_FWD_CROSS) {
+          unpack8(r0[i], p);
+          unpack8(r1[i], q);
+#pragma unroll
+          for (int k = 0; k < 8; ++k) v[k] = fmaf(p[k], v[k] + bias[k], q[k]);
+          stn(e.y, e.ldy, m, n, N, pack8(v));
+        } else if constexpr (KIND == GK_FWD_LIN) {
+          if (e.res) {
+            unpack8(r0[i], p);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] += p[k];
+          }
+          stn(e.y, e.ldy, m, n, N, pack8(v));
+        } else if constexpr (KIND == GK_FWD_GELU) {
+          if (e.gout) stn(e.gout, e.ldgout, m, n, N, pack8(v));
+#pragma unroll
+          for (int k = 0; k < 8; ++k) v[k] = gelu_f(v[k]);
+          stn(e.y, e.ldy, m, n, N, pack8(v));
+        } else if constexpr (KIND == GK_DGRAD_GELU) {
+          unpack8(r0[i], p);
+#pragma unroll
+          for (int k = 0; k < 8; ++k) v[k] *= gelu_grad_f(p[k]);
+          stn(e.dmn, e.lddmn, m, n, N, pack8(v));
+        } else {
+          if (e.res) {
+            unpack8(r0[i], p);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] += p[k];
+          }
+          if (e.below_cross) {
+            const u32x4_t gq = pack8(v);
+            if (e.gout) stn(e.gout, e.ldgout, m, n, N, gq);
+            unpack8(gq, p);
+            unpack8(r1[i], q);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = p[k] * q[k];
+          } else if (e.mask) {
+            unpack8(r1[i], q);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = q[k] > 0.f ? v[k] : 0.f;
+          }
+          stn(e.dmn, e.lddmn, m, n, N, pack8(v));
+        }
+      }
+    }
+  }
+}
+
+// Weight-gradient slice: fp32 partials (a lane holds four consecutive columns
+// of a row per block) and the bias row sums.
+template <int HA, int HB, class A, class R>
+__device__ __forceinline__ void epi_wgrad(const EpiParams& e, const A& acc, const R& accr, int M, int N,
+                                          const TileIdx& ti, bool rows, int wm, int wn, int fr, int fg) {
+  constexpr int TA = HA / 32, TB = HB / 64;
+  const int m0 = ti.m * 2 * HA, n0 = ti.n * 2 * HB;
+  float* out = e.part + (int64_t)ti.z * e.pstride;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int i = 0; i < TA; ++i) {
+      const int m = m0 + a * HA + wm * (HA / 2) + i * 16 + fr;
+      if (m >= M) continue;
+      float* row = out + (int64_t)m * e.ldp;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int j = 0; j < TB; ++j) {
+          const int n = n0 + b * HB + wn * (HB / 4) + j * 16 + 4 * fg;
+          if (n < N) *reinterpret_cast<f32x4_t*>(row + n) = acc[a][b][i][j];  // rows padded to 64 columns
+        }
+      if (rows && wn == i && fg == 0) e.bpart[(int64_t)ti.z * M + m] = accr[a][0];
+    }
+}
+}  // namespace wide
+
+template <int HA, int HB, int KIND>
+__global__ __launch_bounds__(wide::NT) void erase_wide_nt(GemmDesc g, EpiParams e, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  wide::run<HA, HB, false>(
+      g, (int)blockIdx.x, (int)gridDim.x, ntiles, false, smem,
+      [&](const auto& acc, const auto&, const TileIdx& ti, bool, int wm, int wn, int fr, int fg) {
+        wide::epi_nt<HA, HB, KIND>(e, acc, g.M, g.N, ti, wm, wn, fr, fg);
+      });
+}
+
+template <int HA, int HB>
+__global__ __launch_bounds__(wide::NT) void erase_wide_wgrad(GemmDesc g, EpiParams e, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  wide::run<HA, HB, true>(
+      g, (int)blockIdx.x, (int)gridDim.x, ntiles, e.bpart != nullptr, smem,
+      [&](const auto& acc, const auto& accr, const TileIdx& ti, bool rows, int wm, int wn, int fr, int fg) {
+        wide::epi_wgrad<HA, HB>(e, acc, accr, g.M, g.N, ti, rows, wm, wn, fr, fg);
+      });
+}
+
+// Both backward GEMMs of a layer.  The workgroups of the longer contraction
+// come first (`first`: the weight gradient's).
+template <int HA, int HB>
+__global__ __launch_bounds__(wide::NT) void erase_wide_bwd(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew,
+                                                           int nd, int nw, int first) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  const int b = (int)blockIdx.x - (first ? 0 : nd);
+  if (b >= 0 && b < nw) {
+    wide::run<HA, HB, true>(
+        gw, b, nw, nw, ew.bpart != nullptr, smem,
+        [&](const auto& acc, const auto& accr, const TileIdx& ti, bool rows, int wm, int wn, int fr, int fg) {
+          wide::epi_wgrad<HA, HB>(ew, acc, accr, gw.M, gw.N, ti, rows, wm, wn, fr, fg);
+        });
+  } else {
+    wide::run<HA, HB, false>(
+        gd, first ? b - nw : (int)blockIdx.x, nd, nd, false, smem,
+        [&](const auto& acc, const auto&, const TileIdx& ti, bool, int wm, int wn, int fr, int fg) {
+          wide::epi_nt<HA, HB, GK_DGRAD>(ed, acc, gd.M, gd.N, ti, wm, wn, fr, fg);
+        });
+  }
+}
+
+static int wide_tiles(const GemmDesc& g, int bm, int bn) {
+  return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.split;
+}
+
+template <int HA, int HB>
+static hipError_t launch_wide_t(int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev) {
+  const int nt = wide_tiles(g, 2 * HA, 2 * HB);
+  const dim3 grid((unsigned)nt), block(wide::NT);
+  switch (kind) {
+    case GK_FWD_RELU: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_RELU>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_FWD_CROSS: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_CROSS>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_FWD_LIN: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_LIN>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_FWD_GELU: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_DGRAD: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_DGRAD>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_DGRAD_GELU: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_DGRAD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_WGRAD: ERASE_LAUNCH((erase_wide_wgrad<HA, HB>), grid, block, 0, s, ev, g, e, nt); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_wide(int kind, const GemmDesc& g0, const EpiParams& e, hipStream_t s, const LaunchEv& ev) {
+  GemmDesc g = g0;
+  if (g.group <= 0) g.group = xcd_group((g.M + g.bm - 1) / g.bm, (g.N + g.bn - 1) / g.bn, g.split, g.bm, g.bn);
+  if (g.K % 64 || g.kps % 64 || g.kps <= 0 || g.lda % 8 || g.ldb % 8) return hipErrorInvalidValue;
+  if (g.bm == 256 && g.bn == 256) return launch_wide_t<128, 128>(kind, g, e, s, ev);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
+                           hipStream_t s, const LaunchEv& ev) {
+  GemmDesc d = gd, w = gw;
+  if (d.K % 64 || d.kps < d.K || d.lda % 8 || d.ldb % 8 || w.K % 64 || w.kps % 64 || w.kps <= 0 || w.lda % 8 ||
+      w.ldb % 8)
+    return hipErrorInvalidValue;
+  if (d.group <= 0) d.group = xcd_group((d.M + d.bm - 1) / d.bm, (d.N + d.bn - 1) / d.bn, 1, d.bm, d.bn);
+  if (w.group <= 0) w.group = xcd_group((w.M + w.bm - 1) / w.bm, (w.N + w.bn - 1) / w.bn, w.split, w.bm, w.bn);
+  const int nd = wide_tiles(d, d.bm, d.bn), nw = wide_tiles(w, w.bm, w.bn);
+  if (d.bm == 256 && d.bn == 256 && w.bm == 256 && w.bn == 256) {
+    ERASE_LAUNCH((erase_wide_bwd<128, 128>), dim3((unsigned)(nd + nw)), dim3(wide::NT), 0, s, ev, d, ed, w, ew, nd, nw,
+                 w.kps >= d.K ? 1 : 0);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace erase
