@@ -312,8 +312,8 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
       if (l >= 1) {
         R.dgrad = choose_gemm(P->bf16, M, R.K, roundup(R.N, BK), false);
         // one launch for both backward GEMMs when they can share a tile
-        int wsplit = 1;
-        const bool wide = P->bf16 && wide_pair_pays(M, R.N, R.K, &wsplit);
+        const int wsplit = P->bf16 ? wide_pair_split(M, R.N, R.K) : 0;
+        const bool wide = wsplit > 0;
         if (wide) {
           R.dgrad = wide_plan(roundup(R.N, 64), 1);
           R.wgrad = wide_plan(roundup(M, 64), wsplit);
@@ -363,9 +363,11 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
       // rows 273 us).
       const int64_t t64 = cdiv(R.N, 64) * cdiv(R.K, 64);
       const double t64_us = double(cdiv(M, 128)) * (t64 <= 256 ? 0.62 : 1.07 * double(cdiv(t64, 512)));
-      const WideSplit ws = wide_wgrad_split(R.N, R.K, M);
-      if (P->bf16 && l == 0 && ws.us < (dgrad ? wide_core_wgrad_us(R.N, R.K, M) : t64_us)) {
-        R.wgrad = wide_plan(roundup(M, 64), ws.split);
+      const int wsp0 = P->bf16 && l == 0
+                           ? wide_wgrad_split(R.N, R.K, M, dgrad ? wide_core_wgrad_us(R.N, R.K, M) : t64_us).split
+                           : 0;
+      if (wsp0 > 0) {
+        R.wgrad = wide_plan(roundup(M, 64), wsp0);
         R.wgrad.group = xcd_group((int)cdiv(R.N, 256), (int)cdiv(R.K, 256), R.wgrad.split, 256, 256);
       } else if (l == 0 && !dgrad) {
         R.fused_adam = true;
@@ -407,7 +409,7 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
       RL.fwd.group = xcd_group((int)cdiv(M, RL.fwd.bm), 1, 1, RL.fwd.bm, RL.fwd.bn);
       B.nhead = (int)cdiv(M, RL.fwd.bm);
     } else {
-      B.nhead = (int)cdiv(M, head_rows(NL, esz));
+      B.nhead = (int)cdiv(M, head_rows(M));
     }
     B.pdw = static_cast<float*>(cv.take(size_t(B.nhead) * NL * 4));
     B.pdc = static_cast<float*>(cv.take(size_t(B.nhead) * 4));
@@ -446,7 +448,8 @@ void build_segments(Plan* P, const erase_block_buffers* bufs) {
       s.ldsh = ldsh;
       s.sht = sht;
       s.ldsht = ldsht;
-      s.tcols = (int)cdiv(cols, ADAM_TC);
+      s.vtc = adam_vtc(nsplit);
+      s.tcols = (int)cdiv(cols, rows == 1 ? s.vtc : ADAM_TC);
       s.chunk0 = rchunk;
       rchunk += cdiv(rows, ADAM_TR) * s.tcols;
       B.rsegs.push_back(s);
@@ -856,6 +859,7 @@ erase_status enqueue_head(Ctx* c, Enqueuer& q, int b, const float* labels, hipSt
   h.inv_m = 1.0f / float(M);
   h.M = M;
   h.N = Rl.N;
+  h.rows = head_rows(M);
   h.dmn = Rl.dmn;
   h.lddmn = Rl.lddmn;
 

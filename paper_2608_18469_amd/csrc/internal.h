@@ -138,40 +138,33 @@ struct PrologueArgs {
 };
 hipError_t launch_prologue(int bf16, const PrologueArgs& a, hipStream_t s, const LaunchEv& ev = {});
 
-// Fused local head + sigmoid-BCE + gradient at z (one workgroup per 64 rows).
+// Local head + sigmoid-BCE + gradient at z (one workgroup per `rows` rows).  z
+// and dmn rows hold roundup(N, 16 bytes) elements, zero past N.
 struct HeadArgs {
   const void* z; int64_t ldz;    // [M][N] block output
   const float* w;                // head weight [N] (fp32 master)
   const float* c;                // head bias [1]
   const float* y;                // labels [M]
   float lam, inv_m;
-  int M, N;
+  int M, N, rows;
   void* dmn; int64_t lddmn;      // dz row-major
   float* pdw;                    // [nblk][N]
   float* pdc;                    // [nblk]
   float* ploss;                  // [nblk]
 };
-// Rows of z per head workgroup: the [rows][N] tile is staged in LDS (at most
-// 64 KiB), 32 rows when it fits, never fewer than one 16-byte column item.
+// Rows per head workgroup: few for small batches (each workgroup is a chain
+// of short steps), 32 from 8192 rows on, where 256 workgroups fill the chip
+// and more would only add partials for Adam to sum.
 constexpr int HEAD_MAX_N = 2048;
-__host__ __device__ inline int head_pitch(int N, int esz) {  // elements per LDS row: 16-byte multiple plus one chunk
-  const int kch = 16 / esz;
-  return (N + kch - 1) / kch * kch + kch;
-}
-__host__ __device__ inline int head_rows(int N, int esz) {
-  int r = 32;
-  while (r > 16 / esz && r * head_pitch(N, esz) * esz > 65536) r /= 2;
-  return r;
-}
-inline size_t head_lds_bytes(int N, int esz) { return (size_t)head_rows(N, esz) * head_pitch(N, esz) * esz; }
+inline int head_rows(int64_t M) { return M <= 4096 ? 8 : M < 8192 ? 16 : 32; }
 hipError_t launch_head(int bf16, const HeadArgs& a, hipStream_t s, const LaunchEv& ev = {});
 
 // Fused split-reduction + Adam + GEMM-copy refresh for one block.  The
 // segment table lives in device memory (written once at init).  A segment
 // is a [rows][cols] parameter matrix (a vector is one row) processed in
 // tiles of ADAM_TR rows x ADAM_TC columns, one workgroup per tile (a
-// thread owns 4 columns of one row of a matrix tile, one element of a
-// vector).
+// thread owns 4 columns of one row of a matrix tile, a range of one element's
+// partials of a vector).
 constexpr int ADAM_TR = 16, ADAM_TC = 64;
 struct AdamSeg {
   float* p; float* m; float* v; float* g;   // flat [rows*cols] fp32 (g nullable)
@@ -181,8 +174,12 @@ struct AdamSeg {
   void* sh;  int64_t ldsh;                  // GEMM copy [rows][ldsh], nullable
   void* sht; int64_t ldsht;                 // transposed GEMM copy [cols][ldsht], nullable
   int64_t chunk0;                           // first tile index of this segment
-  int tcols;                                // tiles per row of tiles: ceil(cols / ADAM_TC)
+  int tcols;                                // tiles per row of tiles: ceil(cols / ADAM_TC), a vector's ceil(cols / vtc)
+  int vtc;                                  // a vector's elements per chunk (a divisor of 256)
 };
+// A vector's elements per chunk: many partials (the head's, one per workgroup)
+// take more threads per element.
+inline int adam_vtc(int nsplit) { return nsplit > 256 ? 8 : nsplit > 64 ? 32 : ADAM_TC; }
 constexpr int ADAM_MAX_SEG = 34;  // 16 layers x (W, b) + head (w, c)
 struct AdamArgs {
   const AdamSeg* seg;  // device [nseg]

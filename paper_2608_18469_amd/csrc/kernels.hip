@@ -1290,121 +1290,156 @@ hipError_t launch_prologue(int bf16, const PrologueArgs& a, hipStream_t s, const
 }
 
 // ---------------------------------------------------------------------------
-// local head + sigmoid-BCE + gradient at z.  One workgroup stages R rows of z
-// ([R][N] tile in LDS, 16-byte global loads), then:
+// local head + sigmoid-BCE + gradient at z, rows in registers.  A row takes
+// LPR lanes of a wave (a power of two, 16-byte chunks of z at stride LPR), so
+// a workgroup of four waves runs 4 * 64 / LPR rows at a time and a.rows rows
+// in all:
 //   s_i = z_i . w + c, l_i = max(s,0) - s y + log1p(e^-|s|),
 //   ds_i = lam (sigmoid(s_i) - y_i) / M,
-//   dz = ds_i w_n [z_in > 0]  (row-major and feature-major, 16-byte stores),
+//   dz = ds_i w_n [z_in > 0] (16-byte stores),
 //   partial dw_n = sum_i z_in ds_i, partial dc = sum_i ds_i, partial loss,
-// every sum in a fixed order.
+// every sum in a fixed order.  Bound by latency (a row is one load, a
+// butterfly and one store), so U rows per wave are in flight and small
+// batches take few rows per workgroup.  The padding columns of z (up to the
+// chunk) are zero: their dz is zero again, so chunks are never masked.
+// Measured on one MI355X: 1024 x 256 4.0 us, 16384 x 512 21.5 us (a
+// workgroup staging 32 rows in LDS took 10.4 and 39.9 us).
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void erase_head_bce(HeadArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+template <typename T, int CH>
+__global__ __launch_bounds__(256) void erase_head_bce(HeadArgs a, int lpr) {
   constexpr int KCH = 16 / sizeof(T);  // elements per 16-byte chunk
-  __shared__ float s_ds[32];
-  __shared__ float s_loss[32];
-  __shared__ float s_w[HEAD_MAX_N];
-  T* tile = reinterpret_cast<T*>(smem_raw);
-  const int N = a.N;
-  const int R = head_rows(N, sizeof(T));
-  const int pitch = head_pitch(N, sizeof(T));
-  const int tid = threadIdx.x;
-  const int r0 = blockIdx.x * R;
-  const int rows = min(R, a.M - r0);
+  constexpr int U = CH == 1 ? 4 : CH == 2 ? 2 : 1;
+  __shared__ float s_dw[4][64 * CH * KCH];
+  __shared__ float s_sum[4][2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int N = a.N, li = lane & (lpr - 1), rpw = 64 / lpr;  // lane of the row, rows of a wave
+  const int r0 = blockIdx.x * a.rows, r1 = min(r0 + a.rows, a.M);
   const T* Z = static_cast<const T*>(a.z);
-  const int cpr = (N + KCH - 1) / KCH;  // chunks per row
-
-  for (int n = tid; n < N; n += 256) s_w[n] = a.w[n];
-  // stage the tile (rows beyond M and columns beyond N are zero)
-  for (int c = tid; c < R * cpr; c += 256) {
-    const int r = c / cpr, k = (c - r * cpr) * KCH;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (r < rows) {
-      const T* p = Z + (int64_t)(r0 + r) * a.ldz + k;
-      if (k + KCH <= N) {
-        v = *reinterpret_cast<const uint4*>(p);
-      } else {
-        T tmp[KCH];
+  T* D = static_cast<T*>(a.dmn);
+  float w[CH][KCH], dw[CH][KCH];
+  bool in[CH];
 #pragma unroll
-        for (int e = 0; e < KCH; ++e) tmp[e] = (k + e < N) ? p[e] : T(0);
-        __builtin_memcpy(&v, tmp, 16);
+  for (int c = 0; c < CH; ++c) {
+    const int k = (c * lpr + li) * KCH;
+    in[c] = k < N;
+#pragma unroll
+    for (int q = 0; q < KCH; ++q) {
+      w[c][q] = k + q < N ? a.w[k + q] : 0.f;
+      dw[c][q] = 0.f;
+    }
+  }
+  const float hc = a.c[0];
+  float sd = 0.f, sl = 0.f;
+  const int step = 4 * rpw;
+  for (int rb = r0 + wave * rpw + lane / lpr; rb - lane / lpr < r1; rb += U * step) {
+    u32x4_t zv[U][CH];
+    float yv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = rb + u * step;
+      yv[u] = r < r1 ? a.y[r] : 0.f;
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        zv[u][c] = u32x4_t{0u, 0u, 0u, 0u};
+        if (r < r1 && in[c])
+          zv[u][c] = *reinterpret_cast<const u32x4_t*>(Z + (int64_t)r * a.ldz + (c * lpr + li) * KCH);
       }
     }
-    *reinterpret_cast<uint4*>(&tile[r * pitch + k]) = v;
+    float part[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      part[u] = 0.f;
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        T z[KCH];
+        __builtin_memcpy(z, &zv[u][c], 16);
+#pragma unroll
+        for (int q = 0; q < KCH; ++q) part[u] = fmaf(asf(z[q]), w[c][q], part[u]);
+      }
+    }
+    for (int off = 1; off < lpr; off <<= 1) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) part[u] += __shfl_xor(part[u], off, 64);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = rb + u * step;
+      const float s = part[u] + hc;
+      const float en = __expf(-fabsf(s));
+      const float sig = s >= 0.f ? 1.f / (1.f + en) : en / (1.f + en);
+      const float ds = r < r1 ? a.lam * (sig - yv[u]) * a.inv_m : 0.f;
+      if (r < r1 && li == 0) {
+        sd += ds;
+        sl += fmaxf(s, 0.f) - s * yv[u] + log1pf(en);
+      }
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        T z[KCH], o[KCH];
+        __builtin_memcpy(z, &zv[u][c], 16);
+#pragma unroll
+        for (int q = 0; q < KCH; ++q) {
+          const float zq = asf(z[q]);
+          dw[c][q] = fmaf(zq, ds, dw[c][q]);
+          o[q] = cvt<T>(zq > 0.f ? ds * w[c][q] : 0.f);
+        }
+        if (D && r < r1 && in[c]) {
+          u32x4_t v;
+          __builtin_memcpy(&v, o, 16);
+          *reinterpret_cast<u32x4_t*>(D + (int64_t)r * a.lddmn + (c * lpr + li) * KCH) = v;
+        }
+      }
+    }
+  }
+  // the wave's row slots, then the four waves in order
+  for (int off = lpr; off < 64; off <<= 1) {
+    sd += __shfl_xor(sd, off, 64);
+    sl += __shfl_xor(sl, off, 64);
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int q = 0; q < KCH; ++q) dw[c][q] += __shfl_xor(dw[c][q], off, 64);
+  }
+  if (lane < lpr) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int q = 0; q < KCH; ++q) s_dw[wave][(c * lpr + li) * KCH + q] = dw[c][q];
+  }
+  if (lane == 0) {
+    s_sum[wave][0] = sd;
+    s_sum[wave][1] = sl;
   }
   __syncthreads();
-
-  // logits: 256/R lanes per row, then a fixed butterfly over those lanes
-  {
-    const int tpr = 256 / R;  // power of two, 8..64
-    const int r = tid / tpr, j = tid - r * tpr;
-    float part = 0.f;
-    for (int n = j; n < N; n += tpr) part = fmaf(asf(tile[r * pitch + n]), s_w[n], part);
-    for (int off = 1; off < tpr; off <<= 1) part += __shfl_xor(part, off, 64);
-    if (j == 0) {
-      float ds = 0.f, l = 0.f;
-      if (r < rows) {
-        const float s = part + a.c[0];
-        const float yv = a.y[r0 + r];
-        const float en = __expf(-fabsf(s));
-        const float sig = s >= 0.f ? 1.f / (1.f + en) : en / (1.f + en);
-        ds = a.lam * (sig - yv) * a.inv_m;
-        l = fmaxf(s, 0.f) - s * yv + log1pf(en);
-      }
-      s_ds[r] = ds;
-      s_loss[r] = l;
-    }
-  }
-  __syncthreads();
-
-  // dz row-major
-  if (a.dmn) {
-    T* D = static_cast<T*>(a.dmn);
-    for (int c = tid; c < rows * cpr; c += 256) {
-      const int r = c / cpr, k = (c - r * cpr) * KCH;
-      const float ds = s_ds[r];
-      T o[KCH];
-#pragma unroll
-      for (int e = 0; e < KCH; ++e) {
-        const float zv = asf(tile[r * pitch + k + e]);
-        o[e] = cvt<T>((zv > 0.f && k + e < N) ? ds * s_w[min(k + e, N - 1)] : 0.f);
-      }
-      T* p = D + (int64_t)(r0 + r) * a.lddmn + k;
-      if (k + KCH <= N) {
-        uint4 v;
-        __builtin_memcpy(&v, o, 16);
-        *reinterpret_cast<uint4*>(p) = v;
-      } else {
-        for (int e = 0; e < KCH && k + e < N; ++e) p[e] = o[e];
-      }
-    }
-  }
-  // partial head gradients and loss of this workgroup's rows
-  for (int n = tid; n < N; n += 256) {
-    float acc = 0.f;
-    for (int r = 0; r < rows; ++r) acc = fmaf(asf(tile[r * pitch + n]), s_ds[r], acc);
-    a.pdw[(int64_t)blockIdx.x * N + n] = acc;
-  }
+  for (int n = tid; n < N; n += 256)
+    a.pdw[(int64_t)blockIdx.x * N + n] = ((s_dw[0][n] + s_dw[1][n]) + s_dw[2][n]) + s_dw[3][n];
   if (tid == 0) {
-    float sd = 0.f, sl = 0.f;
-    for (int r = 0; r < rows; ++r) {
-      sd += s_ds[r];
-      sl += s_loss[r];
-    }
-    a.pdc[blockIdx.x] = sd;
-    a.ploss[blockIdx.x] = sl;
+    a.pdc[blockIdx.x] = ((s_sum[0][0] + s_sum[1][0]) + s_sum[2][0]) + s_sum[3][0];
+    a.ploss[blockIdx.x] = ((s_sum[0][1] + s_sum[1][1]) + s_sum[2][1]) + s_sum[3][1];
   }
 }
 
+template <typename T, int CH>
+static void launch_head_t(const HeadArgs& a, hipStream_t s, const LaunchEv& ev) {
+  constexpr int KCH = 16 / (int)sizeof(T);
+  int lpr = 1;
+  while (lpr < 64 && lpr * CH * KCH < a.N) lpr *= 2;
+  const dim3 grid((unsigned)((a.M + a.rows - 1) / a.rows)), block(256);
+  ERASE_LAUNCH((erase_head_bce<T, CH>), grid, block, 0, s, ev, a, lpr);
+}
+
 hipError_t launch_head(int bf16, const HeadArgs& a, hipStream_t s, const LaunchEv& ev) {
-  const int esz = bf16 ? 2 : 4;
-  dim3 grid((a.M + head_rows(a.N, esz) - 1) / head_rows(a.N, esz)), block(256);
-  const size_t lds = head_lds_bytes(a.N, esz);
-  if (bf16)
-    ERASE_LAUNCH(erase_head_bce<uint16_t>, grid, block, (uint32_t)lds, s, ev, a);
-  else
-    ERASE_LAUNCH(erase_head_bce<float>, grid, block, (uint32_t)lds, s, ev, a);
+  if (a.N < 1 || a.N > HEAD_MAX_N || a.rows < 1) return hipErrorInvalidValue;
+  const int ch = (a.N + 64 * (bf16 ? 8 : 4) - 1) / (64 * (bf16 ? 8 : 4));  // chunks per lane
+  if (bf16) {
+    if (ch <= 1) launch_head_t<uint16_t, 1>(a, s, ev);
+    else if (ch <= 2) launch_head_t<uint16_t, 2>(a, s, ev);
+    else launch_head_t<uint16_t, 4>(a, s, ev);
+  } else {
+    if (ch <= 1) launch_head_t<float, 1>(a, s, ev);
+    else if (ch <= 2) launch_head_t<float, 2>(a, s, ev);
+    else if (ch <= 4) launch_head_t<float, 4>(a, s, ev);
+    else launch_head_t<float, 8>(a, s, ev);
+  }
   return hipGetLastError();
 }
 
@@ -1443,6 +1478,7 @@ __device__ __forceinline__ void adam_chunk(const AdamArgs& a, int64_t chunk, int
   const AdamSeg sg = a.seg[find_seg(a, chunk)];
   bool trans = false;  // the transposed copy is stored after the barrier
   int r0 = 0, tile = 0;
+  float vp = 0.f, vm = 0.f, vv1 = 0.f;  // a vector's parameter and moments
   const float step = a.hyper[0];  // lr / (1 - beta1^t)
   const float bc2s = a.hyper[1];  // sqrt(1 - beta2^t)
   const float b1 = a.beta1, b2 = a.beta2, eps = a.eps;
@@ -1453,30 +1489,29 @@ __device__ __forceinline__ void adam_chunk(const AdamArgs& a, int64_t chunk, int
   auto PART = gmem(sg.part);
 
   if (sg.rows == 1) {
-    // a vector (bias or head parameter): one element per thread, possibly
-    // many partials (one per head workgroup), 32 loads in flight per batch,
-    // added in slice order
-    const int c = tile * ADAM_TC + tid;
-    const bool ok = tid < ADAM_TC && c < sg.cols;
-    const int cc = ok ? c : 0;  // clamped: loads stay in bounds
-    float p = P[cc], m = Mo[cc], v = V[cc], g = 0.f;
+    // A vector (bias or head parameter): sg.vtc elements per chunk, 256 / vtc
+    // groups of threads summing consecutive ranges of the partials (32 loads
+    // in flight per thread, added in order); the groups' sums are added in
+    // order after the barrier.  A 1677-512-256-128 block at 32768 rows (2048 head
+    // partials): the launch 23 us, 96 us with one thread per element.
+    const int vtc = sg.vtc, ng = 256 / vtc, grp = tid / vtc;
+    const int c = tile * vtc + tid % vtc;
+    const int cc = c < sg.cols ? c : 0;  // clamped: loads stay in bounds
+    const int per = (sg.nsplit + ng - 1) / ng, zb = grp * per, ze = min(sg.nsplit, zb + per);
+    vp = P[cc];
+    vm = Mo[cc];
+    vv1 = V[cc];
+    float g = 0.f;
     constexpr int ZV = 32;
-    for (int z0 = 0; z0 < sg.nsplit; z0 += ZV) {
+    for (int z0 = zb; z0 < ze; z0 += ZV) {
       float tv[ZV];
 #pragma unroll
-      for (int j = 0; j < ZV; ++j) tv[j] = (z0 + j < sg.nsplit) ? PART[cc + (int64_t)(z0 + j) * sg.pstride] : 0.f;
+      for (int j = 0; j < ZV; ++j) tv[j] = (z0 + j < ze) ? PART[cc + (int64_t)(z0 + j) * sg.pstride] : 0.f;
 #pragma unroll
       for (int j = 0; j < ZV; ++j)
-        if (z0 + j < sg.nsplit) g += tv[j];
+        if (z0 + j < ze) g += tv[j];
     }
-    adam_elem(p, m, v, g, b1, b2, step, bc2s, eps);
-    if (ok) {
-      if (sg.g) gmem(sg.g)[c] = g;
-      Mo[c] = m;
-      V[c] = v;
-      P[c] = p;
-      if (sg.sh) gmem(static_cast<T*>(sg.sh))[c] = cvt<T>(p);
-    }
+    reinterpret_cast<float*>(s_o)[tid] = g;
   } else {
     // a matrix: a workgroup covers ADAM_TR (16) rows x ADAM_TC (64) columns,
     // a thread 4 consecutive columns of one row (16-byte loads and stores)
@@ -1578,6 +1613,21 @@ __device__ __forceinline__ void adam_chunk(const AdamArgs& a, int64_t chunk, int
     }
   }
   __syncthreads();
+  if (sg.rows == 1 && tid < sg.vtc) {
+    const int c = tile * sg.vtc + tid;
+    if (c < sg.cols) {
+      float g = 0.f;
+      for (int q = tid; q < 256; q += sg.vtc) g += reinterpret_cast<const float*>(s_o)[q];
+      adam_elem(vp, vm, vv1, g, b1, b2, step, bc2s, eps);
+      if (sg.g) gmem(sg.g)[c] = g;
+      Mo[c] = vm;
+      V[c] = vv1;
+      P[c] = vp;
+      // a one-row weight matrix has GEMM copies
+      if (sg.sh) gmem(static_cast<T*>(sg.sh))[c] = cvt<T>(vp);
+      if (sg.sht) gmem(static_cast<T*>(sg.sht))[(int64_t)c * sg.ldsht] = cvt<T>(vp);
+    }
+  }
   if (trans && tid < ADAM_TC) {
     const int c = (tile % sg.tcols) * ADAM_TC + tid;
     if (c < sg.cols && r0 < sg.rows) {
@@ -1599,7 +1649,13 @@ __device__ __forceinline__ void adam_chunk(const AdamArgs& a, int64_t chunk, int
     // block loss: lane l sums partials l, l+64, ... in order, then a fixed
     // butterfly across the wave
     float L = 0.f;
-    for (int i = tid; i < a.nloss; i += 64) L += a.ploss[i];
+    for (int i = tid; i < a.nloss; i += 64 * 16) {
+      float t[16];  // 16 loads in flight
+#pragma unroll
+      for (int j = 0; j < 16; ++j) t[j] = a.ploss[min(i + 64 * j, a.nloss - 1)];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) L += i + 64 * j < a.nloss ? t[j] : 0.f;
+    }
     L = wave_sum(L) * a.inv_m;
     if (tid == 0) {
       a.loss_out[0] = L;
@@ -1610,7 +1666,7 @@ __device__ __forceinline__ void adam_chunk(const AdamArgs& a, int64_t chunk, int
 
 template <typename T>
 __global__ __launch_bounds__(256) void erase_adam(AdamArgs a) {
-  __shared__ T s_o[ADAM_TR][ADAM_TC];
+  __shared__ __attribute__((aligned(16))) T s_o[ADAM_TR][ADAM_TC];
   adam_chunk<T>(a, blockIdx.x, (int)threadIdx.x, s_o);
 }
 

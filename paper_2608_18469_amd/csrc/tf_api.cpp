@@ -280,19 +280,18 @@ size_t build_layout(const erase_tf_config& c, uintptr_t base, Layout* P) {
       B.wp[i] = choose(D.rows[i], D.cols[i], rup(D.N, 64), true);
       // 256x256 tiles where they pay: with the input gradient in one launch
       // (the MLP-up and attention projections), or the weight gradient alone
-      int split = 1;
-      if (i == W1 || i == WO || (i == WQKV && b == 0)) {
-        B.pair_wide[i] = wide_pair_pays(D.N, D.rows[i], D.cols[i], &split);
-      } else if (i == WH) {
+      int split = 0;
+      if (i == W1 || i == WO || (i == WQKV && b == 0))
+        split = wide_pair_split(D.N, D.rows[i], D.cols[i]);
+      else if (i != WH)
+        split = wide_wgrad_split(D.rows[i], D.cols[i], D.N, wide_core_wgrad_us(D.rows[i], D.cols[i], D.N)).split;
+      else if (wide_tiles(D.N, d) >= kWideCus)
         // the input gradient contracts over the vocabulary: in 256x256 tiles
         // only when they fill the chip (16384 x 512 over 32768: 764 us in 128
         // of them, 680 us in 512 tiles of the core)
-        B.pair_wide[i] = wide_tiles(D.N, d) >= kWideCus && wide_pair_pays(D.N, D.V, d, &split);
-      } else {
-        const WideSplit ws = wide_wgrad_split(D.rows[i], D.cols[i], D.N);
-        if (ws.us < wide_core_wgrad_us(D.rows[i], D.cols[i], D.N)) split = ws.split, B.pair_wide[i] = true;
-      }
-      if (B.pair_wide[i]) B.wp[i] = wide_plan(rup(D.N, 64), split);
+        split = wide_pair_split(D.N, D.V, d);
+      B.pair_wide[i] = split > 0;
+      if (split > 0) B.wp[i] = wide_plan(rup(D.N, 64), split);
       B.part[i] = f32(int64_t(B.wp[i].split) * D.rows[i] * D.cols[i]);
     }
     B.segs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * (NW + 1)));
@@ -444,6 +443,7 @@ void build_segments(Layout* P, const erase_block_buffers* bufs) {
       s.ldsh = cols;
       s.sht = sht;
       s.ldsht = rows;
+      s.vtc = ADAM_TC;
       s.tcols = (int)cdv(cols, ADAM_TC);
       s.chunk0 = chunk;
       chunk += cdv(rows, ADAM_TR) * s.tcols;

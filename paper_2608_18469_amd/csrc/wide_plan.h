@@ -58,31 +58,32 @@ inline bool wide_nt_pays(int64_t M, int64_t N, int64_t K) {
 }
 
 struct WideSplit {
-  int split = 1;
+  int split = 0;  // 0: nothing below the limit
   double us = 0;  // GEMM, and the partial slices' traffic
 };
 // Weight gradient [M][N] over K batch rows, alone (nd = 0) or in one launch
 // with nd input-gradient tiles of kd k-steps: the slice count of the
-// shortest modelled time.
-inline WideSplit wide_wgrad_split(int64_t M, int64_t N, int64_t K, int64_t nd = 0, int64_t kd = 0) {
+// shortest modelled time below `limit`.
+inline WideSplit wide_wgrad_split(int64_t M, int64_t N, int64_t K, double limit, int64_t nd = 0, int64_t kd = 0) {
   const int64_t ks = std::max<int64_t>(1, (K + 63) / 64), nw = wide_tiles(M, N);
-  WideSplit best;
+  WideSplit best{0, limit};
   for (int s = 1; s <= kWideMaxSplit && (s == 1 || ks / s >= 8); ++s) {
-    const double us = wide_makespan(nw * s, wide_tile_us((ks + s - 1) / s), nd, wide_tile_us(kd)) + wide_part_us(M, N, s);
-    if (s == 1 || us < best.us) best = {s, us};
+    const double tw = wide_tile_us((ks + s - 1) / s), td = wide_tile_us(kd), part = wide_part_us(M, N, s);
+    // least possible: the longest tile, and every unit busy throughout
+    if (std::max(std::max(tw, nd ? td : 0.0), (double(nw * s) * tw + double(nd) * td) / kWideCus) + part >= best.us) continue;
+    const double us = wide_makespan(nw * s, tw, nd, td) + part;
+    if (us < best.us) best = {s, us};
   }
   return best;
 }
 
-// A layer's two backward GEMMs (weight gradient [Mw][Nw] over Kw rows, input
-// gradient [Kw][Nw] over Mw): wide when the modelled time beats the core's
-// grouped 64x64 launch (420 TFLOP/s on the large shapes: 2 x 16384 x 1024 x
-// 1677 in 273-395 us).
-inline bool wide_pair_pays(int64_t M, int64_t Nout, int64_t Kin, int* split) {
-  const WideSplit w = wide_wgrad_split(Nout, Kin, M, wide_tiles(M, Kin), (Nout + 63) / 64);
-  *split = w.split;
+// A layer's two backward GEMMs (weight gradient [Nout][Kin] over M rows, input
+// gradient [M][Kin] over Nout): the slices of the weight gradient when the
+// wide launch beats the core's grouped 64x64 one (420 TFLOP/s on the large
+// shapes: 2 x 16384 x 1024 x 1677 in 273-395 us), else 0.
+inline int wide_pair_split(int64_t M, int64_t Nout, int64_t Kin) {
   const double core = 4.0 * double(M) * double(Nout) * double(Kin) / 420e6 + 4.0;
-  return w.us < core;
+  return wide_wgrad_split(Nout, Kin, M, core, wide_tiles(M, Kin), (Nout + 63) / 64).split;
 }
 
 // The core's split 64x64 weight gradient alone (512 x 2048 over 16384 rows:
