@@ -5,6 +5,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 
 #include "internal.h"
@@ -140,6 +141,70 @@ __device__ __forceinline__ void lds_dma16(const void* src, uint32_t lds) {
 // lane's 32-bit byte offset from it (no 64-bit address per lane and load).
 __device__ __forceinline__ void lds_dma16s(const void* base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+
+
+// Arguments of a batched launch (BlockJob in device memory, written at
+// init): scalar loads through the constant address space, pointers typed as
+// global so that every access through them takes the global path.
+typedef const __attribute__((address_space(4))) char* cmem_t;
+template <typename T>
+__device__ __forceinline__ void ld_field(cmem_t p, T& v) {
+  v = *reinterpret_cast<const __attribute__((address_space(4))) T*>(p);
+}
+template <typename T>
+__device__ __forceinline__ void ld_field(cmem_t p, T*& v) {
+  typedef __attribute__((address_space(1))) T* gptr;
+  v = (T*)*reinterpret_cast<const __attribute__((address_space(4))) gptr*>(p);
+}
+__device__ __forceinline__ cmem_t job_of(const BlockJob* jobs) { return (cmem_t)(uintptr_t)(jobs + blockIdx.y); }
+#define ERASE_LD(S, F) ld_field(p + offsetof(S, F), v.F)
+__device__ __forceinline__ void ld_gemm(cmem_t p, GemmDesc& v, const StepPtrs& st) {
+  ERASE_LD(GemmDesc, A), ERASE_LD(GemmDesc, lda), ERASE_LD(GemmDesc, B), ERASE_LD(GemmDesc, ldb);
+  ERASE_LD(GemmDesc, M), ERASE_LD(GemmDesc, N), ERASE_LD(GemmDesc, K), ERASE_LD(GemmDesc, kps);
+  ERASE_LD(GemmDesc, split), ERASE_LD(GemmDesc, bm), ERASE_LD(GemmDesc, bn), ERASE_LD(GemmDesc, group);
+  ERASE_LD(GemmDesc, kgroups);
+  if (v.A == reinterpret_cast<const void*>(uintptr_t(16))) v.A = st.x;
+  if (v.B == reinterpret_cast<const void*>(uintptr_t(16))) v.B = st.x;
+}
+__device__ __forceinline__ void ld_epi(cmem_t p, EpiParams& v, const StepPtrs& st) {
+  ERASE_LD(EpiParams, bias), ERASE_LD(EpiParams, y), ERASE_LD(EpiParams, ldy), ERASE_LD(EpiParams, x0);
+  ERASE_LD(EpiParams, ldx0), ERASE_LD(EpiParams, xl), ERASE_LD(EpiParams, ldxl), ERASE_LD(EpiParams, part);
+  ERASE_LD(EpiParams, ldp), ERASE_LD(EpiParams, pstride), ERASE_LD(EpiParams, bpart), ERASE_LD(EpiParams, res);
+  ERASE_LD(EpiParams, ldres), ERASE_LD(EpiParams, mask), ERASE_LD(EpiParams, ldmask), ERASE_LD(EpiParams, gout);
+  ERASE_LD(EpiParams, ldgout), ERASE_LD(EpiParams, dmn), ERASE_LD(EpiParams, lddmn);
+  ERASE_LD(EpiParams, below_cross), ERASE_LD(EpiParams, hw), ERASE_LD(EpiParams, hc), ERASE_LD(EpiParams, lam);
+  ERASE_LD(EpiParams, inv_m), ERASE_LD(EpiParams, pdw), ERASE_LD(EpiParams, pdc), ERASE_LD(EpiParams, ploss);
+  ERASE_LD(EpiParams, ap), ERASE_LD(EpiParams, am), ERASE_LD(EpiParams, av), ERASE_LD(EpiParams, ag);
+  ERASE_LD(EpiParams, ash), ERASE_LD(EpiParams, ldash), ERASE_LD(EpiParams, b1), ERASE_LD(EpiParams, b2);
+  ERASE_LD(EpiParams, eps), ERASE_LD(EpiParams, bp), ERASE_LD(EpiParams, bm), ERASE_LD(EpiParams, bv);
+  ERASE_LD(EpiParams, bg);
+  v.labels = st.labels;
+  v.hyper = st.hyper;
+  if (v.x0 == reinterpret_cast<const void*>(uintptr_t(16))) v.x0 = st.x;
+  if (v.xl == reinterpret_cast<const void*>(uintptr_t(16))) v.xl = st.x;
+}
+// (not the first chunks of the segments: adam_chunk's search reads them
+// from the table)
+__device__ __forceinline__ void ld_adam(cmem_t p, AdamArgs& v, const StepPtrs& st, int64_t block) {
+  ERASE_LD(AdamArgs, seg), ERASE_LD(AdamArgs, nseg), ERASE_LD(AdamArgs, nchunks), ERASE_LD(AdamArgs, beta1);
+  ERASE_LD(AdamArgs, beta2), ERASE_LD(AdamArgs, eps), ERASE_LD(AdamArgs, ploss), ERASE_LD(AdamArgs, nloss);
+  ERASE_LD(AdamArgs, inv_m), ERASE_LD(AdamArgs, status);
+  v.hyper = st.hyper;
+  v.loss_out = st.losses + block;
+}
+__device__ __forceinline__ void ld_head(cmem_t p, HeadArgs& v, const StepPtrs& st) {
+  ERASE_LD(HeadArgs, z), ERASE_LD(HeadArgs, ldz), ERASE_LD(HeadArgs, w), ERASE_LD(HeadArgs, c);
+  ERASE_LD(HeadArgs, lam), ERASE_LD(HeadArgs, inv_m), ERASE_LD(HeadArgs, M), ERASE_LD(HeadArgs, N);
+  ERASE_LD(HeadArgs, rows), ERASE_LD(HeadArgs, dmn), ERASE_LD(HeadArgs, lddmn), ERASE_LD(HeadArgs, pdw);
+  ERASE_LD(HeadArgs, pdc), ERASE_LD(HeadArgs, ploss);
+  v.y = st.labels;
+}
+#undef ERASE_LD
+__device__ __forceinline__ int64_t ld_block(cmem_t j) {
+  int64_t b;
+  ld_field(j + offsetof(BlockJob, block), b);
+  return b;
 }
 
 }  // namespace erase

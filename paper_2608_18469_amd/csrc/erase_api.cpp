@@ -127,7 +127,9 @@ struct LayerRT {
   float* part = nullptr; int64_t ldp = 0, pstride = 0;
   float* bpart = nullptr;
   GemmPlan fwd, wgrad, dgrad;
-  bool grouped = false;  // input- and weight-gradient GEMMs share one launch
+  // input- and weight-gradient GEMMs share one launch (a block's first layer:
+  // in the undetached schedule)
+  bool grouped = false;
   // Adam of the weight matrix fused into its (standalone, unsplit, two
   // k-group) weight-gradient launch
   bool fused_adam = false;
@@ -154,7 +156,26 @@ struct BlockRT {
   erase_block_buffers buf{};
 };
 
+// Consecutive blocks of equal shape that share launches (jobs: the arguments
+// of launch slot i of member j at jobs[i n + j], device memory; null: a
+// single block).  Their backward is independent block by block (the block
+// inputs are detached); they share the forward too when they read x and feed
+// no later block.
+struct Group {
+  int first = 0, n = 1;
+  bool share_fwd = false;
+  BlockJob* jobs = nullptr;
+};
+// Consecutive blocks handed to a backward stream together.
+struct Unit {
+  int first = 0, n = 1;
+  std::vector<Group> groups;
+};
+
 struct Plan {
+  Unit serial;                // every block (the schedules on one stream)
+  std::vector<Unit> overlap;  // the ERASE schedules' units
+  std::vector<BlockJob> jobs_host;  // the tables as uploaded (the copies are asynchronous)
   int bf16 = 1, esz = 2, M = 0;
   bool undet_ok = true;  // every chained block can send its input gradient back
   int64_t Mr = 0;   // allocated rows of row-major arrays: roundup(M, 128)
@@ -168,6 +189,12 @@ struct Plan {
   std::vector<BlockRT> blk;
   size_t bytes = 0;
 };
+
+template <class F>
+void for_each_unit(Plan* P, F&& f) {
+  f(P->serial);
+  for (Unit& u : P->overlap) f(u);
+}
 
 struct Carver {
   uintptr_t base;
@@ -233,6 +260,72 @@ GemmPlan wide_plan(int64_t Kc, int split) {
   p.kps = (int)roundup(cdiv(std::max<int64_t>(Kc, 1), split), 64);
   p.split = (int)cdiv(std::max<int64_t>(Kc, 1), p.kps);
   return p;
+}
+
+// Launch slots of a block: forward layer l at l, the head at L, the backward
+// launches of layer l at L + 1 + 2 l (and + 1, its input gradient alone),
+// Adam at 3 L + 1.
+int job_slots(int L) { return 3 * L + 2; }
+
+bool feeds_next(const erase_config& c, int b) {
+  return b + 1 < c.n_blocks && c.blocks[b + 1].input_src == ERASE_IN_PREV;
+}
+
+// Blocks a and b take equal backward launches (their lambdas may differ).
+bool same_launches(const erase_config& c, int a, int b) {
+  const erase_block_spec &A = c.blocks[a], &B = c.blocks[b];
+  if (A.input_src != B.input_src || A.n_layers != B.n_layers) return false;
+  for (int l = 0; l < A.n_layers; ++l)
+    if (A.layers[l].kind != B.layers[l].kind || A.layers[l].in_dim != B.layers[l].in_dim ||
+        A.layers[l].out_dim != B.layers[l].out_dim)
+      return false;
+  return true;
+}
+
+// The unit of blocks [first, first + n): runs of equal launches as groups.
+Unit make_unit(const erase_config& c, int first, int n) {
+  Unit u;
+  u.first = first;
+  u.n = n;
+  for (int b = first; b < first + n;) {
+    Group g;
+    g.first = b;
+    while (b + g.n < first + n && same_launches(c, b, b + g.n)) ++g.n;
+    g.share_fwd = g.n > 1 && c.blocks[b].input_src == ERASE_IN_X;
+    for (int i = 0; i < g.n; ++i) g.share_fwd = g.share_fwd && !feeds_next(c, b + i);
+    u.groups.push_back(g);
+    b += g.n;
+  }
+  return u;
+}
+
+// Units of at most `cap` blocks: runs of equal launches on x, and runs of a
+// chain.
+std::vector<Unit> make_units(const erase_config& c, int cap) {
+  std::vector<Unit> us;
+  for (int b = 0; b < c.n_blocks;) {
+    int n = 1;
+    while (b + n < c.n_blocks && n < cap &&
+           (c.blocks[b + n].input_src == ERASE_IN_PREV || (same_launches(c, b, b + n) && !feeds_next(c, b + n))))
+      ++n;
+    us.push_back(make_unit(c, b, n));
+    b += n;
+  }
+  return us;
+}
+
+// Most blocks of an ERASE unit.  A handoff to a backward stream costs the host
+// about 13 us (hipStreamWaitEvent) and a launch 3 us, so blocks are handed
+// over in groups, a third of the network at most: the backward of one group
+// then still runs beside the forward of the next.  A network whose whole step
+// is below 0.1 GFLOP is one unit (its launches cost the host more than the
+// device).
+int erase_unit_cap(const erase_config& c) {
+  double flops = 0;
+  for (int b = 0; b < c.n_blocks; ++b)
+    for (int l = 0; l < c.blocks[b].n_layers; ++l)
+      flops += 6.0 * c.batch * double(c.blocks[b].layers[l].in_dim) * c.blocks[b].layers[l].out_dim;
+  return flops < 1e8 ? c.n_blocks : std::max(1, c.n_blocks / 3);
 }
 
 size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
@@ -308,6 +401,7 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
         R.dgrad = choose_gemm(P->bf16, M, R.K, roundup(R.N, BK), false);
         if (P->bf16 && wide_nt_pays(M, R.K, R.N)) R.dgrad = wide_plan(roundup(R.N, 64), 1);
         R.dgrad.group = xcd_group((int)cdiv(M, R.dgrad.bm), (int)cdiv(R.K, R.dgrad.bn), 1, R.dgrad.bm, R.dgrad.bn);
+        R.dgrad.kgroups = 1;
       }
       if (l >= 1) {
         R.dgrad = choose_gemm(P->bf16, M, R.K, roundup(R.N, BK), false);
@@ -377,6 +471,8 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
         R.wgrad.kgroups = 2;
         R.wgrad.group = xcd_group((int)cdiv(R.N, 64), (int)cdiv(R.K, 64), 1, 64, 64);
       }
+      if (l == 0 && dgrad)
+        R.grouped = R.dgrad.bm == R.wgrad.bm && R.dgrad.bn == R.wgrad.bn && R.dgrad.bm == R.dgrad.bn;
       R.part = static_cast<float*>(cv.take(size_t(R.wgrad.split) * R.pstride * 4));
       R.bpart = static_cast<float*>(cv.take(size_t(R.wgrad.split) * R.N * 4));
     }
@@ -418,6 +514,13 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
     B.segs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * nseg));
     B.rsegs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * nseg));
   }
+  P->serial = make_unit(c, 0, c.n_blocks);
+  P->overlap = make_units(c, erase_unit_cap(c));
+  for_each_unit(P, [&](Unit& u) {
+    for (Group& g : u.groups)
+      if (g.n > 1)
+        g.jobs = static_cast<BlockJob*>(cv.take(sizeof(BlockJob) * job_slots(c.blocks[g.first].n_layers) * g.n));
+  });
   P->bytes = cv.off;
   return cv.off;
 }
@@ -590,7 +693,7 @@ struct Ctx {
   hipStream_t sf = nullptr;
   std::vector<hipStream_t> sbs;  // backward streams; block b uses sbs[b % size]
   int device = 0;
-  std::vector<hipEvent_t> ef, eb;
+  std::vector<hipEvent_t> ef, eb;  // per unit of the ERASE schedules: end of its forward, of its backward
   erase_status sticky = ERASE_OK;
   std::string err;
   std::vector<GraphEntry> graphs;
@@ -604,8 +707,8 @@ struct Ctx {
   int par = 0;           // parity of the step being enqueued
   bool pending = false;  // a PIPELINE step left backward work unjoined
   // worker dispatch: the backward streams' launches are enqueued by
-  // `worker` (created on first use); job_of[b] is the job that enqueued
-  // block b's backward most recently
+  // `worker` (created on first use); job_of[i] is the job that enqueued unit
+  // i's backward most recently
   bool use_worker = false;
   std::unique_ptr<Worker> worker;
   std::vector<uint64_t> job_of;
@@ -717,11 +820,12 @@ class Enqueuer {
     return ERASE_OK;
   }
   std::vector<TimedLaunch>& launches() { return out_; }
-  // Stream-ordering event to be recorded by the launches that follow, at
-  // each kernel's end (in place of a record after them, which costs a packet
-  // of its own on the stream); none while timing (the launches carry their
-  // timing events) or under graph capture.  end_recorded() tells whether a
-  // launch took it since set_end.
+  // Stream-ordering event to be recorded by the launch that follows, at the
+  // kernel's end (in place of a record after it, which costs a packet of its
+  // own on the stream; a launch with an event costs the host about 1.5 us more
+  // than one without); none while timing (the launches carry their timing
+  // events) or under graph capture.  end_recorded() tells whether a launch
+  // took it since set_end.
   void set_end(hipEvent_t e) {
     end_ = ends_ok_ ? e : nullptr;
     end_used_ = false;
@@ -744,21 +848,40 @@ class Enqueuer {
     if (st_ != ERASE_OK) return st_;               \
   } while (0)
 
+// What a step brings: x as the GEMMs read it, labels, losses and the step's
+// Adam factors.
+struct StepIn {
+  const void* x;
+  int64_t ldx;
+  StepPtrs p;
+};
+StepIn step_in(const Ctx* c, const void* x, const float* labels, float* losses, int par) {
+  const Plan& P = c->P;
+  StepIn in;
+  in.x = P.x_in_place ? x : P.xp[par];
+  in.ldx = P.x_in_place ? c->cfg.x_ld : P.ldxp;
+  in.p = {in.x, labels, losses, reinterpret_cast<const float*>(P.t + 2) + 2 * par};
+  return in;
+}
+
+// One launch of one block: its kind and arguments.
+struct Op {
+  enum Type { GEMM, PAIR, WGRAD_ADAM, HEAD, ADAM } type = GEMM;
+  int tkind = 0, layer = -1, slot = 0, kind = 0;
+  Cost cost;
+  BlockJob j{};
+};
+
 // Input of layer l of block b (row-major).
-void layer_input(const Ctx* c, int b, int l, const void* x, int par, const void** mn, int64_t* ldmn) {
+void layer_input(const Ctx* c, int b, int l, const StepIn& in, const void** mn, int64_t* ldmn) {
   const Plan& P = c->P;
   const BlockRT& B = P.blk[b];
   if (l > 0) {
     *mn = B.layer[l - 1].y;
     *ldmn = B.layer[l - 1].ldy;
   } else if (B.input_src == ERASE_IN_X) {
-    if (P.x_in_place) {
-      *mn = x;
-      *ldmn = c->cfg.x_ld;
-    } else {
-      *mn = P.xp[par];
-      *ldmn = P.ldxp;
-    }
+    *mn = in.x;
+    *ldmn = in.ldx;
   } else {
     const BlockRT& A = P.blk[b - 1];
     const LayerRT& R = A.layer[A.L - 1];
@@ -767,28 +890,57 @@ void layer_input(const Ctx* c, int b, int l, const void* x, int par, const void*
   }
 }
 
-erase_status enqueue_head(Ctx* c, Enqueuer& q, int b, const float* labels, hipStream_t s, int sid);
-
-// Block b's forward GEMMs and, unless it is fused into the last GEMM or
-// `with_head` is false, its local head and loss.
-erase_status enqueue_forward(Ctx* c, Enqueuer& q, int b, const void* x, const float* labels, hipStream_t s, int sid,
-                             bool with_head = true, int l_begin = 0, int l_end = -1, int par = -1) {
+// Standalone local head, loss and loss gradient of block b (Section 2.1).
+template <class F>
+erase_status head_op(const Ctx* c, int b, const StepIn& in, F&& emit) {
   const Plan& P = c->P;
   const BlockRT& B = P.blk[b];
   const int M = P.M, esz = P.esz;
-  // (the worker thread passes the step parity it was given; c->par may
-  // already belong to the next step)
-  if (par < 0) par = c->par;
+  const LayerRT& Rl = B.layer[B.L - 1];
+  Op op;
+  op.type = Op::HEAD;
+  op.tkind = 2;
+  op.slot = B.L;
+  HeadArgs& h = op.j.h;
+  h.z = Rl.y;
+  h.ldz = Rl.ldy;
+  h.w = B.buf.param + B.off_w;
+  h.c = B.buf.param + B.off_c;
+  h.y = in.p.labels;
+  h.lam = B.lam;
+  h.inv_m = 1.0f / float(M);
+  h.M = M;
+  h.N = Rl.N;
+  h.rows = head_rows(M);
+  h.dmn = Rl.dmn;
+  h.lddmn = Rl.lddmn;
+  h.pdw = B.pdw;
+  h.pdc = B.pdc;
+  h.ploss = B.ploss;
+  op.cost.grid = B.nhead;
+  op.cost.flops = 4.0 * M * Rl.N;
+  op.cost.bytes =
+      double(esz) * M * Rl.N * (1 + 1 + (Rl.dmn ? 1 : 0)) + 4.0 * M + 4.0 * Rl.N + 4.0 * B.nhead * (Rl.N + 2);
+  return emit(op);
+}
+
+// Block b's forward GEMMs, layers [l_begin, l_end), and, unless it is fused
+// into the last GEMM or `with_head` is false, its local head and loss.
+template <class F>
+erase_status forward_ops(const Ctx* c, int b, const StepIn& in, bool with_head, int l_begin, int l_end, F&& emit) {
+  const Plan& P = c->P;
+  const BlockRT& B = P.blk[b];
+  const int M = P.M, esz = P.esz;
   const void* x0;
   int64_t ldx0;
-  layer_input(c, b, 0, x, par, &x0, &ldx0);
-  if (l_end < 0) l_end = B.L;
+  layer_input(c, b, 0, in, &x0, &ldx0);
   for (int l = l_begin; l < l_end; ++l) {
     const LayerRT& R = B.layer[l];
     const void* a;
     int64_t lda;
-    layer_input(c, b, l, x, par, &a, &lda);
-    GemmDesc g{};
+    layer_input(c, b, l, in, &a, &lda);
+    Op op;
+    GemmDesc& g = op.j.g;
     g.A = a;
     g.lda = lda;
     g.B = R.wsh;
@@ -802,28 +954,28 @@ erase_status enqueue_forward(Ctx* c, Enqueuer& q, int b, const void* x, const fl
     g.bn = R.fwd.bn;
     g.group = R.fwd.group;
     g.kgroups = R.fwd.kgroups;
-    EpiParams e{};
+    EpiParams& e = op.j.e;
     e.bias = B.buf.param + R.offb;
     e.y = R.y;
     e.ldy = R.ldy;
     const bool fused = B.head_fused && l == B.L - 1;
-    const int kind = R.kind == ERASE_LAYER_CROSS ? GK_FWD_CROSS : fused ? GK_FWD_HEAD : GK_FWD_RELU;
-    if (kind == GK_FWD_CROSS) {
+    op.kind = R.kind == ERASE_LAYER_CROSS ? GK_FWD_CROSS : fused ? GK_FWD_HEAD : GK_FWD_RELU;
+    if (op.kind == GK_FWD_CROSS) {
       e.x0 = x0;
       e.ldx0 = ldx0;
       e.xl = a;
       e.ldxl = lda;
     }
-    Cost cost = gemm_cost(g);
-    cost.flops = 2.0 * M * R.N * R.K;
-    cost.bytes = double(esz) * (double(M) * R.K + double(R.N) * R.K + double(M) * R.N) + 4.0 * R.N +
-                 (kind == GK_FWD_CROSS ? 2.0 * esz * M * R.N : 0.0);
+    op.cost = gemm_cost(g);
+    op.cost.flops = 2.0 * M * R.N * R.K;
+    op.cost.bytes = double(esz) * (double(M) * R.K + double(R.N) * R.K + double(M) * R.N) + 4.0 * R.N +
+                    (op.kind == GK_FWD_CROSS ? 2.0 * esz * M * R.N : 0.0);
     if (fused) {
       // z leaves the chip only when the next block reads it
       if (!R.needy) e.y = nullptr;
       e.hw = B.buf.param + B.off_w;
       e.hc = B.buf.param + B.off_c;
-      e.labels = labels;
+      e.labels = in.p.labels;
       e.lam = B.lam;
       e.inv_m = 1.0f / float(M);
       e.dmn = R.dmn;
@@ -831,58 +983,23 @@ erase_status enqueue_forward(Ctx* c, Enqueuer& q, int b, const void* x, const fl
       e.pdw = B.pdw;
       e.pdc = B.pdc;
       e.ploss = B.ploss;
-      cost.flops += 4.0 * M * R.N;
-      cost.bytes = double(esz) * (double(M) * R.K + double(R.N) * R.K + double(M) * R.N * ((R.needy ? 1 : 0) + 1)) +
-                   4.0 * R.N + 4.0 * M + 4.0 * R.N + 4.0 * B.nhead * (R.N + 2);
+      op.cost.flops += 4.0 * M * R.N;
+      op.cost.bytes = double(esz) * (double(M) * R.K + double(R.N) * R.K + double(M) * R.N * ((R.needy ? 1 : 0) + 1)) +
+                      4.0 * R.N + 4.0 * M + 4.0 * R.N + 4.0 * B.nhead * (R.N + 2);
     }
-    const int bf = P.bf16;
-    RUN(fused ? 8 : g.kgroups == 2 ? 9 : 1, b, l, sid, s, cost,
-        [&](const LaunchEv& ev) { return launch_gemm(bf, kind, g, e, s, ev); });
+    op.tkind = fused ? 8 : g.kgroups == 2 ? 9 : 1;
+    op.layer = l;
+    op.slot = l;
+    erase_status st = emit(op);
+    if (st != ERASE_OK) return st;
   }
   if (B.head_fused || !with_head || l_end < B.L) return ERASE_OK;
-  return enqueue_head(c, q, b, labels, s, sid);
+  return head_op(c, b, in, emit);
 }
 
-// Standalone local head, loss and loss gradient of block b (Section 2.1).
-erase_status enqueue_head(Ctx* c, Enqueuer& q, int b, const float* labels, hipStream_t s, int sid) {
-  const Plan& P = c->P;
-  const BlockRT& B = P.blk[b];
-  const int M = P.M, esz = P.esz;
-  const LayerRT& Rl = B.layer[B.L - 1];
-  HeadArgs h{};
-  h.z = Rl.y;
-  h.ldz = Rl.ldy;
-  h.w = B.buf.param + B.off_w;
-  h.c = B.buf.param + B.off_c;
-  h.y = labels;
-  h.lam = B.lam;
-  h.inv_m = 1.0f / float(M);
-  h.M = M;
-  h.N = Rl.N;
-  h.rows = head_rows(M);
-  h.dmn = Rl.dmn;
-  h.lddmn = Rl.lddmn;
-
-  h.pdw = B.pdw;
-  h.pdc = B.pdc;
-  h.ploss = B.ploss;
-  Cost cost;
-  cost.grid = B.nhead;
-  cost.flops = 4.0 * M * Rl.N;
-  cost.bytes = double(esz) * M * Rl.N * (1 + 1 + (Rl.dmn ? 1 : 0)) + 4.0 * M + 4.0 * Rl.N + 4.0 * B.nhead * (Rl.N + 2);
-  const int bf = P.bf16;
-  RUN(2, b, -1, sid, s, cost, [&](const LaunchEv& ev) { return launch_head(bf, h, s, ev); });
-  return ERASE_OK;
-}
-
-// Backward GEMMs of block b, last layer first.  Per layer l: the weight and
-// bias gradient dW = dH^T a_{l-1}, db = row sums of dH^T, and (l > 0) the
-// input gradient of the layer below; the block input is detached (Eq. 1), so
-// layer 0 has no input gradient.  When both GEMMs of a layer share a tile
-// they go out as one launch.
 // Arguments and cost of block b's Adam launch (the parameters not updated by
 // a fused weight-gradient launch).
-AdamArgs adam_args(const Ctx* c, int b, float* losses, int par, Cost* cost) {
+AdamArgs adam_args(const Ctx* c, int b, const StepIn& in, Cost* cost) {
   const Plan& P = c->P;
   const BlockRT& B = P.blk[b];
   AdamArgs a{};
@@ -890,14 +1007,14 @@ AdamArgs adam_args(const Ctx* c, int b, float* losses, int par, Cost* cost) {
   a.nseg = (int)B.segs.size();
   for (int i = 0; i < a.nseg; ++i) a.chunk0[i] = B.segs[i].chunk0;
   a.nchunks = B.nchunks;
-  a.hyper = reinterpret_cast<const float*>(P.t + 2) + 2 * par;
+  a.hyper = in.p.hyper;
   a.beta1 = c->cfg.beta1;
   a.beta2 = c->cfg.beta2;
   a.eps = c->cfg.eps;
   a.ploss = B.ploss;
   a.nloss = B.nhead;
   a.inv_m = 1.0f / float(P.M);
-  a.loss_out = losses + b;
+  a.loss_out = in.p.losses ? in.p.losses + b : nullptr;
   a.status = P.status;
   cost->grid = (int)B.nchunks;
   for (const AdamSeg& sg : B.segs) {
@@ -908,26 +1025,42 @@ AdamArgs adam_args(const Ctx* c, int b, float* losses, int par, Cost* cost) {
   return a;
 }
 
-// Block b's backward.  With `losses` set, a block whose first-layer weight
-// gradient carries the fused Adam update also runs the Adam update of its
-// other parameters in that launch (*adam_done = true); the caller then
-// launches no separate Adam for the block.
-erase_status enqueue_backward(Ctx* c, Enqueuer& q, int b, const void* x, hipStream_t s, int sid, int par,
-                              bool send = false, float* losses = nullptr, bool* adam_done = nullptr) {
-  if (adam_done) *adam_done = false;
+template <class F>
+erase_status adam_op(const Ctx* c, int b, const StepIn& in, F&& emit) {
+  Op op;
+  op.type = Op::ADAM;
+  op.tkind = 5;
+  op.slot = 3 * c->P.blk[b].L + 1;
+  op.j.a = adam_args(c, b, in, &op.cost);
+  return emit(op);
+}
+
+// Backward GEMMs of block b, last layer first, then Adam.  Per layer l: the
+// weight and bias gradient dW = dH^T a_{l-1}, db = row sums of dH^T, and
+// (l > 0) the input gradient of the layer below; the block input is detached
+// (Eq. 1), so layer 0 has no input gradient.  When both GEMMs of a layer
+// share a tile they go out as one launch.  With `adam`, the block's
+// parameters are updated too: in the first layer's launch when it carries
+// the fused update, else in a launch of their own.
+template <class F>
+erase_status backward_ops(const Ctx* c, int b, const StepIn& in, bool send, bool adam, F&& emit) {
   const Plan& P = c->P;
   const BlockRT& B = P.blk[b];
-  const int M = P.M, esz = P.esz, bf = P.bf16;
+  const int M = P.M, esz = P.esz;
   const void* x0;
   int64_t ldx0;
-  layer_input(c, b, 0, x, par, &x0, &ldx0);
+  layer_input(c, b, 0, in, &x0, &ldx0);
   for (int l = B.L - 1; l >= 0; --l) {
     const LayerRT& R = B.layer[l];
     const void* inmn;
     int64_t ldinmn;
-    layer_input(c, b, l, x, par, &inmn, &ldinmn);
+    layer_input(c, b, l, in, &inmn, &ldinmn);
     // dW[n][k] = sum over the batch of dH[m][n] a[m][k]: both row-major
-    GemmDesc gw{};
+    Op wop;
+    wop.kind = GK_WGRAD;
+    wop.layer = l;
+    wop.slot = B.L + 1 + 2 * l;
+    GemmDesc& gw = wop.j.g;
     gw.A = R.dmn;
     gw.lda = R.lddmn;
     gw.B = inmn;
@@ -940,12 +1073,13 @@ erase_status enqueue_backward(Ctx* c, Enqueuer& q, int b, const void* x, hipStre
     gw.bm = R.wgrad.bm;
     gw.bn = R.wgrad.bn;
     gw.group = R.wgrad.group;
-    EpiParams ew{};
+    EpiParams& ew = wop.j.e;
     ew.part = R.part;
     ew.ldp = R.ldp;
     ew.pstride = R.pstride;
     ew.bpart = R.bpart;
-    Cost cw = gemm_cost(gw);
+    Cost& cw = wop.cost;
+    cw = gemm_cost(gw);
     cw.flops = 2.0 * M * R.N * R.K;
     cw.bytes = double(esz) * M * (double(R.N) + R.K) + 4.0 * R.wgrad.split * (double(R.N) * R.K + R.N);
     gw.kgroups = R.wgrad.kgroups;
@@ -960,7 +1094,7 @@ erase_status enqueue_backward(Ctx* c, Enqueuer& q, int b, const void* x, hipStre
       ew.bm = B.buf.m + R.offb;
       ew.bv = B.buf.v + R.offb;
       ew.bg = B.buf.grad ? B.buf.grad + R.offb : nullptr;
-      ew.hyper = reinterpret_cast<const float*>(P.t + 2) + 2 * par;
+      ew.hyper = in.p.hyper;
       ew.b1 = c->cfg.beta1;
       ew.b2 = c->cfg.beta2;
       ew.eps = c->cfg.eps;
@@ -970,24 +1104,30 @@ erase_status enqueue_backward(Ctx* c, Enqueuer& q, int b, const void* x, hipStre
       cw.bytes += n * (24.0 + (ew.ag ? 4.0 : 0.0)) + double(R.N) * R.K * esz - 4.0 * n;
     }
     if (l == 0) {
-      if (losses && R.fused_adam) {
+      const bool both = adam && R.fused_adam;
+      wop.tkind = both ? 11 : gw.kgroups == 2 ? 10 : 3;
+      if (both) {
         Cost ca;
-        const AdamArgs aa = adam_args(c, b, losses, par, &ca);
+        wop.type = Op::WGRAD_ADAM;
+        wop.j.a = adam_args(c, b, in, &ca);
         cw.flops += ca.flops;
         cw.bytes += ca.bytes;
         cw.grid += (ca.grid + 1) / 2;
-        RUN(11, b, l, sid, s, cw, [&](const LaunchEv& ev) { return launch_wgrad_adam(bf, gw, ew, aa, s, ev); });
-        if (adam_done) *adam_done = true;
-      } else {
-        RUN(gw.kgroups == 2 ? 10 : 3, b, l, sid, s, cw,
-            [&](const LaunchEv& ev) { return launch_gemm(bf, GK_WGRAD, gw, ew, s, ev); });
       }
-      if (send && B.send) {
+      erase_status st = ERASE_OK;
+      if (!(send && B.send)) {
+        st = emit(wop);
+      } else {
         // undetached: the gradient at the block input, dX = dH_0 W_0, is
         // added to the previous block's output gradient (its head's term,
         // already in place) under that block's ReLU mask
         const LayerRT& Rp = P.blk[b - 1].layer[P.blk[b - 1].L - 1];
-        GemmDesc gx{};
+        Op op;
+        op.kind = GK_DGRAD;
+        op.tkind = 4;
+        op.layer = l;
+        op.slot = wop.slot + 1;
+        GemmDesc& gx = op.j.g;
         gx.A = R.dmn;
         gx.lda = R.lddmn;
         gx.B = R.wsht;
@@ -1000,7 +1140,7 @@ erase_status enqueue_backward(Ctx* c, Enqueuer& q, int b, const void* x, hipStre
         gx.bm = R.dgrad.bm;
         gx.bn = R.dgrad.bn;
         gx.group = R.dgrad.group;
-        EpiParams ex{};
+        EpiParams& ex = op.j.e;
         ex.res = Rp.dmn;
         ex.ldres = Rp.lddmn;
         ex.mask = Rp.y;
@@ -1008,15 +1148,34 @@ erase_status enqueue_backward(Ctx* c, Enqueuer& q, int b, const void* x, hipStre
         ex.below_cross = 0;
         ex.dmn = Rp.dmn;
         ex.lddmn = Rp.lddmn;
-        Cost cx = gemm_cost(gx);
-        cx.flops = 2.0 * M * R.N * R.K;
-        cx.bytes = double(esz) * (double(M) * R.N + double(R.N) * R.K + 3.0 * double(M) * R.K);
-        RUN(4, b, l, sid, s, cx, [&](const LaunchEv& ev) { return launch_gemm(bf, GK_DGRAD, gx, ex, s, ev); });
+        op.cost = gemm_cost(gx);
+        op.cost.flops = 2.0 * M * R.N * R.K;
+        op.cost.bytes = double(esz) * (double(M) * R.N + double(R.N) * R.K + 3.0 * double(M) * R.K);
+        if (R.grouped) {
+          op.type = Op::PAIR;
+          op.tkind = 6;
+          op.j.g2 = gw;
+          op.j.e2 = ew;
+          op.cost.flops += cw.flops;
+          op.cost.bytes += cw.bytes;
+          op.cost.grid += cw.grid;
+          op.cost.split = cw.split;
+        } else {
+          st = emit(wop);
+          if (st != ERASE_OK) return st;
+        }
+        st = emit(op);
       }
-      break;
+      if (st != ERASE_OK) return st;
+      return adam && !both ? adam_op(c, b, in, emit) : ERASE_OK;
     }
     const LayerRT& Rb = B.layer[l - 1];
-    GemmDesc gd{};
+    Op dop;
+    dop.kind = GK_DGRAD;
+    dop.tkind = 4;
+    dop.layer = l;
+    dop.slot = wop.slot + 1;
+    GemmDesc& gd = dop.j.g;
     gd.A = R.dmn;
     gd.lda = R.lddmn;
     gd.B = R.wsht;
@@ -1029,7 +1188,7 @@ erase_status enqueue_backward(Ctx* c, Enqueuer& q, int b, const void* x, hipStre
     gd.bm = R.dgrad.bm;
     gd.bn = R.dgrad.bn;
     gd.group = R.dgrad.group;
-    EpiParams ed{};
+    EpiParams& ed = dop.j.e;
     if (R.kind == ERASE_LAYER_CROSS) {
       ed.res = R.g;
       ed.ldres = R.ldg;
@@ -1047,50 +1206,113 @@ erase_status enqueue_backward(Ctx* c, Enqueuer& q, int b, const void* x, hipStre
       ed.mask = Rb.y;
       ed.ldmask = Rb.ldy;
     }
-    Cost cd = gemm_cost(gd);
+    Cost& cd = dop.cost;
+    cd = gemm_cost(gd);
     cd.flops = 2.0 * M * R.N * R.K;
     const double outs = 1.0 + (ed.gout ? 1.0 : 0.0);
     cd.bytes = double(esz) * (double(M) * R.N + double(R.N) * R.K + double(M) * R.K * (outs + 1.0) +
                               (ed.res ? double(M) * R.K : 0.0));
+    erase_status st;
     if (R.grouped) {
-      Cost cg = cd;
-      cg.flops += cw.flops;
-      cg.bytes += cw.bytes;
-      cg.grid += cw.grid;
-      cg.split = cw.split;
-      RUN(6, b, l, sid, s, cg, [&](const LaunchEv& ev) { return launch_bwd_gemm(bf, gd, ed, gw, ew, s, ev); });
+      dop.type = Op::PAIR;
+      dop.tkind = 6;
+      dop.slot = wop.slot;
+      dop.j.g2 = gw;
+      dop.j.e2 = ew;
+      cd.flops += cw.flops;
+      cd.bytes += cw.bytes;
+      cd.grid += cw.grid;
+      cd.split = cw.split;
+      st = emit(dop);
     } else {
-      RUN(3, b, l, sid, s, cw, [&](const LaunchEv& ev) { return launch_gemm(bf, GK_WGRAD, gw, ew, s, ev); });
-      RUN(4, b, l, sid, s, cd, [&](const LaunchEv& ev) { return launch_gemm(bf, GK_DGRAD, gd, ed, s, ev); });
+      wop.tkind = 3;
+      st = emit(wop);
+      if (st == ERASE_OK) st = emit(dop);
     }
+    if (st != ERASE_OK) return st;
   }
   return ERASE_OK;
 }
 
-erase_status enqueue_adam(Ctx* c, Enqueuer& q, int b, float* losses, hipStream_t s, int sid, int par) {
-  const Plan& P = c->P;
-  Cost cost;
-  const AdamArgs a = adam_args(c, b, losses, par, &cost);
-  const int bf = P.bf16;
-  RUN(5, b, -1, sid, s, cost, [&](const LaunchEv& ev) { return launch_adam(bf, a, s, ev); });
+// Enqueue one launch: a block's, or (gr) the same of every block of a group.
+erase_status launch_op(Ctx* c, Enqueuer& q, const Group* gr, int b, const StepIn& in, Op& op, hipStream_t s, int sid) {
+  const int bf = c->P.bf16;
+  Batch bt{};
+  if (gr) {
+    bt = {gr->jobs + (int64_t)op.slot * gr->n, gr->n, in.p};
+    op.cost.flops *= gr->n;
+    op.cost.bytes *= gr->n;
+    op.cost.grid *= gr->n;
+  }
+  const Batch* pb = gr ? &bt : nullptr;
+  const BlockJob& j = op.j;
+  RUN(op.tkind, b, op.layer, sid, s, op.cost, [&](const LaunchEv& ev) {
+    switch (op.type) {
+      case Op::GEMM: return launch_gemm(bf, op.kind, j.g, j.e, s, ev, pb);
+      case Op::PAIR: return launch_bwd_gemm(bf, j.g, j.e, j.g2, j.e2, s, ev, pb);
+      case Op::WGRAD_ADAM: return launch_wgrad_adam(bf, j.g, j.e, j.a, s, ev, pb);
+      case Op::HEAD: return launch_head(bf, j.h, s, ev, pb);
+      default: return launch_adam(bf, j.a, s, ev, pb);
+    }
+  });
   return ERASE_OK;
+}
+
+// A phase of a group: once for all its blocks when they share it (f(block,
+// group)), else block by block (f(block, null)), in reverse when set.
+template <class F>
+erase_status each_block(const Group& g, bool share, bool reverse, F&& f) {
+  if (g.jobs && share) return f(g.first, &g);
+  for (int i = 0; i < g.n; ++i) {
+    erase_status st = f(g.first + (reverse ? g.n - 1 - i : i), static_cast<const Group*>(nullptr));
+    if (st != ERASE_OK) return st;
+  }
+  return ERASE_OK;
+}
+
+// The argument tables of the groups (host copies, in P.jobs_host, group after
+// group; uploaded by erase_init).
+void build_jobs(Ctx* c) {
+  Plan& P = c->P;
+  P.jobs_host.clear();
+  StepIn in;
+  in.x = kStepX;
+  in.ldx = P.x_in_place ? c->cfg.x_ld : P.ldxp;
+  in.p = {kStepX, nullptr, nullptr, nullptr};
+  for_each_unit(&P, [&](Unit& u) {
+    for (const Group& g : u.groups) {
+      if (!g.jobs) continue;
+      const size_t base = P.jobs_host.size();
+      const int L = P.blk[g.first].L;
+      P.jobs_host.resize(base + size_t(job_slots(L)) * g.n);
+      for (int i = 0; i < g.n; ++i) {
+        auto put = [&](Op& op) {
+          op.j.block = g.first + i;
+          P.jobs_host[base + size_t(op.slot) * g.n + i] = op.j;
+          return ERASE_OK;
+        };
+        (void)forward_ops(c, g.first + i, in, true, 0, L, put);
+        (void)backward_ops(c, g.first + i, in, false, true, put);
+        (void)adam_op(c, g.first + i, in, put);
+      }
+    }
+  });
 }
 
 // One step's launches.  `sched` selects serial or overlapped order; graph
 // schedules call this under stream capture.  With `threaded` (uncaptured,
-// untimed, worker dispatch on) the ERASE schedules hand each block's backward
+// untimed, worker dispatch on) the ERASE schedules hand each unit's backward
 // and Adam to the worker thread, which enqueues them on the backward stream
-// while this thread goes on with the next block's forward.
+// while this thread goes on with the next unit's forward.
 erase_status enqueue_step(Ctx* c, Enqueuer& q, const void* x, const float* labels, int sched, float* losses,
                           bool threaded = false) {
   const Plan& P = c->P;
   const bool pipeline = sched == ERASE_SCHED_PIPELINE;
   const bool adam_end = sched == ERASE_SCHED_OVERLAP_ADAM_END;
   const bool overlap = sched == ERASE_SCHED_OVERLAP || sched == ERASE_SCHED_OVERLAP_GRAPH || pipeline || adam_end;
-  const int nb = (int)P.blk.size();
   const int ns = (int)c->sbs.size();
-  const int par = c->par;
   hipStream_t sf = c->sf;
+  const StepIn in = step_in(c, x, labels, losses, c->par);
   {
     PrologueArgs pa{};
     pa.t = P.t;
@@ -1099,10 +1321,9 @@ erase_status enqueue_step(Ctx* c, Enqueuer& q, const void* x, const float* label
     pa.beta2 = c->cfg.beta2;
     pa.x = x;
     pa.ldx = c->cfg.x_ld;
-    pa.hyper = reinterpret_cast<float*>(P.t + 2) + 2 * par;
-    pa.xp = P.xp[par];
+    pa.hyper = const_cast<float*>(in.p.hyper);
+    pa.xp = P.xp[c->par];
     pa.ldxp = P.ldxp;
-
     pa.M = P.M;
     pa.K = c->cfg.in_dim;
     Cost cost;
@@ -1111,83 +1332,99 @@ erase_status enqueue_step(Ctx* c, Enqueuer& q, const void* x, const float* label
     RUN(0, -1, -1, 0, sf, cost, [&](const LaunchEv& ev) { return launch_prologue(bf, pa, sf, ev); });
   }
   if (overlap) {
-    // ERASE: block b's backward and Adam go to backward stream b % ns as soon
-    // as its forward and local loss are enqueued; the step ends with the
-    // forward stream joined on every backward stream used.
+    // ERASE: a unit's backward and Adam go to a backward stream (unit k to
+    // stream k % ns) as soon as its forward and local loss are enqueued; the
+    // step ends with the forward stream joined on every backward stream used.
     threaded = threaded && c->worker != nullptr;
-    for (int b = 0; b < nb; ++b) {
-      const int k = b % ns;
+    const int nu = (int)P.overlap.size();
+    for (int i = 0; i < nu; ++i) {
+      const Unit& u = P.overlap[i];
+      const int k = i % ns;
       hipStream_t sb = c->sbs[k];
-      const bool chained_next = b + 1 < nb && P.blk[b + 1].input_src == ERASE_IN_PREV;
+      const erase_config& cfg = c->cfg;
       if (pipeline && c->pending) {
-        // no end-of-step join: block b's forward waits only for the previous
-        // step's backward of block b (its weights, its activation buffers)
-        // and, in a chain, of block b+1 (which reads block b's output).  With
-        // the worker, those backward launches (and their event records) must
-        // have been enqueued before this thread waits on the events.
+        // no end-of-step join: a unit's forward waits only for the previous
+        // step's backward of its blocks (their weights and activation
+        // buffers) and, in a chain, of the next unit (whose first block reads
+        // the last one's output).  With the worker, those backward launches
+        // (and their event records) must have been enqueued before this
+        // thread waits on the events.
+        const bool next = feeds_next(cfg, u.first + u.n - 1);
         if (threaded) {
-          erase_status st = wait_job(c, c->job_of[b]);
-          if (st == ERASE_OK && chained_next) st = wait_job(c, c->job_of[b + 1]);
+          erase_status st = wait_job(c, c->job_of[i]);
+          if (st == ERASE_OK && next) st = wait_job(c, c->job_of[i + 1]);
           if (st != ERASE_OK) return st;
         }
-        HIPCHK(c, hipStreamWaitEvent(sf, c->eb[b], 0));
-        if (chained_next) HIPCHK(c, hipStreamWaitEvent(sf, c->eb[b + 1], 0));
+        HIPCHK(c, hipStreamWaitEvent(sf, c->eb[i], 0));
+        if (next) HIPCHK(c, hipStreamWaitEvent(sf, c->eb[i + 1], 0));
       }
       // a standalone head goes to the backward stream, in front of the
       // block's backward: the next block's forward waits only for the body.
       // A head fused into the last layer takes that layer with it when no
       // later block reads the block's output.
-      const bool head_b = !P.blk[b].head_fused;
-      const int L = P.blk[b].L;
-      const bool last_b = !head_b && L >= 2 && !chained_next;
-      q.set_end(c->ef[b]);
-      erase_status st = enqueue_forward(c, q, b, x, labels, sf, 0, !head_b, 0, last_b ? L - 1 : L);
-      if (st != ERASE_OK) return st;
-      if (!q.end_recorded()) HIPCHK(c, hipEventRecord(c->ef[b], sf));
+      auto last_b = [c](int b) {
+        return c->P.blk[b].head_fused && c->P.blk[b].L >= 2 && !feeds_next(c->cfg, b);
+      };
       q.set_end(nullptr);
+      erase_status st = ERASE_OK;
+      for (const Group& gr : u.groups) {
+        st = each_block(gr, gr.share_fwd, false, [&](int b, const Group* sh) {
+          const int le = last_b(b) ? P.blk[b].L - 1 : P.blk[b].L;
+          const bool last = &gr == &u.groups.back() && (sh || b == u.first + u.n - 1);
+          return forward_ops(c, b, in, false, 0, le, [&](Op& op) {
+            if (last && op.layer == le - 1) q.set_end(c->ef[i]);
+            return launch_op(c, q, sh, b, in, op, sf, 0);
+          });
+        });
+        if (st != ERASE_OK) return st;
+      }
+      if (!q.end_recorded()) HIPCHK(c, hipEventRecord(c->ef[i], sf));
+      q.set_end(nullptr);
+      hipEvent_t efu = c->ef[i], ebu = c->eb[i];
+      const Unit* up = &u;
+      auto back = [c, up, in, sb, k, adam_end, last_b, efu, ebu](Enqueuer& bq) -> erase_status {
+        HIPCHK(c, hipStreamWaitEvent(sb, efu, 0));
+        bq.set_end(nullptr);
+        const Plan& P2 = c->P;
+        for (const Group& gr : up->groups) {
+          erase_status s2 = ERASE_OK;
+          if (P2.blk[gr.first].head_fused) {
+            s2 = each_block(gr, gr.share_fwd, false, [&](int b, const Group* sh) {
+              const int L = P2.blk[b].L;
+              if (!last_b(b)) return ERASE_OK;
+              return forward_ops(c, b, in, true, L - 1, L,
+                                 [&](Op& op) { return launch_op(c, bq, sh, b, in, op, sb, 1 + k); });
+            });
+          } else {
+            s2 = each_block(gr, true, false, [&](int b, const Group* sh) {
+              return head_op(c, b, in, [&](Op& op) { return launch_op(c, bq, sh, b, in, op, sb, 1 + k); });
+            });
+          }
+          if (s2 != ERASE_OK) return s2;
+          s2 = each_block(gr, true, false, [&](int b, const Group* sh) {
+            return backward_ops(c, b, in, false, !adam_end, [&](Op& op) {
+              const bool end = adam_end ? op.layer == 0 : op.type == Op::WGRAD_ADAM || op.type == Op::ADAM;
+              if (end && &gr == &up->groups.back()) bq.set_end(ebu);
+              return launch_op(c, bq, sh, b, in, op, sb, 1 + k);
+            });
+          });
+          if (s2 != ERASE_OK) return s2;
+        }
+        if (!bq.end_recorded()) HIPCHK(c, hipEventRecord(ebu, sb));
+        return ERASE_OK;
+      };
       if (threaded) {
-        // ef[b] is recorded again only in a later step, after this job has
+        // ef[i] is recorded again only in a later step, after this job has
         // finished (the waits above, or the join below), so the job's wait
         // always binds to this step's record
-        hipEvent_t efb = c->ef[b], ebb = c->eb[b];
-        c->job_of[b] = c->worker->push([c, b, x, labels, losses, sb, k, par, adam_end, head_b, last_b, L, efb,
-                                        ebb]() -> erase_status {
-          HIPCHK(c, hipStreamWaitEvent(sb, efb, 0));
+        c->job_of[i] = c->worker->push([c, back]() -> erase_status {
           Enqueuer wq(c, false);
-          wq.set_end(ebb);
-          erase_status s2 = head_b ? enqueue_head(c, wq, b, labels, sb, 1 + k)
-                            : last_b ? enqueue_forward(c, wq, b, x, labels, sb, 1 + k, true, L - 1, L, par)
-                                     : ERASE_OK;
-          if (s2 != ERASE_OK) return s2;
-          bool done = false;
-          s2 = enqueue_backward(c, wq, b, x, sb, 1 + k, par, false, adam_end ? nullptr : losses, &done);
-          if (s2 != ERASE_OK) return s2;
-          if (!adam_end && !done) {
-            s2 = enqueue_adam(c, wq, b, losses, sb, 1 + k, par);
-            if (s2 != ERASE_OK) return s2;
-          }
-          if (!wq.end_recorded()) HIPCHK(c, hipEventRecord(ebb, sb));
-          return ERASE_OK;
+          return back(wq);
         });
         continue;
       }
-      HIPCHK(c, hipStreamWaitEvent(sb, c->ef[b], 0));
-      q.set_end(c->eb[b]);
-      if (head_b) {
-        st = enqueue_head(c, q, b, labels, sb, 1 + k);
-        if (st != ERASE_OK) return st;
-      } else if (last_b) {
-        st = enqueue_forward(c, q, b, x, labels, sb, 1 + k, true, L - 1, L, par);
-        if (st != ERASE_OK) return st;
-      }
-      bool done = false;
-      st = enqueue_backward(c, q, b, x, sb, 1 + k, par, false, adam_end ? nullptr : losses, &done);
+      st = back(q);
       if (st != ERASE_OK) return st;
-      if (!adam_end && !done) {
-        st = enqueue_adam(c, q, b, losses, sb, 1 + k, par);
-        if (st != ERASE_OK) return st;
-      }
-      if (!q.end_recorded()) HIPCHK(c, hipEventRecord(c->eb[b], sb));
       q.set_end(nullptr);
     }
     if (threaded && !pipeline) {
@@ -1195,32 +1432,45 @@ erase_status enqueue_step(Ctx* c, Enqueuer& q, const void* x, const float* label
       if (st != ERASE_OK) return st;
     }
     if (!pipeline)
-      for (int b = std::max(0, nb - ns); b < nb; ++b) HIPCHK(c, hipStreamWaitEvent(sf, c->eb[b], 0));
+      for (int i = std::max(0, nu - ns); i < nu; ++i) HIPCHK(c, hipStreamWaitEvent(sf, c->eb[i], 0));
     if (adam_end) {
       // the optimizer steps once, after every block's backward
-      for (int b = 0; b < nb; ++b) {
-        erase_status st = enqueue_adam(c, q, b, losses, sf, 0, par);
-        if (st != ERASE_OK) return st;
-      }
+      for (const Unit& u : P.overlap)
+        for (const Group& gr : u.groups) {
+          erase_status st = each_block(gr, true, false, [&](int b, const Group* sh) {
+            return adam_op(c, b, in, [&](Op& op) { return launch_op(c, q, sh, b, in, op, sf, 0); });
+          });
+          if (st != ERASE_OK) return st;
+        }
     }
   } else {
     // SERIAL, and the conventional (undetached) baseline: every forward,
-    // then one backward from the last block to the first, then Adam
+    // then one backward from the last block to the first, each block's Adam
+    // behind its own backward or, shared, at the end.  Undetached, the blocks
+    // of a chain run their backward one by one (each sends its input gradient
+    // to the one before), after their standalone heads in one launch.
     const bool send = sched == ERASE_SCHED_UNDETACHED || sched == ERASE_SCHED_UNDETACHED_GRAPH;
-    for (int b = 0; b < nb; ++b) {
-      erase_status st = enqueue_forward(c, q, b, x, labels, sf, 0);
+    const std::vector<Group>& gs = P.serial.groups;
+    erase_status st = ERASE_OK;
+    for (const Group& gr : gs) {
+      const bool heads = send && gr.jobs && !gr.share_fwd && !P.blk[gr.first].head_fused;
+      st = each_block(gr, gr.share_fwd, false, [&](int b, const Group* sh) {
+        return forward_ops(c, b, in, !heads, 0, P.blk[b].L,
+                           [&](Op& op) { return launch_op(c, q, sh, b, in, op, sf, 0); });
+      });
+      if (st == ERASE_OK && heads)
+        st = head_op(c, gr.first, in, [&](Op& op) { return launch_op(c, q, &gr, gr.first, in, op, sf, 0); });
       if (st != ERASE_OK) return st;
     }
-    std::vector<char> done(nb, 0);
-    for (int b = nb - 1; b >= 0; --b) {
-      bool d = false;
-      erase_status st = enqueue_backward(c, q, b, x, sf, 0, par, send, losses, &d);
-      if (st != ERASE_OK) return st;
-      done[b] = d;
-    }
-    for (int b = 0; b < nb; ++b) {
-      if (done[b]) continue;
-      erase_status st = enqueue_adam(c, q, b, losses, sf, 0, par);
+    for (int i = (int)gs.size() - 1; i >= 0; --i) {
+      const Group& gr = gs[i];
+      const bool chain = send && !gr.share_fwd;
+      const bool late = chain && gr.jobs && !P.blk[gr.first].layer[0].fused_adam;  // Adam shared, behind the backward
+      st = each_block(gr, !chain, true, [&](int b, const Group* sh) {
+        return backward_ops(c, b, in, send, !late, [&](Op& op) { return launch_op(c, q, sh, b, in, op, sf, 0); });
+      });
+      if (st == ERASE_OK && late)
+        st = adam_op(c, gr.first, in, [&](Op& op) { return launch_op(c, q, &gr, gr.first, in, op, sf, 0); });
       if (st != ERASE_OK) return st;
     }
   }
@@ -1243,7 +1493,7 @@ erase_status join_pending(Ctx* c) {
   if (!c->pending) return ERASE_OK;
   erase_status st = quiesce(c);
   if (st != ERASE_OK) return st;
-  for (size_t b = 0; b < c->eb.size(); ++b) HIPCHK(c, hipStreamWaitEvent(c->sf, c->eb[b], 0));
+  for (size_t i = 0; i < c->P.overlap.size(); ++i) HIPCHK(c, hipStreamWaitEvent(c->sf, c->eb[i], 0));
   c->pending = false;
   return ERASE_OK;
 }
@@ -1384,8 +1634,23 @@ erase_status erase_init_streams(const erase_config* cfg, const erase_block_buffe
                        c->sf) != hipSuccess)
       return bail(ERASE_ERR_HIP);
   }
+  build_jobs(c);
+  {
+    size_t o = 0;
+    bool ok = true;
+    for_each_unit(&c->P, [&](Unit& u) {
+      for (const Group& g : u.groups) {
+        if (!g.jobs) continue;
+        const size_t n = size_t(job_slots(c->P.blk[g.first].L)) * g.n;
+        ok = ok && hipMemcpyAsync(g.jobs, c->P.jobs_host.data() + o, n * sizeof(BlockJob), hipMemcpyHostToDevice,
+                                  c->sf) == hipSuccess;
+        o += n;
+      }
+    });
+    if (!ok) return bail(ERASE_ERR_HIP);
+  }
   if (refresh(c) != ERASE_OK) return bail(ERASE_ERR_HIP);
-  // the host copies of the segment tables must outlive the async copies:
+  // the host copies of the segment and argument tables must outlive the async copies:
   // they live in the context, which outlives the stream work it enqueued
   *ctx_out = h;
   return ERASE_OK;

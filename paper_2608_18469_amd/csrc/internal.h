@@ -109,19 +109,6 @@ struct EpiParams {
   const float* xref;
 };
 
-hipError_t launch_gemm(int bf16, int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s,
-                       const LaunchEv& ev = {});
-// Input-gradient (gd, split 1) and weight-gradient (gw) GEMMs of one layer in
-// one launch; both must use the same tile, 64x64 or 128x128.
-hipError_t launch_bwd_gemm(int bf16, const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
-                           hipStream_t s, const LaunchEv& ev = {});
-
-// The wide tiles (bf16): GK_FWD_RELU/CROSS/LIN/GELU, GK_DGRAD(_GELU) and
-// GK_WGRAD in 256x256 tiles, and a layer's two backward GEMMs in one launch.
-hipError_t launch_wide(int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev = {});
-hipError_t launch_wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
-                           hipStream_t s, const LaunchEv& ev = {});
-
 // Step prologue: t += 1 and the zero-padded copy xp[m][k] = x[m][k] (its
 // padding stays zero).
 // Workspace header (first 256 bytes): step counter t (int64 at 0), status
@@ -157,7 +144,6 @@ struct HeadArgs {
 // and more would only add partials for Adam to sum.
 constexpr int HEAD_MAX_N = 2048;
 inline int head_rows(int64_t M) { return M <= 4096 ? 8 : M < 8192 ? 16 : 32; }
-hipError_t launch_head(int bf16, const HeadArgs& a, hipStream_t s, const LaunchEv& ev = {});
 
 // Fused split-reduction + Adam + GEMM-copy refresh for one block.  The
 // segment table lives in device memory (written once at init).  A segment
@@ -192,13 +178,52 @@ struct AdamArgs {
   float* loss_out;
   int* status;
 };
-hipError_t launch_adam(int bf16, const AdamArgs& a, hipStream_t s, const LaunchEv& ev = {});
+
+// One launch of several blocks of equal shape that read the same input:
+// job j (grid row j) takes its arguments from jobs[j] in device memory, in
+// place of the launch's own, and what changes from step to step from `st`.
+// Operands that are x carry kStepX.
+struct BlockJob {
+  GemmDesc g; EpiParams e;    // a GEMM, a pair's input gradient, a first-layer weight gradient
+  GemmDesc g2; EpiParams e2;  // a pair's weight gradient
+  AdamArgs a;
+  HeadArgs h;
+  int64_t block;
+};
+struct StepPtrs {
+  const void* x;
+  const float* labels;
+  float* losses;       // [n_blocks]
+  const float* hyper;  // this step's Adam factors
+};
+inline const void* const kStepX = reinterpret_cast<const void*>(uintptr_t(16));
+struct Batch {
+  const BlockJob* jobs;
+  int n;
+  StepPtrs st;
+};
+
+hipError_t launch_gemm(int bf16, int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s,
+                       const LaunchEv& ev = {}, const Batch* bt = nullptr);
+// Input-gradient (gd, split 1) and weight-gradient (gw) GEMMs of one layer in
+// one launch; both must use the same tile, 64x64 or 128x128.
+hipError_t launch_bwd_gemm(int bf16, const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
+                           hipStream_t s, const LaunchEv& ev = {}, const Batch* bt = nullptr);
+
+// The wide tiles (bf16): GK_FWD_RELU/CROSS/LIN/GELU, GK_DGRAD(_GELU) and
+// GK_WGRAD in 256x256 tiles, and a layer's two backward GEMMs in one launch.
+hipError_t launch_wide(int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev = {}, const Batch* bt = nullptr);
+hipError_t launch_wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
+                           hipStream_t s, const LaunchEv& ev = {}, const Batch* bt = nullptr);
+
+hipError_t launch_head(int bf16, const HeadArgs& a, hipStream_t s, const LaunchEv& ev = {}, const Batch* bt = nullptr);
+hipError_t launch_adam(int bf16, const AdamArgs& a, hipStream_t s, const LaunchEv& ev = {}, const Batch* bt = nullptr);
 
 // A block's first-layer weight gradient with its fused Adam (g: 64x64, two
 // k-groups, unsplit; e.ap set) and the Adam launch `a` of the block's other
 // parameters in one launch (extra workgroups beside the GEMM tiles).
 hipError_t launch_wgrad_adam(int bf16, const GemmDesc& g, const EpiParams& e, const AdamArgs& a, hipStream_t s,
-                             const LaunchEv& ev = {});
+                             const LaunchEv& ev = {}, const Batch* bt = nullptr);
 
 // Weight copies only (init / refresh): same segments, no update.
 hipError_t launch_refresh(int bf16, const AdamArgs& a, hipStream_t s);

@@ -867,16 +867,32 @@ __device__ __forceinline__ void gemm_body(const GemmDesc& g, const EpiParams& e,
     const TileIdx ti = tile_from(xcd_linear(blockIdx.x, gridDim.x), gm, gn, g.group);   \
     gemm_body<T, BM, BN, KIND>(g, e, ti.m, ti.n, ti.z, smem);                            \
   }
-ERASE_GEMM_KERNEL(erase_fwd_gemm, GK_FWD_RELU)
-ERASE_GEMM_KERNEL(erase_fwd_cross_gemm, GK_FWD_CROSS)
-ERASE_GEMM_KERNEL(erase_wgrad_gemm, GK_WGRAD)
-ERASE_GEMM_KERNEL(erase_dgrad_gemm, GK_DGRAD)
-ERASE_GEMM_KERNEL(erase_fwd_head_gemm, GK_FWD_HEAD)
+// the same for several blocks (grid row j: job j)
+#define ERASE_GEMM_KERNEL_B(NAME, KIND)                                                  \
+  ERASE_GEMM_KERNEL(NAME, KIND)                                                          \
+  template <typename T, int BM, int BN>                                                  \
+  __global__ __launch_bounds__(256) void NAME##_b(const BlockJob* jobs, StepPtrs st) {   \
+    __shared__ __attribute__((aligned(16))) char smem[GemmSmem<T, BM, BN, KIND>::BYTES]; \
+    GemmDesc g;                                                                          \
+    EpiParams e;                                                                         \
+    const cmem_t jb = job_of(jobs);                                                      \
+    ld_gemm(jb + offsetof(BlockJob, g), g, st);                                          \
+    ld_epi(jb + offsetof(BlockJob, e), e, st);                                           \
+    const int gm = (g.M + BM - 1) / BM, gn = (g.N + BN - 1) / BN;                        \
+    const TileIdx ti = tile_from(xcd_linear(blockIdx.x, gridDim.x), gm, gn, g.group);   \
+    gemm_body<T, BM, BN, KIND>(g, e, ti.m, ti.n, ti.z, smem);                            \
+  }
+ERASE_GEMM_KERNEL_B(erase_fwd_gemm, GK_FWD_RELU)
+ERASE_GEMM_KERNEL_B(erase_fwd_cross_gemm, GK_FWD_CROSS)
+ERASE_GEMM_KERNEL_B(erase_wgrad_gemm, GK_WGRAD)
+ERASE_GEMM_KERNEL_B(erase_dgrad_gemm, GK_DGRAD)
+ERASE_GEMM_KERNEL_B(erase_fwd_head_gemm, GK_FWD_HEAD)
 ERASE_GEMM_KERNEL(erase_fwd_lin_gemm, GK_FWD_LIN)
 ERASE_GEMM_KERNEL(erase_fwd_gelu_gemm, GK_FWD_GELU)
 ERASE_GEMM_KERNEL(erase_dgrad_gelu_gemm, GK_DGRAD_GELU)
 ERASE_GEMM_KERNEL(erase_fwd_logits_gemm, GK_FWD_LOGITS)
 #undef ERASE_GEMM_KERNEL
+#undef ERASE_GEMM_KERNEL_B
 
 // Two k-groups of four waves (512 threads): forward tiles of launches with at
 // most one workgroup per CU, which then run two waves per SIMD.
@@ -885,6 +901,19 @@ ERASE_GEMM_KERNEL(erase_fwd_logits_gemm, GK_FWD_LOGITS)
   __global__ __launch_bounds__(512) void NAME(GemmDesc g, EpiParams e) {                      \
     constexpr int BKK = sizeof(T) == 2 ? BKX : 0;                                            \
     __shared__ __attribute__((aligned(16))) char smem[GemmSmem<T, BM, BN, KIND, BKK>::BYTES_KG2]; \
+    const int gm = (g.M + BM - 1) / BM, gn = (g.N + BN - 1) / BN;                             \
+    const TileIdx ti = tile_from(xcd_linear(blockIdx.x, gridDim.x), gm, gn, g.group);        \
+    gemm_body<T, BM, BN, KIND, 2, 2, BKK>(g, e, ti.m, ti.n, ti.z, smem);                      \
+  }                                                                                           \
+  template <typename T, int BM, int BN>                                                       \
+  __global__ __launch_bounds__(512) void NAME##_b(const BlockJob* jobs, StepPtrs st) {        \
+    constexpr int BKK = sizeof(T) == 2 ? BKX : 0;                                            \
+    __shared__ __attribute__((aligned(16))) char smem[GemmSmem<T, BM, BN, KIND, BKK>::BYTES_KG2]; \
+    GemmDesc g;                                                                               \
+    EpiParams e;                                                                              \
+    const cmem_t jb = job_of(jobs);                                                           \
+    ld_gemm(jb + offsetof(BlockJob, g), g, st);                                               \
+    ld_epi(jb + offsetof(BlockJob, e), e, st);                                                \
     const int gm = (g.M + BM - 1) / BM, gn = (g.N + BN - 1) / BN;                             \
     const TileIdx ti = tile_from(xcd_linear(blockIdx.x, gridDim.x), gm, gn, g.group);        \
     gemm_body<T, BM, BN, KIND, 2, 2, BKK>(g, e, ti.m, ti.n, ti.z, smem);                      \
@@ -920,6 +949,19 @@ template <typename T, int BM, int BN>
 __global__ __launch_bounds__(256) void erase_bwd_gemm(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew, int nw) {
   constexpr int SD = GemmSmem<T, BM, BN, GK_DGRAD>::BYTES, SW = GemmSmem<T, BM, BN, GK_WGRAD>::BYTES;
   __shared__ __attribute__((aligned(16))) char smem[SD > SW ? SD : SW];
+  bwd_pair<T, BM, BN, 1>(gd, ed, gw, ew, nw, smem);
+}
+template <typename T, int BM, int BN>
+__global__ __launch_bounds__(256) void erase_bwd_gemm_b(const BlockJob* jobs, StepPtrs st, int nw) {
+  constexpr int SD = GemmSmem<T, BM, BN, GK_DGRAD>::BYTES, SW = GemmSmem<T, BM, BN, GK_WGRAD>::BYTES;
+  __shared__ __attribute__((aligned(16))) char smem[SD > SW ? SD : SW];
+  GemmDesc gd, gw;
+  EpiParams ed, ew;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), gd, st);
+  ld_epi(jb + offsetof(BlockJob, e), ed, st);
+  ld_gemm(jb + offsetof(BlockJob, g2), gw, st);
+  ld_epi(jb + offsetof(BlockJob, e2), ew, st);
   bwd_pair<T, BM, BN, 1>(gd, ed, gw, ew, nw, smem);
 }
 
@@ -967,10 +1009,23 @@ static GemmDesc with_group(const GemmDesc& g0, int BM, int BN) {
 // bf16 first-layer weight gradient with its Adam update (eight waves per
 // tile) and the Adam chunks of `a` (none when a.nchunks is 0)
 static hipError_t launch_wgrad_w8(const GemmDesc& g, const EpiParams& e, const AdamArgs& a, hipStream_t s,
-                                  const LaunchEv& ev);
+                                  const LaunchEv& ev, const Batch* bt);
+
+// a kernel, or its form for several blocks when `bt` is set
+#define ERASE_LAUNCH_B(NAME, TARGS, GRID, BLOCK, SHMEM, BARGS, ...)                                       \
+  do {                                                                                                   \
+    if (bt)                                                                                              \
+      ERASE_LAUNCH((NAME##_b ERASE_T TARGS), dim3((GRID).x, (unsigned)bt->n), BLOCK, SHMEM, s, ev, bt->jobs, \
+                   bt->st ERASE_A BARGS);                                                                \
+    else                                                                                                 \
+      ERASE_LAUNCH((NAME ERASE_T TARGS), GRID, BLOCK, SHMEM, s, ev, __VA_ARGS__);                        \
+  } while (0)
+#define ERASE_T(...) <__VA_ARGS__>
+#define ERASE_A(...) __VA_OPT__(, ) __VA_ARGS__
 
 template <typename T, int BM, int BN>
-static hipError_t launch_gemm_t(int kind, const GemmDesc& g0, const EpiParams& e, hipStream_t s, const LaunchEv& ev) {
+static hipError_t launch_gemm_t(int kind, const GemmDesc& g0, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
+                                const Batch* bt) {
   const GemmDesc g = with_group(g0, BM, BN);
   dim3 grid(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * g.split), block(256);
   // the fused Adam update exists only in the two k-group weight gradient
@@ -982,40 +1037,41 @@ static hipError_t launch_gemm_t(int kind, const GemmDesc& g0, const EpiParams& e
         // bf16: the eight-wave tiles of the launch that also updates the
         // block's other parameters (the same sums, so every schedule gives
         // the same bits), here without those; they need the fused update
-        if constexpr (sizeof(T) == 2) return e.ap ? launch_wgrad_w8(g, e, AdamArgs{}, s, ev) : hipErrorInvalidValue;
-        ERASE_LAUNCH((erase_wgrad_gemm_kg2<T, BM, BN>), grid, dim3(512), 0, s, ev, g, e);
+        if constexpr (sizeof(T) == 2) return e.ap ? launch_wgrad_w8(g, e, AdamArgs{}, s, ev, bt) : hipErrorInvalidValue;
+        ERASE_LAUNCH_B(erase_wgrad_gemm_kg2, (T, BM, BN), grid, dim3(512), 0, (), g, e);
         return hipGetLastError();
       }
     }
     // and bf16 64x128 and 64x64 forward tiles
     if constexpr (sizeof(T) == 2 && BM == 64 && (BN == 128 || BN == 64)) {
       if (kind == GK_FWD_RELU) {
-        ERASE_LAUNCH((erase_fwd_gemm_kg2<T, BM, BN>), grid, dim3(512), 0, s, ev, g, e);
+        ERASE_LAUNCH_B(erase_fwd_gemm_kg2, (T, BM, BN), grid, dim3(512), 0, (), g, e);
         return hipGetLastError();
       }
       if (kind == GK_FWD_CROSS) {
-        ERASE_LAUNCH((erase_fwd_cross_gemm_kg2<T, BM, BN>), grid, dim3(512), 0, s, ev, g, e);
+        ERASE_LAUNCH_B(erase_fwd_cross_gemm_kg2, (T, BM, BN), grid, dim3(512), 0, (), g, e);
         return hipGetLastError();
       }
     }
     return hipErrorInvalidValue;
   }
   switch (kind) {
-    case GK_FWD_RELU: ERASE_LAUNCH((erase_fwd_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e); break;
-    case GK_FWD_CROSS: ERASE_LAUNCH((erase_fwd_cross_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e); break;
+    case GK_FWD_RELU: ERASE_LAUNCH_B(erase_fwd_gemm, (T, BM, BN), grid, block, 0, (), g, e); break;
+    case GK_FWD_CROSS: ERASE_LAUNCH_B(erase_fwd_cross_gemm, (T, BM, BN), grid, block, 0, (), g, e); break;
     case GK_WGRAD:
       if constexpr (BM >= 64) {  // k-major tiles of 64 or 128 columns
-        ERASE_LAUNCH((erase_wgrad_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e);
+        ERASE_LAUNCH_B(erase_wgrad_gemm, (T, BM, BN), grid, block, 0, (), g, e);
       } else {
         return hipErrorInvalidValue;
       }
       break;
-    case GK_DGRAD: ERASE_LAUNCH((erase_dgrad_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e); break;
+    case GK_DGRAD: ERASE_LAUNCH_B(erase_dgrad_gemm, (T, BM, BN), grid, block, 0, (), g, e); break;
     case GK_FWD_LIN:
     case GK_FWD_GELU:
     case GK_DGRAD_GELU:
     case GK_FWD_LOGITS:
       // transformer kinds: bf16, 64- and 128-row tiles
+      if (bt) return hipErrorInvalidValue;
       if constexpr (sizeof(T) == 2 && BM >= 64) {
         if (kind == GK_FWD_LIN) ERASE_LAUNCH((erase_fwd_lin_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e);
         if (kind == GK_FWD_GELU) ERASE_LAUNCH((erase_fwd_gelu_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e);
@@ -1029,7 +1085,7 @@ static hipError_t launch_gemm_t(int kind, const GemmDesc& g0, const EpiParams& e
       // the tile must span the whole width; 32- and 64-row tiles only
       if constexpr (BM <= 64) {
         if (g.N > BN) return hipErrorInvalidValue;
-        ERASE_LAUNCH((erase_fwd_head_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e);
+        ERASE_LAUNCH_B(erase_fwd_head_gemm, (T, BM, BN), grid, block, 0, (), g, e);
       } else {
         return hipErrorInvalidValue;
       }
@@ -1041,7 +1097,7 @@ static hipError_t launch_gemm_t(int kind, const GemmDesc& g0, const EpiParams& e
 
 template <typename T, int BM, int BN, int KG = 1>
 static hipError_t launch_bwd_t(const GemmDesc& gd0, const EpiParams& ed, const GemmDesc& gw0, const EpiParams& ew,
-                               hipStream_t s, const LaunchEv& ev) {
+                               hipStream_t s, const LaunchEv& ev, const Batch* bt) {
   const GemmDesc gd = with_group(gd0, BM, BN), gw = with_group(gw0, BM, BN);
   const int nd = ((gd.M + BM - 1) / BM) * ((gd.N + BN - 1) / BN);
   const int nw = ((gw.M + BM - 1) / BM) * ((gw.N + BN - 1) / BN) * gw.split;
@@ -1049,6 +1105,7 @@ static hipError_t launch_bwd_t(const GemmDesc& gd0, const EpiParams& ed, const G
   // co-resident 128x128 workgroups measured 20% slower on the vocabulary
   // head's backward (1.69 vs 1.41 ms)
   if constexpr (KG == 2) {
+    if (bt) return hipErrorInvalidValue;
     ERASE_LAUNCH((erase_bwd_gemm_kg2<T, BM, BN>), dim3(nd + nw), dim3(512), 0, s, ev, gd, ed, gw, ew, nw);
     return hipGetLastError();
   }
@@ -1057,25 +1114,29 @@ static hipError_t launch_bwd_t(const GemmDesc& gd0, const EpiParams& ed, const G
     static const hipError_t attr = hipFuncSetAttribute(
         reinterpret_cast<const void*>(&erase_bwd_gemm<T, BM, BN>), hipFuncAttributeMaxDynamicSharedMemorySize,
         (int)kReserve);
+    static const hipError_t attr_b = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&erase_bwd_gemm_b<T, BM, BN>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        (int)kReserve);
     if (attr != hipSuccess) return attr;
+    if (attr_b != hipSuccess) return attr_b;
   }
-  ERASE_LAUNCH((erase_bwd_gemm<T, BM, BN>), dim3(nd + nw), dim3(256), kReserve, s, ev, gd, ed, gw, ew, nw);
+  ERASE_LAUNCH_B(erase_bwd_gemm, (T, BM, BN), dim3(nd + nw), dim3(256), kReserve, (nw), gd, ed, gw, ew, nw);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_gemm(int bf16, const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
-                           hipStream_t s, const LaunchEv& ev) {
+                           hipStream_t s, const LaunchEv& ev, const Batch* bt) {
   if (gd.bm != gw.bm || gd.bn != gw.bn || gd.split != 1 || gw.split <= 0 || ew.ap) return hipErrorInvalidValue;
-  if (bf16 && gd.bn == 256) return launch_wide_bwd(gd, ed, gw, ew, s, ev);
+  if (bf16 && gd.bn == 256) return launch_wide_bwd(gd, ed, gw, ew, s, ev, bt);
   if (gd.kgroups == 2 || gw.kgroups == 2) {  // two k-groups: bf16 128x128 only
     if (!bf16 || gd.kgroups != gw.kgroups || gd.bm != 128 || gd.bn != 128) return hipErrorInvalidValue;
-    return launch_bwd_t<uint16_t, 128, 128, 2>(gd, ed, gw, ew, s, ev);
+    return launch_bwd_t<uint16_t, 128, 128, 2>(gd, ed, gw, ew, s, ev, bt);
   }
   if (bf16) {
-    if (gd.bm == 128 && gd.bn == 128) return launch_bwd_t<uint16_t, 128, 128>(gd, ed, gw, ew, s, ev);
-    if (gd.bm == 64 && gd.bn == 64) return launch_bwd_t<uint16_t, 64, 64>(gd, ed, gw, ew, s, ev);
+    if (gd.bm == 128 && gd.bn == 128) return launch_bwd_t<uint16_t, 128, 128>(gd, ed, gw, ew, s, ev, bt);
+    if (gd.bm == 64 && gd.bn == 64) return launch_bwd_t<uint16_t, 64, 64>(gd, ed, gw, ew, s, ev, bt);
   } else {
-    if (gd.bm == 64 && gd.bn == 64) return launch_bwd_t<float, 64, 64>(gd, ed, gw, ew, s, ev);
+    if (gd.bm == 64 && gd.bn == 64) return launch_bwd_t<float, 64, 64>(gd, ed, gw, ew, s, ev, bt);
   }
   return hipErrorInvalidValue;
 }
@@ -1091,7 +1152,7 @@ hipError_t launch_bwd_gemm(int bf16, const GemmDesc& gd, const EpiParams& ed, co
 //   loss_m = max(s,0) - s y_m + log1p(e^-|s|),  ds_m = lam (sigmoid(s_m) - y_m) / M,
 //   dz_mn = ds_m w_n [z_mn > 0],  partials dw_n = sum_m z_mn ds_m, dc, loss,
 // every sum in a fixed order.
-__global__ __launch_bounds__(256) void erase_fwd_head16(GemmDesc g, EpiParams e) {
+__device__ __forceinline__ void fwd_head16(const GemmDesc& g, const EpiParams& e) {
   constexpr int TR = 16, TC = 128, OP = TC + 8;  // tile rows, columns, LDS pitch (bf16)
   __shared__ float s_part[4][TR];
   __shared__ float s_ds[TR], s_l[TR];
@@ -1217,29 +1278,44 @@ __global__ __launch_bounds__(256) void erase_fwd_head16(GemmDesc g, EpiParams e)
   }
 }
 
+__global__ __launch_bounds__(256) void erase_fwd_head16(GemmDesc g, EpiParams e) { fwd_head16(g, e); }
+__global__ __launch_bounds__(256) void erase_fwd_head16_b(const BlockJob* jobs, StepPtrs st) {
+  GemmDesc g;
+  EpiParams e;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), g, st);
+  ld_epi(jb + offsetof(BlockJob, e), e, st);
+  fwd_head16(g, e);
+}
+
 // bf16 vocabulary logits in 256x256 tiles; false when the shape does not fit
 static bool logits_wide_fits(const GemmDesc& g, const EpiParams& e);
 static hipError_t launch_logits_wide(const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev);
 
-hipError_t launch_gemm(int bf16, int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev) {
+hipError_t launch_gemm(int bf16, int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
+                       const Batch* bt) {
   if (g.M <= 0 || g.N <= 0 || g.split <= 0) return hipErrorInvalidValue;
   if (bf16 && kind == GK_FWD_LOGITS && g.bm == 256 && g.bn == 256)
     return logits_wide_fits(g, e) ? launch_logits_wide(g, e, s, ev) : hipErrorInvalidValue;
-  if (bf16 && g.bn == 256) return launch_wide(kind, g, e, s, ev);
+  if (bf16 && g.bn == 256) return launch_wide(kind, g, e, s, ev, bt);
   if (bf16 && kind == GK_FWD_HEAD && g.bm == 16) {
     // 16-row tiles: outputs at most 128 wide, contraction a multiple of 32
     if (g.N > 128 || g.K % 32 || g.split != 1) return hipErrorInvalidValue;
-    ERASE_LAUNCH(erase_fwd_head16, dim3((unsigned)((g.M + 15) / 16)), dim3(256), 0, s, ev, g, e);
+    const dim3 grid((unsigned)((g.M + 15) / 16), bt ? (unsigned)bt->n : 1u);
+    if (bt)
+      ERASE_LAUNCH(erase_fwd_head16_b, grid, dim3(256), 0, s, ev, bt->jobs, bt->st);
+    else
+      ERASE_LAUNCH(erase_fwd_head16, grid, dim3(256), 0, s, ev, g, e);
     return hipGetLastError();
   }
   if (bf16) {
-    if (g.bm == 128 && g.bn == 128) return launch_gemm_t<uint16_t, 128, 128>(kind, g, e, s, ev);
-    if (g.bm == 128 && g.bn == 64) return launch_gemm_t<uint16_t, 128, 64>(kind, g, e, s, ev);
-    if (g.bm == 64 && g.bn == 128) return launch_gemm_t<uint16_t, 64, 128>(kind, g, e, s, ev);
-    if (g.bm == 64 && g.bn == 64) return launch_gemm_t<uint16_t, 64, 64>(kind, g, e, s, ev);
-    if (g.bm == 32 && g.bn == 128 && kind == GK_FWD_HEAD) return launch_gemm_t<uint16_t, 32, 128>(kind, g, e, s, ev);
+    if (g.bm == 128 && g.bn == 128) return launch_gemm_t<uint16_t, 128, 128>(kind, g, e, s, ev, bt);
+    if (g.bm == 128 && g.bn == 64) return launch_gemm_t<uint16_t, 128, 64>(kind, g, e, s, ev, bt);
+    if (g.bm == 64 && g.bn == 128) return launch_gemm_t<uint16_t, 64, 128>(kind, g, e, s, ev, bt);
+    if (g.bm == 64 && g.bn == 64) return launch_gemm_t<uint16_t, 64, 64>(kind, g, e, s, ev, bt);
+    if (g.bm == 32 && g.bn == 128 && kind == GK_FWD_HEAD) return launch_gemm_t<uint16_t, 32, 128>(kind, g, e, s, ev, bt);
   } else {
-    if (g.bm == 64 && g.bn == 64) return launch_gemm_t<float, 64, 64>(kind, g, e, s, ev);
+    if (g.bm == 64 && g.bn == 64) return launch_gemm_t<float, 64, 64>(kind, g, e, s, ev, bt);
   }
   return hipErrorInvalidValue;
 }
@@ -1306,7 +1382,7 @@ hipError_t launch_prologue(int bf16, const PrologueArgs& a, hipStream_t s, const
 // workgroup staging 32 rows in LDS took 10.4 and 39.9 us).
 // ---------------------------------------------------------------------------
 template <typename T, int CH>
-__global__ __launch_bounds__(256) void erase_head_bce(HeadArgs a, int lpr) {
+__device__ __forceinline__ void head_bce(const HeadArgs& a, int lpr) {
   constexpr int KCH = 16 / sizeof(T);  // elements per 16-byte chunk
   constexpr int U = CH == 1 ? 4 : CH == 2 ? 2 : 1;
   __shared__ float s_dw[4][64 * CH * KCH];
@@ -1419,26 +1495,37 @@ __global__ __launch_bounds__(256) void erase_head_bce(HeadArgs a, int lpr) {
 }
 
 template <typename T, int CH>
-static void launch_head_t(const HeadArgs& a, hipStream_t s, const LaunchEv& ev) {
+__global__ __launch_bounds__(256) void erase_head_bce(HeadArgs a, int lpr) {
+  head_bce<T, CH>(a, lpr);
+}
+template <typename T, int CH>
+__global__ __launch_bounds__(256) void erase_head_bce_b(const BlockJob* jobs, StepPtrs st, int lpr) {
+  HeadArgs a;
+  ld_head(job_of(jobs) + offsetof(BlockJob, h), a, st);
+  head_bce<T, CH>(a, lpr);
+}
+
+template <typename T, int CH>
+static void launch_head_t(const HeadArgs& a, hipStream_t s, const LaunchEv& ev, const Batch* bt) {
   constexpr int KCH = 16 / (int)sizeof(T);
   int lpr = 1;
   while (lpr < 64 && lpr * CH * KCH < a.N) lpr *= 2;
   const dim3 grid((unsigned)((a.M + a.rows - 1) / a.rows)), block(256);
-  ERASE_LAUNCH((erase_head_bce<T, CH>), grid, block, 0, s, ev, a, lpr);
+  ERASE_LAUNCH_B(erase_head_bce, (T, CH), grid, block, 0, (lpr), a, lpr);
 }
 
-hipError_t launch_head(int bf16, const HeadArgs& a, hipStream_t s, const LaunchEv& ev) {
+hipError_t launch_head(int bf16, const HeadArgs& a, hipStream_t s, const LaunchEv& ev, const Batch* bt) {
   if (a.N < 1 || a.N > HEAD_MAX_N || a.rows < 1) return hipErrorInvalidValue;
   const int ch = (a.N + 64 * (bf16 ? 8 : 4) - 1) / (64 * (bf16 ? 8 : 4));  // chunks per lane
   if (bf16) {
-    if (ch <= 1) launch_head_t<uint16_t, 1>(a, s, ev);
-    else if (ch <= 2) launch_head_t<uint16_t, 2>(a, s, ev);
-    else launch_head_t<uint16_t, 4>(a, s, ev);
+    if (ch <= 1) launch_head_t<uint16_t, 1>(a, s, ev, bt);
+    else if (ch <= 2) launch_head_t<uint16_t, 2>(a, s, ev, bt);
+    else launch_head_t<uint16_t, 4>(a, s, ev, bt);
   } else {
-    if (ch <= 1) launch_head_t<float, 1>(a, s, ev);
-    else if (ch <= 2) launch_head_t<float, 2>(a, s, ev);
-    else if (ch <= 4) launch_head_t<float, 4>(a, s, ev);
-    else launch_head_t<float, 8>(a, s, ev);
+    if (ch <= 1) launch_head_t<float, 1>(a, s, ev, bt);
+    else if (ch <= 2) launch_head_t<float, 2>(a, s, ev, bt);
+    else if (ch <= 4) launch_head_t<float, 4>(a, s, ev, bt);
+    else launch_head_t<float, 8>(a, s, ev, bt);
   }
   return hipGetLastError();
 }
@@ -1448,9 +1535,12 @@ hipError_t launch_head(int bf16, const HeadArgs& a, hipStream_t s, const LaunchE
 // per workgroup), with the ordered reduction of split partials fused in
 // front and the GEMM copies of the updated weights written behind.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int find_seg(const AdamArgs& a, int64_t chunk) {
+// (chunk0: the first chunk of each segment, from the kernel arguments or from
+// a batched launch's table)
+template <typename C>
+__device__ __forceinline__ int find_seg(C chunk0, int nseg, int64_t chunk) {
   int s = 0;
-  while (s + 1 < a.nseg && a.chunk0[s + 1] <= chunk) ++s;
+  while (s + 1 < nseg && chunk0[s + 1] <= chunk) ++s;
   return s;
 }
 
@@ -1469,13 +1559,13 @@ typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
 // Every call executes exactly one __syncthreads (whatever the segment kind;
 // a negative chunk only takes part in it), so the two halves of a
 // 512-thread workgroup can each run a chunk.
-template <typename T>
-__device__ __forceinline__ void adam_chunk(const AdamArgs& a, int64_t chunk, int tid, T (*s_o)[ADAM_TC]) {
+template <typename T, typename C>
+__device__ __forceinline__ void adam_chunk(const AdamArgs& a, C chunk0, int64_t chunk, int tid, T (*s_o)[ADAM_TC]) {
   if (chunk < 0) {
     __syncthreads();
     return;
   }
-  const AdamSeg sg = a.seg[find_seg(a, chunk)];
+  const AdamSeg sg = a.seg[find_seg(chunk0, a.nseg, chunk)];
   bool trans = false;  // the transposed copy is stored after the barrier
   int r0 = 0, tile = 0;
   float vp = 0.f, vm = 0.f, vv1 = 0.f;  // a vector's parameter and moments
@@ -1667,7 +1757,17 @@ __device__ __forceinline__ void adam_chunk(const AdamArgs& a, int64_t chunk, int
 template <typename T>
 __global__ __launch_bounds__(256) void erase_adam(AdamArgs a) {
   __shared__ __attribute__((aligned(16))) T s_o[ADAM_TR][ADAM_TC];
-  adam_chunk<T>(a, blockIdx.x, (int)threadIdx.x, s_o);
+  adam_chunk<T>(a, a.chunk0, blockIdx.x, (int)threadIdx.x, s_o);
+}
+typedef const __attribute__((address_space(4))) int64_t* cchunk_t;
+template <typename T>
+__global__ __launch_bounds__(256) void erase_adam_b(const BlockJob* jobs, StepPtrs st) {
+  __shared__ __attribute__((aligned(16))) T s_o[ADAM_TR][ADAM_TC];
+  AdamArgs a;
+  const cmem_t jb = job_of(jobs);
+  ld_adam(jb + offsetof(BlockJob, a), a, st, ld_block(jb));
+  adam_chunk<T>(a, (cchunk_t)(jb + offsetof(BlockJob, a) + offsetof(AdamArgs, chunk0)), blockIdx.x, (int)threadIdx.x,
+                s_o);
 }
 
 // A block's first-layer weight gradient with its fused Adam (two k-groups,
@@ -1676,10 +1776,10 @@ __global__ __launch_bounds__(256) void erase_adam(AdamArgs a) {
 // most), the rest run two Adam chunks each (one per half of the workgroup)
 // on the CUs the tiles leave free.  The two parts touch disjoint parameters,
 // and the Adam part reads only gradients finished by earlier launches.
-template <typename T, int BM, int BN>
-__global__ __launch_bounds__(512) void erase_wgrad_adam_kg2(GemmDesc g, EpiParams e, AdamArgs a, int ntiles) {
+template <typename T, int BM, int BN, typename C>
+__device__ __forceinline__ void wgrad_adam_kg2(const GemmDesc& g, const EpiParams& e, const AdamArgs& a, C chunk0,
+                                               int ntiles, char* smem) {
   constexpr int BKK = sizeof(T) == 2 ? 128 : 0;
-  __shared__ __attribute__((aligned(16))) char smem[GemmSmem<T, BM, BN, GK_WGRAD, BKK>::BYTES];
   static_assert(GemmSmem<T, BM, BN, GK_WGRAD, BKK>::BYTES >= 2 * ADAM_TR * ADAM_TC * (int)sizeof(T), "staging");
   const int b = blockIdx.x;
   if (b < ntiles) {
@@ -1690,8 +1790,25 @@ __global__ __launch_bounds__(512) void erase_wgrad_adam_kg2(GemmDesc g, EpiParam
     const int half = (int)threadIdx.x >> 8;
     T(*s_o)[ADAM_TC] = reinterpret_cast<T(*)[ADAM_TC]>(smem) + half * ADAM_TR;
     const int64_t chunk = 2 * (int64_t)(b - ntiles) + half;
-    adam_chunk<T>(a, chunk < a.nchunks ? chunk : -1, (int)threadIdx.x & 255, s_o);
+    adam_chunk<T>(a, chunk0, chunk < a.nchunks ? chunk : -1, (int)threadIdx.x & 255, s_o);
   }
+}
+template <typename T, int BM, int BN>
+__global__ __launch_bounds__(512) void erase_wgrad_adam_kg2(GemmDesc g, EpiParams e, AdamArgs a, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[GemmSmem<T, BM, BN, GK_WGRAD, sizeof(T) == 2 ? 128 : 0>::BYTES];
+  wgrad_adam_kg2<T, BM, BN>(g, e, a, a.chunk0, ntiles, smem);
+}
+template <typename T, int BM, int BN>
+__global__ __launch_bounds__(512) void erase_wgrad_adam_kg2_b(const BlockJob* jobs, StepPtrs st, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[GemmSmem<T, BM, BN, GK_WGRAD, sizeof(T) == 2 ? 128 : 0>::BYTES];
+  GemmDesc g;
+  EpiParams e;
+  AdamArgs a;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), g, st);
+  ld_epi(jb + offsetof(BlockJob, e), e, st);
+  ld_adam(jb + offsetof(BlockJob, a), a, st, ld_block(jb));
+  wgrad_adam_kg2<T, BM, BN>(g, e, a, (cchunk_t)(jb + offsetof(BlockJob, a) + offsetof(AdamArgs, chunk0)), ntiles, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1919,8 +2036,9 @@ __device__ __forceinline__ void wgrad_adam_w4_tile(const GemmDesc& g, const EpiP
   }
 }
 
-__global__ __launch_bounds__(256) void erase_wgrad_adam_w4(GemmDesc g, EpiParams e, AdamArgs a, int ntiles) {
-  __shared__ __attribute__((aligned(16))) char smem[w4::BYTES];
+template <typename C>
+__device__ __forceinline__ void wgrad_adam_w4(const GemmDesc& g, const EpiParams& e, const AdamArgs& a, C chunk0,
+                                              int ntiles, char* smem) {
   static_assert(w4::BYTES >= ADAM_TR * ADAM_TC * 2, "staging");
   const int b = blockIdx.x;
   if (b < ntiles) {
@@ -1928,17 +2046,35 @@ __global__ __launch_bounds__(256) void erase_wgrad_adam_w4(GemmDesc g, EpiParams
     wgrad_adam_w4_tile(g, e, ti.m, ti.n, smem);
   } else {
     uint16_t(*s_o)[ADAM_TC] = reinterpret_cast<uint16_t(*)[ADAM_TC]>(smem);
-    adam_chunk<uint16_t>(a, b - ntiles, (int)threadIdx.x, s_o);
+    adam_chunk<uint16_t>(a, chunk0, b - ntiles, (int)threadIdx.x, s_o);
   }
+}
+__global__ __launch_bounds__(256) void erase_wgrad_adam_w4(GemmDesc g, EpiParams e, AdamArgs a, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[w4::BYTES];
+  wgrad_adam_w4(g, e, a, a.chunk0, ntiles, smem);
+}
+__global__ __launch_bounds__(256) void erase_wgrad_adam_w4_b(const BlockJob* jobs, StepPtrs st, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[w4::BYTES];
+  GemmDesc g;
+  EpiParams e;
+  AdamArgs a;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), g, st);
+  ld_epi(jb + offsetof(BlockJob, e), e, st);
+  ld_adam(jb + offsetof(BlockJob, a), a, st, ld_block(jb));
+  wgrad_adam_w4(g, e, a, (cchunk_t)(jb + offsetof(BlockJob, a) + offsetof(AdamArgs, chunk0)), ntiles, smem);
 }
 
 static hipError_t launch_wgrad_w8(const GemmDesc& g0, const EpiParams& e, const AdamArgs& a, hipStream_t s,
-                                  const LaunchEv& ev) {
+                                  const LaunchEv& ev, const Batch* bt) {
   if (g0.K % 64 != 0) return hipErrorInvalidValue;  // whole 32-row slices
   const GemmDesc g = with_group(g0, 64, 64);
   const int ntiles = ((g.M + 63) / 64) * ((g.N + 63) / 64);
   const dim3 grid((unsigned)(ntiles + a.nchunks)), block(256);
-  ERASE_LAUNCH(erase_wgrad_adam_w4, grid, block, 0, s, ev, g, e, a, ntiles);
+  if (bt)
+    ERASE_LAUNCH(erase_wgrad_adam_w4_b, dim3(grid.x, (unsigned)bt->n), block, 0, s, ev, bt->jobs, bt->st, ntiles);
+  else
+    ERASE_LAUNCH(erase_wgrad_adam_w4, grid, block, 0, s, ev, g, e, a, ntiles);
   return hipGetLastError();
 }
 
@@ -2169,20 +2305,20 @@ static hipError_t launch_logits_wide(const GemmDesc& g, const EpiParams& e, hipS
 }
 
 hipError_t launch_wgrad_adam(int bf16, const GemmDesc& g0, const EpiParams& e, const AdamArgs& a, hipStream_t s,
-                             const LaunchEv& ev) {
+                             const LaunchEv& ev, const Batch* bt) {
   if (g0.bm != 64 || g0.bn != 64 || g0.kgroups != 2 || g0.split != 1 || !e.ap) return hipErrorInvalidValue;
-  if (bf16) return launch_wgrad_w8(g0, e, a, s, ev);
+  if (bf16) return launch_wgrad_w8(g0, e, a, s, ev, bt);
   const GemmDesc g = with_group(g0, 64, 64);
   const int ntiles = ((g.M + 63) / 64) * ((g.N + 63) / 64);
   const dim3 grid((unsigned)(ntiles + (a.nchunks + 1) / 2)), block(512);
-  ERASE_LAUNCH((erase_wgrad_adam_kg2<float, 64, 64>), grid, block, 0, s, ev, g, e, a, ntiles);
+  ERASE_LAUNCH_B(erase_wgrad_adam_kg2, (float, 64, 64), grid, block, 0, (ntiles), g, e, a, ntiles);
   return hipGetLastError();
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void erase_refresh(AdamArgs a) {
   const int64_t chunk = blockIdx.x;
-  const AdamSeg sg = a.seg[find_seg(a, chunk)];
+  const AdamSeg sg = a.seg[find_seg(a.chunk0, a.nseg, chunk)];
   const int tile = (int)(chunk - sg.chunk0);
   const int r0 = (tile / sg.tcols) * ADAM_TR;
   const int c = (tile % sg.tcols) * ADAM_TC + (int)threadIdx.x;
@@ -2195,12 +2331,12 @@ __global__ __launch_bounds__(256) void erase_refresh(AdamArgs a) {
   }
 }
 
-hipError_t launch_adam(int bf16, const AdamArgs& a, hipStream_t s, const LaunchEv& ev) {
+hipError_t launch_adam(int bf16, const AdamArgs& a, hipStream_t s, const LaunchEv& ev, const Batch* bt) {
   dim3 grid((unsigned)a.nchunks), block(256);
   if (bf16)
-    ERASE_LAUNCH(erase_adam<uint16_t>, grid, block, 0, s, ev, a);
+    ERASE_LAUNCH_B(erase_adam, (uint16_t), grid, block, 0, (), a);
   else
-    ERASE_LAUNCH(erase_adam<float>, grid, block, 0, s, ev, a);
+    ERASE_LAUNCH_B(erase_adam, (float), grid, block, 0, (), a);
   return hipGetLastError();
 }
 

@@ -503,38 +503,29 @@ __device__ __forceinline__ void epi_wgrad(const EpiParams& e, const A& acc, cons
 }  // namespace wide
 
 template <int HA, int HB, int KIND>
-__global__ __launch_bounds__(wide::NT) void erase_wide_nt(GemmDesc g, EpiParams e, int ntiles) {
-  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+__device__ __forceinline__ void wide_nt(const GemmDesc& g, const EpiParams& e, int ntiles, char* smem) {
   wide::run<HA, HB, false>(
       g, (int)blockIdx.x, (int)gridDim.x, ntiles, false, smem,
       [&](const auto& acc, const auto&, const TileIdx& ti, bool, int wm, int wn, int fr, int fg) {
         wide::epi_nt<HA, HB, KIND>(e, acc, g.M, g.N, ti, wm, wn, fr, fg);
       });
 }
-
 template <int HA, int HB>
-__global__ __launch_bounds__(wide::NT) void erase_wide_wgrad(GemmDesc g, EpiParams e, int ntiles) {
-  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+__device__ __forceinline__ void wide_wgrad(const GemmDesc& g, const EpiParams& e, int b, int G, int ntiles, char* smem) {
   wide::run<HA, HB, true>(
-      g, (int)blockIdx.x, (int)gridDim.x, ntiles, e.bpart != nullptr, smem,
+      g, b, G, ntiles, e.bpart != nullptr, smem,
       [&](const auto& acc, const auto& accr, const TileIdx& ti, bool rows, int wm, int wn, int fr, int fg) {
         wide::epi_wgrad<HA, HB>(e, acc, accr, g.M, g.N, ti, rows, wm, wn, fr, fg);
       });
 }
-
 // Both backward GEMMs of a layer.  The workgroups of the longer contraction
 // come first (`first`: the weight gradient's).
 template <int HA, int HB>
-__global__ __launch_bounds__(wide::NT) void erase_wide_bwd(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew,
-                                                           int nd, int nw, int first) {
-  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+__device__ __forceinline__ void wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw,
+                                         const EpiParams& ew, int nd, int nw, int first, char* smem) {
   const int b = (int)blockIdx.x - (first ? 0 : nd);
   if (b >= 0 && b < nw) {
-    wide::run<HA, HB, true>(
-        gw, b, nw, nw, ew.bpart != nullptr, smem,
-        [&](const auto& acc, const auto& accr, const TileIdx& ti, bool rows, int wm, int wn, int fr, int fg) {
-          wide::epi_wgrad<HA, HB>(ew, acc, accr, gw.M, gw.N, ti, rows, wm, wn, fr, fg);
-        });
+    wide_wgrad<HA, HB>(gw, ew, b, nw, nw, smem);
   } else {
     wide::run<HA, HB, false>(
         gd, first ? b - nw : (int)blockIdx.x, nd, nd, false, smem,
@@ -544,37 +535,98 @@ __global__ __launch_bounds__(wide::NT) void erase_wide_bwd(GemmDesc gd, EpiParam
   }
 }
 
+template <int HA, int HB, int KIND>
+__global__ __launch_bounds__(wide::NT) void erase_wide_nt(GemmDesc g, EpiParams e, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  wide_nt<HA, HB, KIND>(g, e, ntiles, smem);
+}
+template <int HA, int HB>
+__global__ __launch_bounds__(wide::NT) void erase_wide_wgrad(GemmDesc g, EpiParams e, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  wide_wgrad<HA, HB>(g, e, (int)blockIdx.x, (int)gridDim.x, ntiles, smem);
+}
+template <int HA, int HB>
+__global__ __launch_bounds__(wide::NT) void erase_wide_bwd(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew,
+                                                           int nd, int nw, int first) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  wide_bwd<HA, HB>(gd, ed, gw, ew, nd, nw, first, smem);
+}
+// the same for several blocks (grid row j: job j)
+template <int HA, int HB, int KIND>
+__global__ __launch_bounds__(wide::NT) void erase_wide_nt_b(const BlockJob* jobs, StepPtrs st, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  GemmDesc g;
+  EpiParams e;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), g, st);
+  ld_epi(jb + offsetof(BlockJob, e), e, st);
+  wide_nt<HA, HB, KIND>(g, e, ntiles, smem);
+}
+template <int HA, int HB>
+__global__ __launch_bounds__(wide::NT) void erase_wide_wgrad_b(const BlockJob* jobs, StepPtrs st, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  GemmDesc g;
+  EpiParams e;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), g, st);
+  ld_epi(jb + offsetof(BlockJob, e), e, st);
+  wide_wgrad<HA, HB>(g, e, (int)blockIdx.x, (int)gridDim.x, ntiles, smem);
+}
+template <int HA, int HB>
+__global__ __launch_bounds__(wide::NT) void erase_wide_bwd_b(const BlockJob* jobs, StepPtrs st, int nd, int nw,
+                                                             int first) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  GemmDesc gd, gw;
+  EpiParams ed, ew;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), gd, st);
+  ld_epi(jb + offsetof(BlockJob, e), ed, st);
+  ld_gemm(jb + offsetof(BlockJob, g2), gw, st);
+  ld_epi(jb + offsetof(BlockJob, e2), ew, st);
+  wide_bwd<HA, HB>(gd, ed, gw, ew, nd, nw, first, smem);
+}
+
 static int wide_tiles(const GemmDesc& g, int bm, int bn) {
   return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.split;
 }
 
 template <int HA, int HB>
-static hipError_t launch_wide_t(int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev) {
+static hipError_t launch_wide_t(int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
+                       const Batch* bt) {
   const int nt = wide_tiles(g, 2 * HA, 2 * HB);
-  const dim3 grid((unsigned)nt), block(wide::NT);
+  const dim3 grid((unsigned)nt, bt ? (unsigned)bt->n : 1u), block(wide::NT);
+  if (bt && (kind == GK_FWD_LIN || kind == GK_FWD_GELU || kind == GK_DGRAD_GELU)) return hipErrorInvalidValue;
+#define ERASE_WIDE(ONE, MANY)                                          \
+  if (bt)                                                             \
+    ERASE_LAUNCH(MANY, grid, block, 0, s, ev, bt->jobs, bt->st, nt);   \
+  else                                                                \
+    ERASE_LAUNCH(ONE, grid, block, 0, s, ev, g, e, nt)
   switch (kind) {
-    case GK_FWD_RELU: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_RELU>), grid, block, 0, s, ev, g, e, nt); break;
-    case GK_FWD_CROSS: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_CROSS>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_FWD_RELU: ERASE_WIDE((erase_wide_nt<HA, HB, GK_FWD_RELU>), (erase_wide_nt_b<HA, HB, GK_FWD_RELU>)); break;
+    case GK_FWD_CROSS: ERASE_WIDE((erase_wide_nt<HA, HB, GK_FWD_CROSS>), (erase_wide_nt_b<HA, HB, GK_FWD_CROSS>)); break;
     case GK_FWD_LIN: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_LIN>), grid, block, 0, s, ev, g, e, nt); break;
     case GK_FWD_GELU: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
-    case GK_DGRAD: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_DGRAD>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_DGRAD: ERASE_WIDE((erase_wide_nt<HA, HB, GK_DGRAD>), (erase_wide_nt_b<HA, HB, GK_DGRAD>)); break;
     case GK_DGRAD_GELU: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_DGRAD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
-    case GK_WGRAD: ERASE_LAUNCH((erase_wide_wgrad<HA, HB>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_WGRAD: ERASE_WIDE((erase_wide_wgrad<HA, HB>), (erase_wide_wgrad_b<HA, HB>)); break;
     default: return hipErrorInvalidValue;
   }
+#undef ERASE_WIDE
   return hipGetLastError();
 }
 
-hipError_t launch_wide(int kind, const GemmDesc& g0, const EpiParams& e, hipStream_t s, const LaunchEv& ev) {
+hipError_t launch_wide(int kind, const GemmDesc& g0, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
+                       const Batch* bt) {
   GemmDesc g = g0;
   if (g.group <= 0) g.group = xcd_group((g.M + g.bm - 1) / g.bm, (g.N + g.bn - 1) / g.bn, g.split, g.bm, g.bn);
   if (g.K % 64 || g.kps % 64 || g.kps <= 0 || g.lda % 8 || g.ldb % 8) return hipErrorInvalidValue;
-  if (g.bm == 256 && g.bn == 256) return launch_wide_t<128, 128>(kind, g, e, s, ev);
+  if (g.bm == 256 && g.bn == 256) return launch_wide_t<128, 128>(kind, g, e, s, ev, bt);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
-                           hipStream_t s, const LaunchEv& ev) {
+                           hipStream_t s, const LaunchEv& ev,
+                       const Batch* bt) {
   GemmDesc d = gd, w = gw;
   if (d.K % 64 || d.kps < d.K || d.lda % 8 || d.ldb % 8 || w.K % 64 || w.kps % 64 || w.kps <= 0 || w.lda % 8 ||
       w.ldb % 8)
@@ -583,8 +635,12 @@ hipError_t launch_wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDe
   if (w.group <= 0) w.group = xcd_group((w.M + w.bm - 1) / w.bm, (w.N + w.bn - 1) / w.bn, w.split, w.bm, w.bn);
   const int nd = wide_tiles(d, d.bm, d.bn), nw = wide_tiles(w, w.bm, w.bn);
   if (d.bm == 256 && d.bn == 256 && w.bm == 256 && w.bn == 256) {
-    ERASE_LAUNCH((erase_wide_bwd<128, 128>), dim3((unsigned)(nd + nw)), dim3(wide::NT), 0, s, ev, d, ed, w, ew, nd, nw,
-                 w.kps >= d.K ? 1 : 0);
+    const dim3 grid((unsigned)(nd + nw), bt ? (unsigned)bt->n : 1u), block(wide::NT);
+    const int first = w.kps >= d.K ? 1 : 0;
+    if (bt)
+      ERASE_LAUNCH((erase_wide_bwd_b<128, 128>), grid, block, 0, s, ev, bt->jobs, bt->st, nd, nw, first);
+    else
+      ERASE_LAUNCH((erase_wide_bwd<128, 128>), grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first);
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
