@@ -207,9 +207,9 @@ struct Carver {
   }
 };
 
-// Workgroup tile and split of one GEMM.  Enough workgroups to cover the 256
-// CUs when the shape allows it, the largest tile that still does, and a
-// split of the contraction only for weight gradients (whose outputs are few).
+// Tile and split of a GEMM of the core (fp32, and the bf16 shapes too small
+// for the tiles of wide_plan.h): a split of the contraction only for weight
+// gradients (whose outputs are few).
 GemmPlan choose_gemm(int bf16, int64_t Mg, int64_t Ng, int64_t Kc, bool allow_split) {
   GemmPlan p;
   const int BK = bf16 ? 64 : 32;
@@ -222,41 +222,30 @@ GemmPlan choose_gemm(int bf16, int64_t Mg, int64_t Ng, int64_t Kc, bool allow_sp
   };
   if (!bf16) return finish(64, 64, 1);
   // At least `target` workgroups (1.5 per CU) so the launch covers the
-  // chip; the largest tile that reaches it (fewer LDS bytes per MFMA).  A
-  // long contraction (>= 1024) takes one 64x128 workgroup per CU over two
-  // 64x64 ones (4096 x 512 x 1728: 14.7 vs 15.8 us).  Otherwise a short
-  // contraction falls back to 64x64, split only for weight gradients (a
-  // 128x64 split 4 of the 512 x 1677 weight gradient over 4096 rows is 1.5
-  // us faster than 64x64 split 2, but its two extra partial slices cost
-  // Adam 2.1 us more).
+  // chip.  A long contraction (>= 1024) takes one 64x128 workgroup per CU over
+  // two 64x64 ones (4096 x 512 x 1728: 14.7 vs 15.8 us).  Otherwise 64x64,
+  // split only for weight gradients.
   const int64_t target = 384;
   auto wgs = [&](int bm, int bn) { return cdiv(Mg, bm) * cdiv(Ng, bn); };
-  const int tiles[3][2] = {{128, 128}, {128, 64}, {64, 128}};
-  for (int i = 0; i < 3; ++i)
-    if (wgs(tiles[i][0], tiles[i][1]) >= target) return finish(tiles[i][0], tiles[i][1], 1);
   if (!allow_split && Kc >= 1024 && wgs(64, 128) >= 256) {
     // one workgroup per CU: two k-groups give each SIMD two waves
     p.kgroups = 2;
     return finish(64, 128, 1);
   }
-  if (wgs(64, 64) >= target) return finish(64, 64, 1);
   // at most one 64x64 workgroup per CU: two k-groups give each SIMD two waves
   if (!allow_split && wgs(64, 64) <= 256) p.kgroups = 2;
   if (allow_split) {
     int s = 1;
-    while (s < 16 && wgs(128, 128) * s < target && Kc / (s * 2) >= 2048) s *= 2;
-    if (wgs(128, 128) * s >= target) return finish(128, 128, s);
-    s = 1;
     while (s < 16 && wgs(64, 64) * s < target && Kc / (s * 2) >= 256) s *= 2;
     return finish(64, 64, s);
   }
   return finish(64, 64, 1);
 }
 
-// 256x256 tiles over `split` slices of the contraction.
-GemmPlan wide_plan(int64_t Kc, int split) {
+// 256x256 or 128x128 tiles over `split` slices of the contraction.
+GemmPlan wide_plan(int tile, int64_t Kc, int split) {
   GemmPlan p;
-  p.bm = p.bn = 256;
+  p.bm = p.bn = tile;
   p.kps = (int)roundup(cdiv(std::max<int64_t>(Kc, 1), split), 64);
   p.split = (int)cdiv(std::max<int64_t>(Kc, 1), p.kps);
   return p;
@@ -349,6 +338,17 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
     for (int q = 0; q < 2; ++q) P->xp[q] = cv.take(size_t(Mr) * P->ldxp * esz);
   }
   P->blk.assign(c.n_blocks, BlockRT{});
+  P->serial = make_unit(c, 0, c.n_blocks);
+  P->overlap = make_units(c, erase_unit_cap(c));
+  // blocks that share a launch in the ERASE schedules (the plan is the same
+  // for every schedule)
+  std::vector<int> share_f(c.n_blocks, 1), share_b(c.n_blocks, 1);
+  for (const Unit& u : P->overlap)
+    for (const Group& g : u.groups)
+      for (int i = 0; i < g.n; ++i) {
+        share_b[g.first + i] = g.n;
+        share_f[g.first + i] = g.share_fwd ? g.n : 1;
+      }
   for (int b = 0; b < c.n_blocks; ++b) {
     const erase_block_spec& S = c.blocks[b];
     BlockRT& B = P->blk[b];
@@ -395,22 +395,24 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
       // launch shapes (contraction lengths padded to the k-step)
       const int BK = P->bf16 ? 64 : 32;
       R.fwd = choose_gemm(P->bf16, M, R.N, roundup(R.K, BK), false);
-      if (P->bf16 && wide_nt_pays(M, R.N, R.K)) R.fwd = wide_plan(roundup(R.K, 64), 1);
+      if (P->bf16)
+        if (const int t = wide_nt_tile(M, R.N, R.K, share_f[b])) R.fwd = wide_plan(t, roundup(R.K, 64), 1);
       R.wgrad = choose_gemm(P->bf16, R.N, R.K, roundup(M, BK), true);
       if (l == 0 && dgrad) {
         R.dgrad = choose_gemm(P->bf16, M, R.K, roundup(R.N, BK), false);
-        if (P->bf16 && wide_nt_pays(M, R.K, R.N)) R.dgrad = wide_plan(roundup(R.N, 64), 1);
+        if (P->bf16)
+          if (const int t = wide_nt_tile(M, R.K, R.N, 1)) R.dgrad = wide_plan(t, roundup(R.N, 64), 1);
         R.dgrad.group = xcd_group((int)cdiv(M, R.dgrad.bm), (int)cdiv(R.K, R.dgrad.bn), 1, R.dgrad.bm, R.dgrad.bn);
         R.dgrad.kgroups = 1;
       }
       if (l >= 1) {
         R.dgrad = choose_gemm(P->bf16, M, R.K, roundup(R.N, BK), false);
         // one launch for both backward GEMMs when they can share a tile
-        const int wsplit = P->bf16 ? wide_pair_split(M, R.N, R.K) : 0;
-        const bool wide = wsplit > 0;
+        const WidePair wp = P->bf16 ? wide_pair(M, R.N, R.K, share_b[b]) : WidePair{};
+        const bool wide = wp.tile > 0;
         if (wide) {
-          R.dgrad = wide_plan(roundup(R.N, 64), 1);
-          R.wgrad = wide_plan(roundup(M, 64), wsplit);
+          R.dgrad = wide_plan(wp.tile, roundup(R.N, 64), 1);
+          R.wgrad = wide_plan(wp.tile, roundup(M, 64), wp.split);
         } else if (R.dgrad.bm != R.wgrad.bm || R.dgrad.bn != R.wgrad.bn) {
           GemmPlan d64 = choose_gemm(P->bf16, 1, 1, roundup(R.N, BK), false);  // 64x64, split 1
           d64.kgroups = 1;  // the grouped launch runs 256-thread workgroups at 64x64
@@ -423,7 +425,7 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
           R.dgrad = d64;
           R.wgrad = w64;
         }
-        R.grouped = wide || (R.dgrad.bm == 64 && R.dgrad.bn == 64) || (R.dgrad.bm == 128 && R.dgrad.bn == 128);
+        R.grouped = wide || (R.dgrad.bm == 64 && R.dgrad.bn == 64);
         if (!wide && R.grouped && R.wgrad.split > 1) {
           // the input-gradient tiles of the same launch fill the chip: the
           // weight gradient keeps slices of >= 512 batch rows, so Adam reads
@@ -451,18 +453,27 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
       // in that launch's epilogue and no partial slice goes to memory.  Not
       // when the transposed GEMM copy is needed (the undetached schedule's
       // input gradient), which only the Adam kernel writes.
-      // Large batches take 256x256 tiles and slices instead: the 64x64 tiles
+      // Large batches take larger tiles and slices instead, and Adam a launch
+      // of its own (30 bytes a parameter, and the slices): the 64x64 tiles
       // cost 0.62 us per 128 batch rows with one on a compute unit, 1.07 us
       // with two (512 x 1677 over 32768 rows 166 us, 1677 x 1677 over 16384
       // rows 273 us).
-      const int64_t t64 = cdiv(R.N, 64) * cdiv(R.K, 64);
-      const double t64_us = double(cdiv(M, 128)) * (t64 <= 256 ? 0.62 : 1.07 * double(cdiv(t64, 512)));
-      const int wsp0 = P->bf16 && l == 0
-                           ? wide_wgrad_split(R.N, R.K, M, dgrad ? wide_core_wgrad_us(R.N, R.K, M) : t64_us).split
-                           : 0;
-      if (wsp0 > 0) {
-        R.wgrad = wide_plan(roundup(M, 64), wsp0);
-        R.wgrad.group = xcd_group((int)cdiv(R.N, 256), (int)cdiv(R.K, 256), R.wgrad.split, 256, 256);
+      WidePair w0;
+      if (P->bf16 && l == 0) {
+        const int sh = share_b[b];
+        const int64_t t64 = cdiv(R.N, 64) * cdiv(R.K, 64) * sh;
+        const double own = dgrad ? wide_core_wgrad_us(R.N, R.K, M, sh)
+                                 : double(cdiv(M, 128)) * (t64 <= 256 ? 0.62 : 1.07 * double(cdiv(t64, 512))) -
+                                       (30.0 * double(R.N) * R.K * sh / 5e6 + 3.0);
+        w0 = wide_wgrad(R.N, R.K, M, own, sh);
+      }
+      if (w0.tile > 0) {
+        R.wgrad = wide_plan(w0.tile, roundup(M, 64), w0.split);
+        R.wgrad.group = xcd_group((int)cdiv(R.N, w0.tile), (int)cdiv(R.K, w0.tile), R.wgrad.split, w0.tile, w0.tile);
+        if (dgrad) {  // in the same tiles: one launch (undetached schedule)
+          R.dgrad = wide_plan(w0.tile, roundup(R.N, 64), 1);
+          R.dgrad.group = xcd_group((int)cdiv(M, w0.tile), (int)cdiv(R.K, w0.tile), 1, w0.tile, w0.tile);
+        }
       } else if (l == 0 && !dgrad) {
         R.fused_adam = true;
         R.wgrad.bm = R.wgrad.bn = 64;
@@ -514,8 +525,6 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
     B.segs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * nseg));
     B.rsegs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * nseg));
   }
-  P->serial = make_unit(c, 0, c.n_blocks);
-  P->overlap = make_units(c, erase_unit_cap(c));
   for_each_unit(P, [&](Unit& u) {
     for (Group& g : u.groups)
       if (g.n > 1)

@@ -929,7 +929,7 @@ ERASE_GEMM_KERNEL_KG2(erase_wgrad_gemm_kg2, GK_WGRAD, 128)
 // activation gradient and are independent): workgroups [0, nw) compute the
 // weight-gradient tiles and slices (the longer contractions, so they start
 // first), the rest the input-gradient tiles.
-template <typename T, int BM, int BN, int KG>
+template <typename T, int BM, int BN>
 __device__ __forceinline__ void bwd_pair(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw,
                                          const EpiParams& ew, int nw, char* smem) {
   // each GEMM is renumbered on its own (workgroups b and b + 8 still share an
@@ -937,11 +937,11 @@ __device__ __forceinline__ void bwd_pair(const GemmDesc& gd, const EpiParams& ed
   const int b = blockIdx.x;
   if (b < nw) {
     const TileIdx ti = tile_from(xcd_linear(b, nw), (gw.M + BM - 1) / BM, (gw.N + BN - 1) / BN, gw.group);
-    gemm_body<T, BM, BN, GK_WGRAD, 2, KG>(gw, ew, ti.m, ti.n, ti.z, smem);
+    gemm_body<T, BM, BN, GK_WGRAD>(gw, ew, ti.m, ti.n, ti.z, smem);
   } else {
     const int nd = gridDim.x - nw;
     const TileIdx ti = tile_from(xcd_linear(b - nw, nd), (gd.M + BM - 1) / BM, (gd.N + BN - 1) / BN, gd.group);
-    gemm_body<T, BM, BN, GK_DGRAD, 2, KG>(gd, ed, ti.m, ti.n, 0, smem);
+    gemm_body<T, BM, BN, GK_DGRAD>(gd, ed, ti.m, ti.n, 0, smem);
   }
 }
 
@@ -949,7 +949,7 @@ template <typename T, int BM, int BN>
 __global__ __launch_bounds__(256) void erase_bwd_gemm(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew, int nw) {
   constexpr int SD = GemmSmem<T, BM, BN, GK_DGRAD>::BYTES, SW = GemmSmem<T, BM, BN, GK_WGRAD>::BYTES;
   __shared__ __attribute__((aligned(16))) char smem[SD > SW ? SD : SW];
-  bwd_pair<T, BM, BN, 1>(gd, ed, gw, ew, nw, smem);
+  bwd_pair<T, BM, BN>(gd, ed, gw, ew, nw, smem);
 }
 template <typename T, int BM, int BN>
 __global__ __launch_bounds__(256) void erase_bwd_gemm_b(const BlockJob* jobs, StepPtrs st, int nw) {
@@ -962,18 +962,7 @@ __global__ __launch_bounds__(256) void erase_bwd_gemm_b(const BlockJob* jobs, St
   ld_epi(jb + offsetof(BlockJob, e), ed, st);
   ld_gemm(jb + offsetof(BlockJob, g2), gw, st);
   ld_epi(jb + offsetof(BlockJob, e2), ew, st);
-  bwd_pair<T, BM, BN, 1>(gd, ed, gw, ew, nw, smem);
-}
-
-// The same pair with 512-thread workgroups: two k-groups of four waves, each
-// over half of every k-step of the whole tile, so every SIMD runs two waves
-// of one tile (the large 128x128 tiles, one workgroup per CU).
-template <typename T, int BM, int BN>
-__global__ __launch_bounds__(512) void erase_bwd_gemm_kg2(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew,
-                                                          int nw) {
-  constexpr int SD = GemmSmem<T, BM, BN, GK_DGRAD>::BYTES_KG2, SW = GemmSmem<T, BM, BN, GK_WGRAD>::BYTES_KG2;
-  __shared__ __attribute__((aligned(16))) char smem[SD > SW ? SD : SW];
-  bwd_pair<T, BM, BN, 2>(gd, ed, gw, ew, nw, smem);
+  bwd_pair<T, BM, BN>(gd, ed, gw, ew, nw, smem);
 }
 
 int xcd_group(int gm, int gn, int split, int bm, int bn) {
@@ -1023,69 +1012,65 @@ static hipError_t launch_wgrad_w8(const GemmDesc& g, const EpiParams& e, const A
 #define ERASE_T(...) <__VA_ARGS__>
 #define ERASE_A(...) __VA_OPT__(, ) __VA_ARGS__
 
-template <typename T, int BM, int BN>
+// The core's 64x64 tiles.
+template <typename T>
 static hipError_t launch_gemm_t(int kind, const GemmDesc& g0, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
                                 const Batch* bt) {
-  const GemmDesc g = with_group(g0, BM, BN);
-  dim3 grid(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * g.split), block(256);
+  const GemmDesc g = with_group(g0, 64, 64);
+  dim3 grid(((g.M + 63) / 64) * ((g.N + 63) / 64) * g.split), block(256);
   // the fused Adam update exists only in the two k-group weight gradient
   if (kind == GK_WGRAD && e.ap && (g.kgroups != 2 || g.split != 1)) return hipErrorInvalidValue;
   if (g.kgroups == 2) {
-    // two k-groups: the unsplit 64x64 weight gradient (fp32 or bf16)
-    if constexpr (BM == 64 && BN == 64) {
-      if (kind == GK_WGRAD && g.split == 1) {
-        // bf16: the eight-wave tiles of the launch that also updates the
-        // block's other parameters (the same sums, so every schedule gives
-        // the same bits), here without those; they need the fused update
-        if constexpr (sizeof(T) == 2) return e.ap ? launch_wgrad_w8(g, e, AdamArgs{}, s, ev, bt) : hipErrorInvalidValue;
-        ERASE_LAUNCH_B(erase_wgrad_gemm_kg2, (T, BM, BN), grid, dim3(512), 0, (), g, e);
+    // two k-groups: the unsplit weight gradient
+    if (kind == GK_WGRAD && g.split == 1) {
+      // bf16: the four-wave tiles of the launch that also updates the
+      // block's other parameters (the same sums, so every schedule gives
+      // the same bits), here without those; they need the fused update
+      if constexpr (sizeof(T) == 2) {
+        return e.ap ? launch_wgrad_w8(g, e, AdamArgs{}, s, ev, bt) : hipErrorInvalidValue;
+      } else {
+        ERASE_LAUNCH_B(erase_wgrad_gemm_kg2, (T, 64, 64), grid, dim3(512), 0, (), g, e);
         return hipGetLastError();
       }
     }
-    // and bf16 64x128 and 64x64 forward tiles
-    if constexpr (sizeof(T) == 2 && BM == 64 && (BN == 128 || BN == 64)) {
+    // and bf16 forward tiles
+    if constexpr (sizeof(T) == 2) {
       if (kind == GK_FWD_RELU) {
-        ERASE_LAUNCH_B(erase_fwd_gemm_kg2, (T, BM, BN), grid, dim3(512), 0, (), g, e);
+        ERASE_LAUNCH_B(erase_fwd_gemm_kg2, (T, 64, 64), grid, dim3(512), 0, (), g, e);
         return hipGetLastError();
       }
       if (kind == GK_FWD_CROSS) {
-        ERASE_LAUNCH_B(erase_fwd_cross_gemm_kg2, (T, BM, BN), grid, dim3(512), 0, (), g, e);
+        ERASE_LAUNCH_B(erase_fwd_cross_gemm_kg2, (T, 64, 64), grid, dim3(512), 0, (), g, e);
         return hipGetLastError();
       }
     }
     return hipErrorInvalidValue;
   }
   switch (kind) {
-    case GK_FWD_RELU: ERASE_LAUNCH_B(erase_fwd_gemm, (T, BM, BN), grid, block, 0, (), g, e); break;
-    case GK_FWD_CROSS: ERASE_LAUNCH_B(erase_fwd_cross_gemm, (T, BM, BN), grid, block, 0, (), g, e); break;
-    case GK_WGRAD:
-      if constexpr (BM >= 64) {  // k-major tiles of 64 or 128 columns
-        ERASE_LAUNCH_B(erase_wgrad_gemm, (T, BM, BN), grid, block, 0, (), g, e);
-      } else {
-        return hipErrorInvalidValue;
-      }
-      break;
-    case GK_DGRAD: ERASE_LAUNCH_B(erase_dgrad_gemm, (T, BM, BN), grid, block, 0, (), g, e); break;
+    case GK_FWD_RELU: ERASE_LAUNCH_B(erase_fwd_gemm, (T, 64, 64), grid, block, 0, (), g, e); break;
+    case GK_FWD_CROSS: ERASE_LAUNCH_B(erase_fwd_cross_gemm, (T, 64, 64), grid, block, 0, (), g, e); break;
+    case GK_WGRAD: ERASE_LAUNCH_B(erase_wgrad_gemm, (T, 64, 64), grid, block, 0, (), g, e); break;
+    case GK_DGRAD: ERASE_LAUNCH_B(erase_dgrad_gemm, (T, 64, 64), grid, block, 0, (), g, e); break;
     case GK_FWD_LIN:
     case GK_FWD_GELU:
     case GK_DGRAD_GELU:
     case GK_FWD_LOGITS:
-      // transformer kinds: bf16, 64- and 128-row tiles
+      // transformer kinds: bf16
       if (bt) return hipErrorInvalidValue;
-      if constexpr (sizeof(T) == 2 && BM >= 64) {
-        if (kind == GK_FWD_LIN) ERASE_LAUNCH((erase_fwd_lin_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e);
-        if (kind == GK_FWD_GELU) ERASE_LAUNCH((erase_fwd_gelu_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e);
-        if (kind == GK_DGRAD_GELU) ERASE_LAUNCH((erase_dgrad_gelu_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e);
-        if (kind == GK_FWD_LOGITS) ERASE_LAUNCH((erase_fwd_logits_gemm<T, BM, BN>), grid, block, 0, s, ev, g, e);
+      if constexpr (sizeof(T) == 2) {
+        if (kind == GK_FWD_LIN) ERASE_LAUNCH((erase_fwd_lin_gemm<T, 64, 64>), grid, block, 0, s, ev, g, e);
+        if (kind == GK_FWD_GELU) ERASE_LAUNCH((erase_fwd_gelu_gemm<T, 64, 64>), grid, block, 0, s, ev, g, e);
+        if (kind == GK_DGRAD_GELU) ERASE_LAUNCH((erase_dgrad_gelu_gemm<T, 64, 64>), grid, block, 0, s, ev, g, e);
+        if (kind == GK_FWD_LOGITS) ERASE_LAUNCH((erase_fwd_logits_gemm<T, 64, 64>), grid, block, 0, s, ev, g, e);
       } else {
         return hipErrorInvalidValue;
       }
       break;
     case GK_FWD_HEAD:
-      // the tile must span the whole width; 32- and 64-row tiles only
-      if constexpr (BM <= 64) {
-        if (g.N > BN) return hipErrorInvalidValue;
-        ERASE_LAUNCH_B(erase_fwd_head_gemm, (T, BM, BN), grid, block, 0, (), g, e);
+      // the tile must span the whole width (fp32; bf16 has 16-row tiles)
+      if constexpr (sizeof(T) == 4) {
+        if (g.N > 64) return hipErrorInvalidValue;
+        ERASE_LAUNCH_B(erase_fwd_head_gemm, (T, 64, 64), grid, block, 0, (), g, e);
       } else {
         return hipErrorInvalidValue;
       }
@@ -1095,45 +1080,21 @@ static hipError_t launch_gemm_t(int kind, const GemmDesc& g0, const EpiParams& e
   return hipGetLastError();
 }
 
-template <typename T, int BM, int BN, int KG = 1>
+template <typename T, int BM, int BN>
 static hipError_t launch_bwd_t(const GemmDesc& gd0, const EpiParams& ed, const GemmDesc& gw0, const EpiParams& ew,
                                hipStream_t s, const LaunchEv& ev, const Batch* bt) {
   const GemmDesc gd = with_group(gd0, BM, BN), gw = with_group(gw0, BM, BN);
   const int nd = ((gd.M + BM - 1) / BM) * ((gd.N + BN - 1) / BN);
   const int nw = ((gw.M + BM - 1) / BM) * ((gw.N + BN - 1) / BN) * gw.split;
-  // 128x128: one workgroup per CU (an unused dynamic LDS reservation): two
-  // co-resident 128x128 workgroups measured 20% slower on the vocabulary
-  // head's backward (1.69 vs 1.41 ms)
-  if constexpr (KG == 2) {
-    if (bt) return hipErrorInvalidValue;
-    ERASE_LAUNCH((erase_bwd_gemm_kg2<T, BM, BN>), dim3(nd + nw), dim3(512), 0, s, ev, gd, ed, gw, ew, nw);
-    return hipGetLastError();
-  }
-  constexpr size_t kReserve = BM == 128 ? 40960 : 0;
-  if constexpr (kReserve > 0) {
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&erase_bwd_gemm<T, BM, BN>), hipFuncAttributeMaxDynamicSharedMemorySize,
-        (int)kReserve);
-    static const hipError_t attr_b = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&erase_bwd_gemm_b<T, BM, BN>), hipFuncAttributeMaxDynamicSharedMemorySize,
-        (int)kReserve);
-    if (attr != hipSuccess) return attr;
-    if (attr_b != hipSuccess) return attr_b;
-  }
-  ERASE_LAUNCH_B(erase_bwd_gemm, (T, BM, BN), dim3(nd + nw), dim3(256), kReserve, (nw), gd, ed, gw, ew, nw);
+  ERASE_LAUNCH_B(erase_bwd_gemm, (T, BM, BN), dim3(nd + nw), dim3(256), 0, (nw), gd, ed, gw, ew, nw);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_gemm(int bf16, const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
                            hipStream_t s, const LaunchEv& ev, const Batch* bt) {
   if (gd.bm != gw.bm || gd.bn != gw.bn || gd.split != 1 || gw.split <= 0 || ew.ap) return hipErrorInvalidValue;
-  if (bf16 && gd.bn == 256) return launch_wide_bwd(gd, ed, gw, ew, s, ev, bt);
-  if (gd.kgroups == 2 || gw.kgroups == 2) {  // two k-groups: bf16 128x128 only
-    if (!bf16 || gd.kgroups != gw.kgroups || gd.bm != 128 || gd.bn != 128) return hipErrorInvalidValue;
-    return launch_bwd_t<uint16_t, 128, 128, 2>(gd, ed, gw, ew, s, ev, bt);
-  }
+  if (bf16 && gd.bm >= 128) return launch_wide_bwd(gd, ed, gw, ew, s, ev, bt);
   if (bf16) {
-    if (gd.bm == 128 && gd.bn == 128) return launch_bwd_t<uint16_t, 128, 128>(gd, ed, gw, ew, s, ev, bt);
     if (gd.bm == 64 && gd.bn == 64) return launch_bwd_t<uint16_t, 64, 64>(gd, ed, gw, ew, s, ev, bt);
   } else {
     if (gd.bm == 64 && gd.bn == 64) return launch_bwd_t<float, 64, 64>(gd, ed, gw, ew, s, ev, bt);
@@ -1297,7 +1258,7 @@ hipError_t launch_gemm(int bf16, int kind, const GemmDesc& g, const EpiParams& e
   if (g.M <= 0 || g.N <= 0 || g.split <= 0) return hipErrorInvalidValue;
   if (bf16 && kind == GK_FWD_LOGITS && g.bm == 256 && g.bn == 256)
     return logits_wide_fits(g, e) ? launch_logits_wide(g, e, s, ev) : hipErrorInvalidValue;
-  if (bf16 && g.bn == 256) return launch_wide(kind, g, e, s, ev, bt);
+  if (bf16 && (g.bn == 256 || (g.bm == 128 && g.bn == 128))) return launch_wide(kind, g, e, s, ev, bt);
   if (bf16 && kind == GK_FWD_HEAD && g.bm == 16) {
     // 16-row tiles: outputs at most 128 wide, contraction a multiple of 32
     if (g.N > 128 || g.K % 32 || g.split != 1) return hipErrorInvalidValue;
@@ -1309,13 +1270,34 @@ hipError_t launch_gemm(int bf16, int kind, const GemmDesc& g, const EpiParams& e
     return hipGetLastError();
   }
   if (bf16) {
-    if (g.bm == 128 && g.bn == 128) return launch_gemm_t<uint16_t, 128, 128>(kind, g, e, s, ev, bt);
-    if (g.bm == 128 && g.bn == 64) return launch_gemm_t<uint16_t, 128, 64>(kind, g, e, s, ev, bt);
-    if (g.bm == 64 && g.bn == 128) return launch_gemm_t<uint16_t, 64, 128>(kind, g, e, s, ev, bt);
-    if (g.bm == 64 && g.bn == 64) return launch_gemm_t<uint16_t, 64, 64>(kind, g, e, s, ev, bt);
-    if (g.bm == 32 && g.bn == 128 && kind == GK_FWD_HEAD) return launch_gemm_t<uint16_t, 32, 128>(kind, g, e, s, ev, bt);
+    // vocabulary logits, and 64x128 with two k-groups forward
+    if (g.bm == 128 && g.bn == 64 && kind == GK_FWD_LOGITS) {
+      const GemmDesc w = with_group(g, 128, 64);
+      ERASE_LAUNCH((erase_fwd_logits_gemm<uint16_t, 128, 64>),
+                   dim3(((g.M + 127) / 128) * ((g.N + 63) / 64)), dim3(256), 0, s, ev, w, e);
+      return hipGetLastError();
+    }
+    if (g.bm == 64 && g.bn == 128) {
+      if (kind == GK_FWD_LOGITS) {
+        const GemmDesc w = with_group(g, 64, 128);
+        ERASE_LAUNCH((erase_fwd_logits_gemm<uint16_t, 64, 128>),
+                     dim3(((g.M + 63) / 64) * ((g.N + 127) / 128)), dim3(256), 0, s, ev, w, e);
+        return hipGetLastError();
+      }
+      if (g.kgroups != 2 || g.split != 1) return hipErrorInvalidValue;
+      const GemmDesc w = with_group(g, 64, 128);
+      const dim3 grid(((g.M + 63) / 64) * ((g.N + 127) / 128));
+      if (kind == GK_FWD_RELU)
+        ERASE_LAUNCH_B(erase_fwd_gemm_kg2, (uint16_t, 64, 128), grid, dim3(512), 0, (), w, e);
+      else if (kind == GK_FWD_CROSS)
+        ERASE_LAUNCH_B(erase_fwd_cross_gemm_kg2, (uint16_t, 64, 128), grid, dim3(512), 0, (), w, e);
+      else
+        return hipErrorInvalidValue;
+      return hipGetLastError();
+    }
+    if (g.bm == 64 && g.bn == 64) return launch_gemm_t<uint16_t>(kind, g, e, s, ev, bt);
   } else {
-    if (g.bm == 64 && g.bn == 64) return launch_gemm_t<float, 64, 64>(kind, g, e, s, ev, bt);
+    if (g.bm == 64 && g.bn == 64) return launch_gemm_t<float>(kind, g, e, s, ev, bt);
   }
   return hipErrorInvalidValue;
 }

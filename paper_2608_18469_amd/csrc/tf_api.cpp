@@ -89,56 +89,44 @@ int64_t param_count(const Dims& D, int b) {
   return n;
 }
 
-// Workgroup tile and contraction split of one GEMM: the largest tile giving
-// at least 384 workgroups (1.5 per CU), else 64x64; weight gradients (fp32
-// partial slices reduced by Adam) split the contraction until they reach it.
 struct Plan1 {
   int bm = 64, bn = 64, split = 1, kps = 0;
 };
-Plan1 wide_plan(int64_t K, int split) {
+// 256x256 or 128x128 tiles over `split` slices of the contraction.
+Plan1 wide_plan(int tile, int64_t K, int split) {
   Plan1 p;
-  p.bm = p.bn = 256;
+  p.bm = p.bn = tile;
   p.kps = (int)rup(cdv(std::max<int64_t>(K, 1), split), 64);
   p.split = (int)cdv(std::max<int64_t>(K, 1), p.kps);
   return p;
 }
+// The core's 64x64 tiles; weight gradients (fp32 partial slices reduced by
+// Adam) split the contraction until they reach 384 workgroups (1.5 per CU).
 Plan1 choose(int64_t M, int64_t N, int64_t K, bool wgrad) {
-  Plan1 p;
-  const int64_t target = 384;
-  auto wgs = [&](int bm, int bn) { return cdv(M, bm) * cdv(N, bn); };
-  const int tiles[4][2] = {{128, 128}, {128, 64}, {64, 128}, {64, 64}};
-  bool done = false;
-  for (auto& t : tiles)
-    if (!done && wgs(t[0], t[1]) >= target) {
-      p.bm = t[0];
-      p.bn = t[1];
-      done = true;
-    }
-  if (!done && wgrad) {
-    int s = 1;
-    while (s < 16 && wgs(64, 64) * s < target && K / (s * 2) >= 256) s *= 2;
-    p.split = s;
-  }
-  p.kps = (int)rup(cdv(std::max<int64_t>(K, 1), p.split), 64);
-  p.split = (int)cdv(std::max<int64_t>(K, 1), p.kps);
-  return p;
+  int s = 1;
+  if (wgrad)
+    while (s < 16 && cdv(M, 64) * cdv(N, 64) * s < 384 && K / (s * 2) >= 256) s *= 2;
+  return wide_plan(64, K, s);
 }
 
-// Forward GEMMs: outputs at least 2048 wide (MLP up-projection, vocabulary
-// logits) take 64x128 tiles, three workgroups per CU instead of two 128x128
-// (measured on the 16384-row shapes: logits 1.10 vs 1.20 ms, MLP-up 87 vs
-// 97 us; the 512-wide outputs are faster with 128x128).
 Plan1 choose_fwd(int64_t M, int64_t N, int64_t K) {
-  if (wide_nt_pays(M, N, K)) return wide_plan(K, 1);
-  Plan1 p = choose(M, N, K, false);
-  if (N >= 2048 && p.bm == 128 && p.bn == 128) p.bm = 64;
-  return p;
+  const int t = wide_nt_tile(M, N, K, 1);
+  return t ? wide_plan(t, K, 1) : choose(M, N, K, false);
 }
 
-// The vocabulary logits in the GEMM core's tiles.
+// The vocabulary logits in the GEMM core's tiles: the largest giving at least
+// 384 workgroups (64x128, three workgroups per CU, over two 128x128 ones: 1.10
+// and 1.20 ms at 16384 x 32768 x 512), else 64x64.
 Plan1 choose_logits(int64_t M, int64_t N, int64_t K) {
   Plan1 p = choose(M, N, K, false);
-  if (N >= 2048 && p.bm == 128 && p.bn == 128) p.bm = 64;
+  const int tiles[3][2] = {{64, 128}, {128, 64}, {64, 128}};
+  const int64_t wgs[3] = {cdv(M, 128) * cdv(N, 128), cdv(M, 128) * cdv(N, 64), cdv(M, 64) * cdv(N, 128)};
+  for (int i = 0; i < 3; ++i)
+    if (wgs[i] >= 384 && (i > 0 || N >= 2048)) {
+      p.bm = tiles[i][0];
+      p.bn = tiles[i][1];
+      break;
+    }
   return p;
 }
 
@@ -181,7 +169,7 @@ struct Block {
   int32_t* flag = nullptr;
   int ntiles = 0, nloss = 0;
   Lin fwd[NW], dgr[NW], wgr[NW];
-  bool pair_wide[NW] = {};  // weight gradient (and input gradient, when grouped) in 256x256 tiles
+  int pair_tile[NW] = {};  // weight gradient (and input gradient, when grouped) in 256x256 or 128x128 tiles
   bool grouped[NW] = {};  // input- and weight-gradient GEMMs of the weight in one launch
   std::vector<AdamSeg> segs;
   AdamSeg* segs_dev = nullptr;
@@ -278,20 +266,24 @@ size_t build_layout(const erase_tf_config& c, uintptr_t base, Layout* P) {
     B.ploss = f32(B.nloss);
     for (int i = 0; i < NW; ++i) {
       B.wp[i] = choose(D.rows[i], D.cols[i], rup(D.N, 64), true);
-      // 256x256 tiles where they pay: with the input gradient in one launch
-      // (the MLP-up and attention projections), or the weight gradient alone
-      int split = 0;
-      if (i == W1 || i == WO || (i == WQKV && b == 0))
-        split = wide_pair_split(D.N, D.rows[i], D.cols[i]);
-      else if (i != WH)
-        split = wide_wgrad_split(D.rows[i], D.cols[i], D.N, wide_core_wgrad_us(D.rows[i], D.cols[i], D.N)).split;
-      else if (wide_tiles(D.N, d) >= kWideCus)
-        // the input gradient contracts over the vocabulary: in 256x256 tiles
-        // only when they fill the chip (16384 x 512 over 32768: 764 us in 128
-        // of them, 680 us in 512 tiles of the core)
-        split = wide_pair_split(D.N, D.V, d);
-      B.pair_wide[i] = split > 0;
-      if (split > 0) B.wp[i] = wide_plan(rup(D.N, 64), split);
+      // larger tiles where they pay: with the input gradient in one launch
+      // (the MLP-up and attention projections, the vocabulary head), or the
+      // weight gradient alone
+      WidePair wp;
+      if (i == W1 || i == WO || (i == WQKV && b == 0)) {
+        wp = wide_pair(D.N, D.rows[i], D.cols[i], 1);
+      } else if (i != WH) {
+        wp = wide_wgrad(D.rows[i], D.cols[i], D.N, wide_core_wgrad_us(D.rows[i], D.cols[i], D.N, 1), 1);
+      } else {
+        // the head's input gradient contracts over the vocabulary: 256x256
+        // tiles only when they fill the chip (16384 x 512 over 32768: 768 us
+        // in 128 of them, 573 us in 512 of 128x128)
+        wp = wide_pair(D.N, D.V, d, 1);
+        if (wp.tile == 256 && wide_tiles(D.N, d) < kWideCus)
+          wp = {128, std::max(1, mid_wgrad_split(D.V, d, D.N, 1e30, 1, mid_tiles(D.N, d), cdv(D.V, 64)).split)};
+      }
+      B.pair_tile[i] = wp.tile;
+      if (wp.tile) B.wp[i] = wide_plan(wp.tile, rup(D.N, 64), wp.split);
       B.part[i] = f32(int64_t(B.wp[i].split) * D.rows[i] * D.cols[i]);
     }
     B.segs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * (NW + 1)));
@@ -320,7 +312,6 @@ GemmDesc gdesc(const void* A, int64_t lda, const void* Bm, int64_t ldb, int64_t 
 }
 
 // GEMM launches of every block, fixed at init
-bool kg2_pair(int w) { return w == WH; }
 
 void build_gemms(const erase_tf_config& c, Layout* P) {
   const Dims& D = P->D;
@@ -366,8 +357,7 @@ void build_gemms(const erase_tf_config& c, Layout* P) {
     auto dgr = [&](int w, const void* A, int64_t lda, int kind, void* out, int64_t ldo) {
       Lin& L = B.dgr[w];
       L.kind = kind;
-      L.g = gdesc(A, lda, B.sht[w], D.rows[w], N, D.cols[w], D.rows[w],
-                  w == WH && !B.pair_wide[w] ? choose_logits(N, D.cols[w], D.rows[w]) : choose_fwd(N, D.cols[w], D.rows[w]));
+      L.g = gdesc(A, lda, B.sht[w], D.rows[w], N, D.cols[w], D.rows[w], choose_fwd(N, D.cols[w], D.rows[w]));
       L.e = EpiParams{};
       L.e.dmn = out;
       L.e.lddmn = ldo;
@@ -396,24 +386,12 @@ void build_gemms(const erase_tf_config& c, Layout* P) {
     wgr(WO, B.da1, P->ldd, B.o, P->ldd);
     wgr(WQKV, B.dqkv, P->ld3, B.n1, P->ldd);
     // both gradient GEMMs of a weight read the same output gradient: one
-    // launch when they can share a tile (the grouped kernel takes the plain
-    // input-gradient epilogue only; a 64x64 weight gradient pulls its
-    // input-gradient GEMM down to 64x64)
+    // launch, in the weight gradient's tiles (the plain input-gradient
+    // epilogue only)
     for (int w = 0; w < NW; ++w) {
       if (B.dgr[w].g.M == 0 || B.dgr[w].kind != GK_DGRAD) continue;
-      GemmDesc& gd = B.dgr[w].g;
-      GemmDesc& gw = B.wgr[w].g;
-      if (B.pair_wide[w]) {
-        gd.bm = gd.bn = 256;
-        B.grouped[w] = true;
-      } else if (gd.bm == gw.bm && gd.bn == gw.bn && (gd.bm == 128 || gd.bm == 64) && gd.bm == gd.bn) {
-        B.grouped[w] = true;
-      } else if (gw.bm == 64 && gw.bn == 64) {
-        gd.bm = gd.bn = 64;
-        B.grouped[w] = true;
-      }
-      // 128x128 pairs: 512-thread workgroups, two k-groups of four waves
-      if (B.grouped[w] && gd.bm == 128 && kg2_pair(w)) gd.kgroups = gw.kgroups = 2;
+      B.dgr[w].g.bm = B.dgr[w].g.bn = B.wgr[w].g.bm;
+      B.grouped[w] = true;
     }
     (void)V;
     (void)c;

@@ -1,5 +1,5 @@
-// Wide GEMM tiles (bf16, gfx950) for launches that fill the chip with them:
-// 256 x 256 outputs per workgroup of eight waves, one workgroup per compute
+// GEMM tiles with direct-to-LDS operands (bf16, gfx950).  First, for launches
+// that fill the chip with them: 256 x 256 outputs per workgroup of eight waves, one workgroup per compute
 // unit (128 KB of LDS stages).
 //
 // What bounds the GEMM core's 128 x 128 tiles is operand movement: a byte
@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "device.h"
+#include "wide_plan.h"
 
 namespace erase {
 
@@ -375,6 +376,88 @@ __device__ __forceinline__ void stn(void* p, int64_t ld, int m, int n, int N, co
   }
 }
 
+// Epilogue operands of eight columns from (m, n), and the values stored there.
+template <int KIND>
+__device__ __forceinline__ void epi_load(const EpiParams& e, int m, int n, u32x4_t& r0, u32x4_t& r1) {
+  if constexpr (KIND == GK_FWD_CROSS) {
+    r0 = ld8(e.x0, e.ldx0, m, n);
+    r1 = ld8(e.xl, e.ldxl, m, n);
+  }
+  if constexpr (KIND == GK_FWD_LIN) {
+    if (e.res) r0 = ld8(e.res, e.ldres, m, n);
+  }
+  if constexpr (KIND == GK_DGRAD_GELU) r0 = ld8(e.mask, e.ldmask, m, n);
+  if constexpr (KIND == GK_DGRAD) {
+    if (e.res) r0 = ld8(e.res, e.ldres, m, n);
+    if (e.below_cross)
+      r1 = ld8(e.x0, e.ldx0, m, n);
+    else if (e.mask)
+      r1 = ld8(e.mask, e.ldmask, m, n);
+  }
+}
+template <int KIND>
+__device__ __forceinline__ void epi_bias(const EpiParams& e, int n, int N, float bias[8]) {
+  if constexpr (KIND == GK_FWD_RELU || KIND == GK_FWD_CROSS) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) bias[k] = n + k < N ? e.bias[n + k] : 0.f;
+  }
+}
+template <int KIND>
+__device__ __forceinline__ void epi_store(const EpiParams& e, float v[8], const float bias[8], int m, int n, int N,
+                                          const u32x4_t& r0, const u32x4_t& r1) {
+  float p[8], q[8];
+  if constexpr (KIND == GK_FWD_RELU) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      v[k] += bias[k];
+      v[k] = v[k] < 0.f ? 0.f : v[k];  // keeps NaN
+    }
+    stn(e.y, e.ldy, m, n, N, pack8(v));
+  } else if constexpr (KIND == GK_FWD_CROSS) {
+    unpack8(r0, p);
+    unpack8(r1, q);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = fmaf(p[k], v[k] + bias[k], q[k]);
+    stn(e.y, e.ldy, m, n, N, pack8(v));
+  } else if constexpr (KIND == GK_FWD_LIN) {
+    if (e.res) {
+      unpack8(r0, p);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] += p[k];
+    }
+    stn(e.y, e.ldy, m, n, N, pack8(v));
+  } else if constexpr (KIND == GK_FWD_GELU) {
+    if (e.gout) stn(e.gout, e.ldgout, m, n, N, pack8(v));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = gelu_f(v[k]);
+    stn(e.y, e.ldy, m, n, N, pack8(v));
+  } else if constexpr (KIND == GK_DGRAD_GELU) {
+    unpack8(r0, p);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] *= gelu_grad_f(p[k]);
+    stn(e.dmn, e.lddmn, m, n, N, pack8(v));
+  } else {
+    if (e.res) {
+      unpack8(r0, p);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] += p[k];
+    }
+    if (e.below_cross) {
+      const u32x4_t gq = pack8(v);
+      if (e.gout) stn(e.gout, e.ldgout, m, n, N, gq);
+      unpack8(gq, p);
+      unpack8(r1, q);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = p[k] * q[k];
+    } else if (e.mask) {
+      unpack8(r1, q);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = q[k] > 0.f ? v[k] : 0.f;
+    }
+    stn(e.dmn, e.lddmn, m, n, N, pack8(v));
+  }
+}
+
 // Epilogue of an NT tile: a lane holds eight consecutive columns of TA rows
 // per quadrant.  The operands of one quadrant are loaded together.
 template <int HA, int HB, int KIND, class A>
@@ -387,89 +470,21 @@ __device__ __forceinline__ void epi_nt(const EpiParams& e, const A& acc, int M, 
     const int n = n0 + b * HB + wn * 32 + fg * 8;
     if (n >= N) continue;
     float bias[8];
-    if constexpr (KIND == GK_FWD_RELU || KIND == GK_FWD_CROSS) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) bias[k] = n + k < N ? e.bias[n + k] : 0.f;
-    }
+    epi_bias<KIND>(e, n, N, bias);
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
       u32x4_t r0[TA], r1[TA];
 #pragma unroll
-      for (int i = 0; i < TA; ++i) {
-        const int m = min(m0 + a * HA + wm * (HA / 2) + i * 16 + fr, M - 1);
-        if constexpr (KIND == GK_FWD_CROSS) {
-          r0[i] = ld8(e.x0, e.ldx0, m, n);
-          r1[i] = ld8(e.xl, e.ldxl, m, n);
-        }
-        if constexpr (KIND == GK_FWD_LIN) {
-          if (e.res) r0[i] = ld8(e.res, e.ldres, m, n);
-        }
-        if constexpr (KIND == GK_DGRAD_GELU) r0[i] = ld8(e.mask, e.ldmask, m, n);
-        if constexpr (KIND == GK_DGRAD) {
-          if (e.res) r0[i] = ld8(e.res, e.ldres, m, n);
-          if (e.below_cross)
-            r1[i] = ld8(e.x0, e.ldx0, m, n);
-          else if (e.mask)
-            r1[i] = ld8(e.mask, e.ldmask, m, n);
-        }
-      }
+      for (int i = 0; i < TA; ++i)
+        epi_load<KIND>(e, min(m0 + a * HA + wm * (HA / 2) + i * 16 + fr, M - 1), n, r0[i], r1[i]);
 #pragma unroll
       for (int i = 0; i < TA; ++i) {
         const int m = m0 + a * HA + wm * (HA / 2) + i * 16 + fr;
         if (m >= M) continue;
-        float v[8], p[8], q[8];
+        float v[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = acc[a][b][i][k >> 2][k & 3];
-        if constexpr (KIND == GK_FWD_RELU) {
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            v[k] += bias[k];
-            v[k] = v[k] < 0.f ? 0.f : v[k];  // keeps NaN
-          }
-          stn(e.y, e.ldy, m, n, N, pack8(v));
-        } else if constexpr (KIND == GK_FWD_CROSS) {
-          unpack8(r0[i], p);
-          unpack8(r1[i], q);
-#pragma unroll
-          for (int k = 0; k < 8; ++k) v[k] = fmaf(p[k], v[k] + bias[k], q[k]);
-          stn(e.y, e.ldy, m, n, N, pack8(v));
-        } else if constexpr (KIND == GK_FWD_LIN) {
-          if (e.res) {
-            unpack8(r0[i], p);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] += p[k];
-          }
-          stn(e.y, e.ldy, m, n, N, pack8(v));
-        } else if constexpr (KIND == GK_FWD_GELU) {
-          if (e.gout) stn(e.gout, e.ldgout, m, n, N, pack8(v));
-#pragma unroll
-          for (int k = 0; k < 8; ++k) v[k] = gelu_f(v[k]);
-          stn(e.y, e.ldy, m, n, N, pack8(v));
-        } else if constexpr (KIND == GK_DGRAD_GELU) {
-          unpack8(r0[i], p);
-#pragma unroll
-          for (int k = 0; k < 8; ++k) v[k] *= gelu_grad_f(p[k]);
-          stn(e.dmn, e.lddmn, m, n, N, pack8(v));
-        } else {
-          if (e.res) {
-            unpack8(r0[i], p);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] += p[k];
-          }
-          if (e.below_cross) {
-            const u32x4_t gq = pack8(v);
-            if (e.gout) stn(e.gout, e.ldgout, m, n, N, gq);
-            unpack8(gq, p);
-            unpack8(r1[i], q);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = p[k] * q[k];
-          } else if (e.mask) {
-            unpack8(r1[i], q);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = q[k] > 0.f ? v[k] : 0.f;
-          }
-          stn(e.dmn, e.lddmn, m, n, N, pack8(v));
-        }
+        epi_store<KIND>(e, v, bias, m, n, N, r0[i], r1[i]);
       }
     }
   }
@@ -501,6 +516,295 @@ __device__ __forceinline__ void epi_wgrad(const EpiParams& e, const A& acc, cons
     }
 }
 }  // namespace wide
+
+// ---------------------------------------------------------------------------
+// 128 x 128 tiles, from about half a workgroup per compute unit on: the
+// operands straight into NST LDS stages of a 64-wide k-step (32 KB), NST - 1
+// k-steps in flight, one barrier per k-step.  Eight waves in two k-groups:
+// each group computes the whole tile over its half of every k-step (a wave
+// 64 x 64), so every SIMD runs two waves of one tile; the groups exchange
+// halves of their partial tiles through LDS and each finishes 32 of a wave's
+// 64 rows.  Bound by the latency of a k-step (load, barrier, fragment reads,
+// MFMAs) when alone on its unit, by L2 and LDS traffic with two workgroups.
+// The order of every sum is the same for any NST.
+// Measured on one MI355X, against the best tile of the register-staged core:
+// 8192 x 512 x 1677 18.3 us (769 TFLOP/s) and 25.7 us, 16384 x 512 x 2048 34.1
+// (1008) and 46.0, 3001 x 1003 x 1003 12.1 and 15.8, 16384 x 512 x 512 14.3
+// and 20.1 us; weight gradients 512 x 1677 over 4096 rows 15.8 and 19.6 us,
+// 1003 x 1003 over 3001 rows 14.3 and 18.8 us.
+// ---------------------------------------------------------------------------
+namespace mid {
+constexpr int BM = 128, BN = 128, BK = 64, NW = 8, NT = 64 * NW;
+constexpr int OPB = BM * BK * 2, STAGE = 2 * OPB;  // bytes of an operand's k-step, of a stage
+constexpr int XCH = 4 * 2 * 8 * 64 * 16;           // exchanged halves: 4 wave pairs x 2 directions x 8 tiles (64 KB)
+template <int NST>
+constexpr int bytes() {
+  return (NST * STAGE > XCH ? NST * STAGE : XCH) + 2 * BM * 4;  // and the groups' bias row sums
+}
+
+// Partial tile of this workgroup; on return acc[0..1] of k-group kg hold the
+// finished rows 32 kg .. 32 kg + 31 of the wave's 64, in all their columns.
+template <int NST, bool KM>
+__device__ __forceinline__ void run(const GemmDesc& g, const TileIdx& ti, bool rows, char* smem, f32x4_t (&out)[2][4],
+                                    const EpiParams& e) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wv >> 2, wm = (wv >> 1) & 1, wn = wv & 1;
+  const int fr = lane & 15, fg = lane >> 4;
+  const int M = g.M, N = g.N, m0 = ti.m * BM, n0 = ti.n * BN, kb = ti.z * g.kps;
+  const int nk = (min(g.K, kb + g.kps) - kb + BK - 1) / BK;
+  const int64_t lda = g.lda, ldb = g.ldb;
+  const uint32_t lbase = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)smem);
+  const char *ga, *gb;
+  uint32_t oa[2], ob[2];
+  if constexpr (KM) {
+    ga = static_cast<const char*>(g.A) + ((int64_t)kb * lda + m0) * 2;
+    gb = static_cast<const char*>(g.B) + ((int64_t)kb * ldb + n0) * 2;
+    const int ml = ((M + 63) & ~63) - 8 - m0, nl = ((N + 63) & ~63) - 8 - n0;  // last whole chunk
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = (wv * 2 + u) * 4 + (lane >> 4), ch = (lane & 15) ^ wide::kperm<16>(r);
+      oa[u] = (uint32_t)((int64_t)r * lda + min(ch * 8, ml)) * 2;
+      ob[u] = (uint32_t)((int64_t)r * ldb + min(ch * 8, nl)) * 2;
+    }
+  } else {
+    ga = static_cast<const char*>(g.A) + ((int64_t)m0 * lda + kb) * 2;
+    gb = static_cast<const char*>(g.B) + ((int64_t)n0 * ldb + kb) * 2;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = (wv * 2 + u) * 8 + (lane >> 3);
+      oa[u] = (uint32_t)(min(r, M - 1 - m0) * (int)lda + ((lane & 7) ^ (r & 7)) * 8) * 2;
+      ob[u] = (uint32_t)(min(r, N - 1 - n0) * (int)ldb + ((lane & 7) ^ ((r & 3) | ((r >> 1) & 4))) * 8) * 2;
+    }
+  }
+  const int64_t sa = KM ? BK * lda * 2 : BK * 2, sb = KM ? BK * ldb * 2 : BK * 2;
+  auto load = [&](int kt, int st) {
+    const uint32_t l = lbase + st * STAGE + wv * 2048;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      lds_dma16s(ga + kt * sa, oa[u], l + u * 1024);
+      lds_dma16s(gb + kt * sb, ob[u], l + OPB + u * 1024);
+    }
+  };
+  const int tq = (lane & 15) >> 2, tc = lane & 3, trow = 8 * fg + tq;
+  int ao[4], bo[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (KM) {
+      const int hp = wide::kperm<16>(trow);
+      ao[i] = ((kg * 32 + trow) * BM + ((((wm * 64 + i * 16) >> 3) + (tc >> 1)) ^ hp) * 8 + (tc & 1) * 4) * 2;
+      bo[i] = OPB + ((kg * 32 + trow) * BN + ((((wn * 64 + i * 16) >> 3) + (tc >> 1)) ^ hp) * 8 + (tc & 1) * 4) * 2;
+    } else {
+      const int sl = ((4 * kg + fg) ^ (fr & 7)) * 16;
+      ao[i] = (wm * 64 + i * 16 + fr) * 128 + sl;
+      bo[i] = OPB + (wn * 64 + 32 * (i >> 1) + 4 * (i & 1) + 8 * (fr >> 2) + (fr & 3)) * 128 + sl;
+    }
+  }
+  f32x4_t acc[4][4], accr[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  accr[0] = accr[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+#pragma unroll
+  for (int s = 0; s < NST - 1; ++s)
+    if (s < nk) load(s, s);
+  int st = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    // k-step kt has landed: at most the loads of the NST - 2 after it are in
+    // flight; behind the barrier that holds for every wave, and every wave is
+    // done with the stage the next loads overwrite (k-step kt - 1's)
+    const int left = nk - 1 - kt;
+    if (left >= NST - 2)
+      wide::wait_vm<4 * (NST - 2)>();
+    else if (NST > 3 && left == 1)
+      wide::wait_vm<4>();
+    else
+      wide::wait_vm<0>();
+    wide::bar();
+    if (kt + NST - 1 < nk) load(kt + NST - 1, st == 0 ? NST - 1 : st - 1);
+    const char* p = smem + st * STAGE;
+    u32x4_t fa[4], fb[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (KM) {
+        fb[i] = tr_frag(reinterpret_cast<const uint16_t*>(p + bo[i]), BN);
+        fa[i] = tr_frag(reinterpret_cast<const uint16_t*>(p + ao[i]), BM);
+      } else {
+        fb[i] = *reinterpret_cast<const u32x4_t*>(p + bo[i]);
+        fa[i] = *reinterpret_cast<const u32x4_t*>(p + ao[i]);
+      }
+    }
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fb[j]),
+                                                            __builtin_bit_cast(bf16x8_t, fa[i]), acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+    if constexpr (KM) {
+      if (rows) {  // row sums of A: ones times the wave's two blocks (blocks over wn)
+        const u32x4_t one = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (wn == i >> 1)
+            accr[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8_t, one), __builtin_bit_cast(bf16x8_t, fa[i]), accr[i & 1], 0, 0, 0);
+      }
+    }
+    st = st + 1 == NST ? 0 : st + 1;
+  }
+  // exchange: group kg keeps row blocks 2 kg, 2 kg + 1 and hands over the
+  // other two
+  __syncthreads();
+  f32x4_t* xc = reinterpret_cast<f32x4_t*>(smem) + (wv & 3) * (2 * 8 * 64) + lane;
+  float* rsum = reinterpret_cast<float*>(smem + (NST * STAGE > XCH ? NST * STAGE : XCH));
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (kg == 0)
+        xc[(i * 4 + j) * 64] = acc[2 + i][j];
+      else
+        xc[(8 + i * 4 + j) * 64] = acc[i][j];
+    }
+  if constexpr (KM) {
+    if (rows && fg == 0) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) rsum[kg * BM + wm * 64 + (2 * wn + i) * 16 + fr] = accr[i][0];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out[i][j] = kg == 0 ? acc[i][j] + xc[(8 + i * 4 + j) * 64] : xc[(i * 4 + j) * 64] + acc[2 + i][j];
+  if constexpr (KM) {
+    if (rows && tid < BM && m0 + tid < M) e.bpart[(int64_t)ti.z * M + m0 + tid] = rsum[tid] + rsum[BM + tid];
+  }
+}
+
+template <int NST, int KIND>
+__device__ __forceinline__ void nt_tile(const GemmDesc& g, const EpiParams& e, int b, int ntiles, char* smem) {
+  const int gm = (g.M + BM - 1) / BM, gn = (g.N + BN - 1) / BN;
+  const TileIdx ti = tile_from(xcd_linear(b, ntiles), gm, gn, g.group);
+  f32x4_t acc[2][4];
+  run<NST, false>(g, ti, false, smem, acc, e);
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int fr = lane & 15, fg = lane >> 4;
+  const int mb = ti.m * BM + ((wv >> 1) & 1) * 64 + (wv >> 2) * 32 + fr, nb = ti.n * BN + (wv & 1) * 64 + fg * 8;
+  const int M = g.M, N = g.N;
+  u32x4_t r0[2][2], r1[2][2];
+  float bias[2][8];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int n = nb + 32 * h;
+    if (n >= N) continue;
+    wide::epi_bias<KIND>(e, n, N, bias[h]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) wide::epi_load<KIND>(e, min(mb + 16 * i, M - 1), n, r0[h][i], r1[h][i]);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int n = nb + 32 * h;
+    if (n >= N) continue;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int m = mb + 16 * i;
+      if (m >= M) continue;
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = acc[i][2 * h + (k >> 2)][k & 3];
+      wide::epi_store<KIND>(e, v, bias[h], m, n, N, r0[h][i], r1[h][i]);
+    }
+  }
+}
+
+template <int NST>
+__device__ __forceinline__ void wgrad_tile(const GemmDesc& g, const EpiParams& e, int b, int ntiles, char* smem) {
+  const int gm = (g.M + BM - 1) / BM, gn = (g.N + BN - 1) / BN;
+  const TileIdx ti = tile_from(xcd_linear(b, ntiles), gm, gn, g.group);
+  f32x4_t acc[2][4];
+  run<NST, true>(g, ti, e.bpart != nullptr && ti.n == 0, smem, acc, e);
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int fr = lane & 15, fg = lane >> 4;
+  float* out = e.part + (int64_t)ti.z * e.pstride;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int m = ti.m * BM + ((wv >> 1) & 1) * 64 + (wv >> 2) * 32 + 16 * i + fr;
+    if (m >= g.M) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = ti.n * BN + (wv & 1) * 64 + 16 * j + 4 * fg;
+      if (n < g.N) *reinterpret_cast<f32x4_t*>(out + (int64_t)m * e.ldp + n) = acc[i][j];  // rows padded to 64 columns
+    }
+  }
+}
+}  // namespace mid
+
+template <int NST>
+__device__ __forceinline__ void mid_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw,
+                                        const EpiParams& ew, int nd, int nw, int first, char* smem) {
+  const int b = (int)blockIdx.x - (first ? 0 : nd);
+  if (b >= 0 && b < nw)
+    mid::wgrad_tile<NST>(gw, ew, b, nw, smem);
+  else
+    mid::nt_tile<NST, GK_DGRAD>(gd, ed, first ? b - nw : (int)blockIdx.x, nd, smem);
+}
+
+template <int NST, int KIND>
+__global__ __launch_bounds__(mid::NT) void erase_mid_nt(GemmDesc g, EpiParams e, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[mid::bytes<NST>()];
+  mid::nt_tile<NST, KIND>(g, e, (int)blockIdx.x, ntiles, smem);
+}
+template <int NST>
+__global__ __launch_bounds__(mid::NT) void erase_mid_wgrad(GemmDesc g, EpiParams e, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[mid::bytes<NST>()];
+  mid::wgrad_tile<NST>(g, e, (int)blockIdx.x, ntiles, smem);
+}
+// Both backward GEMMs of a layer, the longer contraction first (`first`: the
+// weight gradient's).
+template <int NST>
+__global__ __launch_bounds__(mid::NT) void erase_mid_bwd(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew, int nd,
+                                                         int nw, int first) {
+  __shared__ __attribute__((aligned(16))) char smem[mid::bytes<NST>()];
+  mid_bwd<NST>(gd, ed, gw, ew, nd, nw, first, smem);
+}
+// the same for several blocks (grid row j: job j)
+template <int NST, int KIND>
+__global__ __launch_bounds__(mid::NT) void erase_mid_nt_b(const BlockJob* jobs, StepPtrs st, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[mid::bytes<NST>()];
+  GemmDesc g;
+  EpiParams e;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), g, st);
+  ld_epi(jb + offsetof(BlockJob, e), e, st);
+  mid::nt_tile<NST, KIND>(g, e, (int)blockIdx.x, ntiles, smem);
+}
+template <int NST>
+__global__ __launch_bounds__(mid::NT) void erase_mid_wgrad_b(const BlockJob* jobs, StepPtrs st, int ntiles) {
+  __shared__ __attribute__((aligned(16))) char smem[mid::bytes<NST>()];
+  GemmDesc g;
+  EpiParams e;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), g, st);
+  ld_epi(jb + offsetof(BlockJob, e), e, st);
+  mid::wgrad_tile<NST>(g, e, (int)blockIdx.x, ntiles, smem);
+}
+template <int NST>
+__global__ __launch_bounds__(mid::NT) void erase_mid_bwd_b(const BlockJob* jobs, StepPtrs st, int nd, int nw, int first) {
+  __shared__ __attribute__((aligned(16))) char smem[mid::bytes<NST>()];
+  GemmDesc gd, gw;
+  EpiParams ed, ew;
+  const cmem_t jb = job_of(jobs);
+  ld_gemm(jb + offsetof(BlockJob, g), gd, st);
+  ld_epi(jb + offsetof(BlockJob, e), ed, st);
+  ld_gemm(jb + offsetof(BlockJob, g2), gw, st);
+  ld_epi(jb + offsetof(BlockJob, e2), ew, st);
+  mid_bwd<NST>(gd, ed, gw, ew, nd, nw, first, smem);
+}
 
 template <int HA, int HB, int KIND>
 __device__ __forceinline__ void wide_nt(const GemmDesc& g, const EpiParams& e, int ntiles, char* smem) {
@@ -586,64 +890,97 @@ __global__ __launch_bounds__(wide::NT) void erase_wide_bwd_b(const BlockJob* job
   wide_bwd<HA, HB>(gd, ed, gw, ew, nd, nw, first, smem);
 }
 
-static int wide_tiles(const GemmDesc& g, int bm, int bn) {
-  return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.split;
-}
-
-template <int HA, int HB>
-static hipError_t launch_wide_t(int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
-                       const Batch* bt) {
-  const int nt = wide_tiles(g, 2 * HA, 2 * HB);
-  const dim3 grid((unsigned)nt, bt ? (unsigned)bt->n : 1u), block(wide::NT);
-  if (bt && (kind == GK_FWD_LIN || kind == GK_FWD_GELU || kind == GK_DGRAD_GELU)) return hipErrorInvalidValue;
 #define ERASE_WIDE(ONE, MANY)                                          \
   if (bt)                                                             \
     ERASE_LAUNCH(MANY, grid, block, 0, s, ev, bt->jobs, bt->st, nt);   \
   else                                                                \
     ERASE_LAUNCH(ONE, grid, block, 0, s, ev, g, e, nt)
+
+static hipError_t launch_256(int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
+                             const Batch* bt) {
+  const int nt = (int)wide_tiles(g.M, g.N) * g.split;
+  const dim3 grid((unsigned)nt, bt ? (unsigned)bt->n : 1u), block(wide::NT);
   switch (kind) {
-    case GK_FWD_RELU: ERASE_WIDE((erase_wide_nt<HA, HB, GK_FWD_RELU>), (erase_wide_nt_b<HA, HB, GK_FWD_RELU>)); break;
-    case GK_FWD_CROSS: ERASE_WIDE((erase_wide_nt<HA, HB, GK_FWD_CROSS>), (erase_wide_nt_b<HA, HB, GK_FWD_CROSS>)); break;
-    case GK_FWD_LIN: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_LIN>), grid, block, 0, s, ev, g, e, nt); break;
-    case GK_FWD_GELU: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_FWD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
-    case GK_DGRAD: ERASE_WIDE((erase_wide_nt<HA, HB, GK_DGRAD>), (erase_wide_nt_b<HA, HB, GK_DGRAD>)); break;
-    case GK_DGRAD_GELU: ERASE_LAUNCH((erase_wide_nt<HA, HB, GK_DGRAD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
-    case GK_WGRAD: ERASE_WIDE((erase_wide_wgrad<HA, HB>), (erase_wide_wgrad_b<HA, HB>)); break;
+    case GK_FWD_RELU: ERASE_WIDE((erase_wide_nt<128, 128, GK_FWD_RELU>), (erase_wide_nt_b<128, 128, GK_FWD_RELU>)); break;
+    case GK_FWD_CROSS: ERASE_WIDE((erase_wide_nt<128, 128, GK_FWD_CROSS>), (erase_wide_nt_b<128, 128, GK_FWD_CROSS>)); break;
+    case GK_DGRAD: ERASE_WIDE((erase_wide_nt<128, 128, GK_DGRAD>), (erase_wide_nt_b<128, 128, GK_DGRAD>)); break;
+    case GK_WGRAD: ERASE_WIDE((erase_wide_wgrad<128, 128>), (erase_wide_wgrad_b<128, 128>)); break;
+    case GK_FWD_LIN: ERASE_LAUNCH((erase_wide_nt<128, 128, GK_FWD_LIN>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_FWD_GELU: ERASE_LAUNCH((erase_wide_nt<128, 128, GK_FWD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_DGRAD_GELU: ERASE_LAUNCH((erase_wide_nt<128, 128, GK_DGRAD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
     default: return hipErrorInvalidValue;
   }
-#undef ERASE_WIDE
   return hipGetLastError();
 }
 
-hipError_t launch_wide(int kind, const GemmDesc& g0, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
-                       const Batch* bt) {
+// 128x128 tiles: three stages for launches of at most one workgroup per
+// compute unit, else two (two workgroups per unit).  4096 x 512 x 1677 (128
+// tiles) 16.2 and 16.4 us, 8192 rows (256) 18.3 and 22.2, 24576 (768) 50.0
+// and 47.3, 16384 x 512 x 2048 (512) 38.5 and 34.1 us; four stages were
+// never faster than three.
+template <int NST>
+static hipError_t launch_128_t(int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
+                               const Batch* bt) {
+  const int nt = (int)mid_tiles(g.M, g.N) * g.split;
+  const dim3 grid((unsigned)nt, bt ? (unsigned)bt->n : 1u), block(mid::NT);
+  switch (kind) {
+    case GK_FWD_RELU: ERASE_WIDE((erase_mid_nt<NST, GK_FWD_RELU>), (erase_mid_nt_b<NST, GK_FWD_RELU>)); break;
+    case GK_FWD_CROSS: ERASE_WIDE((erase_mid_nt<NST, GK_FWD_CROSS>), (erase_mid_nt_b<NST, GK_FWD_CROSS>)); break;
+    case GK_DGRAD: ERASE_WIDE((erase_mid_nt<NST, GK_DGRAD>), (erase_mid_nt_b<NST, GK_DGRAD>)); break;
+    case GK_WGRAD: ERASE_WIDE((erase_mid_wgrad<NST>), (erase_mid_wgrad_b<NST>)); break;
+    case GK_FWD_LIN: ERASE_LAUNCH((erase_mid_nt<NST, GK_FWD_LIN>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_FWD_GELU: ERASE_LAUNCH((erase_mid_nt<NST, GK_FWD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_DGRAD_GELU: ERASE_LAUNCH((erase_mid_nt<NST, GK_DGRAD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+#undef ERASE_WIDE
+
+static GemmDesc with_order(const GemmDesc& g0) {
   GemmDesc g = g0;
   if (g.group <= 0) g.group = xcd_group((g.M + g.bm - 1) / g.bm, (g.N + g.bn - 1) / g.bn, g.split, g.bm, g.bn);
-  if (g.K % 64 || g.kps % 64 || g.kps <= 0 || g.lda % 8 || g.ldb % 8) return hipErrorInvalidValue;
-  if (g.bm == 256 && g.bn == 256) return launch_wide_t<128, 128>(kind, g, e, s, ev, bt);
-  return hipErrorInvalidValue;
+  return g;
+}
+static bool operands_ok(const GemmDesc& g) { return g.K % 64 == 0 && g.kps > 0 && g.kps % 64 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0; }
+
+hipError_t launch_wide(int kind, const GemmDesc& g0, const EpiParams& e, hipStream_t s, const LaunchEv& ev,
+                       const Batch* bt) {
+  const GemmDesc g = with_order(g0);
+  if (!operands_ok(g) || (kind != GK_WGRAD && g.split != 1)) return hipErrorInvalidValue;
+  if (bt && (kind == GK_FWD_LIN || kind == GK_FWD_GELU || kind == GK_DGRAD_GELU)) return hipErrorInvalidValue;
+  if (g.bm == 256 && g.bn == 256) return launch_256(kind, g, e, s, ev, bt);
+  if (g.bm != 128 || g.bn != 128) return hipErrorInvalidValue;
+  if (mid_tiles(g.M, g.N) * g.split * (bt ? bt->n : 1) <= kWideCus) return launch_128_t<3>(kind, g, e, s, ev, bt);
+  return launch_128_t<2>(kind, g, e, s, ev, bt);
 }
 
 hipError_t launch_wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
-                           hipStream_t s, const LaunchEv& ev,
-                       const Batch* bt) {
-  GemmDesc d = gd, w = gw;
-  if (d.K % 64 || d.kps < d.K || d.lda % 8 || d.ldb % 8 || w.K % 64 || w.kps % 64 || w.kps <= 0 || w.lda % 8 ||
-      w.ldb % 8)
+                           hipStream_t s, const LaunchEv& ev, const Batch* bt) {
+  const GemmDesc d = with_order(gd), w = with_order(gw);
+  if (!operands_ok(d) || !operands_ok(w) || d.split != 1 || d.kps < d.K || d.bm != w.bm || d.bn != w.bn || d.bm != d.bn)
     return hipErrorInvalidValue;
-  if (d.group <= 0) d.group = xcd_group((d.M + d.bm - 1) / d.bm, (d.N + d.bn - 1) / d.bn, 1, d.bm, d.bn);
-  if (w.group <= 0) w.group = xcd_group((w.M + w.bm - 1) / w.bm, (w.N + w.bn - 1) / w.bn, w.split, w.bm, w.bn);
-  const int nd = wide_tiles(d, d.bm, d.bn), nw = wide_tiles(w, w.bm, w.bn);
-  if (d.bm == 256 && d.bn == 256 && w.bm == 256 && w.bn == 256) {
-    const dim3 grid((unsigned)(nd + nw), bt ? (unsigned)bt->n : 1u), block(wide::NT);
-    const int first = w.kps >= d.K ? 1 : 0;
-    if (bt)
-      ERASE_LAUNCH((erase_wide_bwd_b<128, 128>), grid, block, 0, s, ev, bt->jobs, bt->st, nd, nw, first);
-    else
-      ERASE_LAUNCH((erase_wide_bwd<128, 128>), grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidValue;
+  const bool big = d.bm == 256;
+  if (!big && d.bm != 128) return hipErrorInvalidValue;
+  const int nd = (int)(big ? wide_tiles(d.M, d.N) : mid_tiles(d.M, d.N));
+  const int nw = (int)(big ? wide_tiles(w.M, w.N) : mid_tiles(w.M, w.N)) * w.split;
+  const dim3 grid((unsigned)(nd + nw), bt ? (unsigned)bt->n : 1u), block(512);
+  const int first = w.kps >= d.K ? 1 : 0;
+#define ERASE_BWD(ONE, MANY)                                                          \
+  do {                                                                                \
+    if (bt)                                                                           \
+      ERASE_LAUNCH(MANY, grid, block, 0, s, ev, bt->jobs, bt->st, nd, nw, first);      \
+    else                                                                              \
+      ERASE_LAUNCH(ONE, grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first);           \
+  } while (0)
+  if (big)
+    ERASE_BWD((erase_wide_bwd<128, 128>), (erase_wide_bwd_b<128, 128>));
+  else if ((int64_t)grid.x * grid.y <= kWideCus)
+    ERASE_BWD((erase_mid_bwd<3>), (erase_mid_bwd_b<3>));
+  else
+    ERASE_BWD((erase_mid_bwd<2>), (erase_mid_bwd_b<2>));
+#undef ERASE_BWD
+  return hipGetLastError();
 }
 
 }  // namespace erase

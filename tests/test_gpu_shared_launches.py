@@ -2,8 +2,9 @@
 another shape between them keeps their launches apart, in every schedule.
 
 Widths are odd, so every tile, chunk and segment has a remainder; the blocks'
-lambdas differ.  "wide" runs the 256x256 tiles, whose first-layer weight
-gradient leaves Adam a launch of its own.
+lambdas differ.  "256" and "128" run those tiles, "256" with a first-layer
+weight gradient that leaves Adam a launch of its own.  (Two blocks there: they
+share launches in the schedules on one stream, and tiles are chosen for one.)
 """
 import numpy as np
 import pytest
@@ -19,7 +20,8 @@ CASES = {
     "bf16 cross": ("bf16", 777, 150, CROSS),
     "f32 fused head": ("f32", 333, 150, [("linear_relu", 150, 70), ("linear_relu", 70, 33)]),
     "f32 cross": ("f32", 200, 150, CROSS),
-    "wide": ("bf16", 32900, 500, [("cross", 500, 500), ("linear_relu", 500, 520), ("linear_relu", 520, 520)]),
+    "128": ("bf16", 3700, 700, [("cross", 700, 700), ("linear_relu", 700, 650), ("linear_relu", 650, 700)]),
+    "256": ("bf16", 16300, 1000, [("cross", 1000, 1000), ("linear_relu", 1000, 1000), ("linear_relu", 1000, 1000)]),
 }
 
 
@@ -49,20 +51,20 @@ def _kinds(cfg, params, batch, schedule):
 @pytest.mark.parametrize("name", list(CASES))
 def test_equal_blocks_share_launches(name):
     dtype, batch, in_dim, layers = CASES[name]
-    n = 2 if name == "wide" else 7  # seven: groups of two (three units and one block) in the ERASE schedules
+    n = 2 if name in ("128", "256") else 7  # seven: groups of two (three units and one block) in the ERASE schedules
     block = lambda i: {"input": "x", "layers": layers, "lam": 1.0 + 0.25 * i}
     other = {"input": "x", "layers": [("linear_relu", in_dim, 17)], "lam": 1.0}
     apart = [b for i in range(n) for b in (block(i), other)]
     cfg = synth.custom(dtype, batch, in_dim, [block(i) for i in range(n)], label_p=0.3)
     ref_cfg = synth.custom(dtype, batch, in_dim, apart, label_p=0.3)
-    ref_params, batches = synth.make_workload(ref_cfg, 21, 1 if name == "wide" else 2)
+    ref_params, batches = synth.make_workload(ref_cfg, 21, 1 if n == 2 else 2)
     params = ref_params[::2]
     _say(f"[shared] {name}: apart")
     ref = run_gpu(ref_cfg, ref_params, batches, "serial")[1]
     for sched in ("serial", "overlap", "pipeline", "overlap_adam_end", "serial_graph", "undetached"):
         _say(f"[shared] {name}: {sched}")
         _bits(run_gpu(cfg, params, batches, sched, bwd_streams=2)[1], ref, list(range(0, 2 * n, 2)))
-    if name != "wide":
+    if n > 2:
         assert _kinds(cfg, params, batches[0], "serial") * 3 < _kinds(ref_cfg, ref_params, batches[0], "serial")
 
 

@@ -1,10 +1,8 @@
-"""The 256x256 GEMM tiles at ragged sizes against the oracles: every epilogue
-of their forward and input-gradient kernels, split weight gradients with bias
-sums, and the launch that runs both backward GEMMs of a layer.
-
-The batch is past 128 rows of 256, so the plan takes the wide tiles, and
-nothing is a multiple of them: 32900 rows, widths 500, 520 and 260.
-Tolerances as in the other bf16 parity tests (bf16_gate).
+"""The 256x256 and 128x128 GEMM tiles at ragged sizes against the oracles: every
+epilogue of their forward and input-gradient kernels, split weight gradients
+with bias sums, and the launch that runs both backward GEMMs of a layer.  No
+batch or width is a multiple of a tile.  Tolerances as in the other bf16
+parity tests (bf16_gate).
 """
 import numpy as np
 import pytest
@@ -16,28 +14,32 @@ from tests.test_gpu_transformer import _bits_equal, _check_bf16, _gpu_run
 pytestmark = pytest.mark.gpu
 
 
-def _wide(tr, *batch, schedule):
+def _tiles(tr, *batch, schedule):
     tr.set_timing(True)
     tr.step(*batch, schedule)
     tr.sync()
-    return {(r["kind"], r["block"], r["layer"]) for r in tr.read_timing()[1:] if r["tile_m"] == 256}
+    return {(r["kind"], r["block"], r["layer"], r["tile_m"]) for r in tr.read_timing()[1:]}
 
 
-def _cross_cfg():
-    layers = [("cross", 500, 500), ("cross", 500, 500), ("linear_relu", 500, 520), ("linear_relu", 520, 520)]
-    return synth.custom("bf16", 32900, 500, [{"input": "x", "layers": layers, "lam": 1.0}], label_p=0.2)
+def _cross_cfg(batch, d, w):
+    layers = [("cross", d, d), ("cross", d, d), ("linear_relu", d, w), ("linear_relu", w, d)]
+    return synth.custom("bf16", batch, d, [{"input": "x", "layers": layers, "lam": 1.0}], label_p=0.2)
 
 
 def _chain_cfg():
-    blocks = [{"input": "x", "layers": [("linear_relu", 500, 520)], "lam": 1.0},
-              {"input": "prev", "layers": [("linear_relu", 520, 260), ("linear_relu", 260, 516)], "lam": 0.5}]
-    return synth.custom("bf16", 32900, 500, blocks, label_p=0.2)
+    blocks = [{"input": "x", "layers": [("linear_relu", 500, 900)], "lam": 1.0},
+              {"input": "prev", "layers": [("linear_relu", 900, 500), ("linear_relu", 500, 700)], "lam": 0.5}]
+    return synth.custom("bf16", 20000, 500, blocks, label_p=0.2)
 
 
 @pytest.mark.parametrize("name,cfg,schedule,want", [
-    ("cross", _cross_cfg(), "overlap", {("fwd_gemm", 0, 0), ("fwd_gemm", 0, 2), ("bwd_gemm", 0, 1), ("bwd_gemm", 0, 2),
-                                        ("bwd_gemm", 0, 3), ("wgrad_gemm", 0, 0)}),
-    ("chain", _chain_cfg(), "undetached", {("fwd_gemm", 0, 0), ("dgrad_gemm", 1, 0), ("wgrad_gemm", 0, 0)}),
+    ("cross 256", _cross_cfg(16300, 1000, 1000), "overlap",
+     {("fwd_gemm", 0, 0, 256), ("fwd_gemm", 0, 2, 256), ("bwd_gemm", 0, 1, 256), ("bwd_gemm", 0, 2, 256),
+      ("bwd_gemm", 0, 3, 256), ("wgrad_gemm", 0, 0, 128)}),
+    ("cross 128", _cross_cfg(3700, 700, 650), "overlap",
+     {("fwd_gemm", 0, 0, 128), ("fwd_gemm", 0, 2, 128), ("bwd_gemm", 0, 1, 128), ("bwd_gemm", 0, 2, 128),
+      ("bwd_gemm", 0, 3, 128)}),
+    ("chain 128", _chain_cfg(), "undetached", {("fwd_gemm", 0, 0, 128), ("bwd_gemm", 1, 0, 128)}),
 ])
 def test_wide_tiles_vs_oracle(name, cfg, schedule, want):
     print(f"[wide] {name} {schedule}", flush=True)
@@ -47,9 +49,9 @@ def test_wide_tiles_vs_oracle(name, cfg, schedule, want):
         assert_bit_identical(g, run_gpu(cfg, params, batches, "serial")[1])
     check_bf16(cfg, g, params, batches, detach=schedule != "undetached")
     tr = erase.Trainer(cfg, params)
-    got = _wide(tr, *tr.device_batch(*batches[0]), schedule=schedule)
+    got = _tiles(tr, *tr.device_batch(*batches[0]), schedule=schedule)
     tr.close()
-    assert want <= got, sorted(want - got)
+    assert want <= got, (sorted(want - got), sorted(got))
 
 
 def test_wide_tiles_transformer_vs_oracle():
@@ -63,9 +65,9 @@ def test_wide_tiles_transformer_vs_oracle():
     _bits_equal(a, b)
     _check_bf16(cfg, a, params, batches)
     tr = erase_tf.TfTrainer(cfg, params)
-    got = _wide(tr, tr.device_tokens(batches[0]), schedule="serial")
+    got = _tiles(tr, tr.device_tokens(batches[0]), schedule="serial")
     tr.close()
-    names = [{(k, w) for (k, blk, w) in got if blk == i} for i in range(2)]
-    fwd = {("fwd_gemm", w) for w in (0, 1, 2, 3)} | {("dgrad_gemm", 3)}
-    assert all(fwd <= n for n in names), names
+    big = {(k, b, w) for (k, b, w, t) in got if t in (128, 256)}
+    want = {("fwd_gemm", b, w) for w in (0, 1, 2, 3) for b in (0, 1)} | {("dgrad_gemm", b, 3) for b in (0, 1)}
+    assert want <= big, (sorted(want - big), sorted(got, key=str))
     assert np.isfinite(a[0]["losses"]).all()
