@@ -6,9 +6,10 @@
 // Each bag is summed in fp32 in the order of its index list.  A wave pools
 // 64 / G bags at once: G = dim / 4 (rounded up to a power of two) lanes per
 // bag, each lane one 16-byte column chunk, so every row load is one
-// contiguous, coalesced read of the row.  Up to 8 rows per bag are in flight
-// before they are added.  Out-of-range offsets or indices read nothing: they
-// contribute zero and set the status word.
+// contiguous, coalesced read of the row.  The lanes of a bag read its ids
+// together, one id per lane, and pass them round by lane shifts; up to 8 rows
+// per bag are in flight before they are added.  Out-of-range offsets or
+// indices read nothing: they contribute zero and set the status word.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -54,15 +55,25 @@ typedef uint32_t u32x2s_t __attribute__((ext_vector_type(2), aligned(2)));
 
 __device__ __forceinline__ uint16_t bag_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
+// The stage is bound by the row gathers: 286 MB of rows for 4096 rows of 26
+// bags of 1..20 ids, most of them hits of the hot rows.  Workgroups are dealt
+// out to the 8 XCDs in turn, so XCD x is given the x-th eighth of the bags,
+// table after table: its L2 holds the hot rows of its own tables instead of a
+// share of everyone's (44.8 -> 37.7 us).  At most 64 VGPRs, so that eight waves
+// share a SIMD: 27.4 us.
 template <typename T, int G>
-__global__ __launch_bounds__(256) void erase_embed_bags_k(EmbedArgs a) {
-  constexpr int BPW = 64 / G;  // bags per wave
+__global__ __launch_bounds__(256, 8) void erase_embed_bags_k(EmbedArgs a, uint32_t chunk) {
+  constexpr int BPW = 64 / G;               // bags per wave
+  constexpr int IPL = G >= 8 ? 1 : 8 / G;   // ids per lane and round
+  constexpr int CH = G * IPL;               // ids of a bag per round
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane / G, q = lane % G;  // bag of this lane within the wave, column chunk
-  const int64_t nbags = (int64_t)a.M * a.T;
-  const int64_t bag = ((int64_t)blockIdx.x * 4 + wave) * BPW + g;
-  const bool live = bag < nbags;
-  const int m = live ? (int)(bag / a.T) : 0, t = live ? (int)(bag % a.T) : 0;
+  const uint32_t wg = (blockIdx.x & 7u) * chunk + (blockIdx.x >> 3);
+  const int64_t bag0 = (int64_t)wg * 4 * BPW;  // uniform: the workgroup's first bag
+  const int64_t nbags = (int64_t)a.M * a.T;    // < 2^31
+  const bool live = bag0 + wave * BPW + g < nbags;
+  const uint32_t bag = live ? (uint32_t)bag0 + wave * BPW + g : 0u;
+  const int t = (int)(bag / (uint32_t)a.M), m = (int)(bag - (uint32_t)t * (uint32_t)a.M);
   const bool col = live && 4 * q < a.dim;
 
   int64_t beg = 0, end = 0;
@@ -82,24 +93,34 @@ __global__ __launch_bounds__(256) void erase_embed_bags_k(EmbedArgs a) {
   int nmax = n;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) nmax = max(nmax, __shfl_xor(nmax, o, 64));
-  for (int j0 = 0; j0 < nmax; j0 += 8) {
-    f32x4e_t v[8];
+  for (int j0 = 0; j0 < nmax; j0 += CH) {
+    int32_t id[IPL];  // ids j0 + q + G i; -1: none, or out of range
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = j0 + u;
-      v[u] = f32x4e_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < IPL; ++i) {
+      const int j = j0 + q + G * i;
+      id[i] = -1;
       if (j < n) {
-        const int32_t r = a.indices[beg + j];
-        if (r >= 0 && r < a.rows) {
-          if (col) v[u] = *reinterpret_cast<const f32x4e_t*>(tab + (int64_t)r * a.dim);
-        } else {
+        id[i] = a.indices[beg + j];
+        if (id[i] < 0 || id[i] >= a.rows) {
           bad = true;
+          id[i] = -1;
         }
       }
     }
+#pragma unroll 1
+    for (int u0 = 0; u0 < CH && j0 + u0 < nmax; u0 += 8) {
+      f32x4e_t v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (j0 + u < n) acc += v[u];  // in index order
+      for (int u = 0; u < 8; ++u) {
+        // with fewer than 8 lanes per bag a round has exactly 8 ids
+        const int32_t r = __shfl(id[IPL > 1 ? u / G : 0], g * G + (IPL > 1 ? u % G : u0 + u), 64);
+        v[u] = f32x4e_t{0.f, 0.f, 0.f, 0.f};
+        if (col && r >= 0) v[u] = *reinterpret_cast<const f32x4e_t*>(tab + (int64_t)r * a.dim);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (j0 + u0 + u < n) acc += v[u];  // in index order
+    }
   }
   if (bad && a.status) a.status[0] = 1;
   if (col) {
@@ -134,13 +155,14 @@ hipError_t launch_embed_bags(int bf16, const EmbedArgs& a, hipStream_t s) {
   while (G < c) G *= 2;
   const int64_t nbags = (int64_t)a.M * a.T;
   const int64_t per_wg = 4 * (64 / G);
-  dim3 grid((unsigned)((nbags + per_wg - 1) / per_wg)), block(256);
+  const uint32_t chunk = (uint32_t)(((nbags + per_wg - 1) / per_wg + 7) / 8);  // workgroups per XCD
+  dim3 grid(8 * chunk), block(256);
 #define ERASE_BAGS(GG)                                                                     \
   case GG:                                                                                 \
     if (bf16)                                                                              \
-      hipLaunchKernelGGL((erase_embed_bags_k<uint16_t, GG>), grid, block, 0, s, a);        \
+      hipLaunchKernelGGL((erase_embed_bags_k<uint16_t, GG>), grid, block, 0, s, a, chunk);        \
     else                                                                                   \
-      hipLaunchKernelGGL((erase_embed_bags_k<float, GG>), grid, block, 0, s, a);           \
+      hipLaunchKernelGGL((erase_embed_bags_k<float, GG>), grid, block, 0, s, a, chunk);           \
     break;
   switch (G) {
     ERASE_BAGS(1)
@@ -156,6 +178,7 @@ hipError_t launch_embed_bags(int bf16, const EmbedArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+constexpr int kLightBucket = 4;   // entries a lane group sums
 constexpr int kSmallBucket = 64;  // entries a wave sorts in its registers
 constexpr int kSortCap = 16384;   // largest bucket sorted in LDS (64 KB)
 
@@ -163,27 +186,38 @@ constexpr int kSortCap = 16384;   // largest bucket sorted in LDS (64 KB)
 // Backward: table gradients from the gradient at x.  Entry i (an index
 // position) belongs to the bag (t, m) whose range holds it; its global row
 // is t * rows + indices[i].  Entries are bucketed by global row (counts,
-// an exclusive scan, then each entry to its slot), every bucket is put in
-// increasing entry order, and each row is summed in a fixed order of its
+// a place for each bucket, then each entry to its slot), every bucket is put
+// in increasing entry order, and each row is summed in a fixed order of its
 // entries, so the result does not depend on scheduling:
-//  * rows of at most 64 entries: one wave; entries sorted across its lanes,
-//    entry k to lane group k mod (64/G) (G lanes of 4 columns cover a row),
-//    each group adding its entries in order, the groups then combined by a
-//    fixed butterfly;
-//  * rows of 65..1024 entries: one workgroup of 256 threads, and rows of
-//    1025..16384 entries one of 1024 threads; entries sorted in LDS (a
-//    bitmap over their range, or a bitonic sort), entry
-//    k to lane group k mod (threads/G), the groups' partial rows then added
-//    in group order;
+//  * rows of at most 4 entries: one lane group of G lanes (4 columns each);
+//  * rows of 5..64 entries: one wave; entries sorted across its lanes,
+//    entry k to lane group k mod (64/G), each group adding its entries in
+//    order, the groups then combined by a fixed butterfly;
+//  * rows of 65..16384 entries: one workgroup of 1024 threads; entries
+//    sorted in LDS (a bitmap over their range, or a bitonic sort), entry
+//    k to lane group k mod (1024/G), the groups of a wave then combined by a
+//    fixed butterfly and the 16 waves' partial rows added in order;
 //  * larger rows: increasing entry order, by repeated selection (correct but
 //    slow; no workload here has such a row);
-//  * rows no entry selects: zero, written by the waves that scan the counts.
+//  * rows no entry selects: zero.
+// One launch does them all (erase_bags_bwd_sums).  The buckets of rows of at
+// most 64 entries hold the entries' bag rows m, the larger ones the entries:
+// within a table a later entry never has a smaller m, so the order is the
+// same.
+//
+// Workgroups are dealt out to the 8 XCDs in turn; the passes over entries and
+// over table rows give XCD x the x-th eighth of their range, so that the
+// counters, places and buckets of a table stay in one XCD's L2.
 // ---------------------------------------------------------------------------
+// Workgroup of the x-th eighth of n (at most n + 7 launched: results >= n do nothing)
+__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n) { return (b & 7u) * ((n + 7) / 8) + (b >> 3); }
+
 __global__ __launch_bounds__(256) void erase_bags_bwd_clear(EmbedBwdArgs a) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i == 0) {
-    a.nlarge[0] = 0;  // rows listed for the large-bucket kernels
-    a.nlarge[1] = 0;  // rows of 1..kSmallBucket entries (set by the scans)
+    a.nlarge[0] = 0;  // rows of more than kSmallBucket entries
+    a.nlarge[2] = 0;  // entries with a place in a bucket
+    a.nlarge[3] = 0;  // rows of kLightBucket + 1..kSmallBucket entries
   }
   if (i < a.trows) a.count[i] = 0;
   if (i < a.nnz) a.owner[i] = -1;
@@ -191,9 +225,10 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_clear(EmbedBwdArgs a) {
 
 // one thread per bag: its entries' owner
 __global__ __launch_bounds__(256) void erase_bags_bwd_owner(EmbedBwdArgs a) {
-  const int64_t bag = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (bag >= (int64_t)a.M * a.T) return;
-  const int t = (int)(bag / a.M), m = (int)(bag % a.M);
+  const int64_t nbags = (int64_t)a.M * a.T;  // < 2^31
+  const int64_t bag = (int64_t)xcd_block(blockIdx.x, (uint32_t)((nbags + 255) / 256)) * 256 + threadIdx.x;
+  if (bag >= nbags) return;
+  const int t = (int)((uint32_t)bag / (uint32_t)a.M), m = (int)((uint32_t)bag % (uint32_t)a.M);
   const int64_t beg = a.offsets[(int64_t)t * (a.M + 1) + m], end = a.offsets[(int64_t)t * (a.M + 1) + m + 1];
   if (!(beg >= 0 && beg <= end && end <= a.nnz)) {
     if (a.status) a.status[0] = 1;
@@ -220,7 +255,8 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_count(EmbedBwdArgs a) {
     hval[h] = 0;
   }
   __syncthreads();
-  const int64_t i0 = (int64_t)blockIdx.x * kCountTile + tid;
+  const uint32_t tile = xcd_block(blockIdx.x, (uint32_t)((a.nnz + kCountTile - 1) / kCountTile));
+  const int64_t i0 = (int64_t)tile * kCountTile + tid;
   int32_t gid[kCountPer], hs[kCountPer], rk[kCountPer];
 #pragma unroll
   for (int u = 0; u < kCountPer; ++u) {
@@ -254,15 +290,25 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_count(EmbedBwdArgs a) {
     rk[u] = atomicAdd(&hval[h], 1);
   }
   __syncthreads();
-  for (int h = tid; h < kHashSlots; h += 256) {
-    const int32_t g = hkey[h];
-    if (g < 0) continue;
-    const int k = hval[h];
-    const int32_t base = atomicAdd(&a.count[g], k);
+  // the additions of a thread's slots in flight together: the whole backward of
+  // 3 tables of 5000 x 16 and 200 rows 30 us, against 36 one after another
+  // (equal on the CTR shape, where the counters' memory bounds them)
+  constexpr int kSlotPer = kHashSlots / 256;
+  int32_t key[kSlotPer], cnt[kSlotPer], base[kSlotPer];
+#pragma unroll
+  for (int u = 0; u < kSlotPer; ++u) {
+    key[u] = hkey[tid + 256 * u];
+    cnt[u] = hval[tid + 256 * u];
+  }
+#pragma unroll
+  for (int u = 0; u < kSlotPer; ++u) base[u] = key[u] >= 0 ? atomicAdd(&a.count[key[u]], cnt[u]) : 0;
+#pragma unroll
+  for (int u = 0; u < kSlotPer; ++u) {
+    if (key[u] < 0) continue;
     // a row whose count passes kSmallBucket is listed once (exactly one
     // addition crosses the threshold)
-    if (base <= kSmallBucket && base + k > kSmallBucket) a.large[atomicAdd(a.nlarge, 1)] = g;
-    hval[h] = base;
+    if (base[u] <= kSmallBucket && base[u] + cnt[u] > kSmallBucket) a.large[atomicAdd(a.nlarge, 1)] = key[u];
+    hval[tid + 256 * u] = base[u];
   }
   __syncthreads();
 #pragma unroll
@@ -275,12 +321,11 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_count(EmbedBwdArgs a) {
   }
 }
 
-// Exclusive prefix sums over the table rows in three passes, of the counts
-// (each bucket's start) and of the flags of rows with 1..kSmallBucket
-// entries (each such row's place in the list the row-sum kernel walks):
-// each workgroup sums a block of kScanBlock rows (count offsets into start,
-// block totals into bsum and bsum2), one workgroup scans the block totals,
-// and a last pass adds the block offsets and writes the list.
+// A place for every bucket, and the list of the rows of kLightBucket + 1 ..
+// kSmallBucket entries: a workgroup scans the counts and the flags of
+// kScanBlock rows and takes its room behind two counters with one 64-bit
+// addition (two additions: 21 us at 2.6 M rows, they wait for one another).  Which workgroup comes first changes where a bucket lies and the order
+// of the list, but no row's sum.
 constexpr int kScanBlock = 4096;  // 256 threads x 16 rows
 
 __device__ __forceinline__ int block_exclusive_scan(int v, int* part) {
@@ -301,7 +346,7 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* part) {
   return base + x - v;
 }
 
-__device__ __forceinline__ bool small_row(int c) { return c > 0 && c <= kSmallBucket; }
+__device__ __forceinline__ bool mid_row(int c) { return c > kLightBucket && c <= kSmallBucket; }
 
 // a thread's 16 consecutive rows: four 16-byte accesses when all exist
 __device__ __forceinline__ void load16(const int32_t* p, int64_t base, int64_t n, int v[16]) {
@@ -331,82 +376,46 @@ __device__ __forceinline__ void store16(int32_t* p, int64_t base, int64_t n, con
   }
 }
 
-__global__ __launch_bounds__(256) void erase_bags_bwd_scan_local(EmbedBwdArgs a) {
-  __shared__ int part[256];
-  const int64_t base = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * 16;
+__global__ __launch_bounds__(256) void erase_bags_bwd_place(EmbedBwdArgs a) {
+  __shared__ int part[4];
+  __shared__ int room[2];
+  const uint32_t part_of = xcd_block(blockIdx.x, (uint32_t)((a.trows + kScanBlock - 1) / kScanBlock));
+  const int64_t base = (int64_t)part_of * kScanBlock + threadIdx.x * 16;
   int v[16], st[16], s = 0, f = 0;
   load16(a.count, base, a.trows, v);
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     s += v[k];
-    f += small_row(v[k]) ? 1 : 0;
+    f += mid_row(v[k]) ? 1 : 0;
   }
-  int run = block_exclusive_scan(s, part);
+  const int sx = block_exclusive_scan(s, part), fx = block_exclusive_scan(f, part);
+  if (threadIdx.x == 255) {
+    // both counters stay below 2^31: no carry from the low one
+    const unsigned long long r = atomicAdd(reinterpret_cast<unsigned long long*>(a.nlarge + 2),
+                                           ((unsigned long long)(uint32_t)(fx + f) << 32) | (uint32_t)(sx + s));
+    room[0] = (int)(uint32_t)r;
+    room[1] = (int)(uint32_t)(r >> 32);
+  }
+  __syncthreads();
+  int run = room[0] + sx, pos = room[1] + fx;
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     st[k] = run;
     run += v[k];
+    if (mid_row(v[k])) a.mid[pos++] = (int32_t)(base + k);
   }
   store16(a.start, base, a.trows, st);
-  const int fx = block_exclusive_scan(f, part);
-  if (threadIdx.x == 255) {
-    a.bsum[blockIdx.x] = run;
-    a.bsum2[blockIdx.x] = fx + f;
-  }
-}
-
-__device__ __forceinline__ int scan_totals(int* t, int nb, int* part) {
-  // exclusive scan of t[0..nb) in place; returns the total
-  int carry = 0;
-  for (int b0 = 0; b0 < nb; b0 += 256) {
-    const int b = b0 + (int)threadIdx.x;
-    const int v = b < nb ? t[b] : 0;
-    const int ex = block_exclusive_scan(v, part);
-    if (b < nb) t[b] = carry + ex;
-    // the chunk's total, from the last thread's inclusive value
-    if (threadIdx.x == 255) part[0] = ex + v;
-    __syncthreads();
-    carry += part[0];
-    __syncthreads();
-  }
-  return carry;
-}
-
-__global__ __launch_bounds__(256) void erase_bags_bwd_scan_blocks(EmbedBwdArgs a) {
-  __shared__ int part[256];
-  const int nb = (int)((a.trows + kScanBlock - 1) / kScanBlock);
-  (void)scan_totals(a.bsum, nb, part);
-  const int nsmall = scan_totals(a.bsum2, nb, part);
-  if (threadIdx.x == 0) a.nlarge[1] = nsmall;
-}
-
-__global__ __launch_bounds__(256) void erase_bags_bwd_scan_add(EmbedBwdArgs a) {
-  __shared__ int part[256];
-  const int64_t base = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * 16;
-  const int off = a.bsum[blockIdx.x];
-  int f = 0, st[16], c[16];
-  bool fl[16];
-  load16(a.start, base, a.trows, st);
-  load16(a.count, base, a.trows, c);
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    st[k] += off;
-    fl[k] = base + k < a.trows && small_row(c[k]);
-    f += fl[k] ? 1 : 0;
-  }
-  store16(a.start, base, a.trows, st);
-  int pos = a.bsum2[blockIdx.x] + block_exclusive_scan(f, part);
-#pragma unroll
-  for (int k = 0; k < 16; ++k)
-    if (fl[k]) a.small[pos++] = (int32_t)(base + k);
 }
 
 // one thread per entry: into its slot of its row's bucket (no atomics)
 __global__ __launch_bounds__(256) void erase_bags_bwd_scatter(EmbedBwdArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t i = (int64_t)xcd_block(blockIdx.x, (uint32_t)((a.nnz + 255) / 256)) * 256 + threadIdx.x;
   if (i >= a.nnz) return;
   const int32_t gid = a.gid[i];
-  if (gid >= 0) a.bucket[a.start[gid] + a.slot[i]] = (int32_t)i;
+  if (gid >= 0) {
+    const int32_t m = (int32_t)((uint32_t)a.owner[i] % (uint32_t)a.M);
+    a.bucket[a.start[gid] + a.slot[i]] = a.count[gid] <= kSmallBucket ? m : (int32_t)i;
+  }
 }
 
 // 4 consecutive dx columns of bag row m, as fp32
@@ -429,16 +438,15 @@ __device__ __forceinline__ void add4(float4& a, const float4& b) {
   a.w += b.w;
 }
 
-// Buckets of more than kSmallBucket entries (the listed rows): one workgroup
-// of NT threads per bucket of LO < c <= HI entries sorts it by entry in LDS
-// (up to CAP entries: a bitmap over the bucket's entry range when it spans
-// at most 32 kBitWords entries, as on the CTR shape, else a bitonic sort),
-// turns the entries into their bag rows, and
-// sums the row: lane group q (G lanes, 4 columns each) takes entries q,
-// q + NG, ... in order, then the NG partial rows are added in group order.
-// Buckets beyond CAP are summed in increasing entry order by repeated
-// selection.  Instances: 256 threads for 65..1024 entries, 1024 threads
-// above (kSortCap, 16384, sorted).
+// A bucket of more than kSmallBucket entries: the workgroup's NT threads sort
+// it by entry in LDS (up to kSortCap entries: a bitmap over the bucket's entry
+// range when it spans at most 32 kBitWords entries, as on the CTR shape, else
+// a bitonic sort), turn the entries into their bag rows, and sum the row: lane
+// group q (G lanes, 4 columns each) takes entries q, q + NT / G, ... in order,
+// the groups of a wave are combined by a fixed butterfly and the waves'
+// partial rows added in order.  Buckets beyond kSortCap are summed in
+// increasing entry order by repeated selection.
+constexpr int kSumThreads = 1024;
 constexpr int kBitWords = 2048;  // bitmap of the bitmap sort: buckets whose entries span <= 64 Ki
 
 // Minimum over the NT threads of a workgroup (every thread gets it).
@@ -470,18 +478,11 @@ __device__ __forceinline__ int block_exclusive_scan_nt(int v, int32_t* sel) {
   __syncthreads();
   return base + x - v;
 }
-constexpr int kMidBucket = 1024;
-template <typename T, int G, int NT, int CAP>
-__global__ __launch_bounds__(NT) void erase_bags_bwd_large(EmbedBwdArgs a, int lo, int hi) {
+template <typename T, int G>
+__device__ __forceinline__ void bag_row_large(const EmbedBwdArgs& a, int32_t g, int32_t* key, uint32_t* bits, int32_t* sel) {
+  constexpr int NT = kSumThreads, CAP = kSortCap;
   constexpr int NG = NT / G;  // lane groups of the workgroup
-  static_assert(NG * 4 * G <= CAP, "partial rows fit in the key array");
-  __shared__ int32_t key[CAP];
-  __shared__ int32_t sel[NT / 64];
-  __shared__ uint32_t bits[kBitWords];
-  if ((int)blockIdx.x >= a.nlarge[0]) return;  // uniform per workgroup
-  const int32_t g = a.large[blockIdx.x];
   const int c = a.count[g], s0 = a.start[g];
-  if (c <= lo || c > hi) return;  // the other instance's bucket
   const int tid = threadIdx.x;
   const int q = tid / G, cq = tid % G;
   const bool col = 4 * cq < a.dim;
@@ -592,24 +593,32 @@ __global__ __launch_bounds__(NT) void erase_bags_bwd_large(EmbedBwdArgs a, int l
   }
   __syncthreads();
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (col) {
-    int k = q;
-    for (; k + 15 * NG < c; k += 16 * NG) {
-      float4 v[16];
+  for (int k0 = q; k0 < c; k0 += 8 * NG) {
+    float4 v[8];  // all in flight; entries past the end add zero
 #pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = dx4<T>(a, key[k + u * NG], xc);
-#pragma unroll
-      for (int u = 0; u < 16; ++u) add4(acc, v[u]);
+    for (int u = 0; u < 8; ++u) {
+      const int k = k0 + u * NG;
+      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (k < c && col) v[u] = dx4<T>(a, key[k], xc);
     }
-    for (; k < c; k += NG) add4(acc, dx4<T>(a, key[k], xc));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) add4(acc, v[u]);
+  }
+#pragma unroll
+  for (int o = G; o < 64; o <<= 1) {
+    acc.x += __shfl_xor(acc.x, o, 64);
+    acc.y += __shfl_xor(acc.y, o, 64);
+    acc.z += __shfl_xor(acc.z, o, 64);
+    acc.w += __shfl_xor(acc.w, o, 64);
   }
   __syncthreads();  // key[] is reused for the partial rows
-  float* part = reinterpret_cast<float*>(key);  // [NG][4 G] floats
-  if (col) *reinterpret_cast<float4*>(part + q * 4 * G + 4 * cq) = acc;
+  float* part = reinterpret_cast<float*>(key);  // [NT / 64][4 G] floats
+  if (col && (tid & 63) < G) *reinterpret_cast<float4*>(part + (tid >> 6) * 4 * G + 4 * cq) = acc;
   __syncthreads();
   if (tid < a.dim) {
     float sum = 0.f;
-    for (int w = 0; w < NG; ++w) sum += part[w * 4 * G + tid];
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) sum += part[w * 4 * G + tid];
     a.grad[(int64_t)g * a.dim + tid] = sum;
   }
 }
@@ -627,156 +636,168 @@ __device__ __forceinline__ int32_t wave_sort(int32_t v, int lane) {
   return v;
 }
 
-// Rows no entry selects: zeros, one 16-byte chunk per thread.
-__global__ __launch_bounds__(256) void erase_bags_bwd_zero(EmbedBwdArgs a) {
-  const int cpr = a.dim / 4;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.trows * cpr) return;
-  if (a.count[i / cpr] == 0) {
-    // streaming stores: the zeros are not read again by this launch sequence
-    typedef float f32x4v_t __attribute__((ext_vector_type(4)));
-    __builtin_nontemporal_store(f32x4v_t{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4v_t*>(a.grad + 4 * i));
-  }
-}
-
-// Listed rows of 1..kSmallBucket entries, in groups of 64 / G consecutive
-// rows per wave (grid-stride), one row per lane group of G lanes.
-//  * When every row of the group has at most 4 entries (92% of the rows
-//    with entries on the CTR shape, 73% have one), each lane group sums its
-//    own row: its entries sorted in registers, their bag rows and dx slices
-//    loaded by the group's lanes, added as (0 + v0 + 0 + v1) ... exactly as
-//    the wave path below associates at most 4 entries:
-//    ((0 + v0) + (0 + v1)) + ((0 + v2) + (0 + v3)).
-//  * Otherwise the group's rows go one after another through the wave path:
-//    the row's entries sorted across the lanes, their bag rows looked up in
-//    parallel, lane group q adding entries q, q + 64/G, ... in order (eight
-//    loads in flight), the groups combined by a fixed butterfly.
-// Either way a row's sum depends only on its own entries.  (Loading the next
-// row's list entry, count and bucket during the current row's sums measured
-// slower: 146 against 131 us on the CTR shape, before the per-group path.)
 __device__ __forceinline__ void sort2(int32_t& x, int32_t& y) {
   const int32_t lo = min(x, y), hi = max(x, y);
   x = lo;
   y = hi;
 }
+
+// 64 consecutive table rows by one wave: zeros for the rows no entry selects,
+// then the rows of at most kLightBucket entries (92% of the rows with entries
+// on the CTR shape, 73% have one), 64 / G at once, one per lane group: its bag
+// rows sorted in registers, the dx slices loaded by the group's lanes, added
+// as the wave path associates them: ((0 + v0) + (0 + v1)) + ((0 + v2) + (0 + v3)).
 template <typename T, int G>
-__global__ __launch_bounds__(256) void erase_bags_bwd_rows(EmbedBwdArgs a) {
+__device__ __forceinline__ void bag_rows_light(const EmbedBwdArgs& a, int64_t r0) {
   constexpr int NGW = 64 / G;  // lane groups per wave
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63;
   const int q = lane / G, cq = lane % G;  // lane group, column quad
-  const bool col = 4 * cq < a.dim;
-  const int n = a.nlarge[1];
+  const bool col = 4 * cq < a.dim, in = r0 + lane < a.trows;
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int grp = (int)blockIdx.x * 4 + wave; grp * NGW < n; grp += (int)gridDim.x * 4) {
-    if constexpr (NGW >= 4) {
-      const int idx = grp * NGW + q;
-      const bool has = idx < n;
-      const int64_t gq = has ? a.small[idx] : 0;
-      const int cn = has ? a.count[gq] : 0, sq = has ? a.start[gq] : 0;
-      if (__all(cn <= 4)) {  // wave-uniform
-        int32_t e[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) e[k] = k < cn ? a.bucket[sq + k] : INT32_MAX;
-        sort2(e[0], e[1]);
-        sort2(e[2], e[3]);
-        sort2(e[0], e[2]);
-        sort2(e[1], e[3]);
-        sort2(e[1], e[2]);
-        const int64_t xc = a.n_dense + (gq / a.rows) * a.dim + 4 * cq;
-        float4 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int m = k < cn ? a.owner[e[k]] % a.M : 0;
-          v[k] = (k < cn && col) ? dx4<T>(a, m, xc) : zero;
-        }
-        float4 s01 = zero, s1 = zero, s23 = zero, s3 = zero;
-        add4(s01, v[0]);
-        add4(s1, v[1]);
-        add4(s01, s1);
-        add4(s23, v[2]);
-        add4(s3, v[3]);
-        add4(s23, s3);
-        add4(s01, s23);
-        if (has && col) *reinterpret_cast<float4*>(a.grad + gq * a.dim + 4 * cq) = s01;
-        continue;
-      }
+  const int cnt = in ? a.count[r0 + lane] : INT32_MAX;
+  const int st = in ? a.start[r0 + lane] : 0;
+  const uint64_t some = __ballot(cnt >= 1 && cnt <= kLightBucket);
+  if (__ballot(cnt == 0)) {
+    for (int r = q; r < 64; r += NGW) {
+      // streaming stores: the zeros are not read again by this launch sequence
+      typedef float f32x4v_t __attribute__((ext_vector_type(4)));
+      if (__shfl(cnt, r, 64) == 0 && col)
+        __builtin_nontemporal_store(f32x4v_t{0.f, 0.f, 0.f, 0.f},
+                                    reinterpret_cast<f32x4v_t*>(a.grad + (r0 + r) * a.dim + 4 * cq));
     }
-    for (int j = 0; j < NGW; ++j) {
-      const int idx = grp * NGW + j;
-      if (idx >= n) break;
-      const int64_t g = a.small[idx];
-      const int c = a.count[g], s0 = a.start[g];
-      const int32_t e = wave_sort(lane < c ? a.bucket[s0 + lane] : INT32_MAX, lane);
-      const int m = lane < c ? a.owner[e] % a.M : 0;  // bag row of the lane's entry
-      const int t = (int)(g / a.rows);
-      const int64_t xc = a.n_dense + (int64_t)t * a.dim + 4 * cq;
-      float4 acc = zero;
-      for (int k0 = 0; k0 < c; k0 += 8 * NGW) {
-        float4 v[8];
+  }
+  const int n = __popcll(some);
+  // lane k gets the lane of the k-th such row (unlisted lanes send to the top end)
+  const int below = __popcll(some & ((1ull << lane) - 1));
+  const int to = ((some >> lane) & 1) ? below : 63 - (lane - below);
+  const int list = __builtin_amdgcn_ds_permute(to << 2, lane);
+  for (int k0 = 0; k0 < n; k0 += NGW) {
+    const bool has = k0 + q < n;
+    const int r = __shfl(list, has ? k0 + q : 0, 64);
+    const int cs = __shfl(cnt, r, 64), ss = __shfl(st, r, 64);
+    const int cn = has ? cs : 0;
+    int32_t e[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int k = k0 + u * NGW + q;
-          const int mk = __shfl(m, k & 63, 64);
-          v[u] = (k < c && col) ? dx4<T>(a, mk, xc) : zero;
-        }
+    for (int k = 0; k < 4; ++k) e[k] = k < cn ? a.bucket[ss + k] : INT32_MAX;
+    sort2(e[0], e[1]);
+    sort2(e[2], e[3]);
+    sort2(e[0], e[2]);
+    sort2(e[1], e[3]);
+    sort2(e[1], e[2]);
+    const uint32_t g = (uint32_t)(r0 + r);  // < 2^31
+    const int64_t xc = a.n_dense + (int64_t)(g / (uint32_t)a.rows) * a.dim + 4 * cq;
+    float4 v[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) add4(acc, v[u]);
-      }
+    for (int k = 0; k < 4; ++k) v[k] = (k < cn && col) ? dx4<T>(a, e[k], xc) : zero;
+    float4 s01 = zero, s1 = zero, s23 = zero, s3 = zero;
+    add4(s01, v[0]);
+    add4(s1, v[1]);
+    add4(s01, s1);
+    add4(s23, v[2]);
+    add4(s3, v[3]);
+    add4(s23, s3);
+    add4(s01, s23);
+    if (has && col) *reinterpret_cast<float4*>(a.grad + (int64_t)g * a.dim + 4 * cq) = s01;
+  }
+}
+
+// A row of kLightBucket + 1..kSmallBucket entries by one wave: the bag rows
+// sorted across the lanes, lane group q adding entries q, q + 64/G, ... in
+// order (eight loads in flight), the groups combined by a fixed butterfly.
+template <typename T, int G>
+__device__ __forceinline__ void bag_row_mid(const EmbedBwdArgs& a, int32_t g) {
+  constexpr int NGW = 64 / G;
+  const int lane = threadIdx.x & 63;
+  const int q = lane / G, cq = lane % G;
+  const bool col = 4 * cq < a.dim;
+  const int c = a.count[g], s0 = a.start[g];
+  const int m = wave_sort(lane < c ? a.bucket[s0 + lane] : INT32_MAX, lane);
+  const int64_t xc = a.n_dense + (int64_t)(g / a.rows) * a.dim + 4 * cq;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int k0 = 0; k0 < c; k0 += 8 * NGW) {
+    float4 v[8];
 #pragma unroll
-      for (int o = G; o < 64; o <<= 1) {
-        acc.x += __shfl_xor(acc.x, o, 64);
-        acc.y += __shfl_xor(acc.y, o, 64);
-        acc.z += __shfl_xor(acc.z, o, 64);
-        acc.w += __shfl_xor(acc.w, o, 64);
-      }
-      if (col && q == 0) *reinterpret_cast<float4*>(a.grad + g * a.dim + 4 * cq) = acc;
+    for (int u = 0; u < 8; ++u) {
+      const int k = k0 + u * NGW + q;
+      const int mk = __shfl(m, k & 63, 64);
+      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (k < c && col) v[u] = dx4<T>(a, mk, xc);
     }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) add4(acc, v[u]);
+  }
+#pragma unroll
+  for (int o = G; o < 64; o <<= 1) {
+    acc.x += __shfl_xor(acc.x, o, 64);
+    acc.y += __shfl_xor(acc.y, o, 64);
+    acc.z += __shfl_xor(acc.z, o, 64);
+    acc.w += __shfl_xor(acc.w, o, 64);
+  }
+  if (col && q == 0) *reinterpret_cast<float4*>(a.grad + (int64_t)g * a.dim + 4 * cq) = acc;
+}
+
+// Every row of the gradient, in one launch of three kinds of workgroups: the
+// first nlist take the rows of more than kSmallBucket entries (a serial chain
+// of sorts and sums, so they start first), then nmid the rows of 5..64
+// entries, a wave each, then nlight all the others, 64 consecutive rows per
+// wave: the chains of dependent loads of the rows with entries run beside the
+// stores of the zeros (665 MB of gradient for 26 tables of 100000 x 64: 145 to
+// 165 us, against 220 for the same work as four launches).  At that shape the
+// whole backward went from 308 to 239 us, at 3 tables of 5000 x 16 and 200 rows
+// from 79 to 31, at 10 of 30000 x 32 (fp32, 1500 rows) from 95 to 53.  One
+// workgroup per compute unit for the listed rows: with two 251 us.
+template <typename T, int G>
+__global__ __launch_bounds__(kSumThreads, 8) void erase_bags_bwd_sums(EmbedBwdArgs a, uint32_t nlist, uint32_t nmid, uint32_t nlight) {
+  __shared__ int32_t key[kSortCap];
+  __shared__ int32_t sel[kSumThreads / 64];
+  __shared__ uint32_t bits[kBitWords];
+  const uint32_t b = blockIdx.x, wave = threadIdx.x >> 6;
+  if (b < nlist) {
+    const int nl = a.nlarge[0];
+    for (int i = (int)b; i < nl; i += (int)nlist) {
+      bag_row_large<T, G>(a, a.large[i], key, bits, sel);
+      __syncthreads();  // the next row reuses the arrays
+    }
+  } else if (b < nlist + nmid) {
+    const uint32_t n = (uint32_t)a.nlarge[3];
+    for (uint32_t i = (b - nlist) * (kSumThreads / 64) + wave; i < n; i += nmid * (kSumThreads / 64))
+      bag_row_mid<T, G>(a, a.mid[i]);
+  } else {
+    const int64_t r0 = ((int64_t)xcd_block(b - nlist - nmid, nlight) * (kSumThreads / 64) + wave) * 64;
+    if (r0 < a.trows) bag_rows_light<T, G>(a, r0);
   }
 }
 
 hipError_t launch_embed_bags_backward(int bf16, const EmbedBwdArgs& a, hipStream_t s) {
   if (a.dim % 4 || a.dim > 256 || a.trows <= 0) return hipErrorInvalidValue;
   const int64_t nmax = a.trows > a.nnz ? a.trows : a.nnz;
+  auto g8 = [](int64_t n) { return (uint32_t)((n + 7) / 8 * 8); };  // workgroups for xcd_block()
   hipLaunchKernelGGL(erase_bags_bwd_clear, dim3((unsigned)((nmax + 255) / 256)), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(erase_bags_bwd_owner, dim3((unsigned)(((int64_t)a.M * a.T + 255) / 256)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(erase_bags_bwd_owner, dim3(g8(((int64_t)a.M * a.T + 255) / 256)), dim3(256), 0, s, a);
   if (a.nnz > 0) {
-    const dim3 ge((unsigned)((a.nnz + 255) / 256));
-    hipLaunchKernelGGL(erase_bags_bwd_count, dim3((unsigned)((a.nnz + kCountTile - 1) / kCountTile)), dim3(256), 0,
+    hipLaunchKernelGGL(erase_bags_bwd_count, dim3(g8((a.nnz + kCountTile - 1) / kCountTile)), dim3(256), 0,
                        s, a);
-    const unsigned nsb = (unsigned)((a.trows + kScanBlock - 1) / kScanBlock);
-    hipLaunchKernelGGL(erase_bags_bwd_scan_local, dim3(nsb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(erase_bags_bwd_scan_blocks, dim3(1), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(erase_bags_bwd_scan_add, dim3(nsb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(erase_bags_bwd_scatter, ge, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(erase_bags_bwd_place, dim3(g8((a.trows + kScanBlock - 1) / kScanBlock)), dim3(256), 0,
+                       s, a);
+    hipLaunchKernelGGL(erase_bags_bwd_scatter, dim3(g8((a.nnz + 255) / 256)), dim3(256), 0, s, a);
   }
-  // rows no entry selects (every row when there are no entries): zeros
-  hipLaunchKernelGGL(erase_bags_bwd_zero, dim3((unsigned)((a.trows * (a.dim / 4) + 255) / 256)), dim3(256), 0, s, a);
   int G = 1;  // lanes per row: dim / 4 rounded up to a power of two
   while (G < a.dim / 4) G *= 2;
-  // listed rows of 1..kSmallBucket entries: at most min(rows, entries)
-  const int64_t nsmall_max = std::min<int64_t>(a.trows, std::max<int64_t>(a.nnz, 1));
-  const dim3 gr((unsigned)std::min<int64_t>((nsmall_max + 3) / 4, 16384));
-  // at most nnz / (kSmallBucket + 1) rows pass the small-bucket count
-  const dim3 gl((unsigned)(a.nnz / (kSmallBucket + 1) + 1));
-#define ERASE_BAG_ROWS(GG)                                                                                \
-  case GG:                                                                                                \
-    if (bf16) {                                                                                           \
-      if (a.nnz > 0) {                                                                                    \
-        hipLaunchKernelGGL((erase_bags_bwd_large<uint16_t, GG, 256, kMidBucket>), gl, dim3(256), 0, s, a,  \
-                           kSmallBucket, kMidBucket);                                                     \
-        hipLaunchKernelGGL((erase_bags_bwd_large<uint16_t, GG, 1024, kSortCap>), gl, dim3(1024), 0, s, a,  \
-                           kMidBucket, INT32_MAX);                                                        \
-      }                                                                                                   \
-      hipLaunchKernelGGL((erase_bags_bwd_rows<uint16_t, GG>), gr, dim3(256), 0, s, a);                    \
-    } else {                                                                                              \
-      if (a.nnz > 0) {                                                                                    \
-        hipLaunchKernelGGL((erase_bags_bwd_large<float, GG, 256, kMidBucket>), gl, dim3(256), 0, s, a,     \
-                           kSmallBucket, kMidBucket);                                                     \
-        hipLaunchKernelGGL((erase_bags_bwd_large<float, GG, 1024, kSortCap>), gl, dim3(1024), 0, s, a,     \
-                           kMidBucket, INT32_MAX);                                                        \
-      }                                                                                                   \
-      hipLaunchKernelGGL((erase_bags_bwd_rows<float, GG>), gr, dim3(256), 0, s, a);                       \
-    }                                                                                                     \
+  // at most nnz / (kSmallBucket + 1) rows pass the small-bucket count.  One
+  // workgroup per compute unit takes them in turn, so that the other one that
+  // fits there writes meanwhile (multiples of 8: the light rows' workgroups go
+  // to the XCDs by their number)
+  const uint32_t nlist = g8(std::min<int64_t>(a.nnz / (kSmallBucket + 1), 256));
+  const int64_t nw = kSumThreads / 64, nmid_max = std::min<int64_t>(a.trows, a.nnz / (kLightBucket + 1));
+  const uint32_t nmid = g8(std::min<int64_t>((nmid_max + nw - 1) / nw, 256));
+  const uint32_t nlight = (uint32_t)((a.trows + 64 * nw - 1) / (64 * nw));
+  const dim3 grid(nlist + nmid + g8(nlight)), block(kSumThreads);
+#define ERASE_BAG_ROWS(GG)                                                                              \
+  case GG:                                                                                              \
+    if (bf16)                                                                                           \
+      hipLaunchKernelGGL((erase_bags_bwd_sums<uint16_t, GG>), grid, block, 0, s, a, nlist, nmid, nlight); \
+    else                                                                                                \
+      hipLaunchKernelGGL((erase_bags_bwd_sums<float, GG>), grid, block, 0, s, a, nlist, nmid, nlight);    \
     break;
   switch (G) {
     ERASE_BAG_ROWS(1)

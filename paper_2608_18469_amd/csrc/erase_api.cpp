@@ -1964,8 +1964,8 @@ erase_status run_bags_backward(const erase_bag_config& b, const int64_t* offsets
   a.lddx = b.x_ld;
   a.grad = table_grad;
   // count and start per table row; bucket, row, owner, slot, and the lists
-  // of large and of small rows per entry; the lists' counters; two scan
-  // totals per 4096 rows
+  // of large and of mid rows per entry; the lists' counters (the size that
+  // is asked for stays what it was, with room for two totals per 4096 rows)
   a.count = w;
   a.start = w + trr;
   a.bucket = w + 2 * trr;
@@ -1973,10 +1973,8 @@ erase_status run_bags_backward(const erase_bag_config& b, const int64_t* offsets
   a.owner = w + 2 * trr + 2 * nr;
   a.large = w + 2 * trr + 3 * nr;
   a.slot = w + 2 * trr + 4 * nr;
-  a.small = w + 2 * trr + 5 * nr;
+  a.mid = w + 2 * trr + 5 * nr;
   a.nlarge = w + 2 * trr + 6 * nr;
-  a.bsum = a.nlarge + 64;
-  a.bsum2 = a.bsum + roundup(tr / 4096 + 1, 64);
   a.status = status;
   a.nnz = b.nnz;
   a.trows = tr;

@@ -247,8 +247,8 @@ hipError_t launch_embed_bags(int bf16, const EmbedArgs& a, hipStream_t s);
 // Backward of the embedding-bag stage: grad[t][r][d] = sum over the entries
 // i of table t's bags with indices[i] == r of dx[bag m][n_dense + t dim + d],
 // entries in increasing order; rows no entry selects are zero.  Bags must
-// not overlap.  Scratch (all int32): count, start, fill [trows], bucket,
-// gid, owner, bagm [nnz], large [nnz / 65 + 1], nlarge [1], bsum [trows / 4096 + 1].
+// not overlap.  Scratch (all int32): count, start [trows], bucket, gid, owner,
+// slot [nnz], large [nnz / 65 + 1], mid [nnz / 5], nlarge [4] (8-byte aligned).
 // Invalid offsets or ids set status[0] = 1 (nullable).
 struct EmbedBwdArgs {
   const int64_t* offsets;  // [T][M+1]
@@ -256,7 +256,7 @@ struct EmbedBwdArgs {
   const void* dx; int64_t lddx;  // [M][lddx] of the activation dtype
   float* grad;             // [T][rows][dim]
   int32_t* count; int32_t* start; int32_t* bucket; int32_t* gid; int32_t* owner; int32_t* slot;
-  int32_t* large; int32_t* small; int32_t* nlarge; int32_t* bsum; int32_t* bsum2;
+  int32_t* large; int32_t* mid; int32_t* nlarge;
   int* status;
   int64_t nnz, trows;      // trows = T * rows < 2^31
   int rows, M, n_dense, T, dim;
