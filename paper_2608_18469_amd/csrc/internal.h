@@ -308,20 +308,19 @@ struct TfRmsArgs {
 hipError_t launch_tf_rms(int backward, const TfRmsArgs& a, hipStream_t s, const LaunchEv& ev = {});
 
 // Causal attention over qkv [B T][3 d] (q | k | v, head h at columns
-// 64 h .. 64 h + 63 of each), head size 64.  part 0: o and lse
-// [B][H][T] (natural log); 1: dsum = rowsum(dout * o); 2: dK and dV; 3: dQ,
-// into dqkv (same layout as qkv).
+// 64 h .. 64 h + 63 of each), head size 64.  Forward: o and lse [B][H][T]
+// (natural log); backward: dK, dV and dQ from dout, o and lse, into dqkv (same
+// layout as qkv), one launch.
 struct TfAttnArgs {
   const uint16_t* qkv; int64_t ldqkv;
   uint16_t* o; int64_t ldo;
   float* lse;
   const uint16_t* dout; int64_t lddo;
-  float* dsum;
   uint16_t* dqkv; int64_t lddqkv;
   int B, T, H, d;
   float scale;  // 1 / sqrt(64)
 };
-hipError_t launch_tf_attn(int part, const TfAttnArgs& a, hipStream_t s, const LaunchEv& ev = {});
+hipError_t launch_tf_attn(int backward, const TfAttnArgs& a, hipStream_t s, const LaunchEv& ev = {});
 
 // Softmax cross-entropy of the vocabulary head without a pass over the
 // logits.  The logits GEMM stores e[n][v] = exp(x[n][v] - xref[n]) (bf16),
@@ -362,13 +361,13 @@ hipError_t launch_tf_head(int part, const TfHeadArgs& a, hipStream_t s, const La
 
 // Embedding gradient: grad[v] = sum over positions n with input[n] == v, in
 // increasing n, of dx[n] (fp32); zero rows for absent tokens.  count and
-// fill [V] must be zero on entry (count is zero again on exit); start [V],
-// bucket [N] scratch.  Four launches.
+// cursor [1] must be zero on entry (and are zero again on exit); start and
+// fill [V], bucket [N] scratch.  Four launches.
 struct TfEmbGradArgs {
   const int32_t* input;
   int64_t N;
   int V, d;
-  int32_t* count; int32_t* start; int32_t* fill; int32_t* bucket;
+  int32_t* count; int32_t* start; int32_t* fill; int32_t* bucket; int32_t* cursor;
   const float* dx; int64_t lddx;
   float* grad; int64_t ldgrad;
 };

@@ -165,7 +165,7 @@ struct Block {
   // (after tf_head_norm) the head's output gradient up to a row scale
   uint16_t *a0 = nullptr, *n1, *qkv, *o, *a1, *n2, *u, *g, *z, *hn, *logits, *hns;
   uint16_t *dhn, *dz, *du, *dn2, *da1, *dout, *dqkv, *dn1 = nullptr;
-  float *r1, *r2, *r3, *lse, *dsum, *lstat, *xref, *rowscale, *rowloss, *ploss, *da0 = nullptr, *gemb = nullptr;
+  float *r1, *r2, *r3, *lse, *lstat, *xref, *rowscale, *rowloss, *ploss, *da0 = nullptr, *gemb = nullptr;
   int32_t* flag = nullptr;
   int ntiles = 0, nloss = 0;
   Lin fwd[NW], dgr[NW], wgr[NW];
@@ -183,7 +183,7 @@ struct Layout {
   int64_t* t = nullptr;
   int* status = nullptr;
   float* hyper = nullptr;
-  int32_t *target = nullptr, *input = nullptr, *count = nullptr, *start = nullptr, *fill = nullptr,
+  int32_t *target = nullptr, *input = nullptr, *count = nullptr, *start = nullptr, *fill = nullptr, *cursor = nullptr,
           *bucket = nullptr;
   std::vector<Block> blk;
   size_t bytes = 0;
@@ -209,6 +209,7 @@ size_t build_layout(const erase_tf_config& c, uintptr_t base, Layout* P) {
   P->count = i32(D.V);
   P->start = i32(D.V);
   P->fill = i32(D.V);
+  P->cursor = i32(1);
   P->bucket = i32(Np);
   P->blk.assign(D.L, Block{});
   const int64_t BHT = int64_t(D.B) * D.H * D.T;
@@ -254,7 +255,6 @@ size_t build_layout(const erase_tf_config& c, uintptr_t base, Layout* P) {
     B.r2 = f32(Np);
     B.r3 = f32(Np);
     B.lse = f32(BHT);
-    B.dsum = f32(BHT);
     const Plan1 ph = choose_logits(D.N, D.V, d);
     B.ntiles = (int)cdv(D.V, logits_wide(D) ? 128 : ph.bn);
     B.lstat = f32(Np * B.ntiles);
@@ -550,7 +550,6 @@ TfAttnArgs attn_args(const Layout& P, const Block& B) {
   a.lse = B.lse;
   a.dout = B.dout;
   a.lddo = P.ldd;
-  a.dsum = B.dsum;
   a.dqkv = B.dqkv;
   a.lddqkv = P.ld3;
   a.B = P.D.B;
@@ -682,11 +681,8 @@ erase_status enqueue_backward(TfCtx* c, int b, hipStream_t s, int sid) {
   }
   if ((st = G2(WO)) != ERASE_OK) return st;
   const TfAttnArgs at = attn_args(P, B);
-  const int ga = (int)(cdv(D.T, 64) * D.H * D.B);
-  TFRUN(c, 15, b, 1, sid, 0.0, double(D.N) * D.d * 4.0, (int)cdv(int64_t(D.N) * D.H, 32),
+  TFRUN(c, 15, b, 0, sid, 7.0 * attn_flops(D), 0.0, (int)(2 * cdv(D.T, 64) * D.H * D.B),
         [&](const LaunchEv& ev) { return launch_tf_attn(1, at, s, ev); });
-  TFRUN(c, 15, b, 2, sid, 4.0 * attn_flops(D), 0.0, ga, [&](const LaunchEv& ev) { return launch_tf_attn(2, at, s, ev); });
-  TFRUN(c, 15, b, 3, sid, 3.0 * attn_flops(D), 0.0, ga, [&](const LaunchEv& ev) { return launch_tf_attn(3, at, s, ev); });
   if (b == 0) {
     if ((st = G2(WQKV)) != ERASE_OK) return st;
     TfRmsArgs a = rms_args(P, B.a0, B.r1, nullptr);
@@ -705,6 +701,7 @@ erase_status enqueue_backward(TfCtx* c, int b, hipStream_t s, int sid) {
     e.count = P.count;
     e.start = P.start;
     e.fill = P.fill;
+    e.cursor = P.cursor;
     e.bucket = P.bucket;
     e.dx = B.da0;
     e.lddx = P.ldd;

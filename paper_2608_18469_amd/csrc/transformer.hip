@@ -10,8 +10,9 @@
 //                   online over key blocks of 64 (the next block's loads in
 //                   flight during the current one); o and the row
 //                   log-sum-exp.
-//  * tf_attn_bwd_*: D = rowsum(do * o), then dK/dV per key block and dQ per
-//                   query block (no atomics: every output has one writer).
+//  * tf_attn_bwd:   dK/dV per key block and dQ per query block in one launch
+//                   (no atomics: every output has one writer), with
+//                   D = rowsum(do * o) taken from the rows as they are read.
 //  * tf_head_norm:  the softmax normaliser of every row from the logits
 //                   GEMM's per-tile sums of exponentials relative to the
 //                   target logit: the row loss, the row's gradient scale,
@@ -268,16 +269,54 @@ __global__ __launch_bounds__(256) void tf_rms_bwd(TfRmsArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// Order of attention work: `per` kinds of blocks per rank r = 0 .. nb - 1 (rank
+// 0 the longest under the causal mask) and head of the batch bh.  Workgroups go
+// to the 8 XCDs in turn.  With a multiple of 8 heads, or many, an XCD takes
+// whole heads (it re-reads their rows from its own L2), longest blocks first;
+// with few heads the blocks are spread one by one, longest first.  (With the
+// rank as the fastest index an XCD got blocks of 24 steps where another got
+// 10.)  False: no work for this workgroup.  The kernels keep two waves' worth
+// of fragments in flight (156 VGPRs, three waves on a SIMD); held to 128 they
+// spill, and the two-layer step of 16 sequences of 1024 tokens takes 6.23
+// instead of 5.99 ms.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ bool attn_whole_heads(int BH) { return BH % 8 == 0 || BH >= 64; }
+__device__ __forceinline__ bool attn_work(const TfAttnArgs& a, int per, int& r, int& kind, int& b, int& h) {
+  const int BH = a.B * a.H;
+  int bh;
+  if (attn_whole_heads(BH)) {
+    const int heads = (BH + 7) / 8;  // of an XCD
+    const int slot = (int)(blockIdx.x >> 3);
+    const int k = slot % heads;
+    r = slot / heads / per;
+    kind = slot / heads % per;
+    bh = (int)(blockIdx.x & 7) * heads + k;
+    if (bh >= BH) return false;
+  } else {
+    const int id = (int)blockIdx.x;
+    bh = id % BH;
+    r = id / BH / per;
+    kind = id / BH % per;
+  }
+  b = bh / a.H;
+  h = bh % a.H;
+  return true;
+}
+
+// ---------------------------------------------------------------------------
 // attention forward: workgroup = (query block of 64, head, sequence), wave w
-// owns query rows q0 + 16 w + (l & 15)
+// owns query rows q0 + 16 w + (l & 15).  Only the block on the diagonal needs
+// the mask: keys of earlier blocks are before every row of this one, and rows
+// at or past T are not stored.  16 sequences of 1024 tokens, 8 heads: 81 us with
+// every block masked and the ranks fastest, 44 us so.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void tf_attn_fwd(TfAttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t sk[64 * 64];
   __shared__ __attribute__((aligned(16))) uint16_t sv[64 * 64];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4;
-  const int nqb = (a.T + 63) / 64;
-  const int qb = nqb - 1 - (int)blockIdx.x;  // the longest rows first
-  const int h = blockIdx.y, b = blockIdx.z;
+  int rank, kind, b, h;
+  if (!attn_work(a, 1, rank, kind, b, h)) return;
+  const int qb = (a.T + 63) / 64 - 1 - rank;  // the longest rows first
   const int q0 = qb * 64;
   const int qrow = q0 + 16 * wave + (lane & 15);
   const int64_t base = (int64_t)b * a.T;
@@ -318,22 +357,25 @@ __global__ __launch_bounds__(256) void tf_attn_fwd(TfAttnArgs a) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) st4[st][t] = mfma(row_chunk(sk, kr, 4 * s + g), qf[s], st4[st][t]);
       }
+    if (kb == qb) {
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (k0 + 32 * st + 8 * g + 4 * t + q > qrow) st4[st][t][q] = -INFINITY;
+    }
     float mb = -1e30f;
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int key = k0 + 32 * st + 8 * g + 4 * t + q;
-          const bool ok = key <= qrow && key < a.T;
-          const float v = ok ? st4[st][t][q] * sc : -INFINITY;
-          st4[st][t][q] = v;
-          mb = fmaxf(mb, v);
-        }
+        for (int q = 0; q < 4; ++q) mb = fmaxf(mb, st4[st][t][q]);
     mb = fmaxf(mb, __shfl_xor(mb, 16, 64));
     mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
-    const float mnew = fmaxf(mrow, mb);
+    const float mnew = fmaxf(mrow, mb * sc);  // sc > 0
     const float alpha = __builtin_amdgcn_exp2f(mrow - mnew);
     mrow = mnew;
     lpart *= alpha;
@@ -347,7 +389,7 @@ __global__ __launch_bounds__(256) void tf_attn_fwd(TfAttnArgs a) {
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          p[4 * t + q] = __builtin_amdgcn_exp2f(st4[st][t][q] - mnew);
+          p[4 * t + q] = __builtin_amdgcn_exp2f(fmaf(st4[st][t][q], sc, -mnew));
           lpart += p[4 * t + q];
         }
       pf[st] = u32x4_t{pack2(p[0], p[1]), pack2(p[2], p[3]), pack2(p[4], p[5]), pack2(p[6], p[7])};
@@ -373,41 +415,27 @@ __global__ __launch_bounds__(256) void tf_attn_fwd(TfAttnArgs a) {
   }
 }
 
-// D[b][h][t] = sum over the head's 64 columns of do * o: 8 lanes per row
-__global__ __launch_bounds__(256) void tf_attn_bwd_pre(TfAttnArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * 32 + (threadIdx.x >> 3);  // (position, head)
-  const int j = threadIdx.x & 7;
-  const int64_t n = i / a.H;
-  const int h = (int)(i % a.H);
+// sum of do * o over a chunk of 8 columns
+__device__ __forceinline__ float dot8(const u32x4_t& x, const u32x4_t& y) {
   float s = 0.f;
-  if (n < (int64_t)a.B * a.T) {
-    const u32x4_t x = *reinterpret_cast<const u32x4_t*>(a.o + n * a.ldo + h * 64 + 8 * j);
-    const u32x4_t y = *reinterpret_cast<const u32x4_t*>(a.dout + n * a.lddo + h * 64 + 8 * j);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) s += lo16(x[k]) * lo16(y[k]) + hi16(x[k]) * hi16(y[k]);
+  for (int k = 0; k < 4; ++k) {
+    s = fmaf(lo16(x[k]), lo16(y[k]), s);
+    s = fmaf(hi16(x[k]), hi16(y[k]), s);
   }
-  s += __shfl_xor(s, 1, 64);
-  s += __shfl_xor(s, 2, 64);
-  s += __shfl_xor(s, 4, 64);
-  if (j == 0 && n < (int64_t)a.B * a.T) {
-    const int b = (int)(n / a.T), t = (int)(n % a.T);
-    a.dsum[((int64_t)b * a.H + h) * a.T + t] = s;
-  }
+  return s;
 }
 
 // dK, dV of a key block: wave w owns keys k0 + 16 w + (l & 15); for every
 // query block at or after the key block, S = Q K^T and dP = dO V^T with the
 // query rows of the A operand permuted, so lane l holds, for its key, query
 // rows 8g .. 8g + 7 of each 32-row half: the B operand of dV^T = dO^T P and
-// dK^T = Q^T dS.
-__global__ __launch_bounds__(256) void tf_attn_bwd_dkdv(TfAttnArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t sq[64 * 64];
-  __shared__ __attribute__((aligned(16))) uint16_t sdo[64 * 64];
-  __shared__ float sl[64], sd[64];
+// dK^T = Q^T dS.  Only the block on the diagonal needs the mask: rows at or
+// past T have zero Q, dO, log-sum-exp and D, and add nothing.
+__device__ __forceinline__ void attn_bwd_dkdv(const TfAttnArgs& a, int kb, int b, int h, uint16_t* sq, uint16_t* sdo,
+                                              float* sl, float* sd) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4;
   const int nb = (a.T + 63) / 64;
-  const int kb = (int)blockIdx.x;  // the first key blocks see the most query blocks
-  const int h = blockIdx.y, b = blockIdx.z;
   const int k0 = kb * 64;
   const int key = k0 + 16 * wave + (lane & 15);
   const int64_t base = (int64_t)b * a.T;
@@ -423,37 +451,36 @@ __global__ __launch_bounds__(256) void tf_attn_bwd_dkdv(TfAttnArgs a) {
   }
   const float sc = a.scale * kLog2e;
   const float* lse = a.lse + ((int64_t)b * a.H + h) * a.T;
-  const float* dsum = a.dsum + ((int64_t)b * a.H + h) * a.T;
   f32x4_t dvt[4], dkt[4];
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) dvt[dt] = dkt[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const uint16_t* qbase = a.qkv + base * a.ldqkv;
   const uint16_t* dobase = a.dout + base * a.lddo;
-  Stage2 nq = load64(qbase, a.ldqkv, kb * 64, a.T, colq, tid), nd = load64(dobase, a.lddo, kb * 64, a.T, colq, tid);
-  float nl = 0.f, ns = 0.f;
-  if (tid < 64 && kb * 64 + tid < a.T) {
-    nl = lse[kb * 64 + tid] * kLog2e;
-    ns = dsum[kb * 64 + tid];
-  }
+  const uint16_t* obase = a.o + base * a.ldo;
+  Stage2 nq = load64(qbase, a.ldqkv, k0, a.T, colq, tid), nd = load64(dobase, a.lddo, k0, a.T, colq, tid),
+         no = load64(obase, a.ldo, k0, a.T, colq, tid);
+  float nl = tid < 64 && k0 + tid < a.T ? lse[k0 + tid] * kLog2e : 0.f;
   for (int qb = kb; qb < nb; ++qb) {
     const int q0 = qb * 64;
     __syncthreads();
     store64(sq, nq, tid);
     store64(sdo, nd, tid);
-    if (tid < 64) {
-      sl[tid] = nl;
-      sd[tid] = ns;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {  // D of row (tid + 256 i) / 8, from the 8 lanes that hold it
+      float x = dot8(no.v[i], nd.v[i]);
+      x += __shfl_xor(x, 1, 64);
+      x += __shfl_xor(x, 2, 64);
+      x += __shfl_xor(x, 4, 64);
+      if ((tid & 7) == 0) sd[(tid + 256 * i) >> 3] = x;
     }
+    if (tid < 64) sl[tid] = nl;
     __syncthreads();
     if (qb + 1 < nb) {  // next block's loads in flight during this block's compute
       nq = load64(qbase, a.ldqkv, q0 + 64, a.T, colq, tid);
       nd = load64(dobase, a.lddo, q0 + 64, a.T, colq, tid);
-      nl = ns = 0.f;
-      if (tid < 64 && q0 + 64 + tid < a.T) {
-        nl = lse[q0 + 64 + tid] * kLog2e;
-        ns = dsum[q0 + 64 + tid];
-      }
+      no = load64(obase, a.ldo, q0 + 64, a.T, colq, tid);
+      nl = tid < 64 && q0 + 64 + tid < a.T ? lse[q0 + 64 + tid] * kLog2e : 0.f;
     }
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
@@ -474,9 +501,8 @@ __global__ __launch_bounds__(256) void tf_attn_bwd_dkdv(TfAttnArgs a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int ql = 32 * st + 8 * g + 4 * t + q;  // local query row
-          const int qrow = q0 + ql;
-          const bool ok = key <= qrow && qrow < a.T && key < a.T;
-          const float pv = ok ? __builtin_amdgcn_exp2f(s4[t][q] * sc - sl[ql]) : 0.f;
+          float pv = __builtin_amdgcn_exp2f(fmaf(s4[t][q], sc, -sl[ql]));
+          if (qb == kb && key > q0 + ql) pv = 0.f;
           p[4 * t + q] = pv;
           ds[4 * t + q] = pv * (p4[t][q] - sd[ql]);
         }
@@ -505,31 +531,30 @@ __global__ __launch_bounds__(256) void tf_attn_bwd_dkdv(TfAttnArgs a) {
 
 // dQ of a query block: wave w owns query rows q0 + 16 w + (l & 15); for every
 // key block at or before it, S^T and dP^T as in the forward, then
-// dQ^T += K^T dS^T.
-__global__ __launch_bounds__(256) void tf_attn_bwd_dq(TfAttnArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t sk[64 * 64];
-  __shared__ __attribute__((aligned(16))) uint16_t sv[64 * 64];
+// dQ^T += K^T dS^T.  The mask is needed on the diagonal alone, as there.
+__device__ __forceinline__ void attn_bwd_dq(const TfAttnArgs& a, int qb, int b, int h, uint16_t* sk, uint16_t* sv) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4;
-  const int nqb = (a.T + 63) / 64;
-  const int qb = nqb - 1 - (int)blockIdx.x;
-  const int h = blockIdx.y, b = blockIdx.z;
   const int q0 = qb * 64;
   const int qrow = q0 + 16 * wave + (lane & 15);
   const int64_t base = (int64_t)b * a.T;
   const int64_t colq = (int64_t)h * 64, colk = a.d + colq, colv = 2 * (int64_t)a.d + colq;
   u32x4_t qf[2], df[2];
+  float dq = 0.f;  // D of the lane's query row, a quarter of its columns at first
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     qf[s] = df[s] = u32x4_t{0u, 0u, 0u, 0u};
     if (qrow < a.T) {
+      const u32x4_t of = *reinterpret_cast<const u32x4_t*>(a.o + (base + qrow) * a.ldo + colq + 32 * s + 8 * g);
       qf[s] = *reinterpret_cast<const u32x4_t*>(a.qkv + (base + qrow) * a.ldqkv + colq + 32 * s + 8 * g);
       df[s] = *reinterpret_cast<const u32x4_t*>(a.dout + (base + qrow) * a.lddo + colq + 32 * s + 8 * g);
+      dq += dot8(of, df[s]);
     }
   }
+  dq += __shfl_xor(dq, 16, 64);
+  dq += __shfl_xor(dq, 32, 64);
   const float sc = a.scale * kLog2e;
   const int64_t hrow = ((int64_t)b * a.H + h) * a.T;
   const float lq = qrow < a.T ? a.lse[hrow + qrow] * kLog2e : 0.f;
-  const float dq = qrow < a.T ? a.dsum[hrow + qrow] : 0.f;
   f32x4_t acc[4];
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) acc[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -563,9 +588,8 @@ __global__ __launch_bounds__(256) void tf_attn_bwd_dq(TfAttnArgs a) {
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int key = k0 + 32 * st + 8 * g + 4 * t + q;
-          const bool ok = key <= qrow && key < a.T && qrow < a.T;
-          const float pv = ok ? __builtin_amdgcn_exp2f(s4[t][q] * sc - lq) : 0.f;
+          float pv = __builtin_amdgcn_exp2f(fmaf(s4[t][q], sc, -lq));
+          if (kb == qb && k0 + 32 * st + 8 * g + 4 * t + q > qrow) pv = 0.f;
           ds[4 * t + q] = pv * (p4[t][q] - dq);
         }
       const u32x4_t dsf = {pack2(ds[0], ds[1]), pack2(ds[2], ds[3]), pack2(ds[4], ds[5]), pack2(ds[6], ds[7])};
@@ -582,6 +606,23 @@ __global__ __launch_bounds__(256) void tf_attn_bwd_dq(TfAttnArgs a) {
       *reinterpret_cast<uint2*>(a.dqkv + (base + qrow) * a.lddqkv + colq + 16 * dt + 4 * g) = w;
     }
   }
+}
+
+// Both kinds of blocks in one launch, the longest of each first: alone, either
+// leaves compute units idle towards its end (and at 18 heads of 300 positions
+// has 90 workgroups for 256 compute units).  16 sequences of 1024 tokens, 8
+// heads: 131 us, against 9 + 142 + 84 for D, dK/dV and dQ each in a launch; 6 of
+// 300, 3 heads: 13 us against 2 + 13 + 8.
+__global__ __launch_bounds__(256) void tf_attn_bwd(TfAttnArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t t0[64 * 64];
+  __shared__ __attribute__((aligned(16))) uint16_t t1[64 * 64];
+  __shared__ float sl[64], sd[64];
+  int rank, kind, b, h;
+  if (!attn_work(a, 2, rank, kind, b, h)) return;
+  if (kind == 0)
+    attn_bwd_dkdv(a, rank, b, h, t0, t1, sl, sd);  // the first key blocks see the most query blocks
+  else
+    attn_bwd_dq(a, (a.T + 63) / 64 - 1 - rank, b, h, t0, t1);
 }
 
 // ---------------------------------------------------------------------------
@@ -727,27 +768,25 @@ __global__ __launch_bounds__(256) void tf_emb_count(TfEmbGradArgs a) {
   }
 }
 
-// exclusive prefix sum of the counts (one workgroup of 1024 threads), and
-// the fill counters back to zero
-__global__ __launch_bounds__(1024) void tf_emb_scan(TfEmbGradArgs a) {
-  __shared__ int part[1024];
-  const int tid = threadIdx.x;
-  const int per = (a.V + 1023) / 1024;
-  const int lo = tid * per, hi = min(a.V, lo + per);
-  int s = 0;
-  for (int v = lo; v < hi; ++v) s += a.count[v];
-  part[tid] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {  // inclusive Hillis-Steele scan
-    const int x = tid >= off ? part[tid - off] : 0;
-    __syncthreads();
-    part[tid] += x;
-    __syncthreads();
+// A place for every token's bucket: a wave scans 64 counts and takes its room
+// behind one counter, which tf_emb_rows leaves at zero; the fill counters back
+// to zero.  Which wave comes first changes where a bucket lies, but no row's
+// sum.  (One workgroup summing all counts in order took 83 us at 32768 tokens
+// and 16 at 8000; this 9 and 3.)
+__global__ __launch_bounds__(256) void tf_emb_place(TfEmbGradArgs a) {
+  const int v = (int)blockIdx.x * 256 + (int)threadIdx.x, lane = threadIdx.x & 63;
+  const int c = v < a.V ? a.count[v] : 0;
+  int x = c;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
   }
-  int run = part[tid] - s;
-  for (int v = lo; v < hi; ++v) {
-    a.start[v] = run;
-    run += a.count[v];
+  int room = 0;
+  if (lane == 63 && x) room = atomicAdd(a.cursor, x);
+  room = __shfl(room, 63, 64);
+  if (v < a.V) {
+    a.start[v] = room + x - c;
     a.fill[v] = 0;
   }
 }
@@ -809,6 +848,7 @@ __global__ __launch_bounds__(256) void tf_emb_rows(TfEmbGradArgs a) {
     if (cc < a.d / 4) *reinterpret_cast<float4*>(a.grad + v * a.ldgrad + cc * 4) = acc[i];
   }
   if (lane == 0) a.count[v] = 0;
+  if (v == 0 && lane == 0) a.cursor[0] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -830,19 +870,15 @@ hipError_t launch_tf_rms(int backward, const TfRmsArgs& a, hipStream_t s, const 
   return hipGetLastError();
 }
 
-hipError_t launch_tf_attn(int part, const TfAttnArgs& a, hipStream_t s, const LaunchEv& ev) {
-  const dim3 grid((unsigned)((a.T + 63) / 64), (unsigned)a.H, (unsigned)a.B);
-  switch (part) {
-    case 0: ERASE_TF_LAUNCH(tf_attn_fwd, grid, dim3(256), s, ev, a); break;
-    case 1: {
-      const int64_t rows = (int64_t)a.B * a.T * a.H;
-      ERASE_TF_LAUNCH(tf_attn_bwd_pre, dim3((unsigned)((rows + 31) / 32)), dim3(256), s, ev, a);
-      break;
-    }
-    case 2: ERASE_TF_LAUNCH(tf_attn_bwd_dkdv, grid, dim3(256), s, ev, a); break;
-    case 3: ERASE_TF_LAUNCH(tf_attn_bwd_dq, grid, dim3(256), s, ev, a); break;
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch_tf_attn(int backward, const TfAttnArgs& a, hipStream_t s, const LaunchEv& ev) {
+  const int64_t BH = (int64_t)a.B * a.H, nb = (a.T + 63) / 64;
+  const bool whole = BH % 8 == 0 || BH >= 64;  // attn_whole_heads
+  const int64_t n = (whole ? (BH + 7) / 8 * 8 : BH) * nb * (backward ? 2 : 1);
+  if (n > INT32_MAX) return hipErrorInvalidValue;
+  if (backward)
+    ERASE_TF_LAUNCH(tf_attn_bwd, dim3((unsigned)n), dim3(256), s, ev, a);
+  else
+    ERASE_TF_LAUNCH(tf_attn_fwd, dim3((unsigned)n), dim3(256), s, ev, a);
   return hipGetLastError();
 }
 
@@ -860,7 +896,7 @@ hipError_t launch_tf_emb_grad(const TfEmbGradArgs& a, hipStream_t s) {
   if (a.d % 4 || a.d > 4 * 64 * kEmbVec) return hipErrorInvalidValue;
   const dim3 gn((unsigned)((a.N + 255) / 256));
   hipLaunchKernelGGL(tf_emb_count, gn, dim3(256), 0, s, a);
-  hipLaunchKernelGGL(tf_emb_scan, dim3(1), dim3(1024), 0, s, a);
+  hipLaunchKernelGGL(tf_emb_place, dim3((unsigned)((a.V + 255) / 256)), dim3(256), 0, s, a);
   hipLaunchKernelGGL(tf_emb_scatter, gn, dim3(256), 0, s, a);
   hipLaunchKernelGGL(tf_emb_rows, dim3((unsigned)((a.V + 3) / 4)), dim3(256), 0, s, a);
   return hipGetLastError();
