@@ -51,10 +51,12 @@ int xcd_group(int gm, int gn, int split, int bm, int bn);
 //   GK_FWD_LOGITS  y = exp(acc - xref[m]) (the row's exponentials relative to a
 //                  reference logit), plus per row the sum of the stored values
 //                  over this tile's columns into lstat    (vocabulary head)
+//   GK_DGRAD_PART  part[z][m][n] = acc in fp32: an input gradient whose contraction
+//                  is split, its reader adds the slices (the vocabulary head)
 // GK_DGRAD with neither mask nor below_cross stores g = acc (+ res) as is.
 enum GemmKind {
   GK_FWD_RELU = 0, GK_FWD_CROSS = 1, GK_WGRAD = 2, GK_DGRAD = 3, GK_FWD_HEAD = 4,
-  GK_FWD_LIN = 5, GK_FWD_GELU = 6, GK_DGRAD_GELU = 7, GK_FWD_LOGITS = 8
+  GK_FWD_LIN = 5, GK_FWD_GELU = 6, GK_DGRAD_GELU = 7, GK_FWD_LOGITS = 8, GK_DGRAD_PART = 9
 };
 
 // Optional events of one launch: when either is set, the kernel is dispatched
@@ -72,7 +74,7 @@ struct EpiParams {
   void* y;   int64_t ldy;    // [M][ldy] row-major output
   const void* x0; int64_t ldx0;  // block input (cross forward, and cross-below dgrad)
   const void* xl; int64_t ldxl;  // layer input (cross forward residual)
-  // weight gradient: part[z][m][n], row sums of A into bpart[z][m]
+  // weight gradient, split input gradient: part[z][m][n]; row sums of A into bpart[z][m]
   float* part; int64_t ldp; int64_t pstride;
   float* bpart;
   // input gradient: g = acc (+ res); below relu: g*[mask>0]; below cross: g, g*x0
@@ -289,13 +291,15 @@ hipError_t launch_tf_embed(const TfEmbedArgs& a, hipStream_t s, const LaunchEv& 
 // is invalid).
 // Backward: dx = r (s dy - y mean(s dy y)) + res (res nullable), y = x r,
 // s = dyscale[n] (1 when dyscale is null), into out_f32 (fp32) when set,
-// else y (bf16).  N rows of width d (d % 8 == 0, d <= 4096).
+// else y (bf16).  With npart set dy is the sum of its fp32 slices
+// dypart[z][n][ldpart], z = 0 .. npart - 1, in that order.  N rows of width d (d % 8 == 0, d <= 4096).
 struct TfRmsArgs {
   const uint16_t* x; int64_t ldx;
   uint16_t* y; int64_t ldy;
   float* r;
   const uint16_t* dy; int64_t lddy;
   const float* dyscale;
+  const float* dypart; int64_t ldpart, ppstride; int npart;
   const uint16_t* res; int64_t ldres;
   float* out_f32; int64_t ldout;
   const uint16_t* hw; int64_t ldhw;

@@ -123,7 +123,7 @@ struct GemmSmem {
   static constexpr bool KMAJ = KIND == GK_WGRAD;
   static constexpr int PAD = sizeof(T) == 2 ? 0 : 16;
   static constexpr int STAGE = KMAJ ? BK * (BM + BN + 2 * PAD) : (BM + BN) * PITCH;
-  using OT = typename std::conditional<KIND == GK_WGRAD, float, T>::type;
+  using OT = typename std::conditional<KIND == GK_WGRAD || KIND == GK_DGRAD_PART, float, T>::type;
   static constexpr int MAIN = 2 * STAGE * (int)sizeof(T);
   // the logits epilogue stages the fp32 accumulators ([BM][BN + 4] floats)
   static constexpr int TILE = KIND == GK_FWD_LOGITS ? BM * (BN + 4) * 4
@@ -171,7 +171,7 @@ __device__ __forceinline__ void gemm_body(const GemmDesc& g, const EpiParams& e,
                 "k-major chunk permutation: 8 or 16 chunks per row");
   constexpr int AREG = KMAJ ? BK * PA : BM * PITCH;  // elements of the A part of a stage
   constexpr int STAGE = GemmSmem<T, BM, BN, KIND, BKX>::STAGE;
-  using OT = typename std::conditional<KIND == GK_WGRAD, float, T>::type;
+  using OT = typename std::conditional<KIND == GK_WGRAD || KIND == GK_DGRAD_PART, float, T>::type;
   constexpr int OCH = 16 / (int)sizeof(OT);
   constexpr int OPITCH = BN + OCH;
   T* lds = reinterpret_cast<T*>(smem);
@@ -550,7 +550,7 @@ __device__ __forceinline__ void gemm_body(const GemmDesc& g, const EpiParams& e,
   const int M = g.M, N = g.N;
   OT* omn;
   int64_t ldmn;
-  if constexpr (KIND == GK_WGRAD) {
+  if constexpr (KIND == GK_WGRAD || KIND == GK_DGRAD_PART) {
     omn = e.part + (int64_t)z * e.pstride;
     ldmn = e.ldp;
   } else if constexpr (KIND == GK_DGRAD || KIND == GK_DGRAD_GELU) {
@@ -583,7 +583,7 @@ __device__ __forceinline__ void gemm_body(const GemmDesc& g, const EpiParams& e,
           continue;
         }
         OT v;
-        if constexpr (KIND == GK_WGRAD) {
+        if constexpr (KIND == GK_WGRAD || KIND == GK_DGRAD_PART) {
           v = acc[i][j][q];
         } else {
           if (PFM && pfm) {
@@ -929,7 +929,7 @@ ERASE_GEMM_KERNEL_KG2(erase_wgrad_gemm_kg2, GK_WGRAD, 128)
 // activation gradient and are independent): workgroups [0, nw) compute the
 // weight-gradient tiles and slices (the longer contractions, so they start
 // first), the rest the input-gradient tiles.
-template <typename T, int BM, int BN>
+template <typename T, int BM, int BN, int DK = GK_DGRAD>
 __device__ __forceinline__ void bwd_pair(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw,
                                          const EpiParams& ew, int nw, char* smem) {
   // each GEMM is renumbered on its own (workgroups b and b + 8 still share an
@@ -941,15 +941,15 @@ __device__ __forceinline__ void bwd_pair(const GemmDesc& gd, const EpiParams& ed
   } else {
     const int nd = gridDim.x - nw;
     const TileIdx ti = tile_from(xcd_linear(b - nw, nd), (gd.M + BM - 1) / BM, (gd.N + BN - 1) / BN, gd.group);
-    gemm_body<T, BM, BN, GK_DGRAD>(gd, ed, ti.m, ti.n, 0, smem);
+    gemm_body<T, BM, BN, DK>(gd, ed, ti.m, ti.n, ti.z, smem);
   }
 }
 
-template <typename T, int BM, int BN>
+template <typename T, int BM, int BN, int DK>
 __global__ __launch_bounds__(256) void erase_bwd_gemm(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew, int nw) {
-  constexpr int SD = GemmSmem<T, BM, BN, GK_DGRAD>::BYTES, SW = GemmSmem<T, BM, BN, GK_WGRAD>::BYTES;
+  constexpr int SD = GemmSmem<T, BM, BN, DK>::BYTES, SW = GemmSmem<T, BM, BN, GK_WGRAD>::BYTES;
   __shared__ __attribute__((aligned(16))) char smem[SD > SW ? SD : SW];
-  bwd_pair<T, BM, BN>(gd, ed, gw, ew, nw, smem);
+  bwd_pair<T, BM, BN, DK>(gd, ed, gw, ew, nw, smem);
 }
 template <typename T, int BM, int BN>
 __global__ __launch_bounds__(256) void erase_bwd_gemm_b(const BlockJob* jobs, StepPtrs st, int nw) {
@@ -1084,15 +1084,23 @@ template <typename T, int BM, int BN>
 static hipError_t launch_bwd_t(const GemmDesc& gd0, const EpiParams& ed, const GemmDesc& gw0, const EpiParams& ew,
                                hipStream_t s, const LaunchEv& ev, const Batch* bt) {
   const GemmDesc gd = with_group(gd0, BM, BN), gw = with_group(gw0, BM, BN);
-  const int nd = ((gd.M + BM - 1) / BM) * ((gd.N + BN - 1) / BN);
+  const int nd = ((gd.M + BM - 1) / BM) * ((gd.N + BN - 1) / BN) * gd.split;
   const int nw = ((gw.M + BM - 1) / BM) * ((gw.N + BN - 1) / BN) * gw.split;
-  ERASE_LAUNCH_B(erase_bwd_gemm, (T, BM, BN), dim3(nd + nw), dim3(256), 0, (nw), gd, ed, gw, ew, nw);
+  const dim3 grid(nd + nw, bt ? bt->n : 1), block(256);
+  if (bt)
+    ERASE_LAUNCH((erase_bwd_gemm_b<T, BM, BN>), grid, block, 0, s, ev, bt->jobs, bt->st, nw);
+  else if (ed.part)
+    ERASE_LAUNCH((erase_bwd_gemm<T, BM, BN, GK_DGRAD_PART>), grid, block, 0, s, ev, gd, ed, gw, ew, nw);
+  else
+    ERASE_LAUNCH((erase_bwd_gemm<T, BM, BN, GK_DGRAD>), grid, block, 0, s, ev, gd, ed, gw, ew, nw);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_gemm(int bf16, const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
                            hipStream_t s, const LaunchEv& ev, const Batch* bt) {
-  if (gd.bm != gw.bm || gd.bn != gw.bn || gd.split != 1 || gw.split <= 0 || ew.ap) return hipErrorInvalidValue;
+  if (gd.bm != gw.bm || gd.bn != gw.bn || gw.split <= 0 || ew.ap) return hipErrorInvalidValue;
+  // only fp32 slices can be split, and not in a launch of several blocks
+  if (ed.part ? (bt || gd.split < 1) : gd.split != 1) return hipErrorInvalidValue;
   if (bf16 && gd.bm >= 128) return launch_wide_bwd(gd, ed, gw, ew, s, ev, bt);
   if (bf16) {
     if (gd.bm == 64 && gd.bn == 64) return launch_bwd_t<uint16_t, 64, 64>(gd, ed, gw, ew, s, ev, bt);

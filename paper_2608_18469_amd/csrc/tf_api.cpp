@@ -166,6 +166,8 @@ struct Block {
   uint16_t *a0 = nullptr, *n1, *qkv, *o, *a1, *n2, *u, *g, *z, *hn, *logits, *hns;
   uint16_t *dhn, *dz, *du, *dn2, *da1, *dout, *dqkv, *dn1 = nullptr;
   float *r1, *r2, *r3, *lse, *lstat, *xref, *rowscale, *rowloss, *ploss, *da0 = nullptr, *gemb = nullptr;
+  float* dhnp = nullptr;  // the head's input gradient in hsplit fp32 slices [N][d] (hsplit > 1, else dhn)
+  int hsplit = 1;
   int32_t* flag = nullptr;
   int ntiles = 0, nloss = 0;
   Lin fwd[NW], dgr[NW], wgr[NW];
@@ -275,16 +277,14 @@ size_t build_layout(const erase_tf_config& c, uintptr_t base, Layout* P) {
       } else if (i != WH) {
         wp = wide_wgrad(D.rows[i], D.cols[i], D.N, wide_core_wgrad_us(D.rows[i], D.cols[i], D.N, 1), 1);
       } else {
-        // the head's input gradient contracts over the vocabulary: 256x256
-        // tiles only when they fill the chip (16384 x 512 over 32768: 768 us
-        // in 128 of them, 573 us in 512 of 128x128)
-        wp = wide_pair(D.N, D.V, d, 1);
-        if (wp.tile == 256 && wide_tiles(D.N, d) < kWideCus)
-          wp = {128, std::max(1, mid_wgrad_split(D.V, d, D.N, 1e30, 1, mid_tiles(D.N, d), cdv(D.V, 64)).split)};
+        const HeadPair hp = wide_head_pair(D.N, D.V, d, B.wp[i].split);
+        wp = {hp.tile, hp.split};
+        B.hsplit = hp.dsplit;
       }
       B.pair_tile[i] = wp.tile;
       if (wp.tile) B.wp[i] = wide_plan(wp.tile, rup(D.N, 64), wp.split);
       B.part[i] = f32(int64_t(B.wp[i].split) * D.rows[i] * D.cols[i]);
+      if (i == WH && B.hsplit > 1) B.dhnp = f32(int64_t(B.hsplit) * D.N * d);
     }
     B.segs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * (NW + 1)));
   }
@@ -363,6 +363,17 @@ void build_gemms(const erase_tf_config& c, Layout* P) {
       L.e.lddmn = ldo;
     };
     dgr(WH, B.logits, P->ldv, GK_DGRAD, B.dhn, P->ldd);
+    if (B.hsplit > 1) {
+      Lin& L = B.dgr[WH];
+      const Plan1 p = wide_plan(64, D.V, B.hsplit);
+      B.hsplit = p.split;  // no empty slice
+      L.g.split = p.split;
+      L.g.kps = p.kps;
+      L.e = EpiParams{};
+      L.e.part = B.dhnp;
+      L.e.ldp = d;
+      L.e.pstride = N * d;
+    }
     dgr(W2, B.dz, P->ldd, GK_DGRAD_GELU, B.du, P->ld4);
     B.dgr[W2].e.mask = B.u;
     B.dgr[W2].e.ldmask = P->ld4;
@@ -654,7 +665,7 @@ erase_status enqueue_backward(TfCtx* c, int b, hipStream_t s, int sid) {
     }
     const GemmDesc &gd = B.dgr[w].g, &gw = B.wgr[w].g;
     const double flops = 2.0 * gd.M * double(gd.N) * gd.K + 2.0 * gw.M * double(gw.N) * gw.K;
-    const int grid = (int)(cdv(gd.M, gd.bm) * cdv(gd.N, gd.bn) + cdv(gw.M, gw.bm) * cdv(gw.N, gw.bn) * gw.split);
+    const int grid = (int)(cdv(gd.M, gd.bm) * cdv(gd.N, gd.bn) * gd.split + cdv(gw.M, gw.bm) * cdv(gw.N, gw.bn) * gw.split);
     return run(c, 6, b, w, sid, flops, 0.0, grid,
                [&](const LaunchEv& ev) { return launch_bwd_gemm(1, gd, B.dgr[w].e, gw, B.wgr[w].e, s, ev); },
                gd.bm, gd.bn, gw.split);
@@ -666,6 +677,12 @@ erase_status enqueue_backward(TfCtx* c, int b, hipStream_t s, int sid) {
     a.dy = B.dhn;
     a.lddy = P.ldd;
     a.dyscale = B.rowscale;
+    if (B.hsplit > 1) {
+      a.dypart = B.dhnp;
+      a.ldpart = D.d;
+      a.ppstride = D.N * int64_t(D.d);
+      a.npart = B.hsplit;
+    }
     if ((st = rms(c, 1, a, b, 2, sid, s)) != ERASE_OK) return st;
   }
   if ((st = G(B.dgr[W2], 4, W2)) != ERASE_OK) return st;

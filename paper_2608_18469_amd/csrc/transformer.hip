@@ -213,6 +213,8 @@ __global__ __launch_bounds__(256) void tf_rms_fwd(TfRmsArgs a) {
   }
 }
 
+// PART: dy is the sum of npart fp32 slices, kept in fp32 (8 values a chunk).
+template <bool PART>
 __global__ __launch_bounds__(256) void tf_rms_bwd(TfRmsArgs a) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t n = (int64_t)blockIdx.x * 4 + wave;
@@ -220,20 +222,40 @@ __global__ __launch_bounds__(256) void tf_rms_bwd(TfRmsArgs a) {
   const int nc = a.d / 8;
   const float r = a.r[n];
   const float gs = a.dyscale ? a.dyscale[n] : 1.f;
-  u32x4_t xv[kRmsChunks], gv[kRmsChunks];
+  u32x4_t xv[kRmsChunks], gv[PART ? 1 : kRmsChunks];
+  float gf[PART ? kRmsChunks : 1][8];
+  auto dy = [&](int i, int k) {  // element k of chunk i
+    if constexpr (PART)
+      return gf[i][k];
+    else
+      return k & 1 ? hi16(gv[i][k >> 1]) : lo16(gv[i][k >> 1]);
+  };
   float dot = 0.f;
 #pragma unroll
   for (int i = 0; i < kRmsChunks; ++i) {
     const int c = lane + 64 * i;
-    xv[i] = gv[i] = u32x4_t{0u, 0u, 0u, 0u};
-    if (c < nc) {
-      xv[i] = *reinterpret_cast<const u32x4_t*>(a.x + n * a.ldx + c * 8);
-      gv[i] = *reinterpret_cast<const u32x4_t*>(a.dy + n * a.lddy + c * 8);
+    xv[i] = u32x4_t{0u, 0u, 0u, 0u};
+    if (c < nc) xv[i] = *reinterpret_cast<const u32x4_t*>(a.x + n * a.ldx + c * 8);
+    if constexpr (PART) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) gf[i][k] = 0.f;
+      if (c < nc) {
+        const float* p = a.dypart + n * a.ldpart + c * 8;
+        for (int z = 0; z < a.npart; ++z, p += a.ppstride) {
+          const float4 u = *reinterpret_cast<const float4*>(p), w = *reinterpret_cast<const float4*>(p + 4);
+          const float t[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
+#pragma unroll
+          for (int k = 0; k < 8; ++k) gf[i][k] += t[k];
+        }
+      }
+    } else {
+      gv[i] = u32x4_t{0u, 0u, 0u, 0u};
+      if (c < nc) gv[i] = *reinterpret_cast<const u32x4_t*>(a.dy + n * a.lddy + c * 8);
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      dot = fmaf(lo16(gv[i][k]) * gs, lo16(xv[i][k]) * r, dot);
-      dot = fmaf(hi16(gv[i][k]) * gs, hi16(xv[i][k]) * r, dot);
+      dot = fmaf(dy(i, 2 * k) * gs, lo16(xv[i][k]) * r, dot);
+      dot = fmaf(dy(i, 2 * k + 1) * gs, hi16(xv[i][k]) * r, dot);
     }
   }
   const float mdot = wsum(dot) / (float)a.d;
@@ -244,8 +266,8 @@ __global__ __launch_bounds__(256) void tf_rms_bwd(TfRmsArgs a) {
     float o[8];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      o[2 * k] = r * (lo16(gv[i][k]) * gs - lo16(xv[i][k]) * r * mdot);
-      o[2 * k + 1] = r * (hi16(gv[i][k]) * gs - hi16(xv[i][k]) * r * mdot);
+      o[2 * k] = r * (dy(i, 2 * k) * gs - lo16(xv[i][k]) * r * mdot);
+      o[2 * k + 1] = r * (dy(i, 2 * k + 1) * gs - hi16(xv[i][k]) * r * mdot);
     }
     if (a.res) {
       const u32x4_t rv = *reinterpret_cast<const u32x4_t*>(a.res + n * a.ldres + c * 8);
@@ -863,8 +885,10 @@ hipError_t launch_tf_embed(const TfEmbedArgs& a, hipStream_t s, const LaunchEv& 
 hipError_t launch_tf_rms(int backward, const TfRmsArgs& a, hipStream_t s, const LaunchEv& ev) {
   if (a.d % 8 || a.d > 64 * 8 * kRmsChunks) return hipErrorInvalidValue;
   const dim3 grid((unsigned)((a.N + 3) / 4));
-  if (backward)
-    ERASE_TF_LAUNCH(tf_rms_bwd, grid, dim3(256), s, ev, a);
+  if (backward && a.npart)
+    ERASE_TF_LAUNCH(tf_rms_bwd<true>, grid, dim3(256), s, ev, a);
+  else if (backward)
+    ERASE_TF_LAUNCH(tf_rms_bwd<false>, grid, dim3(256), s, ev, a);
   else
     ERASE_TF_LAUNCH(tf_rms_fwd, grid, dim3(256), s, ev, a);
   return hipGetLastError();

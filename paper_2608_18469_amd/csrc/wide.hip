@@ -458,6 +458,13 @@ __device__ __forceinline__ void epi_store(const EpiParams& e, float v[8], const 
   }
 }
 
+// Eight columns of an fp32 slice (rows are a multiple of 64 wide).
+__device__ __forceinline__ void st_part(const EpiParams& e, const float v[8], int m, int n, int z) {
+  f32x4_t* d = reinterpret_cast<f32x4_t*>(e.part + (int64_t)z * e.pstride + (int64_t)m * e.ldp + n);
+  d[0] = f32x4_t{v[0], v[1], v[2], v[3]};
+  d[1] = f32x4_t{v[4], v[5], v[6], v[7]};
+}
+
 // Epilogue of an NT tile: a lane holds eight consecutive columns of TA rows
 // per quadrant.  The operands of one quadrant are loaded together.
 template <int HA, int HB, int KIND, class A>
@@ -484,7 +491,10 @@ __device__ __forceinline__ void epi_nt(const EpiParams& e, const A& acc, int M, 
         float v[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = acc[a][b][i][k >> 2][k & 3];
-        epi_store<KIND>(e, v, bias, m, n, N, r0[i], r1[i]);
+        if constexpr (KIND == GK_DGRAD_PART)
+          st_part(e, v, m, n, ti.z);
+        else
+          epi_store<KIND>(e, v, bias, m, n, N, r0[i], r1[i]);
       }
     }
   }
@@ -717,7 +727,10 @@ __device__ __forceinline__ void nt_tile(const GemmDesc& g, const EpiParams& e, i
       float v[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) v[k] = acc[i][2 * h + (k >> 2)][k & 3];
-      wide::epi_store<KIND>(e, v, bias[h], m, n, N, r0[h][i], r1[h][i]);
+      if constexpr (KIND == GK_DGRAD_PART)
+        wide::st_part(e, v, m, n, ti.z);
+      else
+        wide::epi_store<KIND>(e, v, bias[h], m, n, N, r0[h][i], r1[h][i]);
     }
   }
 }
@@ -744,14 +757,14 @@ __device__ __forceinline__ void wgrad_tile(const GemmDesc& g, const EpiParams& e
 }
 }  // namespace mid
 
-template <int NST>
+template <int NST, int DK = GK_DGRAD>
 __device__ __forceinline__ void mid_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw,
                                         const EpiParams& ew, int nd, int nw, int first, char* smem) {
   const int b = (int)blockIdx.x - (first ? 0 : nd);
   if (b >= 0 && b < nw)
     mid::wgrad_tile<NST>(gw, ew, b, nw, smem);
   else
-    mid::nt_tile<NST, GK_DGRAD>(gd, ed, first ? b - nw : (int)blockIdx.x, nd, smem);
+    mid::nt_tile<NST, DK>(gd, ed, first ? b - nw : (int)blockIdx.x, nd, smem);
 }
 
 template <int NST, int KIND>
@@ -766,11 +779,11 @@ __global__ __launch_bounds__(mid::NT) void erase_mid_wgrad(GemmDesc g, EpiParams
 }
 // Both backward GEMMs of a layer, the longer contraction first (`first`: the
 // weight gradient's).
-template <int NST>
+template <int NST, int DK>
 __global__ __launch_bounds__(mid::NT) void erase_mid_bwd(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew, int nd,
                                                          int nw, int first) {
   __shared__ __attribute__((aligned(16))) char smem[mid::bytes<NST>()];
-  mid_bwd<NST>(gd, ed, gw, ew, nd, nw, first, smem);
+  mid_bwd<NST, DK>(gd, ed, gw, ew, nd, nw, first, smem);
 }
 // the same for several blocks (grid row j: job j)
 template <int NST, int KIND>
@@ -824,7 +837,7 @@ __device__ __forceinline__ void wide_wgrad(const GemmDesc& g, const EpiParams& e
 }
 // Both backward GEMMs of a layer.  The workgroups of the longer contraction
 // come first (`first`: the weight gradient's).
-template <int HA, int HB>
+template <int HA, int HB, int DK = GK_DGRAD>
 __device__ __forceinline__ void wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw,
                                          const EpiParams& ew, int nd, int nw, int first, char* smem) {
   const int b = (int)blockIdx.x - (first ? 0 : nd);
@@ -834,7 +847,7 @@ __device__ __forceinline__ void wide_bwd(const GemmDesc& gd, const EpiParams& ed
     wide::run<HA, HB, false>(
         gd, first ? b - nw : (int)blockIdx.x, nd, nd, false, smem,
         [&](const auto& acc, const auto&, const TileIdx& ti, bool, int wm, int wn, int fr, int fg) {
-          wide::epi_nt<HA, HB, GK_DGRAD>(ed, acc, gd.M, gd.N, ti, wm, wn, fr, fg);
+          wide::epi_nt<HA, HB, DK>(ed, acc, gd.M, gd.N, ti, wm, wn, fr, fg);
         });
   }
 }
@@ -849,11 +862,11 @@ __global__ __launch_bounds__(wide::NT) void erase_wide_wgrad(GemmDesc g, EpiPara
   __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
   wide_wgrad<HA, HB>(g, e, (int)blockIdx.x, (int)gridDim.x, ntiles, smem);
 }
-template <int HA, int HB>
+template <int HA, int HB, int DK>
 __global__ __launch_bounds__(wide::NT) void erase_wide_bwd(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew,
                                                            int nd, int nw, int first) {
   __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
-  wide_bwd<HA, HB>(gd, ed, gw, ew, nd, nw, first, smem);
+  wide_bwd<HA, HB, DK>(gd, ed, gw, ew, nd, nw, first, smem);
 }
 // the same for several blocks (grid row j: job j)
 template <int HA, int HB, int KIND>
@@ -958,27 +971,33 @@ hipError_t launch_wide(int kind, const GemmDesc& g0, const EpiParams& e, hipStre
 hipError_t launch_wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
                            hipStream_t s, const LaunchEv& ev, const Batch* bt) {
   const GemmDesc d = with_order(gd), w = with_order(gw);
-  if (!operands_ok(d) || !operands_ok(w) || d.split != 1 || d.kps < d.K || d.bm != w.bm || d.bn != w.bn || d.bm != d.bn)
+  if (!operands_ok(d) || !operands_ok(w) || d.bm != w.bm || d.bn != w.bn || d.bm != d.bn)
+    return hipErrorInvalidValue;
+  // an input gradient in fp32 slices (the vocabulary head's), else whole
+  const bool part = ed.part != nullptr;
+  if (part ? (bt || d.split < 1 || (int64_t)d.split * d.kps < d.K || d.N % 64) : (d.split != 1 || d.kps < d.K))
     return hipErrorInvalidValue;
   const bool big = d.bm == 256;
   if (!big && d.bm != 128) return hipErrorInvalidValue;
-  const int nd = (int)(big ? wide_tiles(d.M, d.N) : mid_tiles(d.M, d.N));
+  const int nd = (int)(big ? wide_tiles(d.M, d.N) : mid_tiles(d.M, d.N)) * d.split;
   const int nw = (int)(big ? wide_tiles(w.M, w.N) : mid_tiles(w.M, w.N)) * w.split;
   const dim3 grid((unsigned)(nd + nw), bt ? (unsigned)bt->n : 1u), block(512);
-  const int first = w.kps >= d.K ? 1 : 0;
-#define ERASE_BWD(ONE, MANY)                                                          \
-  do {                                                                                \
-    if (bt)                                                                           \
-      ERASE_LAUNCH(MANY, grid, block, 0, s, ev, bt->jobs, bt->st, nd, nw, first);      \
-    else                                                                              \
-      ERASE_LAUNCH(ONE, grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first);           \
+  const int first = w.kps >= std::min(d.K, d.kps) ? 1 : 0;
+#define ERASE_BWD(NAME, ...)                                                                              \
+  do {                                                                                                   \
+    if (bt)                                                                                              \
+      ERASE_LAUNCH((NAME##_b<__VA_ARGS__>), grid, block, 0, s, ev, bt->jobs, bt->st, nd, nw, first);      \
+    else if (part)                                                                                       \
+      ERASE_LAUNCH((NAME<__VA_ARGS__, GK_DGRAD_PART>), grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first); \
+    else                                                                                                 \
+      ERASE_LAUNCH((NAME<__VA_ARGS__, GK_DGRAD>), grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first);    \
   } while (0)
   if (big)
-    ERASE_BWD((erase_wide_bwd<128, 128>), (erase_wide_bwd_b<128, 128>));
+    ERASE_BWD(erase_wide_bwd, 128, 128);
   else if ((int64_t)grid.x * grid.y <= kWideCus)
-    ERASE_BWD((erase_mid_bwd<3>), (erase_mid_bwd_b<3>));
+    ERASE_BWD(erase_mid_bwd, 3);
   else
-    ERASE_BWD((erase_mid_bwd<2>), (erase_mid_bwd_b<2>));
+    ERASE_BWD(erase_mid_bwd, 2);
 #undef ERASE_BWD
   return hipGetLastError();
 }

@@ -131,6 +131,44 @@ inline WidePair wide_pair(int64_t M, int64_t Nout, int64_t Kin, int share) {
   const WideSplit w = wide_wgrad_split(Nout, Kin, M, m.us, share, wide_tiles(M, Kin) * share, kd);
   return w.split ? WidePair{256, w.split} : m.split ? WidePair{128, m.split} : WidePair{};
 }
+// The vocabulary head's backward pair: weight gradient [V][d] over N positions
+// and input gradient [N][d] over the vocabulary, whose few tiles are each a long
+// chain (1800 x 192 over 8000: 87 tiles of 125 k-steps, 42 us).  The input
+// gradient is cut into `dsplit` fp32 slices of at least 8 k-steps where the
+// modelled time with the slices' traffic is the least; core_split: the slices of
+// the core's weight gradient.  The two-layer step of 6 sequences of 300 tokens,
+// width 192, 8000 words 409 -> 373 us (4 slices: the pair 42 -> 22 us), 8 of 500,
+// 256, 4096 502 -> 493, 4 of 64, 128, 1024 254 -> 249.
+struct HeadPair {
+  int tile = 0, split = 1, dsplit = 1;  // tile 0: the core's (its weight-gradient slices stay)
+};
+inline HeadPair wide_head_pair(int64_t N, int64_t V, int64_t d, int core_split) {
+  const int64_t kd = (V + 63) / 64, kw = (N + 63) / 64;
+  const double work = 4.0 * double(N) * double(V) * double(d) / 450e6 + 6.0;
+  HeadPair best;
+  double us = 1e30;
+  for (int ds = 1; ds <= kWideMaxSplit && (ds == 1 || kd / ds >= 8); ds *= 2) {
+    const int64_t kds = (kd + ds - 1) / ds;
+    const double part = ds > 1 ? wide_part_us(N, d, ds) : 0.0;
+    const double chain = 0.32 * double(std::max<int64_t>(kds, (kw + core_split - 1) / core_split)) + 4.0;
+    if (const double t = std::max(work, chain) + part; t < us) {
+      us = t;
+      best = {0, core_split, ds};
+    }
+    const WideSplit m = mid_wgrad_split(V, d, N, us - part, 1, mid_tiles(N, d) * ds, kds);
+    if (m.split) {
+      us = m.us + part;
+      best = {128, m.split, ds};
+    }
+  }
+  // 256x256 tiles only where the input gradient alone fills the chip with them
+  // (16384 x 512 over 32768: 768 us in 128 of them, 573 us in 512 of 128x128)
+  if (wide_tiles(N, d) >= kWideCus) {
+    const WideSplit w = wide_wgrad_split(V, d, N, us, 1, wide_tiles(N, d), kd);
+    if (w.split) best = {256, w.split, 1};
+  }
+  return best;
+}
 // The core's split 64x64 weight gradient alone (512 x 2048 over 16384 rows:
 // 75 us).
 inline double wide_core_wgrad_us(int64_t M, int64_t N, int64_t K, int share) {
