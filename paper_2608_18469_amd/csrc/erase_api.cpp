@@ -156,9 +156,10 @@ struct BlockRT {
   erase_block_buffers buf{};
 };
 
-// Consecutive blocks of equal shape that share launches (jobs: the arguments
-// of launch slot i of member j at jobs[i n + j], device memory; null: a
-// single block).  Their backward is independent block by block (the block
+// Consecutive blocks of equal shape and equal plans that share launches (jobs:
+// the arguments of launch slot i of member j at jobs[i n + j], device memory;
+// null: a single block).  A launch takes its kernel, grid and slices from the
+// first member, everything else from each member's arguments.  Their backward is independent block by block (the block
 // inputs are detached); they share the forward too when they read x and feed
 // no later block.
 struct Group {
@@ -271,15 +272,33 @@ bool same_launches(const erase_config& c, int a, int b) {
   return true;
 }
 
-// The unit of blocks [first, first + n): runs of equal launches as groups.
-Unit make_unit(const erase_config& c, int first, int n) {
+// Two blocks of the same layers are planned alike: same tiles, slices and
+// launches.  (The plans depend on how many blocks share a launch in the ERASE
+// schedules, and units differ in size.)
+bool same_plans(const BlockRT& a, const BlockRT& b) {
+  auto eq = [](const GemmPlan& x, const GemmPlan& y) {
+    return x.bm == y.bm && x.bn == y.bn && x.split == y.split && x.kps == y.kps && x.kgroups == y.kgroups;
+  };
+  for (int l = 0; l < a.L; ++l) {
+    const LayerRT &x = a.layer[l], &y = b.layer[l];
+    if (!eq(x.fwd, y.fwd) || !eq(x.wgrad, y.wgrad) || !eq(x.dgrad, y.dgrad) || x.grouped != y.grouped ||
+        x.fused_adam != y.fused_adam)
+      return false;
+  }
+  return true;
+}
+
+// The unit of blocks [first, first + n): runs of equal blocks (together(a, b))
+// as groups.
+template <class F>
+Unit make_unit(const erase_config& c, int first, int n, F&& together) {
   Unit u;
   u.first = first;
   u.n = n;
   for (int b = first; b < first + n;) {
     Group g;
     g.first = b;
-    while (b + g.n < first + n && same_launches(c, b, b + g.n)) ++g.n;
+    while (b + g.n < first + n && together(b, b + g.n)) ++g.n;
     g.share_fwd = g.n > 1 && c.blocks[b].input_src == ERASE_IN_X;
     for (int i = 0; i < g.n; ++i) g.share_fwd = g.share_fwd && !feeds_next(c, b + i);
     u.groups.push_back(g);
@@ -297,7 +316,7 @@ std::vector<Unit> make_units(const erase_config& c, int cap) {
     while (b + n < c.n_blocks && n < cap &&
            (c.blocks[b + n].input_src == ERASE_IN_PREV || (same_launches(c, b, b + n) && !feeds_next(c, b + n))))
       ++n;
-    us.push_back(make_unit(c, b, n));
+    us.push_back(make_unit(c, b, n, [&](int a, int d) { return same_launches(c, a, d); }));
     b += n;
   }
   return us;
@@ -338,10 +357,9 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
     for (int q = 0; q < 2; ++q) P->xp[q] = cv.take(size_t(Mr) * P->ldxp * esz);
   }
   P->blk.assign(c.n_blocks, BlockRT{});
-  P->serial = make_unit(c, 0, c.n_blocks);
   P->overlap = make_units(c, erase_unit_cap(c));
-  // blocks that share a launch in the ERASE schedules (the plan is the same
-  // for every schedule)
+  // blocks that share a launch in the ERASE schedules (the plan of a block is
+  // the same for every schedule)
   std::vector<int> share_f(c.n_blocks, 1), share_b(c.n_blocks, 1);
   for (const Unit& u : P->overlap)
     for (const Group& g : u.groups)
@@ -525,6 +543,12 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
     B.segs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * nseg));
     B.rsegs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * nseg));
   }
+  // The schedules on one stream share launches over the whole network, among
+  // the blocks that the ERASE units left with equal plans (within such a unit
+  // equal blocks always have them).
+  P->serial = make_unit(c, 0, c.n_blocks, [&](int a, int d) {
+    return same_launches(c, a, d) && same_plans(P->blk[a], P->blk[d]);
+  });
   for_each_unit(P, [&](Unit& u) {
     for (Group& g : u.groups)
       if (g.n > 1)
@@ -1279,9 +1303,21 @@ erase_status each_block(const Group& g, bool share, bool reverse, F&& f) {
   return ERASE_OK;
 }
 
+// Two members of a group agree on what their launch takes from the first.
+bool same_grid(const BlockJob& a, const BlockJob& b) {
+  auto eq = [](const GemmDesc& x, const GemmDesc& y) {
+    return x.M == y.M && x.N == y.N && x.K == y.K && x.kps == y.kps && x.split == y.split && x.bm == y.bm &&
+           x.bn == y.bn && x.kgroups == y.kgroups;
+  };
+  return eq(a.g, b.g) && eq(a.g2, b.g2) && (a.e.ap != nullptr) == (b.e.ap != nullptr) && a.a.nchunks == b.a.nchunks &&
+         a.h.N == b.h.N && a.h.rows == b.h.rows;
+}
+
 // The argument tables of the groups (host copies, in P.jobs_host, group after
-// group; uploaded by erase_init).
-void build_jobs(Ctx* c) {
+// group; uploaded by erase_init).  False: a group's members disagree on the
+// launch they share, which would run one member's grid on another's buffers.
+bool build_jobs(Ctx* c) {
+  bool ok = true;
   Plan& P = c->P;
   P.jobs_host.clear();
   StepIn in;
@@ -1304,8 +1340,11 @@ void build_jobs(Ctx* c) {
         (void)backward_ops(c, g.first + i, in, false, true, put);
         (void)adam_op(c, g.first + i, in, put);
       }
+      for (size_t k = 0; k < P.jobs_host.size() - base; ++k)
+        ok = ok && same_grid(P.jobs_host[base + k], P.jobs_host[base + k / g.n * g.n]);
     }
   });
+  return ok;
 }
 
 // One step's launches.  `sched` selects serial or overlapped order; graph
@@ -1643,7 +1682,7 @@ erase_status erase_init_streams(const erase_config* cfg, const erase_block_buffe
                        c->sf) != hipSuccess)
       return bail(ERASE_ERR_HIP);
   }
-  build_jobs(c);
+  if (!build_jobs(c)) return bail(ERASE_ERR_STATE);
   {
     size_t o = 0;
     bool ok = true;
