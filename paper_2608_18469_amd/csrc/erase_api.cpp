@@ -417,11 +417,12 @@ size_t build_plan(const erase_config& c, uintptr_t base, Plan* P) {
         if (const int t = wide_nt_tile(M, R.N, R.K, share_f[b])) R.fwd = wide_plan(t, roundup(R.K, 64), 1);
       R.wgrad = choose_gemm(P->bf16, R.N, R.K, roundup(M, BK), true);
       if (l == 0 && dgrad) {
-        R.dgrad = choose_gemm(P->bf16, M, R.K, roundup(R.N, BK), false);
+        // the core has input gradients in 64x64 tiles only
+        R.dgrad = choose_gemm(P->bf16, 1, 1, roundup(R.N, BK), false);
+        R.dgrad.kgroups = 1;
         if (P->bf16)
           if (const int t = wide_nt_tile(M, R.K, R.N, 1)) R.dgrad = wide_plan(t, roundup(R.N, 64), 1);
         R.dgrad.group = xcd_group((int)cdiv(M, R.dgrad.bm), (int)cdiv(R.K, R.dgrad.bn), 1, R.dgrad.bm, R.dgrad.bn);
-        R.dgrad.kgroups = 1;
       }
       if (l >= 1) {
         R.dgrad = choose_gemm(P->bf16, M, R.K, roundup(R.N, BK), false);

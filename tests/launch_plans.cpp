@@ -1,8 +1,10 @@
 // Host check of the launch plans of erase_api.cpp, for random networks: no GPU,
 // no HIP call.  The dispatcher is compiled in; the launchers are not needed.
-// The blocks that share a launch agree on everything the host takes from the
-// first of them (kernel, grid, slices): the rest each block reads from its own
-// arguments.
+//  * Every launch of every schedule has a tile, split and kind that the
+//    launchers take.
+//  * The blocks that share a launch agree on everything the host takes from
+//    the first of them (kernel, grid, slices): the rest each block reads from
+//    its own arguments.
 // Arguments: seed, networks, then fixed networks as text (see parse()).
 #include "erase_api.cpp"
 
@@ -158,6 +160,34 @@ bool agree(const Op& a, const Op& b) {
          a.j.h.rows == b.j.h.rows && (a.j.h.dmn != nullptr) == (b.j.h.dmn != nullptr);
 }
 
+// The forms the launchers have.
+bool gemm_taken(int bf, int kind, const GemmDesc& g, const EpiParams& e) {
+  const int BK = bf ? 64 : 32;
+  if (g.K % BK || g.kps % BK || g.kps <= 0 || int64_t(g.split) * g.kps < g.K || int64_t(g.split - 1) * g.kps >= g.K)
+    return false;
+  if (kind != GK_WGRAD && g.split != 1) return false;
+  if (e.ap && !(kind == GK_WGRAD && g.bm == 64 && g.bn == 64 && g.kgroups == 2 && g.split == 1)) return false;
+  const bool fwd = kind == GK_FWD_RELU || kind == GK_FWD_CROSS, other = kind == GK_DGRAD || kind == GK_WGRAD;
+  if (bf && kind == GK_FWD_HEAD) return g.bm == 16 && g.N <= 128;
+  if (bf && (g.bm == 256 || g.bm == 128)) return g.bn == g.bm && (fwd || other);
+  if (bf && g.bm == 64 && g.bn == 128) return fwd && g.kgroups == 2;
+  if (g.bm != 64 || g.bn != 64) return false;
+  if (g.kgroups == 2) return kind == GK_WGRAD ? g.split == 1 && (!bf || e.ap) : bf && fwd;
+  return fwd || other || (kind == GK_FWD_HEAD && g.N <= 64);
+}
+bool taken(int bf, const Op& o) {
+  const GemmDesc &g = o.j.g, &w = o.j.g2;
+  switch (o.type) {
+    case Op::GEMM: return gemm_taken(bf, o.kind, g, o.j.e);
+    case Op::PAIR:
+      return g.bm == w.bm && g.bn == w.bn && g.bm == g.bn && g.split == 1 && !o.j.e2.ap && g.kps >= g.K &&
+             gemm_taken(bf, GK_DGRAD, g, o.j.e) && gemm_taken(bf, GK_WGRAD, w, o.j.e2);
+    case Op::WGRAD_ADAM: return o.j.e.ap && gemm_taken(bf, GK_WGRAD, g, o.j.e);
+    case Op::HEAD: return o.j.h.N >= 1 && o.j.h.N <= HEAD_MAX_N && o.j.h.rows >= 1;
+    default: return o.j.a.nchunks > 0;
+  }
+}
+
 int check(const std::string& text) {
   Net n = parse(text);
   if (validate(&n.c, nullptr) != ERASE_OK) return -1;
@@ -185,6 +215,13 @@ int check(const std::string& text) {
     return v;
   };
   int bad = 0;
+  for (int b = 0; b < n.c.n_blocks; ++b)
+    for (int send = 0; send < (c.P.undet_ok ? 2 : 1); ++send)
+      for (const Op& o : ops(b, send))
+        if (!taken(c.P.bf16, o)) {
+          std::printf("not taken (%s): block %d undetached %d: %s\n", text.c_str(), b, send, describe(o).c_str());
+          ++bad;
+        }
   for_each_unit(&c.P, [&](Unit& u) {
     for (const Group& g : u.groups) {
       const std::vector<Op> a = ops(g.first, false);

@@ -36,3 +36,15 @@ def test_uneven_units(name):
         check_bf16(cfg, und, params, batches, detach=False)
     else:
         assert_bit_identical(und, ref)
+
+
+@pytest.mark.parametrize("batch,width,mid", [(4096, 512, 1024), (3343, 608, 1326)])
+def test_undetached_long_first_layer(batch, width, mid):
+    """An input gradient across a cut with a contraction of 1024 and more into
+    few columns, below the 128x128 tiles' range."""
+    blocks = [{"input": "x", "layers": [(LIN, width, width)], "lam": 1.0}]
+    blocks += [{"input": "prev", "layers": [(LIN, width, mid), (LIN, mid, width)], "lam": 0.5}] * 2
+    cfg = synth.custom("bf16", batch, width, blocks, label_p=0.2)
+    params, batches = synth.make_workload(cfg, 33, 1)
+    print(f"[plans] undetached {batch} {width} {mid}", flush=True)
+    check_bf16(cfg, run_gpu(cfg, params, batches, "undetached")[1], params, batches, detach=False)

@@ -12,6 +12,10 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 UNEVEN = ["bf16 4096 512 x:1:c0:512,512 p:5:c0:512,512", "bf16 1651 512 x:1:c0:508,512 p:8:c0:508,512",
           "bf16 4096 1677 x:10:c0:512,256,128", "bf16 4096 1677 x:7:c0:512,256,128",
           "bf16 4096 1677 x:7:c2:1024,1024,512", "bf16 4096 512 x:7:c0:512,512"]
+# first layers of chained blocks with a long contraction into few input columns
+# (the undetached schedule's input gradient)
+LONG = ["bf16 4096 512 x:1:c0:512 p:3:c0:1024,512", "bf16 3343 953 x:4:c0:563,21,608 p:2:c0:1326,596,608",
+        "bf16 1810 1114 x:2:c0:26,1114 p:1:c0:1616,1114"]
 
 
 @pytest.fixture(scope="module")
@@ -29,5 +33,5 @@ def checker(tmp_path_factory):
 
 
 def test_launch_plans(checker):
-    r = subprocess.run([checker, "7", "5000", *UNEVEN], capture_output=True, text=True, timeout=100)
+    r = subprocess.run([checker, "7", "5000", *UNEVEN, *LONG], capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stdout[-4000:]
