@@ -332,16 +332,15 @@ ERASE_API erase_status erase_embed_bags(const erase_bag_config* cfg, const float
  * detached reading no block sends one):
  *   table_grad[t][r][d] = sum over the entries i of the bags of table t with
  *                         indices[i] == r of dx[m(i)][n_dense + t*dim + d]
- * where m(i) is the bag (row of x) holding entry i.  Each row's entries are
- * summed in fp32 in a fixed order of increasing entry index: rows of at most
- * 64 entries by the lane groups of one wave (G = dim/4 rounded up to a
- * power of two lanes each; entry k to group k mod 64/G, each group in order,
- * the groups then added by a fixed butterfly); rows of 65..1024 entries by
- * the lane groups of a 256-thread workgroup and rows of 1025..16384 entries
- * by those of a 1024-thread one (entry k to group k mod threads/G, the
- * groups' partial rows then added in group order); larger rows
- * in increasing entry order (by repeated selection: correct but slow).  The
- * result does not depend on scheduling; rows no entry selects are zero.
+ * where m(i) is the bag (row of x) holding entry i.  A row's entries are
+ * added in fp32 in a fixed association over increasing entry indexes, which
+ * depends on how many entries and rows there are but not on scheduling: entry
+ * k of the row goes to lane group k mod n, each group adds its entries in
+ * order, and the groups are combined by a fixed butterfly (and fixed sums of
+ * the waves).  n is 64/G in rows that one wave sums and 1024/G in rows that a
+ * workgroup sums, G = dim/4 rounded up to a power of two; a wave sums rows of
+ * at most 64 entries, and of at most 512 where more than 512 rows have over
+ * 64.  Rows no entry selects are zero.
  * Bags must not overlap (each entry belongs to at most one bag; entries of
  * no bag are ignored).
  * Device pointers: offsets, indices as for erase_embed_bags; dx [batch][x_ld]
@@ -349,7 +348,7 @@ ERASE_API erase_status erase_embed_bags(const erase_bag_config* cfg, const float
  * (16-byte aligned, fully written); scratch of
  * erase_embed_bags_backward_scratch_bytes() bytes (16-byte aligned, any
  * contents; the call clears what it needs); status as for erase_embed_bags
- * (invalid offsets or ids set it to 1).  Eleven launches on `stream`, no wait.
+ * (invalid offsets or ids set it to 1).  Six launches on `stream`, no wait.
  * ERASE_ERR_SHAPE also when n_tables * rows >= 2^31; ERASE_ERR_WORKSPACE for
  * a missing, misaligned or small scratch. */
 ERASE_API erase_status erase_embed_bags_backward_scratch_bytes(const erase_bag_config* cfg, size_t* bytes);

@@ -180,7 +180,17 @@ hipError_t launch_embed_bags(int bf16, const EmbedArgs& a, hipStream_t s) {
 
 constexpr int kLightBucket = 4;   // entries a lane group sums
 constexpr int kSmallBucket = 64;  // entries a wave sorts in its registers
-constexpr int kSortCap = 16384;   // largest bucket sorted in LDS (64 KB)
+constexpr int kWaveBucket = 512;  // entries a wave sorts where many rows have over kSmallBucket
+constexpr int kSortCap = 16384;   // entries held in LDS at a time (64 KB)
+// A workgroup takes about 7 us for a row, however short (a chain of sorts, scans
+// and barriers), and 256 of them run at a time; a wave takes longer for rows of
+// over kSmallBucket entries, but 4096 run.  So beyond two rows per workgroup the
+// rows of up to kWaveBucket entries go to waves.  The whole backward of 26 tables
+// of 4096 bags of 1..20 ids, dim 64, with a workgroup for every such row and so:
+// 500 rows (83 entries each) 446 and 116 us, 300 rows 300 and 103, 100 rows (430
+// entries) 164 and 112, 1000 rows with Zipf ids 210 and 168.  With waves
+// always, 4 tables of 512 bags, 1000 rows (44 such rows) took 63 instead of 42.
+constexpr int kFewRows = 512;
 
 // ---------------------------------------------------------------------------
 // Backward: table gradients from the gradient at x.  Entry i (an index
@@ -193,15 +203,16 @@ constexpr int kSortCap = 16384;   // largest bucket sorted in LDS (64 KB)
 //  * rows of 5..64 entries: one wave; entries sorted across its lanes,
 //    entry k to lane group k mod (64/G), each group adding its entries in
 //    order, the groups then combined by a fixed butterfly;
-//  * rows of 65..16384 entries: one workgroup of 1024 threads; entries
-//    sorted in LDS (a bitmap over their range, or a bitonic sort), entry
+//  * rows of 65..512 entries, where more than kFewRows rows have over 64: one
+//    wave in the same way, its entries in LDS;
+//  * larger rows, and those where they are few: one workgroup of 1024
+//    threads; entries put in order in LDS (a bitmap over their range, a
+//    bitonic sort, or above 16384 entries one bitmap after another), entry
 //    k to lane group k mod (1024/G), the groups of a wave then combined by a
 //    fixed butterfly and the 16 waves' partial rows added in order;
-//  * larger rows: increasing entry order, by repeated selection (correct but
-//    slow; no workload here has such a row);
 //  * rows no entry selects: zero.
-// One launch does them all (erase_bags_bwd_sums).  The buckets of rows of at
-// most 64 entries hold the entries' bag rows m, the larger ones the entries:
+// One launch does them all (erase_bags_bwd_sums).  The buckets of rows that a
+// wave sums hold the entries' bag rows m, the larger ones the entries:
 // within a table a later entry never has a smaller m, so the order is the
 // same.
 //
@@ -216,8 +227,9 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_clear(EmbedBwdArgs a) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i == 0) {
     a.nlarge[0] = 0;  // rows of more than kSmallBucket entries
+    a.nlarge[1] = 0;  // rows listed in large: more entries than wave_bucket()
     a.nlarge[2] = 0;  // entries with a place in a bucket
-    a.nlarge[3] = 0;  // rows of kLightBucket + 1..kSmallBucket entries
+    a.nlarge[3] = 0;  // rows listed in mid: kLightBucket + 1..wave_bucket() entries
   }
   if (i < a.trows) a.count[i] = 0;
   if (i < a.nnz) a.owner[i] = -1;
@@ -302,14 +314,13 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_count(EmbedBwdArgs a) {
   }
 #pragma unroll
   for (int u = 0; u < kSlotPer; ++u) base[u] = key[u] >= 0 ? atomicAdd(&a.count[key[u]], cnt[u]) : 0;
+  int over = 0;  // rows whose count passes kSmallBucket: exactly one addition to each crosses it
 #pragma unroll
   for (int u = 0; u < kSlotPer; ++u) {
-    if (key[u] < 0) continue;
-    // a row whose count passes kSmallBucket is listed once (exactly one
-    // addition crosses the threshold)
-    if (base[u] <= kSmallBucket && base[u] + cnt[u] > kSmallBucket) a.large[atomicAdd(a.nlarge, 1)] = key[u];
-    hval[tid + 256 * u] = base[u];
+    over += __popcll(__ballot(key[u] >= 0 && base[u] <= kSmallBucket && base[u] + cnt[u] > kSmallBucket));
+    if (key[u] >= 0) hval[tid + 256 * u] = base[u];
   }
+  if ((tid & 63) == 0 && over) atomicAdd(a.nlarge, over);
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < kCountPer; ++u) {
@@ -321,11 +332,17 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_count(EmbedBwdArgs a) {
   }
 }
 
-// A place for every bucket, and the list of the rows of kLightBucket + 1 ..
-// kSmallBucket entries: a workgroup scans the counts and the flags of
-// kScanBlock rows and takes its room behind two counters with one 64-bit
-// addition (two additions: 21 us at 2.6 M rows, they wait for one another).  Which workgroup comes first changes where a bucket lies and the order
-// of the list, but no row's sum.
+// Most entries of a row that a wave sums (known once the rows are counted).
+__device__ __forceinline__ int wave_bucket(const EmbedBwdArgs& a) {
+  return a.nlarge[0] > kFewRows ? kWaveBucket : kSmallBucket;
+}
+
+// A place for every bucket, the list of the rows of kLightBucket + 1 ..
+// wave_bucket() entries and that of the larger ones: a workgroup scans the
+// counts and the flags of kScanBlock rows and takes its room behind the counters
+// with one 64-bit addition (two additions: 21 us at 2.6 M rows, they wait for
+// one another) and, where it has larger rows, one more.  Which workgroup comes
+// first changes where a bucket lies and the order of the lists, but no row's sum.
 constexpr int kScanBlock = 4096;  // 256 threads x 16 rows
 
 __device__ __forceinline__ int block_exclusive_scan(int v, int* part) {
@@ -345,8 +362,6 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* part) {
   __syncthreads();
   return base + x - v;
 }
-
-__device__ __forceinline__ bool mid_row(int c) { return c > kLightBucket && c <= kSmallBucket; }
 
 // a thread's 16 consecutive rows: four 16-byte accesses when all exist
 __device__ __forceinline__ void load16(const int32_t* p, int64_t base, int64_t n, int v[16]) {
@@ -378,31 +393,37 @@ __device__ __forceinline__ void store16(int32_t* p, int64_t base, int64_t n, con
 
 __global__ __launch_bounds__(256) void erase_bags_bwd_place(EmbedBwdArgs a) {
   __shared__ int part[4];
-  __shared__ int room[2];
+  __shared__ int room[3];
   const uint32_t part_of = xcd_block(blockIdx.x, (uint32_t)((a.trows + kScanBlock - 1) / kScanBlock));
   const int64_t base = (int64_t)part_of * kScanBlock + threadIdx.x * 16;
   int v[16], st[16], s = 0, f = 0;
   load16(a.count, base, a.trows, v);
+  const int wb = wave_bucket(a);
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     s += v[k];
-    f += mid_row(v[k]) ? 1 : 0;
+    f += v[k] > wb ? 0x10000 : v[k] > kLightBucket ? 1 : 0;  // at most 4096 of either in a workgroup
   }
   const int sx = block_exclusive_scan(s, part), fx = block_exclusive_scan(f, part);
   if (threadIdx.x == 255) {
     // both counters stay below 2^31: no carry from the low one
+    const int nm = (fx + f) & 0xffff, nl = (fx + f) >> 16;
     const unsigned long long r = atomicAdd(reinterpret_cast<unsigned long long*>(a.nlarge + 2),
-                                           ((unsigned long long)(uint32_t)(fx + f) << 32) | (uint32_t)(sx + s));
+                                           ((unsigned long long)(uint32_t)nm << 32) | (uint32_t)(sx + s));
+    room[2] = nl ? atomicAdd(a.nlarge + 1, nl) : 0;
     room[0] = (int)(uint32_t)r;
     room[1] = (int)(uint32_t)(r >> 32);
   }
   __syncthreads();
-  int run = room[0] + sx, pos = room[1] + fx;
+  int run = room[0] + sx, pos = room[1] + (fx & 0xffff), lpos = room[2] + (fx >> 16);
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     st[k] = run;
     run += v[k];
-    if (mid_row(v[k])) a.mid[pos++] = (int32_t)(base + k);
+    if (v[k] > wb)
+      a.large[lpos++] = (int32_t)(base + k);
+    else if (v[k] > kLightBucket)
+      a.mid[pos++] = (int32_t)(base + k);
   }
   store16(a.start, base, a.trows, st);
 }
@@ -414,7 +435,8 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_scatter(EmbedBwdArgs a) {
   const int32_t gid = a.gid[i];
   if (gid >= 0) {
     const int32_t m = (int32_t)((uint32_t)a.owner[i] % (uint32_t)a.M);
-    a.bucket[a.start[gid] + a.slot[i]] = a.count[gid] <= kSmallBucket ? m : (int32_t)i;
+    const int c = a.count[gid];
+    a.bucket[a.start[gid] + a.slot[i]] = c <= kSmallBucket || c <= wave_bucket(a) ? m : (int32_t)i;
   }
 }
 
@@ -438,22 +460,33 @@ __device__ __forceinline__ void add4(float4& a, const float4& b) {
   a.w += b.w;
 }
 
-// A bucket of more than kSmallBucket entries: the workgroup's NT threads sort
-// it by entry in LDS (up to kSortCap entries: a bitmap over the bucket's entry
-// range when it spans at most 32 kBitWords entries, as on the CTR shape, else
-// a bitonic sort), turn the entries into their bag rows, and sum the row: lane
+// A bucket of more than wave_bucket() entries: the workgroup's NT threads put its
+// entries in order in LDS, turn them into their bag rows, and sum the row: lane
 // group q (G lanes, 4 columns each) takes entries q, q + NT / G, ... in order,
 // the groups of a wave are combined by a fixed butterfly and the waves'
-// partial rows added in order.  Buckets beyond kSortCap are summed in
-// increasing entry order by repeated selection.
+// partial rows added in order.  Up to kSortCap entries are sorted at once: a
+// bitmap over the bucket's entry range when it spans at most 32 kBitWords
+// entries, as on the CTR shape, else a bitonic sort.  Larger buckets take the
+// bitmap over one range of 32 kBitWords entries after another (each from the
+// first entry past the last, so every pass over the bucket lists some), and
+// sum each range kSortCap entries at a time.
 constexpr int kSumThreads = 1024;
 constexpr int kBitWords = 2048;  // bitmap of the bitmap sort: buckets whose entries span <= 64 Ki
 
+// The lane, opaque: else the lane shifts' indexes are kept over the rows of a
+// workgroup, more of them than registers.
+__device__ __forceinline__ int opaque_lane() {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+__device__ __forceinline__ int32_t lane_read(int32_t v, int lane) { return __builtin_amdgcn_ds_bpermute(lane << 2, v); }
 // Minimum over the NT threads of a workgroup (every thread gets it).
 template <int NT>
 __device__ __forceinline__ int32_t block_min_nt(int32_t v, int32_t* sel) {
+  const int lane = opaque_lane();
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
+  for (int o = 32; o >= 1; o >>= 1) v = min(v, lane_read(v, lane ^ o));
   if ((threadIdx.x & 63) == 0) sel[threadIdx.x >> 6] = v;
   __syncthreads();
   v = sel[0];
@@ -461,107 +494,111 @@ __device__ __forceinline__ int32_t block_min_nt(int32_t v, int32_t* sel) {
   __syncthreads();
   return v;
 }
-// Exclusive prefix sum of one value per thread over the NT threads.
+// Exclusive prefix sum of one value per thread over the NT threads (and the
+// total into *all, when set).
 template <int NT>
-__device__ __forceinline__ int block_exclusive_scan_nt(int v, int32_t* sel) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+__device__ __forceinline__ int block_exclusive_scan_nt(int v, int32_t* sel, int* all = nullptr) {
+  const int lane = opaque_lane(), w = threadIdx.x >> 6;
   int x = v;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
+    const int y = lane_read(x, lane - o);
     if (lane >= o) x += y;
   }
   if (lane == 63) sel[w] = x;
   __syncthreads();
   int base = 0;
   for (int k = 0; k < w; ++k) base += sel[k];
+  if (all) {
+    *all = base;
+    for (int k = w; k < NT / 64; ++k) *all += sel[k];
+  }
   __syncthreads();
   return base + x - v;
 }
+// Adds n bag rows of key[], entries number first .. first + n - 1 of the bucket,
+// to the lane groups' sums (entry k to group k mod NG).
+template <typename T, int NG>
+__device__ __forceinline__ void add_bag_rows(const EmbedBwdArgs& a, const int32_t* key, int first, int n, int q, bool col,
+                                             int64_t xc, float4& acc) {
+  for (int k0 = (q - first) & (NG - 1); k0 < n; k0 += 8 * NG) {
+    float4 v[8];  // all in flight; entries past the end add zero
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int k = k0 + u * NG;
+      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (k < n && col) v[u] = dx4<T>(a, key[k], xc);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) add4(acc, v[u]);
+  }
+}
+// The row's sum from the lane groups' sums; part: LDS for [NT / 64][4 G] floats.
+template <int G>
+__device__ __forceinline__ void store_row_sum(const EmbedBwdArgs& a, int32_t g, float4 acc, float* part) {
+  const int tid = threadIdx.x, cq = tid % G;
+#pragma unroll
+  for (int o = G; o < 64; o <<= 1) {
+    acc.x += __shfl_xor(acc.x, o, 64);
+    acc.y += __shfl_xor(acc.y, o, 64);
+    acc.z += __shfl_xor(acc.z, o, 64);
+    acc.w += __shfl_xor(acc.w, o, 64);
+  }
+  __syncthreads();  // the LDS is reused for the partial rows
+  if (4 * cq < a.dim && (tid & 63) < G) *reinterpret_cast<float4*>(part + (tid >> 6) * 4 * G + 4 * cq) = acc;
+  __syncthreads();
+  if (tid < a.dim) {
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSumThreads / 64; ++w) sum += part[w * 4 * G + tid];
+    a.grad[(int64_t)g * a.dim + tid] = sum;
+  }
+}
+
 template <typename T, int G>
 __device__ __forceinline__ void bag_row_large(const EmbedBwdArgs& a, int32_t g, int32_t* key, uint32_t* bits, int32_t* sel) {
-  constexpr int NT = kSumThreads, CAP = kSortCap;
-  constexpr int NG = NT / G;  // lane groups of the workgroup
-  const int c = a.count[g], s0 = a.start[g];
-  const int tid = threadIdx.x;
-  const int q = tid / G, cq = tid % G;
+  constexpr int NT = kSumThreads, NG = NT / G;  // lane groups of the workgroup
+  const int c = a.count[g];
+  const int32_t* bucket = a.bucket + a.start[g];
+  const int tid = threadIdx.x, q = tid / G, cq = tid % G;
   const bool col = 4 * cq < a.dim;
-  const int t = g / a.rows;
-  const int64_t xc = a.n_dense + (int64_t)t * a.dim + 4 * cq;
-  float* out = a.grad + (int64_t)g * a.dim + 4 * cq;
-  if (c > CAP) {
-    // increasing entry order by repeated selection: a workgroup-wide minimum
-    // of the entries above the last one; group 0 adds
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    int32_t prev = -1;
-    for (int k = 0; k < c; ++k) {
-      int32_t cand = INT32_MAX;
-      for (int j = tid; j < c; j += NT) {
-        const int32_t p = a.bucket[s0 + j];
-        if (p > prev && p < cand) cand = p;
-      }
+  const int64_t xc = a.n_dense + (int64_t)(g / a.rows) * a.dim + 4 * cq;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  // n entries in key[], number `first` and on of the bucket: to their bag rows,
+  // in place (each thread its own keys), and those rows to the sums
+  auto add = [&](int first, int n) {
+    for (int i = tid; i < n; i += 4 * NT) {
+      int32_t m[4];
 #pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) cand = min(cand, __shfl_xor(cand, o, 64));
-      if ((tid & 63) == 0) sel[tid >> 6] = cand;
-      __syncthreads();
-      cand = sel[0];
-      for (int w = 1; w < NT / 64; ++w) cand = min(cand, sel[w]);
-      __syncthreads();
-      prev = cand;
-      if (q == 0 && col) add4(acc, dx4<T>(a, a.owner[cand] % a.M, xc));
+      for (int u = 0; u < 4; ++u) m[u] = i + u * NT < n ? a.owner[key[i + u * NT]] % a.M : 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i + u * NT < n) key[i + u * NT] = m[u];
     }
-    if (q == 0 && col) *reinterpret_cast<float4*>(out) = acc;
-    return;
-  }
-  constexpr int PER = CAP / NT;  // keys per thread
+    __syncthreads();
+    add_bag_rows<T, NG>(a, key, first, n, q, col, xc, acc);
+  };
   // the bucket's entry range
-  int32_t e_lo = INT32_MAX, e_hi = -1;
+  int32_t lo = INT32_MAX, hi = -1;
   for (int i = tid; i < c; i += NT) {
-    const int32_t p = a.bucket[s0 + i];
-    e_lo = min(e_lo, p);
-    e_hi = max(e_hi, p);
+    const int32_t p = bucket[i];
+    lo = min(lo, p);
+    hi = max(hi, p);
   }
-  e_lo = block_min_nt<NT>(e_lo, sel);
-  e_hi = -block_min_nt<NT>(-e_hi, sel);
-  const int64_t range = (int64_t)e_hi - e_lo + 1;
-  if (range <= 32 * (int64_t)kBitWords) {
-    // Bitmap sort (the entries of a bucket are distinct): one bit per entry
-    // of the range, then every thread lists the set bits of its run of
-    // words, in order, at its place from a scan of the runs' bit counts.
-    const int nw = (int)((range + 31) / 32);
-    for (int w = tid; w < nw; w += NT) bits[w] = 0u;
-    __syncthreads();
-    for (int i = tid; i < c; i += NT) {
-      const int32_t p = a.bucket[s0 + i] - e_lo;
-      atomicOr(&bits[p >> 5], 1u << (p & 31));
-    }
-    __syncthreads();
-    const int per = (nw + NT - 1) / NT, w0 = min(nw, tid * per), w1 = min(nw, w0 + per);
-    int cnt = 0;
-    for (int w = w0; w < w1; ++w) cnt += __popc(bits[w]);
-    int pos = block_exclusive_scan_nt<NT>(cnt, sel);
-    for (int w = w0; w < w1; ++w) {
-      uint32_t b = bits[w];
-      while (b) {
-        key[pos++] = e_lo + 32 * w + (__ffs(b) - 1);
-        b &= b - 1u;
-      }
-    }
-    __syncthreads();
-  } else {
+  lo = block_min_nt<NT>(lo, sel);
+  hi = -block_min_nt<NT>(-hi, sel);
+  constexpr int WIN = 32 * kBitWords;
+  if (c <= kSortCap && hi - lo >= WIN) {
     // bitonic sort of the bucket in LDS
     int n2 = 1;
     while (n2 < c) n2 <<= 1;
-    {
-      int32_t tmp[PER];  // every load in flight before the LDS stores
+    for (int i = tid; i < n2; i += 4 * NT) {
+      int32_t e[4];  // the loads in flight before the LDS stores
 #pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        const int i = tid + u * NT;
-        tmp[u] = i < c ? a.bucket[s0 + i] : INT32_MAX;
-      }
+      for (int u = 0; u < 4; ++u) e[u] = i + u * NT < c ? bucket[i + u * NT] : INT32_MAX;
 #pragma unroll
-      for (int u = 0; u < PER; ++u)
-        if (tid + u * NT < n2) key[tid + u * NT] = tmp[u];
+      for (int u = 0; u < 4; ++u)
+        if (i + u * NT < n2) key[i + u * NT] = e[u];
     }
     __syncthreads();
     for (int k = 2; k <= n2; k <<= 1)
@@ -578,62 +615,75 @@ __device__ __forceinline__ void bag_row_large(const EmbedBwdArgs& a, int32_t g, 
         }
         __syncthreads();
       }
+    add(0, c);
+  } else {
+    // Bitmap sort (the entries of a bucket are distinct): one bit per entry of
+    // the range [lo, lo + WIN), then every thread lists the set bits of its run
+    // of words, in order, at its place from a scan of the runs' bit counts:
+    // all words at once, or of larger buckets as many as key[] surely holds.
+    const int cw = c <= kSortCap ? kBitWords : kSortCap / 32;
+    int done = 0;  // entries summed
+    int32_t next;  // the first entry past the range
+    do {
+      const int nw = min(kBitWords, (hi - lo) / 32 + 1);
+      for (int w = tid; w < nw; w += NT) bits[w] = 0u;
+      __syncthreads();
+      next = INT32_MAX;
+      for (int i = tid; i < c; i += NT) {
+        const int32_t p = bucket[i];
+        if (p < lo) continue;
+        if (p - lo < WIN)
+          atomicOr(&bits[(p - lo) >> 5], 1u << ((p - lo) & 31));
+        else
+          next = min(next, p);
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (int wc = 0; wc < nw; wc += cw) {
+        const int we = min(nw, wc + cw), per = (we - wc + NT - 1) / NT;
+        const int w0 = min(we, wc + tid * per), w1 = min(we, w0 + per);
+        int cnt = 0;
+        for (int w = w0; w < w1; ++w) cnt += __popc(bits[w]);
+        int n = c;
+        int pos = block_exclusive_scan_nt<NT>(cnt, sel, c > kSortCap ? &n : nullptr);  // and key[] is free again
+        for (int w = w0; w < w1; ++w)
+          for (uint32_t b = bits[w]; b; b &= b - 1u) key[pos++] = lo + 32 * w + (__ffs(b) - 1);
+        __syncthreads();
+        add(done, n);
+        done += n;
+      }
+    } while (done < c && (lo = block_min_nt<NT>(next, sel)) < INT32_MAX);
   }
-  // entries -> their bag rows (rows of dx), in place (each thread its own keys)
-  {
-    int32_t tmp[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int i = tid + u * NT;
-      tmp[u] = i < c ? a.owner[key[i]] % a.M : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < PER; ++u)
-      if (tid + u * NT < c) key[tid + u * NT] = tmp[u];
-  }
-  __syncthreads();
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int k0 = q; k0 < c; k0 += 8 * NG) {
-    float4 v[8];  // all in flight; entries past the end add zero
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = k0 + u * NG;
-      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (k < c && col) v[u] = dx4<T>(a, key[k], xc);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) add4(acc, v[u]);
-  }
-#pragma unroll
-  for (int o = G; o < 64; o <<= 1) {
-    acc.x += __shfl_xor(acc.x, o, 64);
-    acc.y += __shfl_xor(acc.y, o, 64);
-    acc.z += __shfl_xor(acc.z, o, 64);
-    acc.w += __shfl_xor(acc.w, o, 64);
-  }
-  __syncthreads();  // key[] is reused for the partial rows
-  float* part = reinterpret_cast<float*>(key);  // [NT / 64][4 G] floats
-  if (col && (tid & 63) < G) *reinterpret_cast<float4*>(part + (tid >> 6) * 4 * G + 4 * cq) = acc;
-  __syncthreads();
-  if (tid < a.dim) {
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) sum += part[w * 4 * G + tid];
-    a.grad[(int64_t)g * a.dim + tid] = sum;
-  }
+  store_row_sum<G>(a, g, acc, reinterpret_cast<float*>(key));
 }
 
-// Bitonic sort (ascending) of one value per lane across a wave.
-__device__ __forceinline__ int32_t wave_sort(int32_t v, int lane) {
+// Bitonic sort (ascending) of 64 R values across a wave, value 64 r + lane in
+// v[r] of that lane.
+template <int R>
+__device__ __forceinline__ void wave_sort(int32_t (&v)[R], int lane) {
 #pragma unroll
-  for (int k = 2; k <= 64; k <<= 1)
+  for (int k = 2; k <= 64 * R; k <<= 1)
 #pragma unroll
     for (int j = k >> 1; j > 0; j >>= 1) {
-      const int32_t o = __shfl_xor(v, j, 64);
-      const bool lower = (lane & j) == 0, up = (lane & k) == 0;
-      v = (lower == up) ? min(v, o) : max(v, o);
+      if (j >= 64) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int p = r | (j >> 6);
+          if (r & (j >> 6)) continue;
+          const int32_t lo = min(v[r], v[p]), hi = max(v[r], v[p]);
+          const bool up = ((64 * r) & k) == 0;
+          v[r] = up ? lo : hi;
+          v[p] = up ? hi : lo;
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int32_t o = __shfl_xor(v[r], j, 64);
+          const bool lower = (lane & j) == 0, up = ((64 * r + lane) & k) == 0;
+          v[r] = (lower == up) ? min(v[r], o) : max(v[r], o);
+        }
+      }
     }
-  return v;
 }
 
 __device__ __forceinline__ void sort2(int32_t& x, int32_t& y) {
@@ -705,13 +755,13 @@ __device__ __forceinline__ void bag_rows_light(const EmbedBwdArgs& a, int64_t r0
 // sorted across the lanes, lane group q adding entries q, q + 64/G, ... in
 // order (eight loads in flight), the groups combined by a fixed butterfly.
 template <typename T, int G>
-__device__ __forceinline__ void bag_row_mid(const EmbedBwdArgs& a, int32_t g) {
+__device__ __forceinline__ void bag_row_mid(const EmbedBwdArgs& a, int32_t g, int c, int s0) {
   constexpr int NGW = 64 / G;
   const int lane = threadIdx.x & 63;
   const int q = lane / G, cq = lane % G;
   const bool col = 4 * cq < a.dim;
-  const int c = a.count[g], s0 = a.start[g];
-  const int m = wave_sort(lane < c ? a.bucket[s0 + lane] : INT32_MAX, lane);
+  int32_t m[1] = {lane < c ? a.bucket[s0 + lane] : INT32_MAX};
+  wave_sort<1>(m, lane);
   const int64_t xc = a.n_dense + (int64_t)(g / a.rows) * a.dim + 4 * cq;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int k0 = 0; k0 < c; k0 += 8 * NGW) {
@@ -719,7 +769,7 @@ __device__ __forceinline__ void bag_row_mid(const EmbedBwdArgs& a, int32_t g) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int k = k0 + u * NGW + q;
-      const int mk = __shfl(m, k & 63, 64);
+      const int mk = __shfl(m[0], k & 63, 64);
       v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (k < c && col) v[u] = dx4<T>(a, mk, xc);
     }
@@ -736,10 +786,52 @@ __device__ __forceinline__ void bag_row_mid(const EmbedBwdArgs& a, int32_t g) {
   if (col && q == 0) *reinterpret_cast<float4*>(a.grad + (int64_t)g * a.dim + 4 * cq) = acc;
 }
 
+// The bag rows of a bucket of at most 64 R entries in order.
+template <int R>
+__device__ __forceinline__ void sort_bucket(const int32_t* bucket, int c, int32_t* key) {
+  const int lane = threadIdx.x & 63;
+  int32_t m[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) m[r] = 64 * r + lane < c ? bucket[64 * r + lane] : INT32_MAX;
+  wave_sort<R>(m, lane);
+#pragma unroll
+  for (int r = 0; r < R; ++r) key[64 * r + lane] = m[r];
+}
+
+// A row of kSmallBucket + 1..kWaveBucket entries by one wave.  key: kWaveBucket
+// words of LDS of its own (a wave's stores and loads are served in order).
+template <typename T, int G>
+__device__ __forceinline__ void bag_row_wave(const EmbedBwdArgs& a, int32_t g, int c, int s0, int32_t* key) {
+  constexpr int NGW = 64 / G;
+  static_assert(kWaveBucket == 512, "the longest sort");
+  const int lane = threadIdx.x & 63;
+  const int q = lane / G, cq = lane % G;
+  const bool col = 4 * cq < a.dim;
+  const int32_t* bucket = a.bucket + s0;
+  if (c <= 128)
+    sort_bucket<2>(bucket, c, key);
+  else if (c <= 256)
+    sort_bucket<4>(bucket, c, key);
+  else
+    sort_bucket<8>(bucket, c, key);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const int64_t xc = a.n_dense + (int64_t)(g / a.rows) * a.dim + 4 * cq;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  add_bag_rows<T, NGW>(a, key, 0, c, q, col, xc, acc);
+#pragma unroll
+  for (int o = G; o < 64; o <<= 1) {
+    acc.x += __shfl_xor(acc.x, o, 64);
+    acc.y += __shfl_xor(acc.y, o, 64);
+    acc.z += __shfl_xor(acc.z, o, 64);
+    acc.w += __shfl_xor(acc.w, o, 64);
+  }
+  if (col && q == 0) *reinterpret_cast<float4*>(a.grad + (int64_t)g * a.dim + 4 * cq) = acc;
+}
+
 // Every row of the gradient, in one launch of three kinds of workgroups: the
-// first nlist take the rows of more than kSmallBucket entries (a serial chain
-// of sorts and sums, so they start first), then nmid the rows of 5..64
-// entries, a wave each, then nlight all the others, 64 consecutive rows per
+// first nlist take the rows of more than wave_bucket() entries (a serial chain
+// of sorts and sums, so they start first), then nmid the rows of 5 entries and
+// more up to that, a wave each, then nlight all the others, 64 consecutive rows per
 // wave: the chains of dependent loads of the rows with entries run beside the
 // stores of the zeros (665 MB of gradient for 26 tables of 100000 x 64: 145 to
 // 165 us, against 220 for the same work as four launches).  At that shape the
@@ -753,15 +845,21 @@ __global__ __launch_bounds__(kSumThreads, 8) void erase_bags_bwd_sums(EmbedBwdAr
   __shared__ uint32_t bits[kBitWords];
   const uint32_t b = blockIdx.x, wave = threadIdx.x >> 6;
   if (b < nlist) {
-    const int nl = a.nlarge[0];
+    const int nl = a.nlarge[1];
     for (int i = (int)b; i < nl; i += (int)nlist) {
       bag_row_large<T, G>(a, a.large[i], key, bits, sel);
       __syncthreads();  // the next row reuses the arrays
     }
   } else if (b < nlist + nmid) {
     const uint32_t n = (uint32_t)a.nlarge[3];
-    for (uint32_t i = (b - nlist) * (kSumThreads / 64) + wave; i < n; i += nmid * (kSumThreads / 64))
-      bag_row_mid<T, G>(a, a.mid[i]);
+    for (uint32_t i = (b - nlist) * (kSumThreads / 64) + wave; i < n; i += nmid * (kSumThreads / 64)) {
+      const int32_t g = a.mid[i];
+      const int c = a.count[g], s0 = a.start[g];  // the same in every lane
+      if (c <= kSmallBucket)
+        bag_row_mid<T, G>(a, g, c, s0);
+      else
+        bag_row_wave<T, G>(a, g, c, s0, key + wave * kWaveBucket);
+    }
   } else {
     const int64_t r0 = ((int64_t)xcd_block(b - nlist - nmid, nlight) * (kSumThreads / 64) + wave) * 64;
     if (r0 < a.trows) bag_rows_light<T, G>(a, r0);

@@ -248,8 +248,8 @@ hipError_t launch_embed_bags(int bf16, const EmbedArgs& a, hipStream_t s);
 
 // Backward of the embedding-bag stage: grad[t][r][d] = sum over the entries
 // i of table t's bags with indices[i] == r of dx[bag m][n_dense + t dim + d],
-// entries in increasing order; rows no entry selects are zero.  Bags must
-// not overlap.  Scratch (all int32): count, start [trows], bucket, gid, owner,
+// in a fixed association over entries in increasing order, whatever the
+// scheduling; rows no entry selects are zero.  Bags must not overlap.  Scratch (all int32): count, start [trows], bucket, gid, owner,
 // slot [nnz], large [nnz / 65 + 1], mid [nnz / 5], nlarge [4] (8-byte aligned).
 // Invalid offsets or ids set status[0] = 1 (nullable).
 struct EmbedBwdArgs {

@@ -45,3 +45,38 @@ def test_bucket_sizes(dtype, dim, rows):
     assert status == 0
     ref = oracle.embed_bags_backward(offsets, np.concatenate(ids), dx.astype(np.float64), 1, rows, dim)
     assert np.array_equal(g, ref.astype(np.float32))
+
+
+def _exact(name, counts, M, dim, dtype):
+    """One table whose row r has counts[r] entries, shuffled over M bags; whole
+    numbers, so every sum is exact."""
+    print(f"[bags] {name}", flush=True)
+    rng = np.random.Generator(np.random.PCG64(len(counts) + dim))
+    ids = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
+    rng.shuffle(ids)
+    cut = np.sort(rng.integers(0, ids.size + 1, size=M - 1))
+    offsets = np.concatenate([[0], cut, [ids.size]]).astype(np.int64)[None]
+    dx = rng.integers(-8, 9, size=(M, (1 + dim + 7) // 8 * 8)).astype(np.float32)
+    g, status = _run_bags_bwd(offsets, ids, dx, 1, len(counts), dim, dtype)
+    assert status == 0
+    ref = oracle.embed_bags_backward(offsets, ids, dx.astype(np.float64), 1, len(counts), dim)
+    assert np.array_equal(g, ref.astype(np.float32))
+
+
+@pytest.mark.parametrize("dtype,dim", [("bf16", 64), ("f32", 4), ("f32", 16), ("bf16", 256)])
+@pytest.mark.parametrize("n", [512, 513])
+def test_many_rows_beyond_a_wave(n, dtype, dim):
+    """As many rows of more than 64 entries as take a workgroup each, and one
+    more, beyond which a wave sums those of up to 512."""
+    sizes = [65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1024]
+    counts = np.concatenate([np.resize(sizes, n), [0, 1, 4, 5, 63, 64, 0]])
+    _exact(f"{n} rows, {dtype}, dim {dim}", counts, 777, dim, dtype)
+
+
+@pytest.mark.parametrize("dtype,dim", [("bf16", 16), ("f32", 64)])
+def test_huge_rows(dtype, dim):
+    """Rows of 16384 entries and more: a bitmap after another, dense ranges (the
+    row of 90000 in one half of the entries) and sparse ones."""
+    counts = [16384, 16385, 90000, 40000, 3, 0, 700, 20000]
+    _exact(f"huge, {dtype}, dim {dim}", counts, 3001, dim, dtype)
+    _exact(f"dense, {dtype}, dim {dim}", [70000], 5, dim, dtype)
