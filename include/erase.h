@@ -265,6 +265,12 @@ typedef struct {
 ERASE_API erase_status erase_set_timing(erase_ctx* ctx, int32_t enable);
 ERASE_API erase_status erase_read_timing(erase_ctx* ctx, erase_kernel_time* out, int32_t cap, int32_t* n);
 
+/* 1 when `stream` (of the current device) has no unfinished work and is not
+ * being captured, else 0: whether a caller that produced a step's inputs there
+ * needs an event between it and the forward stream.  May be called while this
+ * or another thread captures other streams, in any capture mode. */
+ERASE_API int32_t erase_stream_idle(void* stream);
+
 /* Host dispatch of the ERASE schedules (Section 2.2: blocking dispatch on
  * the main thread vs non-blocking dispatch on a thread pool).
  *   ERASE_DISPATCH_CALLER (default): erase_step() enqueues every launch and

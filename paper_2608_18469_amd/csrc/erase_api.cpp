@@ -1900,6 +1900,20 @@ erase_status erase_read_timing(erase_ctx* ctx, erase_kernel_time* out, int32_t c
   return ERASE_OK;
 }
 
+int32_t erase_stream_idle(void* stream) {
+  // a query is refused, and ends the capture, while a stream is captured in a
+  // mode that covers this thread, unless the thread is in the relaxed mode
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return 0;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  const bool idle = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+                    hipStreamQuery(s) == hipSuccess;
+  if (!idle) (void)hipGetLastError();  // not ready is no error
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return idle ? 1 : 0;
+}
+
 erase_status erase_set_dispatch(erase_ctx* ctx, int32_t mode) {
   Ctx* c = as_ctx(ctx);
   if (!c) return ERASE_ERR_INVALID_ARG;

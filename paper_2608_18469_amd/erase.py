@@ -79,6 +79,7 @@ SIGNATURES = {
     "erase_set_step": (c_int32, [c_void_p, c_int64]),
     "erase_refresh_weights": (c_int32, [c_void_p]),
     "erase_set_timing": (c_int32, [c_void_p, c_int32]),
+    "erase_stream_idle": (c_int32, [c_void_p]),
     "erase_set_dispatch": (c_int32, [c_void_p, c_int32]),
     "erase_embed_bags": (c_int32, [POINTER(BagConfig), c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,
                                    c_void_p]),
@@ -353,10 +354,9 @@ class Trainer:
         """Enqueue one step on the library's streams (non-blocking)."""
         if wait_current:
             # an idle stream has nothing to wait for (a wait costs the host
-            # about 16 us, the query under 1 us); a capturing one may not be
-            # queried
+            # about 16 us, the query under 1 us)
             cur = self.torch.cuda.current_stream(self.dev)
-            if self.torch.cuda.is_current_stream_capturing() or not cur.query():
+            if not lib().erase_stream_idle(c_void_p(cur.cuda_stream)):
                 self.sf.wait_stream(cur)
         sched = SCHEDULES[schedule] if isinstance(schedule, str) else int(schedule)
         out = self.losses if losses is None else losses
