@@ -19,7 +19,8 @@ namespace erase {
 // a multiple of the k-step (64 bf16 / 32 fp32 elements).  Forward / input
 // gradient: A holds at least roundup(M, 128) rows and B roundup(N, 128) rows
 // of at least K elements.  Weight gradient: A and B hold at least K rows of
-// at least roundup(M, 128) and roundup(N, 128) elements.  Every element
+// at least roundup(M, 128) and roundup(N, 128) elements.  (The 256x256 and
+// 128x128 tiles read rows and chunks past M, N and roundup(., 64) clamped.)  Every element
 // outside the logical block is zero.  M and N are the logical output extents
 // the epilogue stores.
 struct GemmDesc {

@@ -10,8 +10,8 @@
 //  * a 64-wide k-step is four phases, one per 128 x 128 quadrant of the tile:
 //    the quadrant's fragments are read, one half of an operand of a later
 //    k-step is issued, then the 16 MFMAs of each wave run.  A half is free as
-//    soon as its quadrants are done, so a whole k-step (64 KB per compute
-//    unit) is always in flight and no wait ever drains the loads: the waits
+//    soon as its quadrants are done, so up to the tile's end a whole k-step (64 KB
+//    per compute unit) is in flight and no wait drains the loads: the waits
 //    count the newest halves off;
 //  * the two rows of waves run half a phase apart (one barrier more at the
 //    start of the second): while one row's MFMAs run, the other's LDS reads
@@ -44,22 +44,17 @@ namespace erase {
 namespace wide {
 constexpr int BK = 64, NW = 8, NT = 64 * NW;
 
-// HA, HB: rows (forward, input gradient: "NT", both operands contiguous along
-// the contraction) or columns (weight gradient: k-major, both operands
-// row-major over the contraction) of one half of the A and B tile.  A stage
-// is A0 | A1 | B0 | B1; two stages.  NT rows are 128 bytes with 16-byte chunk
-// c at c ^ (3 bits of the row); k-major rows hold HA (HB) elements with the
-// chunks permuted by kperm: fragment reads are conflict-free both ways.
-template <int HA, int HB>
-struct Geo {
-  static constexpr int BM = 2 * HA, BN = 2 * HB;
-  static constexpr int AH = HA * BK * 2, BH = HB * BK * 2;  // bytes of a half
-  static constexpr int STAGE = 2 * (AH + BH);
-  static constexpr int BYTES = 2 * STAGE;
-  static constexpr int LA = AH / 1024 / NW, LB = BH / 1024 / NW;  // 1 KB loads per wave and half
-  static constexpr int TA = HA / 32, TB = HB / 64;                // a wave's 16-wide blocks of a half
-  static_assert(LA >= 1 && LB >= 1, "at least one load per wave and half");
-};
+// A half of an operand's tile is H rows (forward, input gradient: "NT", both
+// operands contiguous along the contraction) or columns (weight gradient:
+// k-major, both operands row-major over the contraction).  A stage is
+// A0 | A1 | B0 | B1; two stages.  NT rows are 128 bytes with 16-byte chunk c at
+// c ^ (3 bits of the row); k-major rows hold H elements with the chunks
+// permuted by kperm16: fragment reads are conflict-free both ways.
+constexpr int H = 128, BM = 2 * H, BN = 2 * H;
+constexpr int HB = H * BK * 2;        // bytes of a half
+constexpr int STAGE = 4 * HB, BYTES = 2 * STAGE;
+constexpr int LD = HB / 1024 / NW;    // 1 KB loads per wave and half
+constexpr int TA = H / 32, TB = H / 64;  // a wave's 16-wide blocks of a half
 
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -72,103 +67,71 @@ __device__ __forceinline__ void bar() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// permutation of the 16-byte chunks of a k-major row (8 or 16 chunks)
-template <int CP>
-__device__ __forceinline__ int kperm(int r) {
-  return 2 * ((r >> 1) & 1) + 4 * ((r >> 3) & 1) + (CP == 16 ? 8 * (r & 1) : 0);
-}
+// permutation of the 16 chunks of 16 bytes of a k-major row
+__device__ __forceinline__ int kperm16(int r) { return 2 * ((r >> 1) & 1) + 4 * ((r >> 3) & 1) + 8 * (r & 1); }
 
-// One workgroup's part of a GEMM: output tiles t0, t0 + G, ... < ntiles, as
-// one stream of k-steps (the loads run on into the next tile).
+// Output tile t of a GEMM's ntiles.
 //
-// Order of a wave's loads in the stream, two per half (LA, LB): k-step p + 1's
-// B1 in phase 0 of p and A1 in phase 1, p + 2's A0 in phase 2 and B0 in phase
-// 3.  A half is overwritten two phases or more after its last read (A0, B0
-// are read in phase 0 of the k-step that used the stage, B1 in 1, A1 in 2):
-// both wave rows are then past the MFMAs that waited for those reads.  A half
-// read in phase q has been waited for by every wave in phase q - 1 or before,
-// in front of a barrier: the waits leave the four newest halves in flight.
-template <int HA, int HB, bool KM, class Epi>
-__device__ __forceinline__ void run(const GemmDesc& g, int t0, int G, int ntiles, bool want_rows, char* smem,
-                                    Epi&& epi) {
-  using X = Geo<HA, HB>;
-  constexpr int TA = X::TA, TB = X::TB, LA = X::LA, LB = X::LB;
-  static_assert(KM || TB == 2, "NT tiles: 128 weight rows per half");
-  if (t0 >= ntiles) return;
+// Order of a wave's loads, LD per half: k-step p + 1's B1 in phase 0 of p and
+// A1 in phase 1, p + 2's A0 in phase 2 and B0 in phase 3.  A half is
+// overwritten two phases or more after its last read (A0, B0 are read in phase
+// 0 of the k-step that used the stage, B1 in 1, A1 in 2): both wave rows are
+// then past the MFMAs that waited for those reads.  A half read in phase q has
+// been waited for by every wave in phase q - 1 or before, in front of a
+// barrier: the waits leave the four newest halves in flight, fewer at the end.
+template <bool KM, class Epi>
+__device__ __forceinline__ void run(const GemmDesc& g, int t, int ntiles, bool want_rows, char* smem, Epi&& epi) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wv >> 2, wn = wv & 3;
   const int fr = lane & 15, fg = lane >> 4;
-  const int gm = (g.M + X::BM - 1) / X::BM, gn = (g.N + X::BN - 1) / X::BN, grp = g.group;
-  const int M = g.M, N = g.N, K = g.K, kps = g.kps;
+  const int M = g.M, N = g.N;
   const int64_t lda = g.lda, ldb = g.ldb;
-  const char* gA = static_cast<const char*>(g.A);
-  const char* gB = static_cast<const char*>(g.B);
+  const TileIdx ti = tile_from(xcd_linear(t, ntiles), (M + BM - 1) / BM, (N + BN - 1) / BN, g.group);
+  const int m0 = ti.m * BM, n0 = ti.n * BN, kb = ti.z * g.kps;
+  const int nk = (min(g.K, kb + g.kps) - kb + BK - 1) / BK;
   const uint32_t lbase = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)smem);
 
-  // ---- loads: cursor h walks the stream of (tile, k-step) for half h of
-  // both operands
-  struct Cur {
-    const char* a;
-    const char* b;
-    uint32_t oa[LA], ob[LB];
-    int k, t;  // k-steps left in the tile; tile
-    bool live;
-  };
-  Cur cu[2];
-  auto aim = [&](Cur& c, int h) {  // start of tile c.t
-    const TileIdx ti = tile_from(xcd_linear(c.t, ntiles), gm, gn, grp);
-    const int m0 = ti.m * X::BM, n0 = ti.n * X::BN, kb = ti.z * kps;
-    c.k = (min(K, kb + kps) - kb + BK - 1) / BK;
-    if constexpr (KM) {
-      constexpr int CA = HA / 8, CB = HB / 8;  // chunks per k-major row
-      c.a = gA + ((int64_t)kb * lda + m0) * 2;
-      c.b = gB + ((int64_t)kb * ldb + n0) * 2;
-      const int ml = ((M + 63) & ~63) - 8 - m0, nl = ((N + 63) & ~63) - 8 - n0;  // last whole chunk
+  // ---- loads: of half h, of the k-step that pa[h], pb[h] point at
+  const char* pa[2];
+  const char* pb[2];
+  uint32_t oa[2][LD], ob[2][LD];
+  if constexpr (KM) {
+    constexpr int CH = H / 8;  // chunks per k-major row
+    pa[0] = pa[1] = static_cast<const char*>(g.A) + ((int64_t)kb * lda + m0) * 2;
+    pb[0] = pb[1] = static_cast<const char*>(g.B) + ((int64_t)kb * ldb + n0) * 2;
+    const int ml = ((M + 63) & ~63) - 8 - m0, nl = ((N + 63) & ~63) - 8 - n0;  // last whole chunk
 #pragma unroll
-      for (int u = 0; u < LA; ++u) {
-        const int r = (wv * LA + u) * (64 / CA) + lane / CA, ch = (lane % CA) ^ kperm<CA>(r);
-        c.oa[u] = (uint32_t)((int64_t)r * lda + min(h * HA + ch * 8, ml)) * 2;
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int u = 0; u < LD; ++u) {
+        const int r = (wv * LD + u) * (64 / CH) + lane / CH, ch = (lane % CH) ^ kperm16(r);
+        oa[h][u] = (uint32_t)((int64_t)r * lda + min(h * H + ch * 8, ml)) * 2;
+        ob[h][u] = (uint32_t)((int64_t)r * ldb + min(h * H + ch * 8, nl)) * 2;
       }
+  } else {
+    pa[0] = pa[1] = static_cast<const char*>(g.A) + ((int64_t)m0 * lda + kb) * 2;
+    pb[0] = pb[1] = static_cast<const char*>(g.B) + ((int64_t)n0 * ldb + kb) * 2;
 #pragma unroll
-      for (int u = 0; u < LB; ++u) {
-        const int r = (wv * LB + u) * (64 / CB) + lane / CB, ch = (lane % CB) ^ kperm<CB>(r);
-        c.ob[u] = (uint32_t)((int64_t)r * ldb + min(h * HB + ch * 8, nl)) * 2;
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int u = 0; u < LD; ++u) {
+        const int r = (wv * LD + u) * 8 + (lane >> 3);
+        oa[h][u] = (uint32_t)(min(h * H + r, M - 1 - m0) * (int)lda + ((lane & 7) ^ (r & 7)) * 8) * 2;
+        ob[h][u] = (uint32_t)(min(h * H + r, N - 1 - n0) * (int)ldb + ((lane & 7) ^ ((r & 3) | ((r >> 1) & 4))) * 8) * 2;
       }
-    } else {
-      c.a = gA + ((int64_t)m0 * lda + kb) * 2;
-      c.b = gB + ((int64_t)n0 * ldb + kb) * 2;
+  }
+  auto load_a = [&](int h, int st) {
 #pragma unroll
-      for (int u = 0; u < LA; ++u) {
-        const int r = (wv * LA + u) * 8 + (lane >> 3), ch = (lane & 7) ^ (r & 7);
-        c.oa[u] = (uint32_t)(min(h * HA + r, M - 1 - m0) * (int)lda + ch * 8) * 2;
-      }
-#pragma unroll
-      for (int u = 0; u < LB; ++u) {
-        const int r = (wv * LB + u) * 8 + (lane >> 3), ch = (lane & 7) ^ ((r & 3) | ((r >> 1) & 4));
-        c.ob[u] = (uint32_t)(min(h * HB + r, N - 1 - n0) * (int)ldb + ch * 8) * 2;
-      }
-    }
+    for (int u = 0; u < LD; ++u) lds_dma16s(pa[h], oa[h][u], lbase + st * STAGE + h * HB + (wv * LD + u) * 1024);
   };
-  auto load_a = [&](const Cur& c, int h, int st) {
+  auto load_b = [&](int h, int st) {
 #pragma unroll
-    for (int u = 0; u < LA; ++u)
-      lds_dma16s(c.a, c.oa[u], lbase + st * X::STAGE + h * X::AH + (wv * LA + u) * 1024);
+    for (int u = 0; u < LD; ++u) lds_dma16s(pb[h], ob[h][u], lbase + st * STAGE + (2 + h) * HB + (wv * LD + u) * 1024);
   };
-  auto load_b = [&](const Cur& c, int h, int st) {
-#pragma unroll
-    for (int u = 0; u < LB; ++u)
-      lds_dma16s(c.b, c.ob[u], lbase + st * X::STAGE + 2 * X::AH + h * X::BH + (wv * LB + u) * 1024);
-  };
-  auto next = [&](Cur& c, int h) {
-    if (--c.k > 0) {
-      c.a += KM ? BK * lda * 2 : BK * 2;
-      c.b += KM ? BK * ldb * 2 : BK * 2;
-    } else {
-      c.t += G;
-      c.live = c.t < ntiles;
-      if (c.live) aim(c, h);
-    }
+  auto next = [&](int h) {
+    pa[h] += KM ? BK * lda * 2 : BK * 2;
+    pb[h] += KM ? BK * ldb * 2 : BK * 2;
   };
 
   // ---- fragments
@@ -179,34 +142,32 @@ __device__ __forceinline__ void run(const GemmDesc& g, int t0, int G, int ntiles
   int ka[TA], kb_[TB];
 #pragma unroll
   for (int i = 0; i < TA; ++i)
-    ka[i] = KM ? (trow * HA + (((((wm * HA / 2) + i * 16) >> 3) + (tc >> 1)) ^ kperm<HA / 8>(trow)) * 8 + (tc & 1) * 4) * 2
-               : 0;
+    ka[i] = KM ? (trow * H + (((((wm * H / 2) + i * 16) >> 3) + (tc >> 1)) ^ kperm16(trow)) * 8 + (tc & 1) * 4) * 2 : 0;
 #pragma unroll
   for (int j = 0; j < TB; ++j)
-    kb_[j] = KM ? (trow * HB + (((((wn * HB / 4) + j * 16) >> 3) + (tc >> 1)) ^ kperm<HB / 8>(trow)) * 8 + (tc & 1) * 4) * 2
-                : 0;
+    kb_[j] = KM ? (trow * H + (((((wn * H / 4) + j * 16) >> 3) + (tc >> 1)) ^ kperm16(trow)) * 8 + (tc & 1) * 4) * 2 : 0;
 
   u32x4_t fa[TA][2], fb[2][TB][2];
   auto read_a = [&](int h, int st) {
-    const char* p = smem + st * X::STAGE + h * X::AH;
+    const char* p = smem + st * STAGE + h * HB;
 #pragma unroll
     for (int kh = 0; kh < 2; ++kh)
 #pragma unroll
       for (int i = 0; i < TA; ++i) {
         if constexpr (KM)
-          fa[i][kh] = tr_frag(reinterpret_cast<const uint16_t*>(p + ka[i] + kh * 32 * HA * 2), HA);
+          fa[i][kh] = tr_frag(reinterpret_cast<const uint16_t*>(p + ka[i] + kh * 32 * H * 2), H);
         else
-          fa[i][kh] = *reinterpret_cast<const u32x4_t*>(p + (wm * (HA / 2) + i * 16) * 128 + (fa0 ^ (kh * 64)));
+          fa[i][kh] = *reinterpret_cast<const u32x4_t*>(p + (wm * (H / 2) + i * 16) * 128 + (fa0 ^ (kh * 64)));
       }
   };
   auto read_b = [&](int h, int st) {
-    const char* p = smem + st * X::STAGE + 2 * X::AH + h * X::BH;
+    const char* p = smem + st * STAGE + (2 + h) * HB;
 #pragma unroll
     for (int kh = 0; kh < 2; ++kh)
 #pragma unroll
       for (int j = 0; j < TB; ++j) {
         if constexpr (KM)
-          fb[h][j][kh] = tr_frag(reinterpret_cast<const uint16_t*>(p + kb_[j] + kh * 32 * HB * 2), HB);
+          fb[h][j][kh] = tr_frag(reinterpret_cast<const uint16_t*>(p + kb_[j] + kh * 32 * H * 2), H);
         else
           fb[h][j][kh] = *reinterpret_cast<const u32x4_t*>(p + (wn * 32 + 4 * j) * 128 + (fb0o ^ (kh * 64)));
       }
@@ -214,19 +175,17 @@ __device__ __forceinline__ void run(const GemmDesc& g, int t0, int G, int ntiles
 
   f32x4_t acc[2][2][TA][TB];
   f32x4_t accr[2];
-  auto clear = [&] {
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      accr[a] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int a = 0; a < 2; ++a) {
+    accr[a] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int i = 0; i < TA; ++i)
+      for (int i = 0; i < TA; ++i)
 #pragma unroll
-          for (int j = 0; j < TB; ++j) acc[a][b][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  bool rows = false;
+        for (int j = 0; j < TB; ++j) acc[a][b][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  const bool rows = want_rows && ti.n == 0;
   auto mma = [&](auto ac, auto bc) {
     constexpr int a = decltype(ac)::value, b = decltype(bc)::value;
     __builtin_amdgcn_s_setprio(1);
@@ -260,87 +219,74 @@ __device__ __forceinline__ void run(const GemmDesc& g, int t0, int G, int ntiles
   constexpr std::integral_constant<int, 0> c0{};
   constexpr std::integral_constant<int, 1> c1{};
 
-  // ---- stream
-  cu[0].t = cu[1].t = t0;
-  cu[0].live = cu[1].live = true;
-  aim(cu[0], 0);
-  aim(cu[1], 1);
-  load_a(cu[0], 0, 0);
-  load_b(cu[0], 0, 0);
-  next(cu[0], 0);
-  load_b(cu[1], 1, 0);
-  load_a(cu[1], 1, 0);
-  next(cu[1], 1);
-  if (cu[0].live) {
-    load_a(cu[0], 0, 1);
-    load_b(cu[0], 0, 1);
-    next(cu[0], 0);
-    wait_vm<2 * LA + 2 * LB>();
+  load_a(0, 0);
+  load_b(0, 0);
+  next(0);
+  load_b(1, 0);
+  load_a(1, 0);
+  next(1);
+  if (nk > 1) {
+    load_a(0, 1);
+    load_b(0, 1);
+    next(0);
+    wait_vm<4 * LD>();
   } else {
-    wait_vm<LA + LB>();
+    wait_vm<2 * LD>();
   }
   bar();
   if (wm == 1) bar();  // the two wave rows run half a phase apart
 
   int st = 0;
-  for (int t = t0; t < ntiles; t += G) {
-    const TileIdx ti = tile_from(xcd_linear(t, ntiles), gm, gn, grp);
-    const int kb = ti.z * kps;
-    int k = (min(K, kb + kps) - kb + BK - 1) / BK;
-    rows = want_rows && ti.n == 0;
-    clear();
-    for (; k > 0; --k, st ^= 1) {
-      const bool more = cu[1].live;  // a next stream position exists
-      // phase 0: A0 x B0; waits for B1
-      read_b(0, st);
-      read_a(0, st);
-      if (more) {
-        load_b(cu[1], 1, st ^ 1);
-        wait_vm<2 * LA + 2 * LB>();
-      } else {
-        wait_vm<LA>();
-      }
-      bar();
-      wait_lds();
-      mma(c0, c0);
-      rowsum(0);
-      bar();
-      // phase 1: A0 x B1; waits for A1
-      read_b(1, st);
-      if (more) {
-        load_a(cu[1], 1, st ^ 1);
-        next(cu[1], 1);
-        wait_vm<2 * LA + 2 * LB>();
-      } else {
-        wait_vm<0>();
-      }
-      bar();
-      wait_lds();
-      mma(c0, c1);
-      bar();
-      // phase 2: A1 x B1
-      const bool more2 = cu[0].live;
-      read_a(1, st);
-      if (more2) load_a(cu[0], 0, st);
-      bar();
-      wait_lds();
-      mma(c1, c1);
-      rowsum(1);
-      bar();
-      // phase 3: A1 x B0 (in registers); waits for the next k-step's A0, B0
-      if (more2) {
-        load_b(cu[0], 0, st);
-        next(cu[0], 0);
-        wait_vm<2 * LA + 2 * LB>();
-      } else if (more) {
-        wait_vm<LA + LB>();
-      }
-      bar();
-      mma(c1, c0);
-      bar();
+  for (int k = nk; k > 0; --k, st ^= 1) {
+    const bool more = k > 1, more2 = k > 2;  // a next k-step, and one after it
+    // phase 0: A0 x B0; waits for B1
+    read_b(0, st);
+    read_a(0, st);
+    if (more) {
+      load_b(1, st ^ 1);
+      wait_vm<4 * LD>();
+    } else {
+      wait_vm<LD>();
     }
-    epi(acc, accr, ti, rows, wm, wn, fr, fg);
+    bar();
+    wait_lds();
+    mma(c0, c0);
+    rowsum(0);
+    bar();
+    // phase 1: A0 x B1; waits for A1
+    read_b(1, st);
+    if (more) {
+      load_a(1, st ^ 1);
+      next(1);
+      wait_vm<4 * LD>();
+    } else {
+      wait_vm<0>();
+    }
+    bar();
+    wait_lds();
+    mma(c0, c1);
+    bar();
+    // phase 2: A1 x B1
+    read_a(1, st);
+    if (more2) load_a(0, st);
+    bar();
+    wait_lds();
+    mma(c1, c1);
+    rowsum(1);
+    bar();
+    // phase 3: A1 x B0 (in registers); waits for the next k-step's A0, B0
+    if (more2) {
+      load_b(0, st);
+      next(0);
+      wait_vm<4 * LD>();
+    } else if (more) {
+      wait_vm<2 * LD>();
+    }
+    bar();
+    mma(c1, c0);
+    bar();
   }
+  epi(acc, accr, ti, rows, wm, wn, fr, fg);
   if (wm == 0) bar();
 }
 
@@ -467,14 +413,13 @@ __device__ __forceinline__ void st_part(const EpiParams& e, const float v[8], in
 
 // Epilogue of an NT tile: a lane holds eight consecutive columns of TA rows
 // per quadrant.  The operands of one quadrant are loaded together.
-template <int HA, int HB, int KIND, class A>
+template <int KIND, class A>
 __device__ __forceinline__ void epi_nt(const EpiParams& e, const A& acc, int M, int N, const TileIdx& ti, int wm,
                                        int wn, int fr, int fg) {
-  constexpr int TA = HA / 32;
-  const int m0 = ti.m * 2 * HA, n0 = ti.n * 2 * HB;
+  const int m0 = ti.m * BM, n0 = ti.n * BN;
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
-    const int n = n0 + b * HB + wn * 32 + fg * 8;
+    const int n = n0 + b * H + wn * 32 + fg * 8;
     if (n >= N) continue;
     float bias[8];
     epi_bias<KIND>(e, n, N, bias);
@@ -483,18 +428,15 @@ __device__ __forceinline__ void epi_nt(const EpiParams& e, const A& acc, int M, 
       u32x4_t r0[TA], r1[TA];
 #pragma unroll
       for (int i = 0; i < TA; ++i)
-        epi_load<KIND>(e, min(m0 + a * HA + wm * (HA / 2) + i * 16 + fr, M - 1), n, r0[i], r1[i]);
+        epi_load<KIND>(e, min(m0 + a * H + wm * (H / 2) + i * 16 + fr, M - 1), n, r0[i], r1[i]);
 #pragma unroll
       for (int i = 0; i < TA; ++i) {
-        const int m = m0 + a * HA + wm * (HA / 2) + i * 16 + fr;
+        const int m = m0 + a * H + wm * (H / 2) + i * 16 + fr;
         if (m >= M) continue;
         float v[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = acc[a][b][i][k >> 2][k & 3];
-        if constexpr (KIND == GK_DGRAD_PART)
-          st_part(e, v, m, n, ti.z);
-        else
-          epi_store<KIND>(e, v, bias, m, n, N, r0[i], r1[i]);
+        epi_store<KIND>(e, v, bias, m, n, N, r0[i], r1[i]);
       }
     }
   }
@@ -502,24 +444,23 @@ __device__ __forceinline__ void epi_nt(const EpiParams& e, const A& acc, int M, 
 
 // Weight-gradient slice: fp32 partials (a lane holds four consecutive columns
 // of a row per block) and the bias row sums.
-template <int HA, int HB, class A, class R>
+template <class A, class R>
 __device__ __forceinline__ void epi_wgrad(const EpiParams& e, const A& acc, const R& accr, int M, int N,
                                           const TileIdx& ti, bool rows, int wm, int wn, int fr, int fg) {
-  constexpr int TA = HA / 32, TB = HB / 64;
-  const int m0 = ti.m * 2 * HA, n0 = ti.n * 2 * HB;
+  const int m0 = ti.m * BM, n0 = ti.n * BN;
   float* out = e.part + (int64_t)ti.z * e.pstride;
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int i = 0; i < TA; ++i) {
-      const int m = m0 + a * HA + wm * (HA / 2) + i * 16 + fr;
+      const int m = m0 + a * H + wm * (H / 2) + i * 16 + fr;
       if (m >= M) continue;
       float* row = out + (int64_t)m * e.ldp;
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int j = 0; j < TB; ++j) {
-          const int n = n0 + b * HB + wn * (HB / 4) + j * 16 + 4 * fg;
+          const int n = n0 + b * H + wn * (H / 4) + j * 16 + 4 * fg;
           if (n < N) *reinterpret_cast<f32x4_t*>(row + n) = acc[a][b][i][j];  // rows padded to 64 columns
         }
       if (rows && wn == i && fg == 0) e.bpart[(int64_t)ti.z * M + m] = accr[a][0];
@@ -573,7 +514,7 @@ __device__ __forceinline__ void run(const GemmDesc& g, const TileIdx& ti, bool r
     const int ml = ((M + 63) & ~63) - 8 - m0, nl = ((N + 63) & ~63) - 8 - n0;  // last whole chunk
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int r = (wv * 2 + u) * 4 + (lane >> 4), ch = (lane & 15) ^ wide::kperm<16>(r);
+      const int r = (wv * 2 + u) * 4 + (lane >> 4), ch = (lane & 15) ^ wide::kperm16(r);
       oa[u] = (uint32_t)((int64_t)r * lda + min(ch * 8, ml)) * 2;
       ob[u] = (uint32_t)((int64_t)r * ldb + min(ch * 8, nl)) * 2;
     }
@@ -601,7 +542,7 @@ __device__ __forceinline__ void run(const GemmDesc& g, const TileIdx& ti, bool r
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     if constexpr (KM) {
-      const int hp = wide::kperm<16>(trow);
+      const int hp = wide::kperm16(trow);
       ao[i] = ((kg * 32 + trow) * BM + ((((wm * 64 + i * 16) >> 3) + (tc >> 1)) ^ hp) * 8 + (tc & 1) * 4) * 2;
       bo[i] = OPB + ((kg * 32 + trow) * BN + ((((wn * 64 + i * 16) >> 3) + (tc >> 1)) ^ hp) * 8 + (tc & 1) * 4) * 2;
     } else {
@@ -628,8 +569,6 @@ __device__ __forceinline__ void run(const GemmDesc& g, const TileIdx& ti, bool r
     const int left = nk - 1 - kt;
     if (left >= NST - 2)
       wide::wait_vm<4 * (NST - 2)>();
-    else if (NST > 3 && left == 1)
-      wide::wait_vm<4>();
     else
       wide::wait_vm<0>();
     wide::bar();
@@ -819,80 +758,66 @@ __global__ __launch_bounds__(mid::NT) void erase_mid_bwd_b(const BlockJob* jobs,
   mid_bwd<NST>(gd, ed, gw, ew, nd, nw, first, smem);
 }
 
-template <int HA, int HB, int KIND>
-__device__ __forceinline__ void wide_nt(const GemmDesc& g, const EpiParams& e, int ntiles, char* smem) {
-  wide::run<HA, HB, false>(
-      g, (int)blockIdx.x, (int)gridDim.x, ntiles, false, smem,
-      [&](const auto& acc, const auto&, const TileIdx& ti, bool, int wm, int wn, int fr, int fg) {
-        wide::epi_nt<HA, HB, KIND>(e, acc, g.M, g.N, ti, wm, wn, fr, fg);
-      });
+template <int KIND>
+__device__ __forceinline__ void wide_nt(const GemmDesc& g, const EpiParams& e, int t, int ntiles, char* smem) {
+  wide::run<false>(g, t, ntiles, false, smem,
+                   [&](const auto& acc, const auto&, const TileIdx& ti, bool, int wm, int wn, int fr, int fg) {
+                     wide::epi_nt<KIND>(e, acc, g.M, g.N, ti, wm, wn, fr, fg);
+                   });
 }
-template <int HA, int HB>
-__device__ __forceinline__ void wide_wgrad(const GemmDesc& g, const EpiParams& e, int b, int G, int ntiles, char* smem) {
-  wide::run<HA, HB, true>(
-      g, b, G, ntiles, e.bpart != nullptr, smem,
-      [&](const auto& acc, const auto& accr, const TileIdx& ti, bool rows, int wm, int wn, int fr, int fg) {
-        wide::epi_wgrad<HA, HB>(e, acc, accr, g.M, g.N, ti, rows, wm, wn, fr, fg);
-      });
+__device__ __forceinline__ void wide_wgrad(const GemmDesc& g, const EpiParams& e, int t, int ntiles, char* smem) {
+  wide::run<true>(g, t, ntiles, e.bpart != nullptr, smem,
+                  [&](const auto& acc, const auto& accr, const TileIdx& ti, bool rows, int wm, int wn, int fr, int fg) {
+                    wide::epi_wgrad(e, acc, accr, g.M, g.N, ti, rows, wm, wn, fr, fg);
+                  });
 }
 // Both backward GEMMs of a layer.  The workgroups of the longer contraction
 // come first (`first`: the weight gradient's).
-template <int HA, int HB, int DK = GK_DGRAD>
 __device__ __forceinline__ void wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw,
                                          const EpiParams& ew, int nd, int nw, int first, char* smem) {
   const int b = (int)blockIdx.x - (first ? 0 : nd);
-  if (b >= 0 && b < nw) {
-    wide_wgrad<HA, HB>(gw, ew, b, nw, nw, smem);
-  } else {
-    wide::run<HA, HB, false>(
-        gd, first ? b - nw : (int)blockIdx.x, nd, nd, false, smem,
-        [&](const auto& acc, const auto&, const TileIdx& ti, bool, int wm, int wn, int fr, int fg) {
-          wide::epi_nt<HA, HB, DK>(ed, acc, gd.M, gd.N, ti, wm, wn, fr, fg);
-        });
-  }
+  if (b >= 0 && b < nw)
+    wide_wgrad(gw, ew, b, nw, smem);
+  else
+    wide_nt<GK_DGRAD>(gd, ed, first ? b - nw : (int)blockIdx.x, nd, smem);
 }
 
-template <int HA, int HB, int KIND>
+template <int KIND>
 __global__ __launch_bounds__(wide::NT) void erase_wide_nt(GemmDesc g, EpiParams e, int ntiles) {
-  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
-  wide_nt<HA, HB, KIND>(g, e, ntiles, smem);
+  __shared__ __attribute__((aligned(16))) char smem[wide::BYTES];
+  wide_nt<KIND>(g, e, (int)blockIdx.x, ntiles, smem);
 }
-template <int HA, int HB>
 __global__ __launch_bounds__(wide::NT) void erase_wide_wgrad(GemmDesc g, EpiParams e, int ntiles) {
-  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
-  wide_wgrad<HA, HB>(g, e, (int)blockIdx.x, (int)gridDim.x, ntiles, smem);
+  __shared__ __attribute__((aligned(16))) char smem[wide::BYTES];
+  wide_wgrad(g, e, (int)blockIdx.x, ntiles, smem);
 }
-template <int HA, int HB, int DK>
-__global__ __launch_bounds__(wide::NT) void erase_wide_bwd(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew,
-                                                           int nd, int nw, int first) {
-  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
-  wide_bwd<HA, HB, DK>(gd, ed, gw, ew, nd, nw, first, smem);
+__global__ __launch_bounds__(wide::NT) void erase_wide_bwd(GemmDesc gd, EpiParams ed, GemmDesc gw, EpiParams ew, int nd,
+                                                           int nw, int first) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::BYTES];
+  wide_bwd(gd, ed, gw, ew, nd, nw, first, smem);
 }
 // the same for several blocks (grid row j: job j)
-template <int HA, int HB, int KIND>
+template <int KIND>
 __global__ __launch_bounds__(wide::NT) void erase_wide_nt_b(const BlockJob* jobs, StepPtrs st, int ntiles) {
-  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  __shared__ __attribute__((aligned(16))) char smem[wide::BYTES];
   GemmDesc g;
   EpiParams e;
   const cmem_t jb = job_of(jobs);
   ld_gemm(jb + offsetof(BlockJob, g), g, st);
   ld_epi(jb + offsetof(BlockJob, e), e, st);
-  wide_nt<HA, HB, KIND>(g, e, ntiles, smem);
+  wide_nt<KIND>(g, e, (int)blockIdx.x, ntiles, smem);
 }
-template <int HA, int HB>
 __global__ __launch_bounds__(wide::NT) void erase_wide_wgrad_b(const BlockJob* jobs, StepPtrs st, int ntiles) {
-  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+  __shared__ __attribute__((aligned(16))) char smem[wide::BYTES];
   GemmDesc g;
   EpiParams e;
   const cmem_t jb = job_of(jobs);
   ld_gemm(jb + offsetof(BlockJob, g), g, st);
   ld_epi(jb + offsetof(BlockJob, e), e, st);
-  wide_wgrad<HA, HB>(g, e, (int)blockIdx.x, (int)gridDim.x, ntiles, smem);
+  wide_wgrad(g, e, (int)blockIdx.x, ntiles, smem);
 }
-template <int HA, int HB>
-__global__ __launch_bounds__(wide::NT) void erase_wide_bwd_b(const BlockJob* jobs, StepPtrs st, int nd, int nw,
-                                                             int first) {
-  __shared__ __attribute__((aligned(16))) char smem[wide::Geo<HA, HB>::BYTES];
+__global__ __launch_bounds__(wide::NT) void erase_wide_bwd_b(const BlockJob* jobs, StepPtrs st, int nd, int nw, int first) {
+  __shared__ __attribute__((aligned(16))) char smem[wide::BYTES];
   GemmDesc gd, gw;
   EpiParams ed, ew;
   const cmem_t jb = job_of(jobs);
@@ -900,7 +825,7 @@ __global__ __launch_bounds__(wide::NT) void erase_wide_bwd_b(const BlockJob* job
   ld_epi(jb + offsetof(BlockJob, e), ed, st);
   ld_gemm(jb + offsetof(BlockJob, g2), gw, st);
   ld_epi(jb + offsetof(BlockJob, e2), ew, st);
-  wide_bwd<HA, HB>(gd, ed, gw, ew, nd, nw, first, smem);
+  wide_bwd(gd, ed, gw, ew, nd, nw, first, smem);
 }
 
 #define ERASE_WIDE(ONE, MANY)                                          \
@@ -914,13 +839,13 @@ static hipError_t launch_256(int kind, const GemmDesc& g, const EpiParams& e, hi
   const int nt = (int)wide_tiles(g.M, g.N) * g.split;
   const dim3 grid((unsigned)nt, bt ? (unsigned)bt->n : 1u), block(wide::NT);
   switch (kind) {
-    case GK_FWD_RELU: ERASE_WIDE((erase_wide_nt<128, 128, GK_FWD_RELU>), (erase_wide_nt_b<128, 128, GK_FWD_RELU>)); break;
-    case GK_FWD_CROSS: ERASE_WIDE((erase_wide_nt<128, 128, GK_FWD_CROSS>), (erase_wide_nt_b<128, 128, GK_FWD_CROSS>)); break;
-    case GK_DGRAD: ERASE_WIDE((erase_wide_nt<128, 128, GK_DGRAD>), (erase_wide_nt_b<128, 128, GK_DGRAD>)); break;
-    case GK_WGRAD: ERASE_WIDE((erase_wide_wgrad<128, 128>), (erase_wide_wgrad_b<128, 128>)); break;
-    case GK_FWD_LIN: ERASE_LAUNCH((erase_wide_nt<128, 128, GK_FWD_LIN>), grid, block, 0, s, ev, g, e, nt); break;
-    case GK_FWD_GELU: ERASE_LAUNCH((erase_wide_nt<128, 128, GK_FWD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
-    case GK_DGRAD_GELU: ERASE_LAUNCH((erase_wide_nt<128, 128, GK_DGRAD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_FWD_RELU: ERASE_WIDE((erase_wide_nt<GK_FWD_RELU>), (erase_wide_nt_b<GK_FWD_RELU>)); break;
+    case GK_FWD_CROSS: ERASE_WIDE((erase_wide_nt<GK_FWD_CROSS>), (erase_wide_nt_b<GK_FWD_CROSS>)); break;
+    case GK_DGRAD: ERASE_WIDE((erase_wide_nt<GK_DGRAD>), (erase_wide_nt_b<GK_DGRAD>)); break;
+    case GK_WGRAD: ERASE_WIDE(erase_wide_wgrad, erase_wide_wgrad_b); break;
+    case GK_FWD_LIN: ERASE_LAUNCH((erase_wide_nt<GK_FWD_LIN>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_FWD_GELU: ERASE_LAUNCH((erase_wide_nt<GK_FWD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
+    case GK_DGRAD_GELU: ERASE_LAUNCH((erase_wide_nt<GK_DGRAD_GELU>), grid, block, 0, s, ev, g, e, nt); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -973,32 +898,33 @@ hipError_t launch_wide_bwd(const GemmDesc& gd, const EpiParams& ed, const GemmDe
   const GemmDesc d = with_order(gd), w = with_order(gw);
   if (!operands_ok(d) || !operands_ok(w) || d.bm != w.bm || d.bn != w.bn || d.bm != d.bn)
     return hipErrorInvalidValue;
-  // an input gradient in fp32 slices (the vocabulary head's), else whole
-  const bool part = ed.part != nullptr;
-  if (part ? (bt || d.split < 1 || (int64_t)d.split * d.kps < d.K || d.N % 64) : (d.split != 1 || d.kps < d.K))
-    return hipErrorInvalidValue;
-  const bool big = d.bm == 256;
+  // an input gradient in fp32 slices (the vocabulary head's, in 128x128 tiles), else whole
+  const bool big = d.bm == 256, part = ed.part != nullptr;
   if (!big && d.bm != 128) return hipErrorInvalidValue;
+  if (part ? (big || bt || d.split < 1 || (int64_t)d.split * d.kps < d.K || d.N % 64) : (d.split != 1 || d.kps < d.K))
+    return hipErrorInvalidValue;
   const int nd = (int)(big ? wide_tiles(d.M, d.N) : mid_tiles(d.M, d.N)) * d.split;
   const int nw = (int)(big ? wide_tiles(w.M, w.N) : mid_tiles(w.M, w.N)) * w.split;
   const dim3 grid((unsigned)(nd + nw), bt ? (unsigned)bt->n : 1u), block(512);
   const int first = w.kps >= std::min(d.K, d.kps) ? 1 : 0;
-#define ERASE_BWD(NAME, ...)                                                                              \
-  do {                                                                                                   \
-    if (bt)                                                                                              \
-      ERASE_LAUNCH((NAME##_b<__VA_ARGS__>), grid, block, 0, s, ev, bt->jobs, bt->st, nd, nw, first);      \
-    else if (part)                                                                                       \
-      ERASE_LAUNCH((NAME<__VA_ARGS__, GK_DGRAD_PART>), grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first); \
-    else                                                                                                 \
-      ERASE_LAUNCH((NAME<__VA_ARGS__, GK_DGRAD>), grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first);    \
+#define ERASE_MID_BWD(NST)                                                                                   \
+  do {                                                                                                       \
+    if (bt)                                                                                                  \
+      ERASE_LAUNCH((erase_mid_bwd_b<NST>), grid, block, 0, s, ev, bt->jobs, bt->st, nd, nw, first);           \
+    else if (part)                                                                                           \
+      ERASE_LAUNCH((erase_mid_bwd<NST, GK_DGRAD_PART>), grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first);   \
+    else                                                                                                     \
+      ERASE_LAUNCH((erase_mid_bwd<NST, GK_DGRAD>), grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first);        \
   } while (0)
-  if (big)
-    ERASE_BWD(erase_wide_bwd, 128, 128);
+  if (big && bt)
+    ERASE_LAUNCH(erase_wide_bwd_b, grid, block, 0, s, ev, bt->jobs, bt->st, nd, nw, first);
+  else if (big)
+    ERASE_LAUNCH(erase_wide_bwd, grid, block, 0, s, ev, d, ed, w, ew, nd, nw, first);
   else if ((int64_t)grid.x * grid.y <= kWideCus)
-    ERASE_BWD(erase_mid_bwd, 3);
+    ERASE_MID_BWD(3);
   else
-    ERASE_BWD(erase_mid_bwd, 2);
-#undef ERASE_BWD
+    ERASE_MID_BWD(2);
+#undef ERASE_MID_BWD
   return hipGetLastError();
 }
 
