@@ -164,7 +164,7 @@ struct Block {
   // logits: the head's exponentials relative to the target logit, then
   // (after tf_head_norm) the head's output gradient up to a row scale
   uint16_t *a0 = nullptr, *n1, *qkv, *o, *a1, *n2, *u, *g, *z, *hn, *logits, *hns;
-  uint16_t *dhn, *dz, *du, *dn2, *da1, *dout, *dqkv, *dn1 = nullptr;
+  uint16_t *dhn = nullptr, *dz, *du, *dn2, *da1, *dout, *dqkv, *dn1 = nullptr;
   float *r1, *r2, *r3, *lse, *lstat, *xref, *rowscale, *rowloss, *ploss, *da0 = nullptr, *gemb = nullptr;
   float* dhnp = nullptr;  // the head's input gradient in hsplit fp32 slices [N][d] (hsplit > 1, else dhn)
   int hsplit = 1;
@@ -246,7 +246,6 @@ size_t build_layout(const erase_tf_config& c, uintptr_t base, Layout* P) {
     B.hn = bf(Np, P->ldd);
     B.logits = bf(Np, P->ldv);
     B.hns = bf(Np, P->ldd);
-    B.dhn = bf(Np, P->ldd);
     B.dz = bf(Np, P->ldd);
     B.du = bf(Np, P->ld4);
     B.dn2 = bf(Np, P->ldd);
@@ -284,7 +283,11 @@ size_t build_layout(const erase_tf_config& c, uintptr_t base, Layout* P) {
       B.pair_tile[i] = wp.tile;
       if (wp.tile) B.wp[i] = wide_plan(wp.tile, rup(D.N, 64), wp.split);
       B.part[i] = f32(int64_t(B.wp[i].split) * D.rows[i] * D.cols[i]);
-      if (i == WH && B.hsplit > 1) B.dhnp = f32(int64_t(B.hsplit) * D.N * d);
+      if (i != WH) continue;
+      if (B.hsplit > 1)
+        B.dhnp = f32(int64_t(B.hsplit) * D.N * d);
+      else
+        B.dhn = bf(Np, P->ldd);
     }
     B.segs_dev = static_cast<AdamSeg*>(cv.take(sizeof(AdamSeg) * (NW + 1)));
   }
