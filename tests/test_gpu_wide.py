@@ -54,6 +54,24 @@ def test_wide_tiles_vs_oracle(name, cfg, schedule, want):
     assert want <= got, (sorted(want - got), sorted(got))
 
 
+@pytest.mark.parametrize("n,batch,d,w", [(1, 12001, 1937, 1457), (6, 19990, 1697, 437)])
+def test_wide_wgrad_alone(n, batch, d, w):
+    """The 256x256 weight gradient without an input gradient beside it, split,
+    in a launch of one block and in launches of two (units of six blocks)."""
+    layers = [("linear_relu", d, w)]
+    cfg = synth.custom("bf16", batch, d, [{"input": "x", "layers": layers, "lam": 1.0 + 0.1 * i} for i in range(n)],
+                       label_p=0.2)
+    params, batches = synth.make_workload(cfg, 4, 1)
+    print(f"[wide] wgrad {n} x {batch} {d} {w}", flush=True)
+    _, g = run_gpu(cfg, params, batches, "overlap")
+    assert_bit_identical(g, run_gpu(cfg, params, batches, "serial")[1])
+    check_bf16(cfg, g, params, batches)
+    tr = erase.Trainer(cfg, params)
+    got = _tiles(tr, *tr.device_batch(*batches[0]), schedule="overlap")
+    tr.close()
+    assert ("wgrad_gemm", 0, 0, 256) in got, sorted(got)
+
+
 def test_wide_tiles_transformer_vs_oracle():
     """The transformer's kinds (residual, GELU and its derivative) over 33000
     ragged positions, width 192."""
