@@ -54,7 +54,10 @@ KIND_SYMBOL = {"prologue": "erase_prologue", "fwd_gemm": "erase_fwd_gemm", "head
                "wgrad_gemm_kg2": "erase_wgrad_gemm_kg2", "wgrad_adam_kg2": "erase_wgrad_adam_kg2"}
 
 
-def kernel_class(r, bf16=True):
+def kernel_class(r, bf16=True, cross=False):
+    """Kernel of a timing record: its name without the instance's stages and
+    the form for several blocks; kernels of several epilogues with the
+    epilogue.  ``cross``: a cross layer's launch."""
     t = "bf16" if bf16 else "f32"
     if r["kind"] == "fwd_head_gemm" and bf16 and r["tile_m"] == 16:
         return "erase_fwd_head16"  # the bf16 16-row last layer + head kernel
@@ -62,11 +65,17 @@ def kernel_class(r, bf16=True):
         # the bf16 first-layer weight gradient with its Adam update: four
         # waves per 64x64 tile, direct-to-LDS slices (one kernel for both)
         return "erase_wgrad_adam_w4"
-    if r["tile_m"] == 256:
-        return {"wgrad_gemm": "erase_wide_wgrad", "bwd_gemm": "erase_wide_bwd"}.get(r["kind"], "erase_wide_nt")
+    if bf16 and r["tile_m"] >= 128 and r["tile_m"] == r["tile_n"]:
+        k = "erase_wide" if r["tile_m"] == 256 else "erase_mid"
+        if r["kind"] in ("wgrad_gemm", "bwd_gemm"):
+            return k + ("_wgrad" if r["kind"] == "wgrad_gemm" else "_bwd")
+        return f"{k}_nt<{'dgrad' if r['kind'] == 'dgrad_gemm' else 'cross' if cross else 'relu'}>"
+    sym = KIND_SYMBOL[r["kind"]]
+    if cross:
+        sym = sym.replace("erase_fwd_gemm", "erase_fwd_cross_gemm")
     if r["tile_m"]:
-        return f"{KIND_SYMBOL[r['kind']]}<{t},{r['tile_m']},{r['tile_n']}>"
-    return f"{KIND_SYMBOL[r['kind']]}<{t}>"
+        return f"{sym}<{t},{r['tile_m']},{r['tile_n']}>"
+    return f"{sym}<{t}>"
 
 
 TF_SOURCES = ("csrc/transformer.hip", "csrc/tf_api.cpp")
@@ -555,8 +564,7 @@ def transformer_section(args, log):
     classes = {}
     for rs in recs["serial"]:
         for r in rs:
-            name = r["kind"] + (":" + erase_tf.GEMM_NAMES[r["layer"]] if r["kind"].endswith("gemm") else
-                                f":{r['layer']}" if r["kind"] == "attn_bwd" else "")
+            name = r["kind"] + (":" + erase_tf.GEMM_NAMES[r["layer"]] if r["kind"].endswith("gemm") else "")
             c = classes.setdefault(name, {"ms": 0.0, "n": 0, "flops": 0.0, "bytes": 0.0})
             c["ms"] += r["end_ms"] - r["start_ms"]
             c["n"] += 1
@@ -573,7 +581,7 @@ def transformer_section(args, log):
     fl = synth_tf.flops_per_step(cfg)
     best = max(("overlap",), key=lambda s: res[s]["tokens_per_s"])
     ovl_all = float(np.mean([_concurrent(r, lambda x: True) for r in recs["overlap"]]))
-    ovl_att = [_concurrent(r, lambda x: x["kind"] == "attn_bwd" and x["layer"] >= 2) for r in recs["overlap"]]
+    ovl_att = [_concurrent(r, lambda x: x["kind"] == "attn_bwd") for r in recs["overlap"]]
     ovl_voc = [_concurrent(r, lambda x: x["kind"].endswith("gemm") and x["layer"] == 4) for r in recs["overlap"]]
     dom = max(kernels.items(), key=lambda kv: kv[1]["us_per_step"])
     cpu = None
@@ -674,9 +682,7 @@ def ctr_section(args, workload, log, scheds, headline, steps, warmup, timing_ste
     classes = {}
     for recs in recs_all:
         for r in recs:
-            name = kernel_class(r, bf16)
-            if layer_kind(cfg, r) == "cross" and r["kind"].startswith("fwd_gemm"):
-                name = name.replace("erase_fwd_gemm", "erase_fwd_cross_gemm")
+            name = kernel_class(r, bf16, layer_kind(cfg, r) == "cross")
             c = classes.setdefault(name, {"ms": 0.0, "n": 0, "flops": 0.0, "bytes": 0.0, "kind": r["kind"]})
             c["ms"] += r["end_ms"] - r["start_ms"]
             c["n"] += 1
@@ -760,7 +766,9 @@ def ctr_section(args, workload, log, scheds, headline, steps, warmup, timing_ste
 
 TRACE_FILE = os.path.join(ROOT, "profiles", "ctr_mlp_overlap_trace.md")
 FWD_PREFIXES = ("erase_prologue", "erase_fwd_")
-BWD_PREFIXES = ("erase_bwd_gemm", "erase_wgrad_", "erase_dgrad_", "erase_adam", "erase_head_bce")
+BWD_PREFIXES = ("erase_bwd_gemm", "erase_wgrad_", "erase_dgrad_", "erase_adam", "erase_head_bce", "erase_mid_bwd",
+                "erase_mid_wgrad", "erase_wide_bwd", "erase_wide_wgrad")
+NT_FWD = ("0", "1", "5", "6")  # forward epilogues of the 128x128 and 256x256 tiles: ReLU, cross, linear, GELU
 
 
 def _kernel_base(name):
@@ -768,6 +776,17 @@ def _kernel_base(name):
     for pre in ("void ", "erase::", "(anonymous namespace)::"):
         n = n.replace(pre, "")
     return n.strip()
+
+
+def trace_direction(name):
+    """"fwd" or "bwd" work of a kernel of the trace, None for others."""
+    base = _kernel_base(name)
+    if base.startswith(("erase_mid_nt", "erase_wide_nt")):
+        epilogue = name.split("<")[1].split(">")[0].split(",")[-1].strip()
+        return "fwd" if epilogue in NT_FWD else "bwd"
+    if base.startswith(FWD_PREFIXES):
+        return "fwd"
+    return "bwd" if base.startswith(BWD_PREFIXES) else None
 
 
 def analyze_trace(path):
@@ -781,14 +800,10 @@ def analyze_trace(path):
     fwd, bwd, streams = [], [], {"fwd": set(), "bwd": set()}
     with open(path) as f:
         for row in csv.DictReader(f):
-            base = _kernel_base(row["Kernel_Name"])
-            a, b = int(row["Start_Timestamp"]), int(row["End_Timestamp"])
-            if base.startswith(FWD_PREFIXES):
-                fwd.append((a, b))
-                streams["fwd"].add(row.get("Stream_Id"))
-            elif base.startswith(BWD_PREFIXES):
-                bwd.append((a, b))
-                streams["bwd"].add(row.get("Stream_Id"))
+            way = trace_direction(row["Kernel_Name"])
+            if way:
+                (fwd if way == "fwd" else bwd).append((int(row["Start_Timestamp"]), int(row["End_Timestamp"])))
+                streams[way].add(row.get("Stream_Id"))
     merged = _merge(fwd)
     tot = inter = 0
     j = 0

@@ -48,3 +48,26 @@ def test_normalized_entropy_of_the_base_rate_predictor():
     r = bench.normalized_entropy([bce, 0.0], y)
     assert math.isclose(r["per_block"][0], 1.0) and r["per_block"][1] == 0.0
     assert math.isclose(r["label_rate"], 0.03)
+
+
+def test_kernel_names_of_timing_records():
+    rec = lambda kind, m, n: {"kind": kind, "tile_m": m, "tile_n": n}
+    assert bench.kernel_class(rec("fwd_gemm", 128, 128)) == "erase_mid_nt<relu>"
+    assert bench.kernel_class(rec("fwd_gemm", 256, 256), cross=True) == "erase_wide_nt<cross>"
+    assert bench.kernel_class(rec("dgrad_gemm", 128, 128)) == "erase_mid_nt<dgrad>"
+    assert bench.kernel_class(rec("bwd_gemm", 128, 128)) == "erase_mid_bwd"
+    assert bench.kernel_class(rec("wgrad_gemm", 256, 256)) == "erase_wide_wgrad"
+    assert bench.kernel_class(rec("fwd_gemm_kg2", 64, 128), cross=True) == "erase_fwd_cross_gemm_kg2<bf16,64,128>"
+    assert bench.kernel_class(rec("bwd_gemm", 64, 64)) == "erase_bwd_gemm<bf16,64,64>"
+    assert bench.kernel_class(rec("bwd_gemm", 64, 64), bf16=False) == "erase_bwd_gemm<f32,64,64>"
+
+
+def test_trace_direction_by_kernel_name_and_epilogue():
+    for name, way in (("void erase::erase_mid_nt_b<3, 0>(erase::BlockJob const*)", "fwd"),
+                      ("void erase::erase_wide_nt<1>(erase::GemmDesc)", "fwd"),
+                      ("void erase::erase_mid_nt<2, 3>(erase::GemmDesc)", "bwd"),
+                      ("erase::erase_wide_wgrad_b(erase::BlockJob const*)", "bwd"),
+                      ("void erase::erase_mid_bwd<2, 9>(erase::GemmDesc)", "bwd"),
+                      ("void erase::erase_adam_b<unsigned short>(erase::BlockJob const*)", "bwd"),
+                      ("erase::tf_attn_bwd(erase::TfAttnArgs)", None)):
+        assert bench.trace_direction(name) == way, name
