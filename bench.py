@@ -867,7 +867,7 @@ def main():
     ap.add_argument("--headline", default="pipeline+worker",
                     help="the ERASE schedule whose throughput is the reported value (declared before the run)")
     ap.add_argument("--bwd-streams", type=int, default=2,
-                    help="backward streams of the ERASE schedules (block b uses stream b %% n); 2 measured "
+                    help="backward streams of the ERASE schedules (unit k of blocks uses stream k %% n); 2 measured "
                          "fastest on ctr_mlp (1 leaves the backward chain serial, 3+ exceed the 4 hardware queues)")
     ap.add_argument("--x-copy", action="store_true",
                     help="hand x over in its plain layout, copied into a padded workspace buffer every step (by "

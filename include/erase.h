@@ -83,22 +83,28 @@ typedef enum { ERASE_IN_X = 0, ERASE_IN_PREV = 1 } erase_input_src;
 
 /* Schedules of one step.  All of them run the identical kernels on identical
  * inputs and produce bit-identical results.
+ * Consecutive blocks of equal layers and launch plans share launches (each
+ * launch runs the same layer of all of them): their backward in every detached
+ * schedule, and their forward when they read x and feed no later block.
  *   SERIAL:        everything on the forward stream: forward+loss of blocks
- *                  1..B, then backward of blocks B..1, then Adam of 1..B
- *                  (a block whose first-layer weight gradient carries its
- *                  Adam update runs all of its Adam in that launch, at the
- *                  end of its backward).
- *   OVERLAP:       ERASE early backward: forward+loss of block b on the
- *                  forward stream, then block b's backward and Adam on the
- *                  backward stream after an event, overlapping block b+1's
- *                  forward; the step ends with the forward stream joined on
- *                  the backward stream.
+ *                  1..B, then the blocks in reverse, each block's Adam (or
+ *                  that of the blocks that share launches) behind its
+ *                  backward (in the launch of the first layer's weight
+ *                  gradient where that carries the update).
+ *   OVERLAP:       ERASE early backward.  The blocks are handed over in units
+ *                  of consecutive blocks, at most a third of the network each
+ *                  (all of a very small network): a unit's forward on the
+ *                  forward stream, then its backward and Adam (and its heads)
+ *                  on a backward stream after an event, overlapping the next
+ *                  unit's forward; unit k goes to backward stream k mod their
+ *                  number; the step ends with the forward stream joined on
+ *                  the backward streams.
  *   SERIAL_GRAPH / OVERLAP_GRAPH: the same sequences captured once into a HIP
  *                  graph (per distinct x/labels/losses pointers and step
  *                  parity) and replayed.
- *   PIPELINE:      the OVERLAP order without the end-of-step join: block
- *                  b's next forward waits only for its own previous backward
- *                  (and, in a chain, for block b+1's), so one step's last
+ *   PIPELINE:      the OVERLAP order without the end-of-step join: a
+ *                  unit's next forward waits only for its own previous backward
+ *                  (and, in a chain, for the next unit's), so one step's last
  *                  backwards overlap the next step's first forwards.  Work
  *                  enqueued on the forward stream after a PIPELINE step is
  *                  not ordered after that step's backward; call erase_sync()
@@ -116,7 +122,9 @@ typedef enum { ERASE_IN_X = 0, ERASE_IN_PREV = 1 } erase_input_src;
  *                  that block, so the gradients differ from the detached
  *                  schedules for chains (identical for blocks on the shared
  *                  input).  Every forward, then one backward from the last
- *                  block to the first, then Adam, all on the forward stream.
+ *                  block to the first with each block's Adam behind it or
+ *                  behind those it shares the launch with, all on the forward
+ *                  stream.
  *                  ERASE_ERR_UNSUPPORTED unless each chained block starts,
  *                  and the block it reads ends, with a linear+ReLU layer.
  *   UNDETACHED_GRAPH: UNDETACHED captured as a HIP graph and replayed (the
@@ -231,7 +239,9 @@ ERASE_API erase_status erase_refresh_weights(erase_ctx* ctx);
  * erase_read_timing() fills up to `cap` records of the last completed step
  * (call after erase_sync()) and sets *n to the number of records: record 0
  * is an empty event pair on the forward stream (kind 7; its length is the
- * cost of the timing itself), then one record per launch in enqueue order. */
+ * cost of the timing itself), then one record per launch in enqueue order: a
+ * launch shared by several blocks is one record, under the first of them, with
+ * the workgroups, operations and bytes of all. */
 typedef struct {
   int32_t kind;      /* 0 prologue, 1 forward GEMM, 2 head+loss, 3 weight-grad GEMM,
                         4 input-grad GEMM, 5 Adam, 6 input- and weight-grad GEMMs of one
@@ -246,10 +256,12 @@ typedef struct {
                         (kind 5 then updates the block's other parameters),
                         11 the launch of kind 10 that also runs the Adam
                         update of the block's other parameters in extra
-                        workgroups (used whenever a block's Adam directly
-                        follows its backward: every schedule but
-                        OVERLAP_ADAM_END; no kind 5 for the block then) */
-  int32_t block;     /* block index, -1 for the step prologue */
+                        workgroups (whenever a block's Adam directly follows
+                        its backward: every schedule but OVERLAP_ADAM_END; no
+                        kind 5 for the block then).  Kinds 10 and 11 are the
+                        batches for which 64x64 tiles over all rows are the
+                        fastest; larger bf16 ones take kinds 3 and 5 */
+  int32_t block;     /* (first) block index, -1 for the step prologue */
   int32_t layer;     /* layer index within the block, -1 if none */
   int32_t stream;    /* 0 forward stream, 1 + k backward stream k */
   float start_ms;    /* relative to the step's first event on the forward stream */
@@ -276,9 +288,9 @@ ERASE_API int32_t erase_stream_idle(void* stream);
  *   ERASE_DISPATCH_CALLER (default): erase_step() enqueues every launch and
  *       event on the calling thread.
  *   ERASE_DISPATCH_WORKER: for OVERLAP, OVERLAP_ADAM_END and PIPELINE, a
- *       host thread owned by the context enqueues each block's backward,
+ *       host thread owned by the context enqueues each unit's backward,
  *       Adam and backward-stream events while the calling thread goes on
- *       with the next block's forward.  erase_step() may return before the
+ *       with the next unit's forward.  erase_step() may return before the
  *       worker has enqueued the step's backward work; the next
  *       erase_step() orders itself against it, and erase_sync() (like every
  *       other call) first waits for it.  HIP errors on the worker surface at

@@ -105,8 +105,8 @@ ERASE_API erase_status erase_tf_refresh_weights(erase_tf_ctx* ctx);
  * vocabulary logits), 3 weight-grad GEMM and 4 input-grad GEMM (layer as for
  * 1), 6 both gradient GEMMs of one weight in one launch (layer as for 1),
  * 5 Adam, 11 embedding gather, 12 RMSNorm forward, 13 RMSNorm backward,
- * 14 attention forward, 15 attention backward (layer 1 row sums, 2 dK/dV,
- * 3 dQ), 16 softmax normaliser of the vocabulary head (layer 0 every row,
+ * 14 attention forward, 15 attention backward (dK, dV and dQ in one launch,
+ * layer 0), 16 softmax normaliser of the vocabulary head (layer 0 every row,
  * 1 the recomputation of out-of-range rows), 17 embedding gradient (four
  * launches, bracketed by stream events rather than kernel-stamped ones). */
 ERASE_API erase_status erase_tf_set_timing(erase_tf_ctx* ctx, int32_t enable);

@@ -725,7 +725,7 @@ struct Ctx {
   char* ws = nullptr;
   size_t ws_bytes = 0;
   hipStream_t sf = nullptr;
-  std::vector<hipStream_t> sbs;  // backward streams; block b uses sbs[b % size]
+  std::vector<hipStream_t> sbs;  // backward streams; unit k of the ERASE schedules uses sbs[k % size]
   int device = 0;
   std::vector<hipEvent_t> ef, eb;  // per unit of the ERASE schedules: end of its forward, of its backward
   erase_status sticky = ERASE_OK;

@@ -33,7 +33,9 @@ def test_library_hides_its_internal_host_functions():
     not exported, only the C entry points (and the kernels, which the HIP
     runtime registers)."""
     L = erase.lib()
-    for internal in ("_ZN5erase11launch_gemmEiiRKNS_8GemmDescERKNS_9EpiParamsEP12ihipStream_tRKNS_8LaunchEvE",
+    for internal in ("_ZN5erase11launch_gemmEiiRKNS_8GemmDescERKNS_9EpiParamsEP12ihipStream_tRKNS_8LaunchEvEPKNS_5BatchE",
+                     "_ZN5erase11launch_adamEiRKNS_8AdamArgsEP12ihipStream_tRKNS_8LaunchEvEPKNS_5BatchE",
+                     "_ZN5erase11launch_gemmEiiRKNS_8GemmDescERKNS_9EpiParamsEP12ihipStream_tRKNS_8LaunchEvE",
                      "_ZN5erase11launch_adamEiRKNS_8AdamArgsEP12ihipStream_tRKNS_8LaunchEvE"):
         assert not hasattr(L, internal), internal
 
