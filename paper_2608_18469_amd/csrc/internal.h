@@ -209,7 +209,7 @@ struct Batch {
 hipError_t launch_gemm(int bf16, int kind, const GemmDesc& g, const EpiParams& e, hipStream_t s,
                        const LaunchEv& ev = {}, const Batch* bt = nullptr);
 // Input-gradient (gd, split 1) and weight-gradient (gw) GEMMs of one layer in
-// one launch; both must use the same tile, 64x64 or 128x128.
+// one launch; both must use the same tile, 64x64, 128x128 or 256x256.
 hipError_t launch_bwd_gemm(int bf16, const GemmDesc& gd, const EpiParams& ed, const GemmDesc& gw, const EpiParams& ew,
                            hipStream_t s, const LaunchEv& ev = {}, const Batch* bt = nullptr);
 

@@ -707,8 +707,8 @@ __device__ __forceinline__ void gemm_body(const GemmDesc& g, const EpiParams& e,
   }
 
   // Only the two k-group kernels take the fused update: its per-thread item
-  // arrays would otherwise hold a 128x128 tile's registers in every
-  // weight-gradient instantiation (one wave per SIMD).
+  // arrays would otherwise hold registers in every weight-gradient
+  // instantiation.
   if constexpr (FADAM) {
     if (e.ap) {
       // Fused Adam: the LDS tile holds this tile's finished gradient (the

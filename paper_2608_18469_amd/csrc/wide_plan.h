@@ -136,9 +136,10 @@ inline WidePair wide_pair(int64_t M, int64_t Nout, int64_t Kin, int share) {
 // chain (1800 x 192 over 8000: 87 tiles of 125 k-steps, 42 us).  The input
 // gradient is cut into `dsplit` fp32 slices of at least 8 k-steps where the
 // modelled time with the slices' traffic is the least; core_split: the slices of
-// the core's weight gradient.  The two-layer step of 6 sequences of 300 tokens,
-// width 192, 8000 words 409 -> 373 us (4 slices: the pair 42 -> 22 us), 8 of 500,
-// 256, 4096 502 -> 493, 4 of 64, 128, 1024 254 -> 249.
+// the core's weight gradient.  Unsliced and so, both builds in turn on one card:
+// the pair of 6 sequences of 300 tokens, width 192, 8000 words 40 -> 21 us (4
+// slices) and the two-layer step, queued steps, 406 -> 380; 8 of 500, 256, 4096
+// 33 -> 24 and 500 -> 495; 4 of 64, 128, 1024 8.7 -> 5.0 and 254 -> 250.
 struct HeadPair {
   int tile = 0, split = 1, dsplit = 1;  // tile 0: the core's (its weight-gradient slices stay)
 };
