@@ -407,12 +407,14 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_place(EmbedBwdArgs a) {
   const int sx = block_exclusive_scan(s, part), fx = block_exclusive_scan(f, part);
   if (threadIdx.x == 255) {
     // both counters stay below 2^31: no carry from the low one
-    const int nm = (fx + f) & 0xffff, nl = (fx + f) >> 16;
+    const int nm = (fx + f) & 0xffff;
     const unsigned long long r = atomicAdd(reinterpret_cast<unsigned long long*>(a.nlarge + 2),
                                            ((unsigned long long)(uint32_t)nm << 32) | (uint32_t)(sx + s));
-    room[2] = nl ? atomicAdd(a.nlarge + 1, nl) : 0;
     room[0] = (int)(uint32_t)r;
     room[1] = (int)(uint32_t)(r >> 32);
+  } else if (threadIdx.x == 0) {  // another wave: at the same time; part[] holds the waves' flags
+    const int nl = (part[0] + part[1] + part[2] + part[3]) >> 16;
+    room[2] = nl ? atomicAdd(a.nlarge + 1, nl) : 0;
   }
   __syncthreads();
   int run = room[0] + sx, pos = room[1] + (fx & 0xffff), lpos = room[2] + (fx >> 16);
@@ -435,8 +437,8 @@ __global__ __launch_bounds__(256) void erase_bags_bwd_scatter(EmbedBwdArgs a) {
   const int32_t gid = a.gid[i];
   if (gid >= 0) {
     const int32_t m = (int32_t)((uint32_t)a.owner[i] % (uint32_t)a.M);
-    const int c = a.count[gid];
-    a.bucket[a.start[gid] + a.slot[i]] = c <= kSmallBucket || c <= wave_bucket(a) ? m : (int32_t)i;
+    const int c = a.count[gid], to = a.start[gid] + a.slot[i];
+    a.bucket[to] = c <= kSmallBucket || c <= wave_bucket(a) ? m : (int32_t)i;
   }
 }
 
@@ -560,7 +562,9 @@ __device__ __forceinline__ void bag_row_large(const EmbedBwdArgs& a, int32_t g, 
   constexpr int NT = kSumThreads, NG = NT / G;  // lane groups of the workgroup
   const int c = a.count[g];
   const int32_t* bucket = a.bucket + a.start[g];
-  const int tid = threadIdx.x, q = tid / G, cq = tid % G;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int q = tid / G, cq = tid % G;
   const bool col = 4 * cq < a.dim;
   const int64_t xc = a.n_dense + (int64_t)(g / a.rows) * a.dim + 4 * cq;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -755,11 +759,12 @@ __device__ __forceinline__ void bag_rows_light(const EmbedBwdArgs& a, int64_t r0
 // sorted across the lanes, lane group q adding entries q, q + 64/G, ... in
 // order (eight loads in flight), the groups combined by a fixed butterfly.
 template <typename T, int G>
-__device__ __forceinline__ void bag_row_mid(const EmbedBwdArgs& a, int32_t g, int c, int s0) {
+__device__ __forceinline__ void bag_row_mid(const EmbedBwdArgs& a, int32_t g) {
   constexpr int NGW = 64 / G;
   const int lane = threadIdx.x & 63;
   const int q = lane / G, cq = lane % G;
   const bool col = 4 * cq < a.dim;
+  const int c = a.count[g], s0 = a.start[g];  // the same in every lane
   int32_t m[1] = {lane < c ? a.bucket[s0 + lane] : INT32_MAX};
   wave_sort<1>(m, lane);
   const int64_t xc = a.n_dense + (int64_t)(g / a.rows) * a.dim + 4 * cq;
@@ -789,7 +794,7 @@ __device__ __forceinline__ void bag_row_mid(const EmbedBwdArgs& a, int32_t g, in
 // The bag rows of a bucket of at most 64 R entries in order.
 template <int R>
 __device__ __forceinline__ void sort_bucket(const int32_t* bucket, int c, int32_t* key) {
-  const int lane = threadIdx.x & 63;
+  const int lane = opaque_lane();
   int32_t m[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) m[r] = 64 * r + lane < c ? bucket[64 * r + lane] : INT32_MAX;
@@ -801,13 +806,14 @@ __device__ __forceinline__ void sort_bucket(const int32_t* bucket, int c, int32_
 // A row of kSmallBucket + 1..kWaveBucket entries by one wave.  key: kWaveBucket
 // words of LDS of its own (a wave's stores and loads are served in order).
 template <typename T, int G>
-__device__ __forceinline__ void bag_row_wave(const EmbedBwdArgs& a, int32_t g, int c, int s0, int32_t* key) {
+__device__ __forceinline__ void bag_row_wave(const EmbedBwdArgs& a, int32_t g, int32_t* key) {
   constexpr int NGW = 64 / G;
   static_assert(kWaveBucket == 512, "the longest sort");
-  const int lane = threadIdx.x & 63;
+  const int lane = opaque_lane();
   const int q = lane / G, cq = lane % G;
   const bool col = 4 * cq < a.dim;
-  const int32_t* bucket = a.bucket + s0;
+  const int c = a.count[g];
+  const int32_t* bucket = a.bucket + a.start[g];
   if (c <= 128)
     sort_bucket<2>(bucket, c, key);
   else if (c <= 256)
@@ -851,14 +857,18 @@ __global__ __launch_bounds__(kSumThreads, 8) void erase_bags_bwd_sums(EmbedBwdAr
       __syncthreads();  // the next row reuses the arrays
     }
   } else if (b < nlist + nmid) {
-    const uint32_t n = (uint32_t)a.nlarge[3];
-    for (uint32_t i = (b - nlist) * (kSumThreads / 64) + wave; i < n; i += nmid * (kSumThreads / 64)) {
-      const int32_t g = a.mid[i];
-      const int c = a.count[g], s0 = a.start[g];  // the same in every lane
-      if (c <= kSmallBucket)
-        bag_row_mid<T, G>(a, g, c, s0);
-      else
-        bag_row_wave<T, G>(a, g, c, s0, key + wave * kWaveBucket);
+    const uint32_t n = (uint32_t)a.nlarge[3], i0 = (b - nlist) * (kSumThreads / 64) + wave, ni = nmid * (kSumThreads / 64);
+    // two loops: the longer sorts' lane masks are not kept in the first one
+    if (wave_bucket(a) == kSmallBucket) {
+      for (uint32_t i = i0; i < n; i += ni) bag_row_mid<T, G>(a, a.mid[i]);
+    } else {
+      for (uint32_t i = i0; i < n; i += ni) {
+        const int32_t g = a.mid[i];
+        if (a.count[g] <= kSmallBucket)
+          bag_row_mid<T, G>(a, g);
+        else
+          bag_row_wave<T, G>(a, g, key + wave * kWaveBucket);
+      }
     }
   } else {
     const int64_t r0 = ((int64_t)xcd_block(b - nlist - nmid, nlight) * (kSumThreads / 64) + wave) * 64;
