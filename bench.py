@@ -482,7 +482,7 @@ def input_stage(args, log, tr, cfg, head, labels, losses):
                     "traffic is lower than the algorithmic bytes",
             "backward": {"entry": "erase_embed_bags_backward", "avg_us": us_b, "algorithmic_bytes": bytes_b,
                          "achieved_gbs": bytes_b / us_b / 1e3,
-                         "note": "dense fp32 table gradient [26][100000][64] written in full (666 MB); eleven launches"}}
+                         "note": "dense fp32 table gradient [26][100000][64] written in full (666 MB); six launches"}}
 
 
 def _merge(iv):

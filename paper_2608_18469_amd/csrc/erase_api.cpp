@@ -327,7 +327,10 @@ std::vector<Unit> make_units(const erase_config& c, int cap) {
 // over in groups, a third of the network at most: the backward of one group
 // then still runs beside the forward of the next.  A network whose whole step
 // is below 0.1 GFLOP is one unit (its launches cost the host more than the
-// device).
+// device).  What units give up is the sharing of a launch by all equal blocks:
+// ctr_mlp (units of two) takes 0.260 ms on one stream, 0.288 so and 0.254 in
+// PIPELINE with the worker, ctr_dcn 5.98, 6.12 and 6.07; the chain of twelve
+// narrow blocks (units of four) 0.229, 0.237 and 0.159 ms.
 int erase_unit_cap(const erase_config& c) {
   double flops = 0;
   for (int b = 0; b < c.n_blocks; ++b)
