@@ -35,6 +35,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "internal.h"
@@ -297,7 +298,8 @@ __global__ __launch_bounds__(256) void tf_rms_bwd(TfRmsArgs a) {
 // whole heads (it re-reads their rows from its own L2), longest blocks first;
 // with few heads the blocks are spread one by one, longest first.  (With the
 // rank as the fastest index an XCD got blocks of 24 steps where another got
-// 10.)  False: no work for this workgroup.  The kernels keep two waves' worth
+// 10.)  Beyond 2^23 workgroups (2^32 threads in x are not launched) the numbers
+// run on over y.  False: no work for this workgroup.  The kernels keep two waves' worth
 // of fragments in flight (156 VGPRs, three waves on a SIMD); held to 128 they
 // spill, and the two-layer step of 16 sequences of 1024 tokens takes 6.23
 // instead of 5.99 ms.
@@ -305,21 +307,22 @@ __global__ __launch_bounds__(256) void tf_rms_bwd(TfRmsArgs a) {
 __device__ __forceinline__ bool attn_whole_heads(int BH) { return BH % 8 == 0 || BH >= 64; }
 __device__ __forceinline__ bool attn_work(const TfAttnArgs& a, int per, int& r, int& kind, int& b, int& h) {
   const int BH = a.B * a.H;
+  const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;  // gridDim.x a multiple of 8 where y is used
   int bh;
   if (attn_whole_heads(BH)) {
     const int heads = (BH + 7) / 8;  // of an XCD
-    const int slot = (int)(blockIdx.x >> 3);
+    const int slot = (int)(id >> 3);
     const int k = slot % heads;
     r = slot / heads / per;
     kind = slot / heads % per;
-    bh = (int)(blockIdx.x & 7) * heads + k;
+    bh = (int)(id & 7) * heads + k;
     if (bh >= BH) return false;
   } else {
-    const int id = (int)blockIdx.x;
-    bh = id % BH;
-    r = id / BH / per;
-    kind = id / BH % per;
+    bh = (int)(id % (uint32_t)BH);
+    r = (int)(id / (uint32_t)BH) / per;
+    kind = (int)(id / (uint32_t)BH) % per;
   }
+  if (r >= (a.T + 63) / 64) return false;
   b = bh / a.H;
   h = bh % a.H;
   return true;
@@ -899,10 +902,12 @@ hipError_t launch_tf_attn(int backward, const TfAttnArgs& a, hipStream_t s, cons
   const bool whole = BH % 8 == 0 || BH >= 64;  // attn_whole_heads
   const int64_t n = (whole ? (BH + 7) / 8 * 8 : BH) * nb * (backward ? 2 : 1);
   if (n > INT32_MAX) return hipErrorInvalidValue;
+  const int64_t nx = std::min<int64_t>(n, int64_t(1) << 23);
+  const dim3 grid((unsigned)nx, (unsigned)((n + nx - 1) / nx));
   if (backward)
-    ERASE_TF_LAUNCH(tf_attn_bwd, dim3((unsigned)n), dim3(256), s, ev, a);
+    ERASE_TF_LAUNCH(tf_attn_bwd, grid, dim3(256), s, ev, a);
   else
-    ERASE_TF_LAUNCH(tf_attn_fwd, dim3((unsigned)n), dim3(256), s, ev, a);
+    ERASE_TF_LAUNCH(tf_attn_fwd, grid, dim3(256), s, ev, a);
   return hipGetLastError();
 }
 
